@@ -28,6 +28,7 @@
 #include "coral_lmhead.h"
 #include "control_words.h"
 #include "device_utils.h"
+#include "fused_kernels.h"
 #include "fused_path.h"
 #include "router_premix.h"
 #include "staged_path.h"
@@ -41,6 +42,11 @@ constexpr size_t kStaticScratchBytes = (size_t)CORAL_NOALLOC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
+
+__global__ void k_zero_words(unsigned int* p, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0u;
+}
 
 // ---------------------------------------------------------------- host side
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -66,12 +72,18 @@ bool sizes_ok(int M, int H, int V, int G, int g, int k) {
     return true;
 }
 
-// pair_pieces: the shape can take the single-launch kernel's log-probability mode (the table
-// of its per-pair pieces is the largest item and is left out otherwise).  tiles: the shape
-// can take the matrix-core path (its logits buffer and span lists are left out otherwise).
-// tiles_only: a layout for a call that is known to take the matrix-core path (the other
-// paths' lists are left out).
-Layout make_layout(int M, int V, int G, int g, int k, bool pair_pieces, bool tiles, bool tiles_only = false) {
+// Which paths' arrays a layout holds: all that calls with these sizes can take (a workspace), or
+// those of one path only (the static scratch array).
+enum class LayoutFor { kWorkspace, kSingleLaunch, kTiles };
+
+// pieces: the log-probability mode's table of per-batch pieces (layout_pieces).  tiles: the shape
+// can take the matrix-core path (its logits buffer and statistics are left out otherwise).
+struct Pieces {
+    size_t entries;             // 0 if the single-launch kernel cannot run the mode
+    bool shared;                // in the memory of the multi-kernel paths' arrays
+};
+Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, bool tiles,
+                   LayoutFor what = LayoutFor::kWorkspace) {
     Layout L;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -80,13 +92,14 @@ Layout make_layout(int M, int V, int G, int g, int k, bool pair_pieces, bool til
         return at;
     };
     L.ctrl = take(kCtrlBytes);
-    const size_t others = tiles_only ? 0 : 1;
-    L.fused_part = take(others * kMaxWorkgroups * M * k * sizeof(Cand));
-    L.fused_lse = take(others * kMaxWorkgroups * M * sizeof(unsigned long long));   // log-probability mode
-    L.fused_glist = take(others * M * (g ? g : 1) * k * sizeof(Cand));
-    // one (max, sum) piece per (row pair of a selected group, token that selected it): a
-    // token's g groups are distinct, so their pairs number V / 2 + g at most
-    L.fused_pairs = take(pair_pieces ? (size_t)M * ((size_t)V / 2 + g) * sizeof(unsigned long long) : 0);
+    const size_t single = what != LayoutFor::kTiles ? 1 : 0;
+    const size_t staged = what == LayoutFor::kWorkspace ? 1 : 0;
+    L.fused_part = take(single * kMaxWorkgroups * M * k * sizeof(Cand));
+    L.fused_lse = take(single * kMaxWorkgroups * M * sizeof(unsigned long long));   // log-probability mode
+    L.fused_glist = take(single * M * (g ? g : 1) * k * sizeof(Cand));
+    L.fused_pairs = off;
+    const size_t pieces_end = align_up(off + pieces.entries * sizeof(unsigned long long), 256);
+    if (!pieces.shared) off = pieces_end;
     L.s = take((size_t)kGateParts * M * (G ? G : 1) * sizeof(float));
     L.sel = take((size_t)M * (g ? g : 1) * sizeof(int32_t));
     L.mask = take((size_t)(G ? G : 1) * sizeof(unsigned long long));
@@ -95,8 +108,8 @@ Layout make_layout(int M, int V, int G, int g, int k, bool pair_pieces, bool til
     L.chunk_base = take((size_t)M * (g ? g : 1) * sizeof(int32_t));
     L.slot_count = take((size_t)M * (g ? g : 1) * sizeof(int32_t));
     L.part_stride = (V + kChunkRows - 1) / kChunkRows + g;
-    L.part = take(others * M * L.part_stride * k * sizeof(Cand));
-    L.lse_part = take(others * M * L.part_stride * 2 * sizeof(float));     // log-probability mode
+    L.part = take(staged * M * L.part_stride * k * sizeof(Cand));
+    L.lse_part = take(staged * M * L.part_stride * 2 * sizeof(float));     // log-probability mode
     L.logp_sel = take((size_t)M * (g ? g : 1) * sizeof(float));
     L.tile_mask = take((size_t)((kMaxM + 15) / 16) * (G ? G : 1) * sizeof(unsigned long long));
     L.tile_first_block = take((size_t)(G ? G : 1) * sizeof(int32_t));
@@ -104,7 +117,7 @@ Layout make_layout(int M, int V, int G, int g, int k, bool pair_pieces, bool til
     const size_t tile_blocks = (size_t)V / kTileRows + G + 1;
     L.tile_z = take(tiles ? tile_blocks * M * kTileRows * sizeof(float) : 0);
     L.tile_stat = take(tiles ? tile_blocks * M * sizeof(float2) : 0);
-    L.total = off;
+    L.total = off > pieces_end ? off : pieces_end;
     return L;
 }
 
@@ -138,6 +151,15 @@ inline coral_status launch_status() {
 // events: they are bound to this launch and take the kernel's own start and stop times (what
 // a kernel trace reports as its duration), not the times at which event records before and
 // after it would be reached, which include the dispatch latency.
+coral_status launch_timed(const void* fn, dim3 grid, dim3 block, size_t lds, hipStream_t stream, void* ev_before,
+                          void* ev_after, void** args) {
+    const hipError_t e =
+        ev_before && ev_after
+            ? hipExtLaunchKernel(fn, grid, block, args, lds, stream, static_cast<hipEvent_t>(ev_before),
+                                 static_cast<hipEvent_t>(ev_after), 0)
+            : hipLaunchKernel(fn, grid, block, args, lds, stream);
+    return e == hipSuccess ? launch_status() : CORAL_ERR_HIP;
+}
 template <class F, class... Args>
 coral_status launch_timed(F fn, dim3 grid, dim3 block, size_t lds, hipStream_t stream, void* ev_before,
                           void* ev_after, Args... args) {
@@ -154,7 +176,7 @@ coral_status launch_timed(F fn, dim3 grid, dim3 block, size_t lds, hipStream_t s
 // kernel has been allowed so far.  Both are properties of the device and of the loaded code
 // object, looked up once instead of on every call; a mutex guards them.
 constexpr int kMaxDevices = 64;
-constexpr int kMaxKernels = 96;
+constexpr int kMaxKernels = 192;
 struct DeviceCache {
     int compute_units;
     void* scratch_ptr;          // this device's copy of `scratch`, looked up on first use
@@ -225,6 +247,10 @@ int fused_gate_mode(bool dense, int M, int G, int g, int k, int jp, coral_dtype 
     return dense || !is_16bit(dt) || M <= 3 ? kGateVector : kGateMfma;
 }
 
+// Rows the single-launch kernel takes: up to 8 KB, and from 10 to 16 KB.  (Nine of sixteen
+// segments in use leave almost half of the loads of a batch empty: the multi-kernel path's.)
+bool fused_rows_fit(int jp) { return jp <= 8 || (jp >= 10 && jp <= kFusedMaxSegs); }
+
 // Activated groups at most.
 inline long long max_union(int M, int G, int g) { return (long long)M * g < G ? (long long)M * g : G; }
 
@@ -232,7 +258,7 @@ inline long long max_union(int M, int G, int g) { return (long long)M * g < G ? 
 // its own and ranks the groups in one wave: at most 64 activated groups, fewer than half the
 // workgroups; a token's g lists share the LDS of one wave's lists.
 bool fused_logprob_fits(int M, int G, int g, int k, int jp, coral_dtype dt, int workgroups) {
-    if (jp > kFusedSegs || g > kFusedWaves) return false;
+    if (!fused_rows_fit(jp) || g > kFusedWaves) return false;
     const long long um = max_union(M, G, g);
     if (um > kWave || 2 * um > workgroups) return false;
     return fused_lds_layout(M, G, g, k, jp, false, fused_gate_mode(false, M, G, g, k, jp, dt, true), true)
@@ -249,10 +275,23 @@ struct LevelExpand {
     float* next_score;
 };
 
-bool layout_has_pair_pieces(int M, int H, int G, int g, int k, coral_dtype dt) {
-    if (G < 1 || !dtype_ok(dt)) return false;
+// The single-launch log-probability mode's table of pieces: one (max, sum) per (batch of rows of
+// a selected group, token that selected it); a token's g groups are distinct, so their batches
+// number V / rows + g at most.  Rows beyond 8 KB (one to a batch): the table shares the memory of
+// the multi-kernel paths' arrays, which no call uses with it, and is sized for the most tokens up
+// to M with which the mode runs in that kernel, so that a workspace for M tokens serves fewer.
+Pieces layout_pieces(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
+    if (G < 1 || !dtype_ok(dt)) return {0, false};
     const int n_vec = H / (is_16bit(dt) ? 8 : 4);
-    return fused_logprob_fits(M, G, g, k, (n_vec + kWave - 1) / kWave, dt, kMaxWorkgroups);
+    const int jp = (n_vec + kWave - 1) / kWave;
+    if (jp < 1 || !fused_rows_fit(jp)) return {0, false};
+    const bool shared = jp > 8;
+    const int in_lds = kLdsLimit / (int)(hidden_lds_stride(jp) * sizeof(uint4));       // hidden vectors alone
+    const int least = shared ? 1 : M;
+    for (int m = M < in_lds ? M : in_lds; m >= least; --m)
+        if (fused_logprob_fits(m, G, g, k, jp, dt, kMaxWorkgroups))
+            return {(size_t)m * ((size_t)V / fused_rows(fused_segs(jp)) + g), shared};
+    return {0, false};
 }
 
 // Enqueues the single-launch path (the caller has checked with plan_path that it fits).
@@ -269,22 +308,35 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
     if (P < 1) return CORAL_ERR_HIP;
     if (P > kMaxWorkgroups) P = kMaxWorkgroups;
     // Collected candidates instead of per-wave lists, where a workgroup is sure to meet at
-    // most kCollectCap rows per token: it takes 16 consecutive row pairs out of every 16 P of
-    // the concatenated activated groups, so of any group (a run of at most `pairs` pairs) it
-    // meets no more than 16 * (pairs / 16P) + min(16, pairs % 16P), and a token has g groups.
-    bool collect = false;
-    if (!dense && !logprob && max_group_rows > 0) {
-        const long long period = (long long)kFusedWaves * P;
-        const long long pairs = ((long long)max_group_rows + kFusedRows - 1) / kFusedRows;
-        const long long rest = pairs % period;
-        const long long per_group = kFusedWaves * (pairs / period) + (rest < kFusedWaves ? rest : kFusedWaves);
-        collect = kFusedRows * per_group * g <= kCollectCap &&
-                  fused_lds_layout(M, G, g, k, jp, false, gate, false, true).total <= kLdsLimit;
+    // most kCollectMax rows per token: it takes D consecutive batches out of every D P of the
+    // concatenated activated groups, so of any group (a run of at most n batches) it meets no
+    // more than D * (n / D P) + min(D, n % D P), and a token has g groups.  (D = kDealFew; the
+    // bound for D = 1, which the kernel uses as well, is never larger.)
+    const int segs = fused_segs(jp), rows = fused_rows(segs);
+    int cap = 0;
+    if (!logprob) {
+        const long long period = (long long)kDealFew * P;
+        const long long n = ((long long)(dense ? V : max_group_rows) + rows - 1) / rows;
+        const long long rest = n % period;
+        const long long per_group = kDealFew * (n / period) + (rest < kDealFew ? rest : kDealFew);
+        const long long bound = (rows * per_group * (dense ? 1 : g) + kWave - 1) / kWave * kWave;
+        if (bound > 0 && bound <= kCollectMax &&
+            fused_lds_layout(M, G, g, k, jp, dense, gate, false, (int)bound).total <= kLdsLimit)
+            cap = (int)bound;
+    } else {
+        // a workgroup's rows depend on the selection: buffers as large as fit beside the pieces,
+        // used by the workgroups whose rows they hold
+        for (int c = kCollectMax; !cap && c > kFusedWaves * k; c -= kWave) {
+            const FusedLds L2 = fused_lds_layout(M, G, g, k, jp, false, gate, true, c);
+            if (L2.total <= kLdsLimit && L2.pieces_bytes >= kLpPiecesMax) cap = c;
+        }
+        if (!cap) cap = kFusedWaves * k;               // the lists' own size
     }
-    const FusedLds F = fused_lds_layout(M, G, g, k, jp, dense, gate, logprob, collect);
-    if (jp > kFusedSegs || F.total > kLdsLimit) return CORAL_ERR_UNSUPPORTED;   // not reached
+    const FusedLds F = fused_lds_layout(M, G, g, k, jp, dense, gate, logprob, cap);
+    if (!fused_rows_fit(jp) || F.total > kLdsLimit) return CORAL_ERR_UNSUPPORTED;   // not reached
+    if (jp > 8 && gate == kGateMfma && M > 16) return CORAL_ERR_UNSUPPORTED;        // not reached: LDS
     FusedParams p = {};
-    p.collect = collect ? 1 : 0;
+    p.cap = cap;
     // Measured with rows of 8 KB (Llama shapes): dense head, one or two tokens: 6 waves 158 us
     // against 165 us with all 16 (Llama2: 46.5 against 48.5 us); four tokens: 10 waves 162 us
     // against 168 us.  Rows of 7 KB (Qwen shape) and the grouped head's gathered rows are
@@ -315,30 +367,16 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
     p.topk_logits = topk_logits;
     p.M = M; p.V = V; p.G = G; p.g = g; p.k = k;
     p.n_vec = n_vec; p.jp = jp;
-    typedef void (*fused_fn)(FusedParams);
     const bool routed = !dense && gate_hidden != hidden;
-    fused_fn fn;
-#define CORAL_FUSED_GATES(DT, R, LP)                                                             \
-    (gate == kGateMfma ? k_fused<DT, false, kGateMfma, R, LP> : k_fused<DT, false, kGateVector, R, LP>)
     if (logprob && (dense || 2 * max_union(M, G, g) > P)) return CORAL_ERR_UNSUPPORTED;   // not reached
-    if (logprob && routed)
-        fn = CORAL_PICK_DT(dt, (k_fused<kF32, false, kGateVector, true, true>),
-                           CORAL_FUSED_GATES(kBF16, true, true), CORAL_FUSED_GATES(kF16, true, true));
-    else if (logprob)
-        fn = CORAL_PICK_DT(dt, (k_fused<kF32, false, kGateVector, false, true>),
-                           CORAL_FUSED_GATES(kBF16, false, true), CORAL_FUSED_GATES(kF16, false, true));
-    else if (dense)
-        fn = CORAL_PICK_DT(dt, (k_fused<kF32, true, kGateVector>), (k_fused<kBF16, true, kGateVector>),
-                           (k_fused<kF16, true, kGateVector>));
-    else if (routed)
-        fn = CORAL_PICK_DT(dt, (k_fused<kF32, false, kGateVector, true>), CORAL_FUSED_GATES(kBF16, true, false),
-                           CORAL_FUSED_GATES(kF16, true, false));
-    else
-        fn = CORAL_PICK_DT(dt, (k_fused<kF32, false, kGateVector, false>), CORAL_FUSED_GATES(kBF16, false, false),
-                           CORAL_FUSED_GATES(kF16, false, false));
-#undef CORAL_FUSED_GATES
-    if (!allow_lds(reinterpret_cast<const void*>(fn), F.total)) return CORAL_ERR_HIP;
-    return launch_timed(fn, dim3(P), dim3(kFusedBlock), F.total, stream, ev_before, ev_after, p);
+    const bool short_rows = segs <= 4;
+    const auto getter = CORAL_PICK_DT(dt, short_rows ? coral_fused_short_f32 : coral_fused_long_f32,
+                                      short_rows ? coral_fused_short_bf16 : coral_fused_long_bf16,
+                                      short_rows ? coral_fused_short_f16 : coral_fused_long_f16);
+    const void* fn = getter(dense, gate, routed, logprob, segs);
+    if (!allow_lds(fn, F.total)) return CORAL_ERR_HIP;
+    void* args[] = {&p};
+    return launch_timed(fn, dim3(P), dim3(kFusedBlock), F.total, stream, ev_before, ev_after, args);
 }
 
 // The dense head goes to the matrix-core path from 8 tokens on, if the vocabulary gives every
@@ -389,7 +427,7 @@ PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_d
         return pl;
     }
     const bool fused_ok =
-        jp <= kFusedSegs &&
+        fused_rows_fit(jp) &&
         fused_lds_layout(M, dense ? 0 : G, dense ? 0 : g, k, jp, dense,
                          fused_gate_mode(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp, dt)).total <= kLdsLimit;
     const bool tiles_ok =
@@ -547,7 +585,7 @@ extern "C" coral_status coral_group_index_validate(const int32_t* host_offsets,
 extern "C" size_t coral_lmhead_workspace_bytes(int M, int H, int V, int G, int g, int k,
                                                coral_dtype dt) {
     if (!sizes_ok(M, H, V, G, g, k)) return 0;
-    return make_layout(M, V, G, g, k, layout_has_pair_pieces(M, H, G, g, k, dt),
+    return make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt),
                        layout_has_tiles(M, H, V, G, g, k, dt)).total;
 }
 
@@ -614,12 +652,21 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
         min_cand += smallest[i];
     }
     if ((long long)k > min_cand) return CORAL_ERR_SHAPE;
-    // (the static scratch serves the logit ranking only: no table of per-pair pieces, and the
-    // matrix-core path's buffers only if this very call takes that path)
-    const bool static_tiles = static_workspace && plan_path(false, M, H, V, G, g, k, dt).path == 2;
-    const Layout L = make_layout(M, V, G, g, k, !static_workspace && layout_has_pair_pieces(M, H, G, g, k, dt),
-                                 static_workspace ? static_tiles : layout_has_tiles(M, H, V, G, g, k, dt),
-                                 static_tiles);
+    // (the static scratch serves the logit ranking only: no table of pieces, and of the arrays
+    // only those of the path that this very call takes; rows beyond 8 KB are taken or refused by
+    // what the multi-kernel path for them would need)
+    Layout L;
+    if (!static_workspace) {
+        L = make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt), layout_has_tiles(M, H, V, G, g, k, dt));
+    } else {
+        const PathPlan sp = plan_path(false, M, H, V, G, g, k, dt);
+        const bool long_rows = sp.path == 1 && (size_t)H * (is_16bit(dt) ? 2 : 4) > 8192;
+        int um, lds;
+        const bool tiles = sp.path == 2 || (long_rows && tiles_fit(M, H, V, G, g, k, dt, &um, &lds));
+        L = make_layout(M, V, G, g, k, Pieces{}, tiles, tiles ? LayoutFor::kTiles : LayoutFor::kWorkspace);
+        if (long_rows && L.total <= kStaticScratchBytes)
+            L = make_layout(M, V, G, g, k, Pieces{}, false, LayoutFor::kSingleLaunch);
+    }
     if (static_workspace) {
         if (logprob || L.total > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;
     } else {
@@ -742,7 +789,7 @@ coral_status dense_impl(const void* hidden, const void* lm_W, int M, int H, int 
     coral_status st = check_common(hidden, lm_W, M, H, V, k, dt, topk_ids, topk_logits);
     if (st != CORAL_OK) return st;
     if (k > V) return CORAL_ERR_SHAPE;
-    const Layout L = make_layout(M, V, 0, 0, k, false, layout_has_tiles(M, H, V, 0, 0, k, dt));
+    const Layout L = make_layout(M, V, 0, 0, k, Pieces{}, layout_has_tiles(M, H, V, 0, 0, k, dt));
     st = check_workspace(workspace, workspace_bytes, L.total);
     if (st != CORAL_OK) return st;
 

@@ -129,6 +129,90 @@ __device__ __forceinline__ float wave_sum(float x) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
+// Exchange between the halves of the wave, and between neighbouring rows of 16 lanes: afterwards
+// a holds both operands' values of the lower halves (even rows), b those of the upper (odd)
+// ones, each in its operand's half: a + b sums a in the lower and b in the upper half.
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_rows(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {       // (every source lane exists)
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+// x combined with the lane whose number differs in bit BIT (8, 16 or 32).
+template <int BIT>
+__device__ __forceinline__ float lane_xor_sum(float x) {
+    if (BIT == 8) return x + dpp_move<0x128>(x);           // row_ror:8
+    float y = x;
+    if (BIT == 32) swap_halves(x, y); else swap_rows(x, y);
+    return x + y;
+}
+template <int BIT>
+__device__ __forceinline__ float lane_xor_max(float x) {
+    if (BIT == 8) return fmaxf(x, dpp_move<0x128>(x));
+    float y = x;
+    if (BIT == 32) swap_halves(x, y); else swap_rows(x, y);
+    return fmaxf(x, y);
+}
+
+// Sums over the 64 lanes of N = 1, 2, 4, 8 or 16 values at once: lane l returns the sum of the
+// value whose index has bit i = bit (5 - i) of l (for log2 N bits; the lanes that differ only
+// below hold the same sum).  Every halving step serves two values, so 16 sums take 35
+// instructions instead of 16 x 7.  All sums are taken in the same order whatever their place and
+// whatever N: lanes 32 apart first, then 16, 8, then l with 7 - l of each 8, then quads.
+template <int N>
+__device__ __forceinline__ float wave_sum_spread(float (&v)[N], int lane) {
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8 || N == 16, "");
+    constexpr int N1 = N > 1 ? N / 2 : 1, N2 = N1 > 1 ? N1 / 2 : 1, N3 = N2 > 1 ? N2 / 2 : 1;
+    float a[N1], b[N2], c[N3];
+#pragma unroll
+    for (int i = 0; i < N1; ++i) {
+        if (N > 1) {
+            float x = v[2 * i], y = v[N > 1 ? 2 * i + 1 : 0];
+            swap_halves(x, y);
+            a[i] = x + y;
+        } else {
+            a[i] = lane_xor_sum<32>(v[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < N2; ++i) {
+        if (N1 > 1) {
+            float x = a[N1 > 1 ? 2 * i : 0], y = a[N1 > 1 ? 2 * i + 1 : 0];
+            swap_rows(x, y);
+            b[i] = x + y;
+        } else {
+            b[i] = lane_xor_sum<16>(a[i]);
+        }
+    }
+    const bool b3 = lane & 8, b2 = lane & 4;
+#pragma unroll
+    for (int i = 0; i < N3; ++i) {
+        if (N2 > 1) {
+            const float x = b[N2 > 1 ? 2 * i : 0], y = b[N2 > 1 ? 2 * i + 1 : 0];
+            c[i] = (b3 ? y : x) + dpp_move<0x128>(b3 ? x : y);
+        } else {
+            c[i] = b[i] + dpp_move<0x128>(b[i]);
+        }
+    }
+    float d;
+    if (N3 > 1) {
+        const float x = c[0], y = c[N3 > 1 ? 1 : 0];
+        d = (b2 ? y : x) + dpp_move<0x141>(b2 ? x : y);        // row_half_mirror
+    } else {
+        d = c[0] + dpp_move<0x141>(c[0]);
+    }
+    d += dpp_move<0xB1>(d);                                    // quad_perm [1,0,3,2]
+    return d + dpp_move<0x4E>(d);                              // quad_perm [2,3,0,1]
+}
+
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ int dpp_add_i32(int x) {
     return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);

@@ -1,0 +1,6 @@
+// k_fused for bf16 rows of up to 4 KB.
+#include "fused_instances.h"
+
+const void* coral_fused_short_bf16(bool dense, int gate, bool routed, bool logprob, int segs) {
+    return fused_short_rows<kBF16>(dense, gate, routed, logprob, segs);
+}

@@ -7,6 +7,233 @@
 
 namespace {
 
+// ---------------------------------------------------------------- merging lists of any number
+// Wave-private LDS scratch of the merges: ranking keys, gathered candidates, list tags.
+struct WaveScratch {
+    unsigned long long keys[kWave];
+    unsigned keys32[kWave];
+    Cand cand[kWave];
+    int tags[kWave];
+};
+
+__device__ __forceinline__ unsigned cand_ord(Cand c) { return is_real(c) ? ord32(c.v) : 0u; }
+
+// One step of a streamed top-k: every lane offers one candidate; those that beat the
+// current k-th entry of the register list (lane i = rank i) are inserted one by one.
+__device__ __forceinline__ void offer_candidates(float& lv, int& li, Cand c, int k, int lane) {
+    const float tv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lv), k - 1));
+    const int ti = __builtin_amdgcn_readlane(li, k - 1);
+    unsigned long long pass = __ballot(better(c.v, c.id, tv, ti));
+    while (pass) {                                     // wave-uniform
+        const int src = __ffsll(pass) - 1;
+        pass &= pass - 1ull;
+        const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c.v), src));
+        const int id = __builtin_amdgcn_readlane(c.id, src);
+        list_insert(lv, li, v, id, lane, k);
+    }
+}
+
+// k-th largest of the keys in lanes [0, n), or 0 if there are fewer than k keys.
+// Wave-uniform.  Used as a bound only: candidates are kept if their key reaches it, ties
+// included.  A key is among the k largest values exactly when fewer than k keys exceed it;
+// the smallest such key is the k-th largest.  keys32: 64 wave-private LDS words.
+__device__ __forceinline__ unsigned list_kth_key(unsigned* keys32, unsigned key, int n, int k, int lane) {
+    if (n < k) return 0u;
+    if (lane >= n) key = 0u;
+    keys32[lane] = key;
+    int above = 0;
+#pragma unroll 16
+    for (int j = 0; j < n; ++j) above += keys32[j] > key ? 1 : 0;   // wave-uniform trip count
+    return wave_min_u32(lane < n && above < k ? key : 0xffffffffu);
+}
+
+// Appends the candidates flagged `keep` to scratch[cnt...] in lane order; returns the
+// new count (entries past `cap` are dropped, the caller checks the count).
+__device__ __forceinline__ int list_append(Cand* scratch, int* tag_scratch, int cnt, int cap,
+                                           bool keep, Cand c, int tag, int lane) {
+    const unsigned long long b = __ballot(keep);
+    if (keep) {
+        const int pos = cnt + __popcll(b & ((1ull << lane) - 1ull));
+        if (pos < cap) {
+            scratch[pos] = c;
+            if (tag_scratch) tag_scratch[pos] = tag;
+        }
+    }
+    return cnt + __popcll(b);
+}
+
+// One wave merges n_lists sorted lists of k candidates (get(list, i), padding entries are
+// sentinels) into the k best, put(rank, candidate) for every rank < k.
+// Fast path: a value that k lists' first entries reach is a lower bound of the result's
+// k-th value, so only lists whose first entry reaches it can contribute, and of those only
+// entries that reach it (ties kept); the few survivors are ranked by counting.  If a bound
+// does not exist (fewer than k lists, more than 256 lists) or too many survive (64), the
+// lists are streamed through a sorted register list instead.  No more than 64 candidates in
+// all are ranked directly; DIRECT > 0 (lists that are far away, in memory): no more than
+// DIRECT per lane are fetched in one trip, bounded by a sample of themselves, and ranked.
+template <int DIRECT = 0, class Get, class Put>
+__device__ __forceinline__ void wave_merge_topk(int n_lists, int k, int lane, WaveScratch* ws,
+                                                Get get, Put put) {
+    constexpr int kCap = kWave;
+    Cand* scratch = ws->cand;
+    int* tags = ws->tags;
+    const int inv_k = inv_small(k);
+    if (n_lists * k <= kWave) {
+        // one candidate per lane: ranked by counting at once
+        const int n_e = n_lists * k;
+        Cand c = sentinel();
+        if (lane < n_e) {
+            const int l = div_small(lane, inv_k);
+            c = get(l, lane - l * k);
+        }
+        const int n_real = __popcll(__ballot(is_real(c)));
+        const int r = wave_rank(ws->keys, c.v, c.id, n_e, lane);   // real ones are distinct
+        if (is_real(c) && r < k) put(r, c);
+        if (lane >= n_real && lane < k) put(lane, sentinel());
+        return;
+    }
+    if (DIRECT && n_lists * k <= DIRECT * kWave) {
+        // up to DIRECT candidates per lane, all requested at once; the k-th largest of the
+        // lanes' best candidates (k lanes reach it) bounds the result's k-th entry, and what
+        // reaches the bound is ranked by counting
+        constexpr int kPerLane = DIRECT > 0 ? DIRECT : 1;
+        const int n_e = n_lists * k;
+        Cand cd[kPerLane];
+        unsigned sample = 0u;
+#pragma unroll
+        for (int u = 0; u < kPerLane; ++u) {
+            const int e = u * kWave + lane;
+            cd[u] = sentinel();
+            if (e < n_e) {
+                const int l = div_small(e, inv_k);
+                cd[u] = get(l, e - l * k);
+            }
+            const unsigned o = cand_ord(cd[u]);
+            sample = o > sample ? o : sample;
+        }
+        const unsigned bound = list_kth_key(ws->keys32, sample, kWave, k, lane);
+        int cnt = 0;
+#pragma unroll
+        for (int u = 0; u < kPerLane; ++u)
+            if (u * kWave < n_e)                       // uniform
+                cnt = list_append(scratch, nullptr, cnt, kCap, is_real(cd[u]) && ord32(cd[u].v) >= bound,
+                                  cd[u], 0, lane);
+        if (cnt <= kCap) {
+            Cand s = sentinel();
+            if (lane < cnt) s = scratch[lane];
+            const int r = wave_rank(ws->keys, s.v, s.id, cnt, lane);
+            if (lane < cnt && r < k) put(r, s);
+            if (lane >= cnt && lane < k) put(lane, sentinel());
+            return;
+        }
+    }
+    bool fast = n_lists >= k && n_lists <= 4 * kWave;
+    int n_s = 0;
+    unsigned tau = 0u;
+    if (fast) {
+        Cand mx[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int l = c * kWave + lane;
+            mx[c] = sentinel();
+            if (c * kWave < n_lists && l < n_lists) mx[c] = get(l, 0);
+        }
+        // bound: the k-th largest of the lanes' best first entries (k lanes reach it, so k
+        // lists do); if more than 64 lists reach it, the 64 kept so far are the next,
+        // tighter sample
+        unsigned sample = cand_ord(mx[0]);
+#pragma unroll
+        for (int c = 1; c < 4; ++c) {
+            const unsigned o = cand_ord(mx[c]);
+            sample = o > sample ? o : sample;
+        }
+        int n_sample = n_lists < kWave ? n_lists : kWave;
+        int cnt = 0;
+#pragma unroll
+        for (int round = 0; round < 3; ++round) {              // wave-uniform
+            tau = list_kth_key(ws->keys32, sample, n_sample, k, lane);
+            cnt = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (c * kWave < n_lists)
+                    cnt = list_append(scratch, tags, cnt, kCap,
+                                      is_real(mx[c]) && ord32(mx[c].v) >= tau, mx[c],
+                                      c * kWave + lane, lane);
+            if (cnt <= kCap) break;
+            sample = cand_ord(scratch[lane]);
+            n_sample = kCap;
+        }
+        if (cnt > kCap) {
+            fast = false;                                      // no usable bound (ties)
+        } else {
+            n_s = cnt;                                         // the lists that reach the bound
+        }
+    }
+    if (fast) {
+        int cnt = 0;
+        const int n_e = n_s * k;
+        for (int base = 0; base < n_e; base += 2 * kWave) {    // wave-uniform; two loads in flight
+            Cand c2[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int e = base + u * kWave + lane;
+                c2[u] = sentinel();
+                if (e < n_e) {
+                    const int sl = div_small(e, inv_k);
+                    c2[u] = get(tags[sl], e - sl * k);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                cnt = list_append(scratch, nullptr, cnt, kCap,
+                                  is_real(c2[u]) && ord32(c2[u].v) >= tau, c2[u], 0, lane);
+        }
+        if (cnt <= kCap) {
+            Cand s = sentinel();
+            if (lane < cnt) s = scratch[lane];
+            const int r = wave_rank(ws->keys, s.v, s.id, cnt, lane);
+            if (lane < cnt && r < k) put(r, s);
+            if (lane >= cnt && lane < k) put(lane, sentinel());
+            return;
+        }
+    }
+    // general path: the candidates stream through a sorted register list (lane i = rank i),
+    // 256 at a time so that their loads are in flight together; the first list, sorted
+    // already, seeds the register list
+    float lv = -INFINITY;
+    int li = INT_MAX;
+    const int n_e = n_lists * k;
+    const bool small = n_e <= 4096;                    // div_small's range
+    for (int base = 0; base < n_e; base += 4 * kWave) {    // wave-uniform
+        Cand c4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = base + u * kWave + lane;
+            c4[u] = sentinel();
+            if (e < n_e) {
+                const int l = small ? div_small(e, inv_k) : e / k;
+                c4[u] = get(l, e - l * k);
+            }
+        }
+        if (base == 0) {
+            if (lane < k) {
+                lv = c4[0].v;
+                li = c4[0].id;
+                c4[0] = sentinel();
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (base + u * kWave < n_e) offer_candidates(lv, li, c4[u], k, lane);
+    }
+    if (lane < k) {
+        Cand o;
+        o.v = lv;
+        o.id = li;
+        put(lane, o);
+    }
+}
+
 // ---------------------------------------------------------------- parameters
 struct LogitsParams {
     const uint4* hidden;        // [M, n_vec]

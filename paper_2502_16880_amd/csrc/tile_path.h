@@ -672,18 +672,6 @@ __host__ __device__ inline TileSelectLds tile_select_lds_layout(int n_groups, in
     return L;
 }
 
-// wave_kth_key for all 64 lanes with the keys read four at a time (keys32 16-byte aligned).
-__device__ __forceinline__ unsigned wave_kth_key4(unsigned* keys32, unsigned key, int k, int lane) {
-    keys32[lane] = key;
-    int above = 0;
-#pragma unroll 4
-    for (int j = 0; j < kWave / 4; ++j) {
-        const uint4 q = reinterpret_cast<const uint4*>(keys32)[j];
-        above += (q.x > key ? 1 : 0) + (q.y > key ? 1 : 0) + (q.z > key ? 1 : 0) + (q.w > key ? 1 : 0);
-    }
-    return wave_min_u32(above < k ? key : 0xffffffffu);
-}
-
 template <bool DENSE, bool LP>
 __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams p) {
     extern __shared__ uint4 smem[];
@@ -811,7 +799,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
         for (int round = 0; round < 3; ++round) {      // block-uniform
             unsigned best = 0u;
             for (int i = threadIdx.x; i < n_q; i += kSelectThreads) best = src_v[i] > best ? src_v[i] : best;
-            const unsigned kth = wave_kth_key4(keys32, best, k, lane);
+            const unsigned kth = wave_kth_key(keys32, best, k, lane);
             if (lane == 0) tau_w[wave] = kth;
             __syncthreads();
             tau = tau_w[0];

@@ -1,0 +1,86 @@
+"""Parity with the fp64 oracle where the single-launch kernel changes its form: batches of one to
+eight rows (rows of 16 KB down to 1 KB, full and partly filled segments), ragged ends of every
+batch, one ranking or another by the number of candidates and of k, and more groups than a wave
+has lanes.  Tolerances are those of test_gpu_parity.py."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from coral_inputs import Head, HeadConfig, make_hidden, to_storage  # noqa: E402
+from test_gpu_parity import (DeviceHead, check_dense, check_grouped, check_logprob, coral, run_dense,  # noqa: E402,F401
+                             run_grouped, run_logprob)
+
+
+def ragged_head(cfg, sizes, bias_std=0.5):
+    rng = np.random.default_rng(cfg.seed)
+    V = int(sum(sizes))
+    perm = rng.permutation(V).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    rows = np.concatenate([np.sort(perm[offsets[n]:offsets[n + 1]]) for n in range(len(sizes))]).astype(np.int32)
+    lm_W = to_storage(rng.standard_normal((V, cfg.H), dtype=np.float32) * np.float32(0.02), cfg.dtype)
+    gate_W = to_storage(rng.standard_normal((len(sizes), cfg.H), dtype=np.float32) * np.float32(0.02), cfg.dtype)
+    bias = (rng.standard_normal(len(sizes)) * bias_std).astype(np.float32)
+    return Head(cfg, lm_W, gate_W, bias, offsets, rows)
+
+
+def check_all(coral, cfg, sizes, Ms, dense=True):
+    dh = DeviceHead(coral, ragged_head(cfg, sizes))
+    for M in Ms:
+        hidden = make_hidden(cfg, M, M)
+        print(f"case {cfg.name} {cfg.dtype} H={cfg.H} M={M} G={cfg.G} g={cfg.g} k={cfg.k}", flush=True)
+        check_grouped(dh, hidden, cfg.g, cfg.k, run_grouped(coral, dh, hidden, cfg.g, cfg.k))
+        out = run_logprob(coral, dh, hidden, cfg.g, cfg.k)
+        check_logprob(dh, hidden, cfg.g, cfg.k, out)
+        again = run_logprob(coral, dh, hidden, cfg.g, cfg.k)
+        assert all(np.array_equal(x, y) for x, y in zip(out, again))
+        if dense:
+            check_dense(dh, hidden, cfg.k, run_dense(coral, dh, hidden, cfg.k))
+
+
+# (storage, H): segments per row 1, 2 | 3, 4 | 5, 8 | 10 (one value short of and past), 13, 16
+WIDTHS = [("bf16", 512), ("f16", 1016), ("bf16", 1032), ("f32", 1024), ("f16", 2056), ("f32", 2048),
+          ("bf16", 4616), ("f16", 5120), ("f32", 2564), ("bf16", 6664), ("f32", 4096), ("bf16", 8192)]
+
+
+@pytest.mark.parametrize("dtype,H", WIDTHS)
+def test_row_widths_and_ragged_batches(coral, dtype, H):
+    sizes = [1, 2, 3, 7, 8, 9, 15, 16, 17, 31, 64, 65, 127, 250]
+    cfg = HeadConfig(f"width{H}", dtype, H, sum(sizes), len(sizes), 5, (1,), 9, 700 + H, True)
+    check_all(coral, cfg, sizes, (1, 2, 3, 5, 8))
+
+
+@pytest.mark.parametrize("k", [16, 17, 32, 33, 64])
+@pytest.mark.parametrize("H,M", [(256, 1), (256, 9), (3072, 2)])
+def test_many_candidates(coral, k, H, M):
+    """k beyond what a sample of 64 lanes bounds, lists of one to a few rows per workgroup."""
+    sizes = [40 + 13 * n for n in range(12)]
+    cfg = HeadConfig(f"k{k}", "bf16", H, sum(sizes), 12, 3, (M,), k, 800 + k + H, True)
+    check_all(coral, cfg, sizes, (M,))
+
+
+@pytest.mark.parametrize("k", [10, 64])
+def test_candidates_beyond_the_collecting_buffers(coral, k):
+    """About 1200 rows per (workgroup, token): sorted lists per wave instead of buffers."""
+    cfg = HeadConfig(f"lists{k}", "bf16", 64, 300_000, 2, 2, (3,), k, 820 + k, True)
+    check_all(coral, cfg, [140_000, 160_000], (3,))
+
+
+@pytest.mark.parametrize("G,g", [(64, 64), (65, 4), (128, 64), (129, 65), (300, 7), (1024, 16), (1024, 70)])
+def test_many_groups(coral, G, g):
+    sizes = [2 + (5 * n) % 7 for n in range(G)]
+    cfg = HeadConfig(f"groups{G}", "f32", 128, sum(sizes), G, g, (1,), min(8, g), 840 + G + g, True)
+    check_all(coral, cfg, sizes, (1, 3, 18), dense=False)
+
+
+def test_equal_logits_in_the_single_launch_kernel(coral):
+    """All-zero hidden vectors: every bound ties, the lower ids win."""
+    sizes = [900, 1100, 1000]
+    for k in (5, 64):
+        cfg = HeadConfig("zero", "bf16", 512, sum(sizes), 3, 2, (2,), k, 860, True)
+        dh = DeviceHead(coral, ragged_head(cfg, sizes))
+        hidden = np.zeros((2, 512), np.uint16)
+        check_grouped(dh, hidden, 2, k, run_grouped(coral, dh, hidden, 2, k))
+        check_dense(dh, hidden, k, run_dense(coral, dh, hidden, k))
