@@ -95,12 +95,14 @@ size_t coral_lmhead_workspace_bytes(int M, int H, int V, int G, int g, int k,
 
 /*
  * Which kernels a call with these sizes will use (dense != 0: coral_lmhead_dense):
- * 0 = staged general path (one launch per stage), 1 = single-launch path (gate,
- * selection, row streaming and top-k of section 3.3 in one persistent kernel),
+ * 0 = general path (one launch per stage: the tile path's kernels in a form for any storage
+ * type and width, or staged kernels on the vector units where these do not fit), 1 =
+ * single-launch path (gate, selection, row streaming and top-k of section 3.3 in one persistent
+ * kernel: rows of up to 8 KB, or of 10 to 16 KB, whose token batch fits on chip),
  * 2 = matrix-core tile path (bf16, H a multiple of 512, weights below 4 GiB: groups
  * shared by many tokens, the appendix's tree-decoding case, when the hidden vectors do
  * not fit on chip; dense head with 8 or more tokens and at least 65536 rows),
- * -1 = sizes not supported (outside the limits above, or a shape only the staged path
+ * -1 = sizes not supported (outside the limits above, or a shape only the general path
  * could take whose token batch does not fit LDS: rows beyond about 10 000 values with 8 or
  * more tokens).  Host-only, no device work; for tests and benchmark reports.
  */
@@ -110,7 +112,7 @@ int coral_lmhead_path(int dense, int M, int H, int V, int G, int g, int k, coral
  * The same for coral_lmhead_grouped_logprob (Eq. 8's output): 1 = single-launch kernel
  * (at most 64 activated groups, min(M*g, G) <= 64, g <= 16, and its LDS plan fits),
  * 2 = matrix-core tile path (where that path's conditions hold and G <= 64),
- * 0 = staged path, -1 = sizes not supported.  Host-only.
+ * 0 = general path, -1 = sizes not supported.  Host-only.
  */
 int coral_lmhead_logprob_path(int M, int H, int V, int G, int g, int k, coral_dtype dt);
 

@@ -76,13 +76,15 @@ bool sizes_ok(int M, int H, int V, int G, int g, int k) {
 // those of one path only (the static scratch array).
 enum class LayoutFor { kWorkspace, kSingleLaunch, kTiles };
 
-// pieces: the log-probability mode's table of per-batch pieces (layout_pieces).  tiles: the shape
-// can take the matrix-core path (its logits buffer and statistics are left out otherwise).
+// pieces: the log-probability mode's table of per-batch pieces (layout_pieces).  tiles: whether the
+// shape can take the tile kernels (their logits buffer and statistics are left out otherwise), as
+// the matrix-core path proper or on the general path.
+enum class Tiles { kNone, kGeneral, kOwn };
 struct Pieces {
     size_t entries;             // 0 if the single-launch kernel cannot run the mode
     bool shared;                // in the memory of the multi-kernel paths' arrays
 };
-Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, bool tiles,
+Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, Tiles tiles,
                    LayoutFor what = LayoutFor::kWorkspace) {
     Layout L;
     size_t off = 0;
@@ -107,16 +109,22 @@ Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, bool tiles,
     L.n_union = take(sizeof(int32_t));
     L.chunk_base = take((size_t)M * (g ? g : 1) * sizeof(int32_t));
     L.slot_count = take((size_t)M * (g ? g : 1) * sizeof(int32_t));
-    L.part_stride = (V + kChunkRows - 1) / kChunkRows + g;
-    L.part = take(staged * M * L.part_stride * k * sizeof(Cand));
-    L.lse_part = take(staged * M * L.part_stride * 2 * sizeof(float));     // log-probability mode
     L.logp_sel = take((size_t)M * (g ? g : 1) * sizeof(float));
     L.tile_mask = take((size_t)((kMaxM + 15) / 16) * (G ? G : 1) * sizeof(unsigned long long));
     L.tile_first_block = take((size_t)(G ? G : 1) * sizeof(int32_t));
-    // a group's blocks round up: V / 128 + G blocks at most (+ 1: V itself rounds up)
-    const size_t tile_blocks = (size_t)V / kTileRows + G + 1;
-    L.tile_z = take(tiles ? tile_blocks * M * kTileRows * sizeof(float) : 0);
-    L.tile_stat = take(tiles ? tile_blocks * M * sizeof(float2) : 0);
+    L.part_stride = (V + kChunkRows - 1) / kChunkRows + g;
+    const size_t lists = off;
+    L.part = take(staged * M * L.part_stride * k * sizeof(Cand));
+    L.lse_part = take(staged * M * L.part_stride * 2 * sizeof(float));     // log-probability mode
+    // A group's blocks round up: V / 128 + G blocks at most (dense: V itself rounds up).  On the
+    // general path the logits take the place of the staged kernels' lists, which no call uses
+    // with them.
+    const size_t after = off;
+    if (tiles == Tiles::kGeneral) off = lists;
+    const size_t tile_blocks = (size_t)V / kTileRows + G + (tiles == Tiles::kOwn || G == 0 ? 1 : 0);
+    L.tile_z = take(tiles != Tiles::kNone ? tile_blocks * M * kTileRows * sizeof(float) : 0);
+    L.tile_stat = take(tiles != Tiles::kNone ? tile_blocks * M * sizeof(float2) : 0);
+    if (off < after) off = after;
     L.total = off > pieces_end ? off : pieces_end;
     return L;
 }
@@ -275,6 +283,19 @@ struct LevelExpand {
     float* next_score;
 };
 
+// Enqueues the expansion of a level from the candidate lists in memory.
+coral_status launch_tree_expand(const LevelExpand& level, const int32_t* cand_ids, const float* cand_logp, int M, int k,
+                                hipStream_t stream) {
+    if (level.n_next <= kWave)
+        hipLaunchKernelGGL(k_tree_topk, dim3(1), dim3(kTreeWaves * kWave), 0, stream, level.parent_score, cand_ids,
+                           cand_logp, M, k, level.n_next, level.next_parent, level.next_token, level.next_score);
+    else
+        hipLaunchKernelGGL(k_tree_expand, dim3(M), dim3(kWave), (size_t)M * k * sizeof(unsigned long long), stream,
+                           level.parent_score, cand_ids, cand_logp, M, k, level.n_next, level.next_parent,
+                           level.next_token, level.next_score);
+    return launch_status();
+}
+
 // The single-launch log-probability mode's table of pieces: one (max, sum) per (batch of rows of
 // a selected group, token that selected it); a token's g groups are distinct, so their batches
 // number V / rows + g at most.  Rows beyond 8 KB (one to a batch): the table shares the memory of
@@ -384,10 +405,10 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
 // dominate and the vector path is faster).
 bool dense_prefers_tiles(int M, int V) { return M >= 8 && V >= 2 * kMaxWorkgroups * kTileRows; }
 
-// Matrix-core path: 16-bit storage, whole 512-column chunks, weights below 4 GiB, LDS plan within the limit.
-bool tiles_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_max_out, int* lds_out) {
-    if (!is_16bit(dt) || k > kMaxK || M > 64 || H % (kChunkVecs * 8) != 0) return false;
-    if ((unsigned long long)V * H * 2ull >= (1ull << 32)) return false;   // 32-bit weight offsets
+// Tile kernels: weights below 4 GiB, LDS plan within the limit.
+bool tile_kernels_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_max_out, int* lds_out) {
+    if (k > kMaxK || M > 64) return false;
+    if ((unsigned long long)V * H * (is_16bit(dt) ? 2ull : 4ull) >= (1ull << 32)) return false;   // 32-bit weight offsets
     long long um = (long long)M * g < G ? (long long)M * g : G;
     if (um < 1) um = 1;
     const TileLds T = tile_lds_layout((int)um);
@@ -400,19 +421,32 @@ bool tiles_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_
     return true;
 }
 
+// Matrix-core path proper: 16-bit storage and whole 512-column chunks as well.
+bool tiles_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_max_out, int* lds_out) {
+    return is_16bit(dt) && H % (kChunkVecs * 8) == 0 && tile_kernels_fit(M, H, V, G, g, k, dt, u_max_out, lds_out);
+}
+
 // Which path a call takes, decided in one place for the entry points and the path query.
 struct PathPlan {
-    int path;            // 0 staged, 1 single launch, 2 tiles, -1 none (the staged path's
+    int path;            // 0 general, 1 single launch, 2 tiles, -1 none (the staged kernels'
                          // token batch and lists do not fit LDS: rows beyond about 10 K values)
     int tile_umax, tile_lds;
+    bool tile_kernels;   // paths 0 and 2: the tile kernels run (path 0: else the staged ones)
 };
 
 bool staged_fits(int M, int jp, int k) {
     return logits_lds_bytes(M < kTokBatch ? M : kTokBatch, jp, k) <= (size_t)kLdsLimit;
 }
 
-PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt,
-                   bool logprob = false) {
+// The general path takes what the other two do not: fp32 rows beyond the single-launch kernel,
+// widths that are no multiple of 512, more than 64 groups with log-probabilities.  It runs the
+// tile kernels too, whose column tail is then guarded and whose fp32 form multiplies in full fp32
+// (v_mfma_f32_16x16x4_f32), wherever these fit; the staged kernels stay for what is left (weights
+// of 4 GiB and more, hundreds of activated groups).  The staged kernels stage eight tokens at a
+// time and read a group's rows again for every eight, and their last merge is one workgroup per
+// token over every chunk's list: fp32 H = 768, 58 tokens 319 us against 61 us here; 16-bit
+// H = 5432, 43 tokens, log-probabilities 529 against 160; 16-bit H = 1664, 40 tokens 97 against 35.
+PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob) {
     PathPlan pl = {};
     const int n_vec = H / (is_16bit(dt) ? 8 : 4);
     const int jp = (n_vec + kWave - 1) / kWave;
@@ -443,20 +477,32 @@ PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_d
     return pl;
 }
 
-// Whether a call with these sizes (grouped in either output mode, or dense when G = 0) can
-// take the matrix-core path: the workspace then holds its logits buffer and span lists.
-bool layout_has_tiles(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
-    if (!dtype_ok(dt) || H % (is_16bit(dt) ? 8 : 4) != 0) return false;
-    if (plan_path(true, M, H, V, 0, 0, k, dt).path == 2) return true;
-    if (G < 1) return false;
-    return plan_path(false, M, H, V, G, g, k, dt).path == 2 ||
-           plan_path(false, M, H, V, G, g, k, dt, true).path == 2;
+PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob = false) {
+    PathPlan pl = plan_path_kind(dense, M, H, V, G, g, k, dt, logprob);
+    pl.tile_kernels = pl.path == 2 || (pl.path == 0 && tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt,
+                                                                        &pl.tile_umax, &pl.tile_lds));
+    return pl;
+}
+
+// Whether a call with these sizes (grouped in either output mode, or dense when G = 0) can run
+// the tile kernels: the workspace then holds their logits buffer.
+Tiles layout_tiles(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
+    if (!dtype_ok(dt) || H % (is_16bit(dt) ? 8 : 4) != 0) return Tiles::kNone;
+    const PathPlan plans[3] = {plan_path(true, M, H, V, 0, 0, k, dt),
+                               G < 1 ? PathPlan{-1} : plan_path(false, M, H, V, G, g, k, dt),
+                               G < 1 ? PathPlan{-1} : plan_path(false, M, H, V, G, g, k, dt, true)};
+    Tiles t = Tiles::kNone;
+    for (const PathPlan& p : plans) {
+        if (p.path == 2) return Tiles::kOwn;
+        if (p.path == 0 && p.tile_kernels) t = Tiles::kGeneral;
+    }
+    return t;
 }
 
 // Enqueues k_tiles and the ranking of the logits it leaves.  For the grouped head the gate
 // and selection kernel must already be enqueued (selection, the token tiles' masks; in the
 // log-probability mode log p_router of the selection too).
-coral_status launch_tiles(bool dense, const void* hidden, const void* lm_W,
+coral_status launch_tiles(bool dense, bool general, const void* hidden, const void* lm_W,
                           const coral_group_index* gi, int M, int H, int V,
                           int G, int k, coral_dtype dt, int u_max, int lds, int32_t* topk_ids,
                           float* topk_out, char* ws, const Layout& L, hipStream_t stream,
@@ -478,11 +524,12 @@ coral_status launch_tiles(bool dense, const void* hidden, const void* lm_W,
     p.want_lse = logprob ? 1 : 0;
     p.next_block = reinterpret_cast<unsigned int*>(ws + L.ctrl) + coral_ctrl::kTileQueue;
     p.M = M; p.V = V; p.G = G;
-    p.n_vec = H / 8;
+    p.n_vec = H / (is_16bit(dt) ? 8 : 4);
     p.n_chunks = (p.n_vec + kChunkVecs - 1) / kChunkVecs;
     p.u_max = u_max;
     typedef void (*tiles_fn)(TileParams, int);
-    const tiles_fn fn = dt == CORAL_F16 ? k_tiles<kF16> : k_tiles<kBF16>;
+    const tiles_fn fn = general ? CORAL_PICK_DT(dt, (k_tiles<kF32, true>), (k_tiles<kBF16, true>), (k_tiles<kF16, true>))
+                                : dt == CORAL_F16 ? k_tiles<kF16, false> : k_tiles<kBF16, false>;
     if (!allow_lds(reinterpret_cast<const void*>(fn), lds)) return CORAL_ERR_HIP;
     coral_status st;
     if ((st = launch_timed(fn, dim3(P), dim3(kTileBlock), lds, stream, ev_before, ev_after, p, dense ? 1 : 0)) !=
@@ -586,7 +633,7 @@ extern "C" size_t coral_lmhead_workspace_bytes(int M, int H, int V, int G, int g
                                                coral_dtype dt) {
     if (!sizes_ok(M, H, V, G, g, k)) return 0;
     return make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt),
-                       layout_has_tiles(M, H, V, G, g, k, dt)).total;
+                       layout_tiles(M, H, V, G, g, k, dt)).total;
 }
 
 extern "C" int coral_lmhead_path(int dense, int M, int H, int V, int G, int g, int k,
@@ -656,16 +703,23 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
     // only those of the path that this very call takes; rows beyond 8 KB are taken or refused by
     // what the multi-kernel path for them would need)
     Layout L;
+    bool static_general = false;
     if (!static_workspace) {
-        L = make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt), layout_has_tiles(M, H, V, G, g, k, dt));
+        L = make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt), layout_tiles(M, H, V, G, g, k, dt));
     } else {
         const PathPlan sp = plan_path(false, M, H, V, G, g, k, dt);
         const bool long_rows = sp.path == 1 && (size_t)H * (is_16bit(dt) ? 2 : 4) > 8192;
         int um, lds;
         const bool tiles = sp.path == 2 || (long_rows && tiles_fit(M, H, V, G, g, k, dt, &um, &lds));
-        L = make_layout(M, V, G, g, k, Pieces{}, tiles, tiles ? LayoutFor::kTiles : LayoutFor::kWorkspace);
+        L = make_layout(M, V, G, g, k, Pieces{}, tiles ? Tiles::kOwn : Tiles::kNone,
+                        tiles ? LayoutFor::kTiles : LayoutFor::kWorkspace);
         if (long_rows && L.total <= kStaticScratchBytes)
-            L = make_layout(M, V, G, g, k, Pieces{}, false, LayoutFor::kSingleLaunch);
+            L = make_layout(M, V, G, g, k, Pieces{}, Tiles::kNone, LayoutFor::kSingleLaunch);
+        if (sp.path == 0 && sp.tile_kernels && L.total <= kStaticScratchBytes) {
+            const Layout T = make_layout(M, V, G, g, k, Pieces{}, Tiles::kGeneral, LayoutFor::kTiles);
+            static_general = T.total <= kStaticScratchBytes;      // else the staged kernels, whose lists are smaller
+            if (static_general) L = T;
+        }
     }
     if (static_workspace) {
         if (logprob || L.total > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;
@@ -681,6 +735,7 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
         if (2 * max_union(M, G, g) > (cu < kMaxWorkgroups ? cu : kMaxWorkgroups))
             plan.path = staged_fits(M, ((H / (is_16bit(dt) ? 8 : 4)) + kWave - 1) / kWave, k) ? 0 : -1;
     }
+    if (static_workspace && plan.path == 0) plan.tile_kernels = static_general;
     if (plan.path < 0) return CORAL_ERR_UNSUPPORTED;       // before anything is enqueued
     if (static_workspace) {
         // this device's copy of the array; its control words are cleared by a fill kernel on
@@ -706,7 +761,7 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
     const uint4* hid = static_cast<const uint4*>(hidden);
     const uint4* ghid = static_cast<const uint4*>(gate_hidden);
     const uint4* gw = static_cast<const uint4*>(gate_W);
-    if (plan.path == 2) {
+    if (plan.tile_kernels) {
         GateSelParams q = {};
         q.hidden = ghid; q.gate_W = gw; q.bias = gate_bias; q.s = s; q.sel = sel;
         q.tile_mask = reinterpret_cast<unsigned long long*>(ws + L.tile_mask);
@@ -715,17 +770,14 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
         if (logprob) q.logp_sel = reinterpret_cast<float*>(ws + L.logp_sel);
         const int tiles = ((G + 15) / 16) * ((M + 15) / 16);
         typedef void (*gate_select_fn)(GateSelParams);
-        const gate_select_fn gs = dt == CORAL_F16 ? k_gate_select<kF16> : k_gate_select<kBF16>;
+        const gate_select_fn gs = CORAL_PICK_DT(dt, k_gate_select<kF32>, k_gate_select<kBF16>, k_gate_select<kF16>);
         hipLaunchKernelGGL(gs, dim3(tiles, kGateParts), dim3(kFusedBlock), 0, stream, q);
         if ((st = launch_status()) != CORAL_OK) return st;
-        st = launch_tiles(false, hidden, lm_W, gi, M, H, V, G, k, dt,
+        st = launch_tiles(false, plan.path == 0, hidden, lm_W, gi, M, H, V, G, k, dt,
                           plan.tile_umax, plan.tile_lds, topk_ids, topk_logits, ws, L, stream, ev_before,
                           ev_after, sel, g, logprob);
         if (st != CORAL_OK || !level) return st;
-        hipLaunchKernelGGL(k_tree_expand, dim3(M), dim3(kWave), (size_t)M * k * sizeof(unsigned long long),
-                           stream, level->parent_score, topk_ids, topk_logits, M, k, level->n_next,
-                           level->next_parent, level->next_token, level->next_score);
-        return launch_status();
+        return launch_tree_expand(*level, topk_ids, topk_logits, M, k, stream);
     }
     typedef void (*gate_fn)(const uint4*, const uint4*, const float*, int, int, int, float*);
     const gate_fn gate_kernel = CORAL_PICK_DT(dt, k_gate<kF32>, k_gate<kBF16>, k_gate<kF16>);
@@ -776,10 +828,7 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
                            gi->group_offsets, g, 0, k, topk_ids, topk_logits);
     if ((st = launch_status()) != CORAL_OK || !level) return st;
     // draft-level call on the multi-kernel path: the expansion is one more launch
-    hipLaunchKernelGGL(k_tree_expand, dim3(M), dim3(kWave), (size_t)M * k * sizeof(unsigned long long),
-                       stream, level->parent_score, topk_ids, topk_logits, M, k, level->n_next,
-                       level->next_parent, level->next_token, level->next_score);
-    return launch_status();
+    return launch_tree_expand(*level, topk_ids, topk_logits, M, k, stream);
 }
 
 coral_status dense_impl(const void* hidden, const void* lm_W, int M, int H, int V, int k,
@@ -789,7 +838,7 @@ coral_status dense_impl(const void* hidden, const void* lm_W, int M, int H, int 
     coral_status st = check_common(hidden, lm_W, M, H, V, k, dt, topk_ids, topk_logits);
     if (st != CORAL_OK) return st;
     if (k > V) return CORAL_ERR_SHAPE;
-    const Layout L = make_layout(M, V, 0, 0, k, Pieces{}, layout_has_tiles(M, H, V, 0, 0, k, dt));
+    const Layout L = make_layout(M, V, 0, 0, k, Pieces{}, layout_tiles(M, H, V, 0, 0, k, dt));
     st = check_workspace(workspace, workspace_bytes, L.total);
     if (st != CORAL_OK) return st;
 
@@ -798,8 +847,8 @@ coral_status dense_impl(const void* hidden, const void* lm_W, int M, int H, int 
     const PathPlan plan = plan_path(true, M, H, V, 0, 0, k, dt);
     if (plan.path < 0) return CORAL_ERR_UNSUPPORTED;
     // many tokens per row: the contraction is no longer cheap on the vector units
-    if (plan.path == 2)
-        return launch_tiles(true, hidden, lm_W, nullptr, M, H, V, 0, k, dt,
+    if (plan.tile_kernels)
+        return launch_tiles(true, plan.path == 0, hidden, lm_W, nullptr, M, H, V, 0, k, dt,
                             plan.tile_umax, plan.tile_lds, topk_ids, topk_logits, ws, L, stream,
                             ev_before, ev_after);
     if (plan.path == 1)
@@ -885,11 +934,8 @@ extern "C" coral_status coral_tree_expand(const float* parent_score, const int32
     if (M < 1 || k < 1 || n_next < 1) return CORAL_ERR_SHAPE;
     if (M > kMaxM || k > kMaxK) return CORAL_ERR_UNSUPPORTED;
     if (n_next > M * k) return CORAL_ERR_SHAPE;
-    hipLaunchKernelGGL(k_tree_expand, dim3(M), dim3(kWave), (size_t)M * k * sizeof(unsigned long long),
-                       static_cast<hipStream_t>(hip_stream),
-                       parent_score, cand_ids, cand_logp, M, k, n_next, next_parent, next_token,
-                       next_score);
-    return launch_status();
+    const LevelExpand level = {parent_score, n_next, next_parent, next_token, next_score};
+    return launch_tree_expand(level, cand_ids, cand_logp, M, k, static_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" coral_status coral_router_premix(const void* hidden, const void* W1, int M, int H,

@@ -86,9 +86,17 @@ __device__ __forceinline__ float dot_vec(uint4 w, uint4 h, float acc) {
 
 // One 16x16 tile step of 32 columns on the matrix cores: lane l feeds row l%16, columns
 // 8*(l/16)..+8 of both operands (eight 16-bit values each) and holds rows 4*(l/16)..+4,
-// column l%16 of the result.
+// column l%16 of the result.  fp32: a 16-byte vector holds four columns, so the step is four
+// products of four columns each (lane l feeds column l/16 of a product: the same component of
+// both operands' vectors, in full fp32).
 template <int DT>
 __device__ __forceinline__ f32x4_t mfma_tile(uint4 a, uint4 b, f32x4_t acc) {
+    if (DT == kF32) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+    }
     if (DT == kF16)
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a),
                                                       __builtin_bit_cast(f16x8_t, b), acc, 0, 0, 0);

@@ -1120,6 +1120,18 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         auto expand_level = [&]() {                    // called by every thread of the workgroup
             if (!expand) return;
             __syncthreads();
+            if (p.n_next <= kWave) {                   // uniform
+                tree_topk(
+                    M * k, p.n_next, reinterpret_cast<unsigned long long*>(lds + lay.o_hidden),
+                    [&](int e) { return tree_keys[e]; },
+                    [&](int r, unsigned long long key) {
+                        const int e = key_id(key);     // (of a real key)
+                        p.next_parent[r] = key != 0ull ? div_small(e, inv_small(k)) : -1;
+                        p.next_token[r] = key != 0ull ? tree_ids[e] : -1;
+                        p.next_score[r] = key != 0ull ? tree_scores[e] : -INFINITY;
+                    });
+                return;
+            }
             for (int m = wave; m < M; m += kFusedWaves) {
                 int e;
                 bool keep;

@@ -1,6 +1,7 @@
-// General path: one launch per stage (gate, selection, chunked weight streaming with
-// per-workgroup partial top-k, per-token merge).  Handles every supported shape; used
-// when the single-launch path's LDS budget does not fit.
+// General path, staged kernels: one launch per stage (gate, selection, chunked weight streaming
+// with per-workgroup partial top-k, per-token merge).  Handles every supported shape; used when
+// neither the single-launch path's LDS budget nor the tile kernels' limits (weights below 4 GiB,
+// a few hundred activated groups) fit.
 #pragma once
 #include "device_utils.h"
 #include "fused_path.h"

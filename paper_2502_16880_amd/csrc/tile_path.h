@@ -100,11 +100,13 @@ struct TileStage {                                     // staging registers, 2 N
     uint4 r0, r1, r2, r3, r4, r5, r6, r7;
 };
 
-template <int NCT>
+template <int NCT, bool GENERAL>
 __device__ __forceinline__ void tile_fetch_hidden(const TileParams& p, const int* tokslot, int n_t,
                                                   TileStage& hst, int c, int lane, int wave) {
     constexpr int kN = 2 * NCT;
-    const uint4* src = p.hidden + c * kChunkVecs + lane;
+    // (past the row's end, in the last chunk: the row's last vector, stored as zero)
+    const int last = p.n_vec - 1 - c * kChunkVecs;
+    const uint4* src = p.hidden + c * kChunkVecs + (GENERAL && lane > last ? last : lane);
     // token of slot wave + 8 i (wave-uniform); slots past the group's tokens repeat its last
     auto tok = [&](int i) {
         const int s = wave + i * kTileWaves;
@@ -119,53 +121,108 @@ __device__ __forceinline__ void tile_fetch_hidden(const TileParams& p, const int
     if (kN > 6) hst.r6 = load_vec(src + tok(6) * p.n_vec);
     if (kN > 7) hst.r7 = load_vec(src + tok(7) * p.n_vec);
 }
-template <int NCT>
-__device__ __forceinline__ void tile_store_hidden(const TileStage& hst, uint4* hbuf, int c, int lane,
+template <int NCT, bool GENERAL>
+__device__ __forceinline__ void tile_store_hidden(int n_vec, const TileStage& hst, uint4* hbuf, int c, int lane,
                                                   int wave) {
     constexpr int kN = 2 * NCT;
     uint4* dst = hbuf + (size_t)(c & 1) * kHbBufVecs + (size_t)wave * kHbStride + lane;
-    if (kN > 0) store_vec(dst + 0 * kTileWaves * kHbStride, hst.r0);
-    if (kN > 1) store_vec(dst + 1 * kTileWaves * kHbStride, hst.r1);
-    if (kN > 2) store_vec(dst + 2 * kTileWaves * kHbStride, hst.r2);
-    if (kN > 3) store_vec(dst + 3 * kTileWaves * kHbStride, hst.r3);
-    if (kN > 4) store_vec(dst + 4 * kTileWaves * kHbStride, hst.r4);
-    if (kN > 5) store_vec(dst + 5 * kTileWaves * kHbStride, hst.r5);
-    if (kN > 6) store_vec(dst + 6 * kTileWaves * kHbStride, hst.r6);
-    if (kN > 7) store_vec(dst + 7 * kTileWaves * kHbStride, hst.r7);
+    if (GENERAL && c * kChunkVecs + lane >= n_vec) {    // past the row's end
+#pragma unroll
+        for (int i = 0; i < kN; ++i) store_vec(dst + i * kTileWaves * kHbStride, make_uint4(0, 0, 0, 0));
+    } else {
+        if (kN > 0) store_vec(dst + 0 * kTileWaves * kHbStride, hst.r0);
+        if (kN > 1) store_vec(dst + 1 * kTileWaves * kHbStride, hst.r1);
+        if (kN > 2) store_vec(dst + 2 * kTileWaves * kHbStride, hst.r2);
+        if (kN > 3) store_vec(dst + 3 * kTileWaves * kHbStride, hst.r3);
+        if (kN > 4) store_vec(dst + 4 * kTileWaves * kHbStride, hst.r4);
+        if (kN > 5) store_vec(dst + 5 * kTileWaves * kHbStride, hst.r5);
+        if (kN > 6) store_vec(dst + 6 * kTileWaves * kHbStride, hst.r6);
+        if (kN > 7) store_vec(dst + 7 * kTileWaves * kHbStride, hst.r7);
+    }
+}
+
+// This lane's vector of step pair sp of chunk c, counted from the row's start.
+__device__ __forceinline__ int tile_lane_vec(int c, int sp) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    return c * kChunkVecs + sp * 8 + (wave % kTileSplit) * (kChunkVecs / kTileSplit) +
+           line_load_chunk(threadIdx.x & (kWave - 1));
 }
 
 // The 128-byte line of step pair sp of chunk c in the lane's row at byte offset `row` of
-// the weight matrix (offsets are 32-bit: the path takes matrices below 4 GiB).
+// the weight matrix (offsets are 32-bit: the path takes matrices below 4 GiB).  GENERAL: `row` is
+// the row's start, and lanes past its end read its last vector (dropped in tile_step_pair);
+// otherwise the lane's place in a chunk is part of `row`.
+template <bool GENERAL>
 __device__ __forceinline__ uint4 tile_load_w(const TileParams& p, unsigned row, int c, int sp) {
-    const unsigned off = row + (unsigned)(c * kChunkVecs + sp * 8) * 16u;
+    unsigned off;
+    if (GENERAL) {
+        const int vec = tile_lane_vec(c, sp);
+        off = row + (unsigned)(vec < p.n_vec ? vec : p.n_vec - 1) * 16u;
+    } else {
+        off = row + (unsigned)(c * kChunkVecs + sp * 8) * 16u;
+    }
     return load_stream(reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(p.lm_W) + off));
 }
 
 // Step pair SP of a chunk: the two 32-column steps whose weight lines sit in ring slots
 // 4 SP .. 4 SP + 3.
-template <int DT, int NCT, bool REFILL, int SP>
+template <int DT, int NCT, bool REFILL, int SP, bool GENERAL>
 __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4 (&a)[kRing],
-                                               f32x4_t (&acc)[2][4], const unsigned (&wrow)[4],
+                                               f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
+                                               const unsigned (&wrow)[4],
                                                uint4* hbuf, TileStage& hst, uint4* my_slice) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int r16 = lane & 15, q4 = lane >> 4;
     const int kq = wave % kTileSplit;
     const uint4* hb = hbuf + (size_t)(c & 1) * kHbBufVecs;
+    if (GENERAL && !REFILL) {                           // the last chunk: nothing past the row's end
+        const unsigned in = tile_lane_vec(c, SP) < p.n_vec ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int o = 0; o < 4; ++o)
+            a[SP * 4 + o] = make_uint4(a[SP * 4 + o].x & in, a[SP * 4 + o].y & in, a[SP * 4 + o].z & in, a[SP * 4 + o].w & in);
+    }
     uint4 op[2][2];                                    // [row tile][step of the pair]
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         mfma_operands_from_lines(a[SP * 4 + 2 * t], a[SP * 4 + 2 * t + 1], lane, my_slice, op[t][0],
                                  op[t][1]);
         if (REFILL) {                                  // refill the two slots just consumed
-            a[SP * 4 + 2 * t] = tile_load_w(p, wrow[2 * t], c + 1, SP);
-            a[SP * 4 + 2 * t + 1] = tile_load_w(p, wrow[2 * t + 1], c + 1, SP);
+            a[SP * 4 + 2 * t] = tile_load_w<GENERAL>(p, wrow[2 * t], c + 1, SP);
+            a[SP * 4 + 2 * t + 1] = tile_load_w<GENERAL>(p, wrow[2 * t + 1], c + 1, SP);
         }
     }
     if (REFILL) keep_memory_order();
-    if (REFILL && SP == 3) {                           // the other buffer is free since the last barrier
-        tile_store_hidden<NCT>(hst, hbuf, c + 1, lane, wave);
+    if (REFILL && SP == 3 && !GENERAL) {             // the other buffer is free since the last barrier
+        tile_store_hidden<NCT, GENERAL>(p.n_vec, hst, hbuf, c + 1, lane, wave);
         keep_memory_order();
+    }
+    if (GENERAL) {
+        // One running fp32 sum over a row's hundreds of products would be less exact than the
+        // staged kernels' lane-split sums (fp32, 2048 columns: 4e-7 against 7e-8).  So the step
+        // pair's products start from zero and are added to the running sum with their rounding
+        // error kept (two-sum).  (The barrier: reading several operands ahead, as the compiler
+        // would, costs more registers than there are.)
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct) {
+            f32x4_t x[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2) {
+                const uint4 hv = hb[(ct * 16 + r16) * kHbStride + (kq * 8 + 2 * SP + s2) * 4 + q4];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) x[t] = mfma_tile<DT>(op[t][s2], hv, x[t]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float hi = acc[t][ct][i], sum = hi + x[t][i], back = sum - hi;
+                    low[t][ct][i] += (hi - (sum - back)) + (x[t][i] - back);
+                    acc[t][ct][i] = sum;
+                }
+        }
+        return;
     }
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
@@ -180,29 +237,39 @@ __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4
     }
 }
 
-template <int DT, int NCT, bool REFILL>
+template <int DT, int NCT, bool REFILL, bool GENERAL>
 __device__ __forceinline__ void tile_chunk(const TileParams& p, int c, uint4 (&a)[kRing],
-                                           f32x4_t (&acc)[2][4], const unsigned (&wrow)[4],
+                                           f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
+                                           const unsigned (&wrow)[4],
                                            uint4* hbuf, const int* tokslot, int n_t, uint4* my_slice) {
     TileStage hst;
     // (the scheduling barriers keep the compiler from sinking the loads to where their
     // registers are first needed, which would undo the ordering)
-    if (REFILL) {
-        tile_fetch_hidden<NCT>(p, tokslot, n_t, hst, c + 1, threadIdx.x & (kWave - 1),
-                               __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
-        keep_memory_order();
-    }
-    tile_step_pair<DT, NCT, REFILL, 0>(p, c, a, acc, wrow, hbuf, hst, my_slice);
-    tile_step_pair<DT, NCT, REFILL, 1>(p, c, a, acc, wrow, hbuf, hst, my_slice);
-    tile_step_pair<DT, NCT, REFILL, 2>(p, c, a, acc, wrow, hbuf, hst, my_slice);
-    tile_step_pair<DT, NCT, REFILL, 3>(p, c, a, acc, wrow, hbuf, hst, my_slice);
+    // General form: no registers for the next hidden vectors through all of the chunk, they are
+    // requested before the last step pair and written behind it.
+    auto fetch = [&]() {
+        if (REFILL) {
+            tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, hst, c + 1, threadIdx.x & (kWave - 1),
+                                           __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+            keep_memory_order();
+        }
+    };
+    if (!GENERAL) fetch();
+    tile_step_pair<DT, NCT, REFILL, 0, GENERAL>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    tile_step_pair<DT, NCT, REFILL, 1, GENERAL>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    tile_step_pair<DT, NCT, REFILL, 2, GENERAL>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    if (GENERAL) fetch();
+    tile_step_pair<DT, NCT, REFILL, 3, GENERAL>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    if (GENERAL && REFILL)
+        tile_store_hidden<NCT, GENERAL>(p.n_vec, hst, hbuf, c + 1, threadIdx.x & (kWave - 1),
+                                       __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
     __syncthreads();
 }
 
 // The K loop of one block.  Hidden chunk staging: slots wave, wave + 8, ... below 16 NCT;
 // lane = vector inside the chunk; slots past the group's tokens repeat its last token
 // (their columns of the tiles are never read back).
-template <int DT, int NCT>
+template <int DT, int NCT, bool GENERAL>
 __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRing], f32x4_t (&acc)[2][4],
                                             const unsigned (&wrow)[4], uint4* hbuf,
                                             const int* tokslot, uint4* my_slice, int n_t) {
@@ -210,16 +277,30 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     {
         TileStage hst;
-        tile_fetch_hidden<NCT>(p, tokslot, n_t, hst, 0, lane, wave);
-        tile_store_hidden<NCT>(hst, hbuf, 0, lane, wave);
+        tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, hst, 0, lane, wave);
+        tile_store_hidden<NCT, GENERAL>(p.n_vec, hst, hbuf, 0, lane, wave);
     }
     __syncthreads();
+    f32x4_t low[2][4];                                 // (general form) what the running sums have rounded off
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) low[t][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     for (int c = 0; c + 1 < p.n_chunks; ++c)
-        tile_chunk<DT, NCT, true>(p, c, a, acc, wrow, hbuf, tokslot, n_t, my_slice);
-    tile_chunk<DT, NCT, false>(p, p.n_chunks - 1, a, acc, wrow, hbuf, tokslot, n_t, my_slice);
+        tile_chunk<DT, NCT, true, GENERAL>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+    tile_chunk<DT, NCT, false, GENERAL>(p, p.n_chunks - 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+    if (GENERAL) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) acc[t][ct] += low[t][ct];
+    }
 }
 
-template <int DT>
+// GENERAL: the general path's form: any storage type, rows of any number of 16-byte vectors (the
+// last chunk partly filled, loads and operands past a row's end guarded) and sums as exact as the
+// staged kernels'.  Otherwise 16-bit storage and whole chunks.
+template <int DT, bool GENERAL>
 __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     extern __shared__ uint4 smem[];
     char* lds = reinterpret_cast<char*>(smem);
@@ -345,16 +426,15 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         }
     };
     // Ring slot sp * 4 + o holds, of the current chunk, octet o's 128-byte line of the step
-    // pair sp (steps kq * 8 + 2 sp and + 1 of the chunk).  H is a multiple of 512 on this
-    // path, so every chunk is whole and the loads need no guards.
+    // pair sp (steps kq * 8 + 2 sp and + 1 of the chunk).
     uint4 a[kRing];
     unsigned wrow[4];                                  // byte offsets of this lane's rows at its place in a chunk
     auto set_rows = [&](const int (&rid)[4]) {
 #pragma unroll
         for (int o = 0; o < 4; ++o)
-            wrow[o] = ((unsigned)rid[o] * (unsigned)p.n_vec + kq * 32 + line_load_chunk(lane)) * 16u;
+            wrow[o] = ((unsigned)rid[o] * (unsigned)p.n_vec + (GENERAL ? 0 : kq * 32 + line_load_chunk(lane))) * 16u;
     };
-    auto load_a = [&](int c, int sp, int o) { a[sp * 4 + o] = tile_load_w(p, wrow[o], c, sp); };
+    auto load_a = [&](int c, int sp, int o) { a[sp * 4 + o] = tile_load_w<GENERAL>(p, wrow[o], c, sp); };
 
     int b = uni(flags[1]);
     int first = 0, end = 0;
@@ -369,14 +449,21 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
 #pragma unroll
             for (int o = 0; o < 4; ++o) load_a(0, sp, o);
     }
+    // General form: the running sums' rounding errors take the registers of two token tiles, so a
+    // block serves 32 tokens at a time and comes round again for the next 32.
+    constexpr bool kPasses = GENERAL;
+    constexpr int kPassTokens = kPasses ? 32 : kMaxM;
+    int s0 = 0;                                        // first token slot of this pass
     while (b < total_blocks) {                         // block-uniform
-        if (threadIdx.x == 0)                          // the draw returns long before the K loop ends
+        const bool last_pass = !kPasses || s0 + kPassTokens >= __popcll(bm);
+        if (threadIdx.x == 0 && last_pass)             // the draw returns long before the K loop ends
             drawn = __hip_atomic_fetch_add(p.next_block, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int n_t = __popcll(bm);
+        const int n_t = kPasses ? min(__popcll(bm) - s0, kPassTokens) : __popcll(bm);
         const int n_ct = (n_t + 15) >> 4;
         if (wave == 0) {                               // token of every slot
             const bool on = (bm >> lane) & 1ull;
-            if (on) tokslot[__popcll(bm & ((1ull << lane) - 1ull))] = lane;
+            const int slot = __popcll(bm & ((1ull << lane) - 1ull)) - (kPasses ? s0 : 0);
+            if (on && (!kPasses || slot >= 0)) tokslot[slot] = lane;   // (slots past this pass's are not read)
         }
         __syncthreads();
 
@@ -386,24 +473,36 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
 #pragma unroll
             for (int ct = 0; ct < 4; ++ct) acc[t][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-        switch (n_ct) {                                    // block-uniform
-            case 1: tile_k_loop<DT, 1>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
-            case 2: tile_k_loop<DT, 2>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
-            case 3: tile_k_loop<DT, 3>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
-            default: tile_k_loop<DT, 4>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+        if constexpr (GENERAL) {
+            if (n_ct == 1) tile_k_loop<DT, 1, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);   // block-uniform
+            else tile_k_loop<DT, 2, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
+        } else {
+            switch (n_ct) {                                // block-uniform
+                case 1: tile_k_loop<DT, 1, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+                case 2: tile_k_loop<DT, 2, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+                case 3: tile_k_loop<DT, 3, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+                default: tile_k_loop<DT, 4, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+            }
         }
 
         // next block: locate it and start its first 16 weight loads before the epilogue
         // (flags[1] was last read before this block's barriers)
-        if (threadIdx.x == 0) flags[1] = (int)drawn;
+        if (threadIdx.x == 0 && last_pass) flags[1] = (int)drawn;
         __syncthreads();
-        const int nb = uni(flags[1]);
+        const int nb = last_pass ? uni(flags[1]) : b;
         int nfirst = 0, nend = 0;
         unsigned long long nbm = 0ull;
+        if (kPasses && !last_pass) {
+            nfirst = first;
+            nend = end;
+            nbm = bm;
+        }
         if (nb < total_blocks) {
-            locate(nb, nfirst, nend, nbm);
-            my_rows(nfirst, nend, rid);
-            set_rows(rid);
+            if (last_pass) {
+                locate(nb, nfirst, nend, nbm);
+                my_rows(nfirst, nend, rid);
+                set_rows(rid);
+            }
 #pragma unroll
             for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
@@ -430,7 +529,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         // kernel reads the logits only of blocks whose largest can matter.  Log-probability
         // mode: the sum of exp(z - largest) as well, the block's piece of the group's lse.
         for (int s = wave; s < n_t; s += kTileWaves) {
-            float* dst = p.z + ((size_t)b * M + s) * kTileRows + lane;
+            float* dst = p.z + ((size_t)b * M + (kPasses ? s0 : 0) + s) * kTileRows + lane;
             float zs[2];
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf) {
@@ -448,9 +547,10 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
             float sum = 0.f;
             if (p.want_lse)                            // block-uniform
                 sum = wave_sum(wm > -INFINITY ? expf(zs[0] - wm) + expf(zs[1] - wm) : 0.f);
-            if (lane == 0) p.stat[(size_t)b * M + s] = make_float2(wm, sum);
+            if (lane == 0) p.stat[(size_t)b * M + (kPasses ? s0 : 0) + s] = make_float2(wm, sum);
         }
         __syncthreads();
+        if (kPasses) s0 = last_pass ? 0 : s0 + kPassTokens;
         b = nb;
         first = nfirst;
         end = nend;
@@ -478,7 +578,7 @@ struct GateSelParams {
     unsigned int* counters;                 // [token tiles] arrival counters, zero between calls
     int M, G, g, n_vec;
     float* logp_sel;                        // [M, g] out: log p_router of the selected group
-                                            // (log-probability mode, G <= 64), else null
+                                            // (log-probability mode), else null
 };
 
 __device__ __forceinline__ float load_score(const float* p) {
@@ -489,7 +589,7 @@ template <int DT>
 __global__ __launch_bounds__(kFusedBlock) void k_gate_select(GateSelParams p) {
     __shared__ __attribute__((aligned(16))) float part[kFusedWaves][kGateTileFloats];
     __shared__ unsigned long long mask[kMaxG];
-    __shared__ unsigned long long sel_keys[kFusedWaves][kWave];
+    __shared__ __attribute__((aligned(16))) unsigned long long sel_keys[kFusedWaves][kWave];
     __shared__ int is_last;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -582,23 +682,66 @@ __global__ __launch_bounds__(kFusedBlock) void k_gate_select(GateSelParams p) {
             }
         }
     } else {
-        const int n_tok = p.M - tt * 16 < 16 ? p.M - tt * 16 : 16;
-        for (int idx = threadIdx.x; idx < n_tok * p.G; idx += kFusedBlock) {
-            const int tm = tt * 16 + idx / p.G;
-            const int gn = idx - (idx / p.G) * p.G;
-            float v = score(tm, gn);
-            if (!(v == v)) v = -INFINITY;
-            int rank = 0;
-            for (int o = 0; o < p.G; ++o) {
-                float ov = score(tm, o);
-                if (!(ov == ov)) ov = -INFINITY;
-                rank += better(ov, o, v, gn) ? 1 : 0;
+        // more groups than lanes: one wave per token, up to 16 scores per lane, the g best cut out
+        // by bisection and ranked among themselves.  (Counting over all pairs of groups, every
+        // score read back from memory, took 20 us and more.)
+        auto select_token = [&](auto regs) {
+            constexpr int N = decltype(regs)::value;
+            const int tm = tt * 16 + wave;
+            if (tm >= p.M) return;                     // wave-uniform
+            float v[N];
+            unsigned long long key[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int n = i * kWave + lane;
+                v[i] = score(tm, n < p.G ? n : p.G - 1);
             }
-            if (rank < p.g) {
-                atomicOr(&mask[gn], 1ull << tm);
-                p.sel[tm * p.g + rank] = gn;
+            float top = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int n = i * kWave + lane;
+                if (!(v[i] == v[i])) v[i] = -INFINITY;
+                if (n >= p.G) v[i] = -INFINITY;
+                key[i] = n < p.G ? cand_key(v[i], n) : 0ull;
+                top = fmaxf(top, v[i]);
             }
-        }
+            float lse_s = 0.f;
+            if (p.logp_sel) {                          // the router's softmax over all G scores (Eq. 7)
+                const float smax = wave_max(top);
+                float sum = 0.f;
+#pragma unroll
+                for (int i = 0; i < N; ++i) sum += i * kWave + lane < p.G ? expf(v[i] - smax) : 0.f;
+                lse_s = smax + logf(wave_sum(sum));
+            }
+            auto chosen = [&](int rank, int n, float s) {
+                atomicOr(&mask[n], 1ull << tm);
+                p.sel[tm * p.g + rank] = n;
+                if (p.logp_sel) p.logp_sel[tm * p.g + rank] = s - lse_s;
+            };
+            if (p.g <= kWave) {                        // uniform
+                wave_topk<N>(key, p.g, lane, sel_keys[wave],
+                             [&](int rank, unsigned long long kk) { chosen(rank, key_id(kk), key_value(kk)); });
+            } else {
+                int rank[N];
+#pragma unroll
+                for (int i = 0; i < N; ++i) rank[i] = 0;
+#pragma unroll
+                for (int o = 0; o < N; ++o)
+                    for (int l = 0; l < kWave; ++l) {  // wave-uniform
+                        const unsigned long long other =
+                            ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(key[o] >> 32), l) << 32) |
+                            (unsigned)__builtin_amdgcn_readlane((int)(unsigned)key[o], l);
+#pragma unroll
+                        for (int i = 0; i < N; ++i) rank[i] += other > key[i] ? 1 : 0;
+                    }
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+                    if (key[i] != 0ull && rank[i] < p.g) chosen(rank[i], i * kWave + lane, v[i]);
+            }
+        };
+        if (p.G <= 2 * kWave) select_token(std::integral_constant<int, 2>());          // uniform
+        else if (p.G <= 4 * kWave) select_token(std::integral_constant<int, 4>());
+        else select_token(std::integral_constant<int, 16>());
     }
     __syncthreads();
     for (int g0 = threadIdx.x; g0 < p.G; g0 += kFusedBlock) p.tile_mask[(size_t)tt * p.G + g0] = mask[g0];

@@ -84,3 +84,39 @@ def test_equal_logits_in_the_single_launch_kernel(coral):
         hidden = np.zeros((2, 512), np.uint16)
         check_grouped(dh, hidden, 2, k, run_grouped(coral, dh, hidden, 2, k))
         check_dense(dh, hidden, k, run_dense(coral, dh, hidden, k))
+
+
+# The general path's tile kernels: widths that leave the last 512-column (fp32: 256-column) chunk
+# partly filled, by one 16-byte vector up to one short of whole; one to four token tiles; fp32.
+GENERAL = [("bf16", 4104, 9), ("f16", 4160, 8), ("bf16", 5112, 33), ("bf16", 520, 64), ("f16", 1000, 50),
+           ("f32", 2052, 20), ("f32", 4092, 17), ("f32", 1024, 64), ("f32", 260, 64), ("f32", 4608, 3)]
+
+
+@pytest.mark.parametrize("dtype,H,M", GENERAL)
+def test_general_path_widths(coral, dtype, H, M):
+    sizes = [1, 5, 127, 128, 129, 300, 90, 64, 260]
+    cfg = HeadConfig(f"gen{H}", dtype, H, sum(sizes), len(sizes), 4, (M,), 12, 900 + H + M, True)
+    check_all(coral, cfg, sizes, (M,))
+
+
+@pytest.mark.parametrize("dtype,G,g,M", [("bf16", 65, 3, 40), ("f16", 128, 8, 64), ("f32", 200, 17, 33), ("bf16", 300, 70, 20)])
+def test_general_path_many_groups(coral, dtype, G, g, M):
+    sizes = [3 + (7 * n) % 40 for n in range(G)]
+    cfg = HeadConfig(f"gengroups{G}", dtype, 1024, sum(sizes), G, g, (M,), 9, 940 + G, True)
+    check_all(coral, cfg, sizes, (M,), dense=False)
+
+
+@pytest.mark.parametrize("M,k,n_next", [(1, 1, 1), (3, 5, 15), (16, 64, 64), (17, 64, 64), (64, 64, 63), (64, 16, 64), (64, 16, 65)])
+def test_tree_level_selection_and_ranking(coral, M, k, n_next):
+    """Up to 64 kept nodes are selected, more are ranked: the same rules, bit for bit."""
+    import oracle
+    rng = np.random.default_rng(960 + M + k + n_next)
+    logp = -np.sort(rng.random((M, k)).astype(np.float32).round(2) * 3, axis=1)   # rounded: ties
+    ids = rng.integers(0, 1000, (M, k)).astype(np.int32)
+    ids[M // 2, k // 2:] = -1                                                       # empty slots
+    parent = (-rng.random(M).round(1) * 2).astype(np.float32)
+    want = oracle.tree_expand(parent, ids, logp, n_next)
+    got = coral.coral_tree_expand(torch.from_numpy(parent).cuda(), torch.from_numpy(ids).cuda(),
+                                  torch.from_numpy(logp).cuda(), n_next)
+    for a, b in zip(want, got):
+        assert np.array_equal(np.asarray(a), b.cpu().numpy())
