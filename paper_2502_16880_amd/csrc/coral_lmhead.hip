@@ -259,6 +259,11 @@ int fused_gate_mode(bool dense, int M, int G, int g, int k, int jp, coral_dtype 
 // segments in use leave almost half of the loads of a batch empty: the multi-kernel path's.)
 bool fused_rows_fit(int jp) { return jp <= 8 || (jp >= 10 && jp <= kFusedMaxSegs); }
 
+// Log-probability mode: beyond 32 tokens the single-launch kernel's per-wave lists (one per token,
+// hardly ever filled) and per-token pieces cost more than the tile kernels' three launches
+// (264-wide head, 59 tokens, 3 of 29 groups: 82 us against 34).
+constexpr int kLogprobFusedMaxTokens = 32;
+
 // Activated groups at most.
 inline long long max_union(int M, int G, int g) { return (long long)M * g < G ? (long long)M * g : G; }
 
@@ -286,9 +291,10 @@ struct LevelExpand {
 // Enqueues the expansion of a level from the candidate lists in memory.
 coral_status launch_tree_expand(const LevelExpand& level, const int32_t* cand_ids, const float* cand_logp, int M, int k,
                                 hipStream_t stream) {
-    if (level.n_next <= kWave)
-        hipLaunchKernelGGL(k_tree_topk, dim3(1), dim3(kTreeWaves * kWave), 0, stream, level.parent_score, cand_ids,
-                           cand_logp, M, k, level.n_next, level.next_parent, level.next_token, level.next_score);
+    if (level.n_next <= kWave && M * k <= kTreeTopkMax)
+        hipLaunchKernelGGL(level.parent_score ? k_tree_topk<true> : k_tree_topk<false>, dim3(1), dim3(kWave), 0, stream,
+                           level.parent_score, cand_ids, cand_logp, M, k, level.n_next, level.next_parent,
+                           level.next_token, level.next_score);
     else
         hipLaunchKernelGGL(k_tree_expand, dim3(M), dim3(kWave), (size_t)M * k * sizeof(unsigned long long), stream,
                            level.parent_score, cand_ids, cand_logp, M, k, level.n_next, level.next_parent,
@@ -309,7 +315,8 @@ Pieces layout_pieces(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
     const bool shared = jp > 8;
     const int in_lds = kLdsLimit / (int)(hidden_lds_stride(jp) * sizeof(uint4));       // hidden vectors alone
     const int least = shared ? 1 : M;
-    for (int m = M < in_lds ? M : in_lds; m >= least; --m)
+    const int most = in_lds < kLogprobFusedMaxTokens ? in_lds : kLogprobFusedMaxTokens;
+    for (int m = M < most ? M : most; m >= least; --m)
         if (fused_logprob_fits(m, G, g, k, jp, dt, kMaxWorkgroups))
             return {(size_t)m * ((size_t)V / fused_rows(fused_segs(jp)) + g), shared};
     return {0, false};
@@ -331,19 +338,25 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
     // Collected candidates instead of per-wave lists, where a workgroup is sure to meet at
     // most kCollectMax rows per token: it takes D consecutive batches out of every D P of the
     // concatenated activated groups, so of any group (a run of at most n batches) it meets no
-    // more than D * (n / D P) + min(D, n % D P), and a token has g groups.  (D = kDealFew; the
-    // bound for D = 1, which the kernel uses as well, is never larger.)
+    // more than D * (n / D P) + min(D, n % D P), and a token has g groups.  D = kDealFew (the
+    // bound for the smaller D that the kernel uses as well is never larger), or, where buffers
+    // that size do not fit, D = 1 throughout (512-wide head, 55 tokens, 7 of 61 groups: 64
+    // entries per token instead of 448, 187 us with lists, 58 with buffers).
     const int segs = fused_segs(jp), rows = fused_rows(segs);
     int cap = 0;
+    bool deal_single = false;
     if (!logprob) {
-        const long long period = (long long)kDealFew * P;
-        const long long n = ((long long)(dense ? V : max_group_rows) + rows - 1) / rows;
-        const long long rest = n % period;
-        const long long per_group = kDealFew * (n / period) + (rest < kDealFew ? rest : kDealFew);
-        const long long bound = (rows * per_group * (dense ? 1 : g) + kWave - 1) / kWave * kWave;
-        if (bound > 0 && bound <= kCollectMax &&
-            fused_lds_layout(M, G, g, k, jp, dense, gate, false, (int)bound).total <= kLdsLimit)
-            cap = (int)bound;
+        for (int deal = kDealFew; deal >= 1 && !cap; deal -= kDealFew - 1) {
+            const long long period = (long long)deal * P;
+            const long long n = ((long long)(dense ? V : max_group_rows) + rows - 1) / rows;
+            const long long rest = n % period;
+            const long long per_group = deal * (n / period) + (rest < deal ? rest : deal);
+            const long long bound = (rows * per_group * (dense ? 1 : g) + kWave - 1) / kWave * kWave;
+            if (bound > 0 && bound <= kCollectMax &&
+                fused_lds_layout(M, G, g, k, jp, dense, gate, false, (int)bound).total <= kLdsLimit)
+                cap = (int)bound;
+            deal_single = cap && deal == 1;
+        }
     } else {
         // a workgroup's rows depend on the selection: buffers as large as fit beside the pieces,
         // used by the workgroups whose rows they hold
@@ -358,6 +371,7 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
     if (jp > 8 && gate == kGateMfma && M > 16) return CORAL_ERR_UNSUPPORTED;        // not reached: LDS
     FusedParams p = {};
     p.cap = cap;
+    p.deal_single = deal_single ? 1 : 0;
     // Measured with rows of 8 KB (Llama shapes): dense head, one or two tokens: 6 waves 158 us
     // against 165 us with all 16 (Llama2: 46.5 against 48.5 us); four tokens: 10 waves 162 us
     // against 168 us.  Rows of 7 KB (Qwen shape) and the grouped head's gathered rows are
@@ -453,7 +467,7 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
     if (logprob) {     // the single-launch kernel where it fits, else the tile path, else the staged path
         pl.path = staged_fits(M, jp, k) ? 0 : -1;
         if (dense) return pl;
-        if (fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups)) {
+        if (M <= kLogprobFusedMaxTokens && fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups)) {
             pl.path = 1;
         } else if (tiles_fit(M, H, V, G, g, k, dt, &pl.tile_umax, &pl.tile_lds) && G <= kWave) {
             pl.path = 2;                    // (k_gate_select leaves log p_router for up to 64 groups)
@@ -479,8 +493,13 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
 
 PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob = false) {
     PathPlan pl = plan_path_kind(dense, M, H, V, G, g, k, dt, logprob);
-    pl.tile_kernels = pl.path == 2 || (pl.path == 0 && tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt,
-                                                                        &pl.tile_umax, &pl.tile_lds));
+    // (One batch of tokens and fewer 128-row blocks than compute units: the staged kernels' 32-row
+    // chunks spread over more of them.  fp32 H = 2304, one token, one group of 710 rows: 32 us
+    // staged, 54 us with the tile kernels.)
+    const long long rows = dense ? V : max_union(M, G, g) * V / (G > 0 ? G : 1);
+    const bool few = M <= kTokBatch && rows < (long long)kMaxWorkgroups * kTileRows && staged_fits(M, (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave, k);
+    pl.tile_kernels = pl.path == 2 || (pl.path == 0 && !few &&
+                                       tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds));
     return pl;
 }
 

@@ -93,6 +93,7 @@ struct FusedParams {
     int n_vec, jp;
     int cap;                    // entries per token of the LDS buffer of collected candidates; 0: lists per
                                 // wave.  Log-probability mode: every workgroup decides by its rows
+    int deal_single;            // batches are dealt singly in any case (cap holds only then)
     int stream_waves;           // waves of a workgroup that stream weight rows (1..16)
 };
 
@@ -822,7 +823,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     // (Log-probability mode: the workgroup's share is a contiguous range of one group's
     // batches instead, the j-th of the equal parts its group's workgroups cut the group into.)
     const int round = gridDim.x * kFusedWaves;
-    const int deal = total_batches >= 4 * round ? 0 : total_batches >= round ? log2_small(kDealFew) : log2_small(kDealFew / 2);
+    const int deal = total_batches >= 4 * round || p.deal_single ? 0
+                     : total_batches >= round ? log2_small(kDealFew) : log2_small(kDealFew / 2);
     auto dealt = [&](int i) {
         return (int)(((i >> deal) * gridDim.x + blockIdx.x) << deal) + (i & ((1 << deal) - 1));
     };
@@ -1120,12 +1122,15 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         auto expand_level = [&]() {                    // called by every thread of the workgroup
             if (!expand) return;
             __syncthreads();
-            if (p.n_next <= kWave) {                   // uniform
-                tree_topk(
-                    M * k, p.n_next, reinterpret_cast<unsigned long long*>(lds + lay.o_hidden),
-                    [&](int e) { return tree_keys[e]; },
+            if (p.n_next <= kWave && M * k <= 4 * kWave) {     // uniform
+                if (wave != 0) return;
+                int ln = lane;
+                asm volatile("" : "+v"(ln));           // (see wave_merge_lists)
+                tree_topk<4>(
+                    M * k, p.n_next, ln, ms->keys, [&](int e) { return tree_keys[e]; },
+                    [&](unsigned long long key, int) { return key; },
                     [&](int r, unsigned long long key) {
-                        const int e = key_id(key);     // (of a real key)
+                        const int e = key != 0ull ? key_id(key) : 0;
                         p.next_parent[r] = key != 0ull ? div_small(e, inv_small(k)) : -1;
                         p.next_token[r] = key != 0ull ? tree_ids[e] : -1;
                         p.next_score[r] = key != 0ull ? tree_scores[e] : -INFINITY;

@@ -4,8 +4,8 @@
 // best scores of all M*k candidates become the next level.  The candidate lists arrive
 // sorted (the head's top-k output), so a candidate's global rank is the sum over the M lists
 // of a binary search; a candidate at position i >= n_next of its own list cannot be kept and
-// is skipped.  Up to 64 nodes kept (tree_topk): four waves select the best of all candidates'
-// keys.  More: one wave per node ranks its own node's candidates against a table of the
+// is skipped.  Up to 64 nodes kept of up to 1024 candidates (tree_topk): one wave selects the best
+// of all candidates' keys.  More: one wave per node ranks its own node's candidates against a table of the
 // keys of all M*k <= 4096 candidates in LDS.  The stand-alone kernel gives every node a
 // workgroup of one wave that builds the whole table itself (32 KB at most; cheaper than a
 // hand-over between workgroups); the single-launch head's log-probability mode calls the
@@ -77,66 +77,61 @@ __device__ __forceinline__ void tree_pad(int n_real, int n_next, int lane, int32
     }
 }
 
-// Up to 64 nodes kept: the n_next largest of the N <= 4096 keys key_at(e), put(rank, key) once per
-// rank, key 0 past the last candidate.  Four waves of the workgroup cut a quarter each down to
-// its n_next best, the first merges these: selection instead of ranking every candidate (64 x 16
-// candidates to 64 nodes took 9.7 us, every node's wave building the whole table and searching
-// it).  Called by every thread; lds: 2 * 4 * 64 words.
-constexpr int kTreeWaves = 4;
-constexpr int kTreeTopkWords = 2 * kTreeWaves * kWave;
-template <class KeyAt, class Put>
-__device__ __forceinline__ void tree_topk(int N, int n_next, unsigned long long* lds, KeyAt key_at, Put put) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    unsigned long long* stage = lds + (size_t)(wave & (kTreeWaves - 1)) * kWave;
-    unsigned long long* buf = lds + (size_t)(kTreeWaves + (wave & (kTreeWaves - 1))) * kWave;
-    if (wave < kTreeWaves) {                               // wave-uniform
-        auto cut = [&](auto regs) {
-            constexpr int R = decltype(regs)::value;
-            unsigned long long key[R];
+// Up to 64 nodes kept: one wave selects the n_next best of R * 64 >= N candidates, put(rank, key)
+// once per rank, key 0 past the last candidate: selection instead of ranking every candidate (64
+// x 16 candidates to 64 nodes took 9.7 us, every node's wave building the whole table and
+// searching it; now 8.1 us).  fetch(e) reads candidate e (all of them before the first is
+// used), key_of(raw, e) makes its key.  buf: 64 LDS words.
+constexpr int kTreeTopkMax = 16 * kWave;
+template <int R, class Fetch, class KeyOf, class Put>
+__device__ __forceinline__ void tree_topk(int N, int n_next, int lane, unsigned long long* buf, Fetch fetch,
+                                          KeyOf key_of, Put put) {
+    decltype(fetch(0)) raw[R];
 #pragma unroll
-            for (int i = 0; i < R; ++i) {
-                const int e = (i * kTreeWaves + wave) * kWave + lane;
-                key[i] = key_at(e < N ? e : N - 1);
-                if (e >= N) key[i] = 0ull;
-            }
-            wave_topk<R>(key, n_next, lane, buf, [&](int r, unsigned long long kk) { stage[r] = kk; });
-        };
-        stage[lane] = 0ull;
-        if (N <= 4 * kTreeWaves * kWave) cut(std::integral_constant<int, 4>());
-        else cut(std::integral_constant<int, 16>());
+    for (int i = 0; i < R; ++i) {
+        const int e = i * kWave + lane;
+        raw[i] = fetch(e < N ? e : N - 1);
     }
-    __syncthreads();
-    if (wave == 0) {
-        unsigned long long key[kTreeWaves];
+    unsigned long long key[R];
 #pragma unroll
-        for (int i = 0; i < kTreeWaves; ++i) key[i] = lds[i * kWave + lane];
-        wave_topk<kTreeWaves>(key, n_next, lane, buf, put);
+    for (int i = 0; i < R; ++i) {
+        const int e = i * kWave + lane;
+        key[i] = e < N ? key_of(raw[i], e) : 0ull;
     }
+    wave_topk<R>(key, n_next, lane, buf, put);
 }
 
-__global__ __launch_bounds__(kTreeWaves * kWave) void k_tree_topk(
+template <bool PARENT>
+__global__ __launch_bounds__(kWave) void k_tree_topk(
     const float* __restrict__ parent_score, const int32_t* __restrict__ cand_ids,
     const float* __restrict__ cand_logp, int M, int k, int n_next, int32_t* __restrict__ next_parent,
     int32_t* __restrict__ next_token, float* __restrict__ next_score) {
-    __shared__ __attribute__((aligned(16))) unsigned long long lds[kTreeTopkWords];
-    const int inv_k = inv_small(k);
-    tree_topk(
-        M * k, n_next, lds,
-        [&](int e) {
-            const float parent = parent_score ? parent_score[div_small(e, inv_k)] : 0.f;
-            return tree_key(parent, cand_logp[e], cand_ids[e], e);
-        },
-        [&](int r, unsigned long long key) {
-            const int e = key_id(key);                     // (of a real key)
-            const int m = key != 0ull ? div_small(e, inv_k) : -1;
-            next_parent[r] = m;
-            next_token[r] = key != 0ull ? cand_ids[e] : -1;
-            next_score[r] = key != 0ull ? (parent_score ? parent_score[m] : 0.f) + cand_logp[e] : -INFINITY;
-        });
+    __shared__ __attribute__((aligned(16))) unsigned long long buf[kWave];
+    struct Raw {
+        float parent, logp;
+        int id;
+    };
+    const int inv_k = inv_small(k), lane = threadIdx.x;
+    auto fetch = [&](int e) {
+        Raw r;
+        r.parent = PARENT ? parent_score[div_small(e, inv_k)] : 0.f;
+        r.logp = cand_logp[e];
+        r.id = cand_ids[e];
+        return r;
+    };
+    auto key_of = [&](const Raw& r, int e) { return tree_key(r.parent, r.logp, r.id, e); };
+    auto put = [&](int r, unsigned long long key) {
+        const int e = key != 0ull ? key_id(key) : 0;
+        const int m = div_small(e, inv_k);
+        next_parent[r] = key != 0ull ? m : -1;
+        next_token[r] = key != 0ull ? cand_ids[e] : -1;
+        next_score[r] = key != 0ull ? (PARENT ? parent_score[m] : 0.f) + cand_logp[e] : -INFINITY;
+    };
+    if (M * k <= 4 * kWave) tree_topk<4>(M * k, n_next, lane, buf, fetch, key_of, put);     // uniform
+    else tree_topk<16>(M * k, n_next, lane, buf, fetch, key_of, put);
 }
 
-// More than 64 nodes kept: one wave per node ranks its node's candidates.
+// More than 64 nodes kept, or more than 1024 candidates: one wave per node ranks its node's.
 __global__ __launch_bounds__(kWave) void k_tree_expand(
     const float* __restrict__ parent_score, const int32_t* __restrict__ cand_ids,
     const float* __restrict__ cand_logp, int M, int k, int n_next, int32_t* __restrict__ next_parent,

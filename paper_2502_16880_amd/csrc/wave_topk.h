@@ -148,6 +148,9 @@ __device__ __forceinline__ unsigned long long wave_bound(const unsigned long lon
         const unsigned kth = wave_kth_key(keys32, best, want, lane);
         if (kth != 0u) lo = (unsigned long long)kth << 32;
         if (count_reach<N>(key, lo) <= most) return lo;
+    } else if (want <= kWave) {                                // the least of the lanes' best is reached by all lanes
+        const unsigned least = wave_min_u32(best);
+        if (least != 0u) lo = (unsigned long long)least << 32;
     }
     const unsigned top = wave_max_u32(best);
     unsigned long long hi = top == 0xffffffffu ? ~0ull : (unsigned long long)(top + 1u) << 32;   // reached by none
