@@ -123,7 +123,8 @@ Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, Tiles tiles
     if (tiles == Tiles::kGeneral) off = lists;
     const size_t tile_blocks = (size_t)V / kTileRows + G + (tiles == Tiles::kOwn || G == 0 ? 1 : 0);
     L.tile_z = take(tiles != Tiles::kNone ? tile_blocks * M * kTileRows * sizeof(float) : 0);
-    L.tile_stat = take(tiles != Tiles::kNone ? tile_blocks * M * sizeof(float2) : 0);
+    // (with blocks of 32 rows the logits take no more, their statistics V / 32 + G entries)
+    L.tile_stat = take(tiles != Tiles::kNone ? ((size_t)V / kTileRowsSmall + G + 1) * M * sizeof(float2) : 0);
     if (off < after) off = after;
     L.total = off > pieces_end ? off : pieces_end;
     return L;
@@ -518,6 +519,19 @@ Tiles layout_tiles(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
     return t;
 }
 
+// Blocks of 32 rows instead of 128, where the 128-row blocks would leave a third of the compute
+// units without work (`groups` activated groups of equal size, `rows` in all), a group's tokens fit
+// one token tile on average (every block stages them again, against a quarter of the weight
+// bytes) and a row is long (a block's start and end, about 4 us, against its chunks).
+// Measured, 128 rows against 32: dense f16 H = 7344, 14561 rows, 16 tokens 88 against 64 us; bf16
+// H = 7680, 12 groups of 1176 rows, 11 tokens 73 against 52; the other way round bf16 H = 1664, 13
+// groups of 2005 rows, 40 tokens 35 against 48; dense f16 H = 5632, 62 tokens 64 against 173.
+bool tile_small_blocks(int V, int g, long long rows, long long groups, long long group_tokens, int n_chunks) {
+    return rows / kTileRows + groups / 2 <= kMaxWorkgroups * 2 / 3 && group_tokens <= 16 && n_chunks >= 8 &&
+           V / kTileRowsSmall + g + 1 <= (1 << 16) &&
+           tile_select_lds_layout(g > 0 ? g : 1, V / kTileRowsSmall + g + 1).total <= kLdsLimit;
+}
+
 // Enqueues k_tiles and the ranking of the logits it leaves.  For the grouped head the gate
 // and selection kernel must already be enqueued (selection, the token tiles' masks; in the
 // log-probability mode log p_router of the selection too).
@@ -547,8 +561,16 @@ coral_status launch_tiles(bool dense, bool general, const void* hidden, const vo
     p.n_chunks = (p.n_vec + kChunkVecs - 1) / kChunkVecs;
     p.u_max = u_max;
     typedef void (*tiles_fn)(TileParams, int);
-    const tiles_fn fn = general ? CORAL_PICK_DT(dt, (k_tiles<kF32, true>), (k_tiles<kBF16, true>), (k_tiles<kF16, true>))
-                                : dt == CORAL_F16 ? k_tiles<kF16, false> : k_tiles<kBF16, false>;
+    const long long groups = dense ? 1 : max_union(M, G, g);
+    const bool small = tile_small_blocks(V, g, dense ? V : groups * V / G, groups,
+                                         dense ? M : ((long long)M * g + groups - 1) / groups, p.n_chunks);
+    const int rows_per_block = small ? kTileRowsSmall : kTileRows;
+    const tiles_fn fn =
+        small     ? CORAL_PICK_DT(dt, (k_tiles<kF32, true, kTileSplitSmall>), (k_tiles<kBF16, true, kTileSplitSmall>),
+                                  (k_tiles<kF16, true, kTileSplitSmall>))
+        : general ? CORAL_PICK_DT(dt, (k_tiles<kF32, true, kTileSplit>), (k_tiles<kBF16, true, kTileSplit>),
+                                  (k_tiles<kF16, true, kTileSplit>))
+        : dt == CORAL_F16 ? k_tiles<kF16, false, kTileSplit> : k_tiles<kBF16, false, kTileSplit>;
     if (!allow_lds(reinterpret_cast<const void*>(fn), lds)) return CORAL_ERR_HIP;
     coral_status st;
     if ((st = launch_timed(fn, dim3(P), dim3(kTileBlock), lds, stream, ev_before, ev_after, p, dense ? 1 : 0)) !=
@@ -568,7 +590,9 @@ coral_status launch_tiles(bool dense, bool general, const void* hidden, const vo
     q.topk_ids = topk_ids;
     q.topk_out = topk_out;
     q.M = M; q.V = V; q.g = g; q.k = k;
-    q.max_blocks = V / kTileRows + g + 1;
+    q.max_blocks = V / rows_per_block + g + 1;
+    q.rows_shift = small ? 5 : 7;
+    static_assert(kTileRowsSmall == 1 << 5 && kTileRows == 1 << 7, "");
     const int select_lds = tile_select_lds_layout(dense ? 1 : g, q.max_blocks).total;
     typedef void (*select_fn)(TileSelectParams);
     const select_fn sf = dense ? k_tile_select<true, false>

@@ -29,9 +29,14 @@
 namespace {
 
 constexpr int kTileWaves = 8;
-constexpr int kTileSplit = 2;                    // waves that share a row group (split of a chunk)
+// Waves that share a row group of 32 rows (split of a chunk's columns): two, a block then being
+// 128 rows, or all eight with blocks of 32 rows, for steps whose 128-row blocks would leave
+// compute units without work (see tile_small_blocks in coral_lmhead.hip).
+constexpr int kTileSplit = 2, kTileSplitSmall = 8;
+__host__ __device__ constexpr int tile_rows(int split) { return 32 * kTileWaves / split; }
 constexpr int kTileBlock = kTileWaves * kWave;
-constexpr int kTileRows = 128;                   // weight rows per block (4 row groups of 32)
+constexpr int kTileRows = tile_rows(kTileSplit);          // weight rows per block (4 row groups of 32)
+constexpr int kTileRowsSmall = tile_rows(kTileSplitSmall);
 constexpr int kChunkVecs = 64;                   // 16-byte vectors per 512-column chunk
 constexpr int kHbStride = kChunkVecs + 1;        // LDS row stride in vectors (pad: no bank conflicts)
 constexpr int kHbBufVecs = 64 * kHbStride;       // one staging buffer: 64 token slots
@@ -142,9 +147,10 @@ __device__ __forceinline__ void tile_store_hidden(int n_vec, const TileStage& hs
 }
 
 // This lane's vector of step pair sp of chunk c, counted from the row's start.
+template <int SPLIT>
 __device__ __forceinline__ int tile_lane_vec(int c, int sp) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    return c * kChunkVecs + sp * 8 + (wave % kTileSplit) * (kChunkVecs / kTileSplit) +
+    return c * kChunkVecs + sp * 8 + (wave % SPLIT) * (kChunkVecs / SPLIT) +
            line_load_chunk(threadIdx.x & (kWave - 1));
 }
 
@@ -152,11 +158,11 @@ __device__ __forceinline__ int tile_lane_vec(int c, int sp) {
 // the weight matrix (offsets are 32-bit: the path takes matrices below 4 GiB).  GENERAL: `row` is
 // the row's start, and lanes past its end read its last vector (dropped in tile_step_pair);
 // otherwise the lane's place in a chunk is part of `row`.
-template <bool GENERAL>
+template <bool GENERAL, int SPLIT>
 __device__ __forceinline__ uint4 tile_load_w(const TileParams& p, unsigned row, int c, int sp) {
     unsigned off;
     if (GENERAL) {
-        const int vec = tile_lane_vec(c, sp);
+        const int vec = tile_lane_vec<SPLIT>(c, sp);
         off = row + (unsigned)(vec < p.n_vec ? vec : p.n_vec - 1) * 16u;
     } else {
         off = row + (unsigned)(c * kChunkVecs + sp * 8) * 16u;
@@ -165,8 +171,9 @@ __device__ __forceinline__ uint4 tile_load_w(const TileParams& p, unsigned row, 
 }
 
 // Step pair SP of a chunk: the two 32-column steps whose weight lines sit in ring slots
-// 4 SP .. 4 SP + 3.
-template <int DT, int NCT, bool REFILL, int SP, bool GENERAL>
+// 4 SLOT .. 4 SLOT + 3.  A wave has 8 / SPLIT step pairs of a chunk, so the ring's four cover
+// SPLIT / 2 chunks and are refilled that far ahead.
+template <int DT, int NCT, bool REFILL, int SP, bool GENERAL, int SPLIT, int SLOT>
 __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4 (&a)[kRing],
                                                f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
                                                const unsigned (&wrow)[4],
@@ -174,26 +181,27 @@ __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int r16 = lane & 15, q4 = lane >> 4;
-    const int kq = wave % kTileSplit;
+    const int kq = wave % SPLIT;
+    constexpr int kAhead = SPLIT / 2, kSteps = 16 / SPLIT;
     const uint4* hb = hbuf + (size_t)(c & 1) * kHbBufVecs;
-    if (GENERAL && !REFILL) {                           // the last chunk: nothing past the row's end
-        const unsigned in = tile_lane_vec(c, SP) < p.n_vec ? 0xffffffffu : 0u;
+    if (GENERAL && (!REFILL || SPLIT == kTileSplitSmall)) {    // the last chunk: nothing past the row's end
+        const unsigned in = tile_lane_vec<SPLIT>(c, SP) < p.n_vec ? 0xffffffffu : 0u;
 #pragma unroll
         for (int o = 0; o < 4; ++o)
-            a[SP * 4 + o] = make_uint4(a[SP * 4 + o].x & in, a[SP * 4 + o].y & in, a[SP * 4 + o].z & in, a[SP * 4 + o].w & in);
+            a[SLOT * 4 + o] = make_uint4(a[SLOT * 4 + o].x & in, a[SLOT * 4 + o].y & in, a[SLOT * 4 + o].z & in, a[SLOT * 4 + o].w & in);
     }
     uint4 op[2][2];                                    // [row tile][step of the pair]
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        mfma_operands_from_lines(a[SP * 4 + 2 * t], a[SP * 4 + 2 * t + 1], lane, my_slice, op[t][0],
+        mfma_operands_from_lines(a[SLOT * 4 + 2 * t], a[SLOT * 4 + 2 * t + 1], lane, my_slice, op[t][0],
                                  op[t][1]);
         if (REFILL) {                                  // refill the two slots just consumed
-            a[SP * 4 + 2 * t] = tile_load_w<GENERAL>(p, wrow[2 * t], c + 1, SP);
-            a[SP * 4 + 2 * t + 1] = tile_load_w<GENERAL>(p, wrow[2 * t + 1], c + 1, SP);
+            a[SLOT * 4 + 2 * t] = tile_load_w<GENERAL, SPLIT>(p, wrow[2 * t], c + kAhead, SP);
+            a[SLOT * 4 + 2 * t + 1] = tile_load_w<GENERAL, SPLIT>(p, wrow[2 * t + 1], c + kAhead, SP);
         }
     }
     if (REFILL) keep_memory_order();
-    if (REFILL && SP == 3 && !GENERAL) {             // the other buffer is free since the last barrier
+    if (REFILL && SP == 3 && SPLIT == kTileSplit) {    // the other buffer is free since the last barrier
         tile_store_hidden<NCT, GENERAL>(p.n_vec, hst, hbuf, c + 1, lane, wave);
         keep_memory_order();
     }
@@ -208,7 +216,7 @@ __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4
             f32x4_t x[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
             for (int s2 = 0; s2 < 2; ++s2) {
-                const uint4 hv = hb[(ct * 16 + r16) * kHbStride + (kq * 8 + 2 * SP + s2) * 4 + q4];
+                const uint4 hv = hb[(ct * 16 + r16) * kHbStride + (kq * kSteps + 2 * SP + s2) * 4 + q4];
 #pragma unroll
                 for (int t = 0; t < 2; ++t) x[t] = mfma_tile<DT>(op[t][s2], hv, x[t]);
             }
@@ -226,7 +234,7 @@ __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4
     }
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
-        const int off = (kq * 8 + 2 * SP + s2) * 4 + q4;
+        const int off = (kq * kSteps + 2 * SP + s2) * 4 + q4;
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct) {
             const uint4 hv = hb[(ct * 16 + r16) * kHbStride + off];
@@ -245,31 +253,50 @@ __device__ __forceinline__ void tile_chunk(const TileParams& p, int c, uint4 (&a
     TileStage hst;
     // (the scheduling barriers keep the compiler from sinking the loads to where their
     // registers are first needed, which would undo the ordering)
-    // General form: no registers for the next hidden vectors through all of the chunk, they are
-    // requested before the last step pair and written behind it.
+    // (general form with two token tiles: after the first step pair, fp32 after the second, there
+    // are no registers for them before)
+    constexpr int kFetchAt = !GENERAL || NCT == 1 ? 0 : DT == kF32 ? 2 : 1;
     auto fetch = [&]() {
-        if (REFILL) {
-            tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, hst, c + 1, threadIdx.x & (kWave - 1),
-                                           __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
-            keep_memory_order();
-        }
+        tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, hst, c + 1, threadIdx.x & (kWave - 1),
+                                        __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+        keep_memory_order();
     };
-    if (!GENERAL) fetch();
-    tile_step_pair<DT, NCT, REFILL, 0, GENERAL>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
-    tile_step_pair<DT, NCT, REFILL, 1, GENERAL>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
-    tile_step_pair<DT, NCT, REFILL, 2, GENERAL>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
-    if (GENERAL) fetch();
-    tile_step_pair<DT, NCT, REFILL, 3, GENERAL>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
-    if (GENERAL && REFILL)
-        tile_store_hidden<NCT, GENERAL>(p.n_vec, hst, hbuf, c + 1, threadIdx.x & (kWave - 1),
-                                       __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+    if (REFILL && kFetchAt == 0) fetch();
+    tile_step_pair<DT, NCT, REFILL, 0, GENERAL, kTileSplit, 0>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    if (REFILL && kFetchAt == 1) fetch();
+    tile_step_pair<DT, NCT, REFILL, 1, GENERAL, kTileSplit, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    if (REFILL && kFetchAt == 2) fetch();
+    tile_step_pair<DT, NCT, REFILL, 2, GENERAL, kTileSplit, 2>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    tile_step_pair<DT, NCT, REFILL, 3, GENERAL, kTileSplit, 3>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    __syncthreads();
+}
+
+// The same with all eight waves on one row group (general form): one step pair of the chunk per
+// wave, from ring slot PH = c % 4.
+template <int DT, int NCT, int PH>
+__device__ __forceinline__ void tile_chunk_small(const TileParams& p, int c, uint4 (&a)[kRing],
+                                                 f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
+                                                 const unsigned (&wrow)[4],
+                                                 uint4* hbuf, const int* tokslot, int n_t, uint4* my_slice) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const bool more = c + 1 < p.n_chunks;              // uniform
+    TileStage hst;
+    if (more) {
+        tile_fetch_hidden<NCT, true>(p, tokslot, n_t, hst, c + 1, lane, wave);
+        keep_memory_order();
+    }
+    // (past the last chunk the refills read the row's last vector, which nothing uses: a form
+    // without them beside this one costs more registers than there are)
+    tile_step_pair<DT, NCT, true, 0, true, kTileSplitSmall, PH>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    if (more) tile_store_hidden<NCT, true>(p.n_vec, hst, hbuf, c + 1, lane, wave);
     __syncthreads();
 }
 
 // The K loop of one block.  Hidden chunk staging: slots wave, wave + 8, ... below 16 NCT;
 // lane = vector inside the chunk; slots past the group's tokens repeat its last token
 // (their columns of the tiles are never read back).
-template <int DT, int NCT, bool GENERAL>
+template <int DT, int NCT, bool GENERAL, int SPLIT>
 __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRing], f32x4_t (&acc)[2][4],
                                             const unsigned (&wrow)[4], uint4* hbuf,
                                             const int* tokslot, uint4* my_slice, int n_t) {
@@ -286,9 +313,18 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct) low[t][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c + 1 < p.n_chunks; ++c)
-        tile_chunk<DT, NCT, true, GENERAL>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
-    tile_chunk<DT, NCT, false, GENERAL>(p, p.n_chunks - 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+    if constexpr (SPLIT == kTileSplit) {
+        for (int c = 0; c + 1 < p.n_chunks; ++c)
+            tile_chunk<DT, NCT, true, GENERAL>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+        tile_chunk<DT, NCT, false, GENERAL>(p, p.n_chunks - 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+    } else {
+        for (int c = 0; c < p.n_chunks; c += 4) {      // uniform
+            tile_chunk_small<DT, NCT, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            if (c + 1 < p.n_chunks) tile_chunk_small<DT, NCT, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            if (c + 2 < p.n_chunks) tile_chunk_small<DT, NCT, 2>(p, c + 2, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            if (c + 3 < p.n_chunks) tile_chunk_small<DT, NCT, 3>(p, c + 3, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+        }
+    }
     if (GENERAL) {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -300,8 +336,10 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
 // GENERAL: the general path's form: any storage type, rows of any number of 16-byte vectors (the
 // last chunk partly filled, loads and operands past a row's end guarded) and sums as exact as the
 // staged kernels'.  Otherwise 16-bit storage and whole chunks.
-template <int DT, bool GENERAL>
+template <int DT, bool GENERAL, int SPLIT>
 __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
+    static_assert(SPLIT == kTileSplit || GENERAL, "blocks of 32 rows exist in the general form");
+    constexpr int ROWS = tile_rows(SPLIT);
     extern __shared__ uint4 smem[];
     char* lds = reinterpret_cast<char*>(smem);
     const TileLds lay = tile_lds_layout(p.u_max);
@@ -315,7 +353,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int rg = wave / kTileSplit, kq = wave % kTileSplit;
+    const int rg = wave / SPLIT, kq = wave % SPLIT;
     const int M = p.M;
     uint4* my_slice = reinterpret_cast<uint4*>(lds + lay.o_scratch) + (size_t)wave * kLinePairSlots;
 
@@ -326,7 +364,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         drawn = __hip_atomic_fetch_add(p.next_block, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int total_blocks;
     if (dense) {
-        total_blocks = (p.V + kTileRows - 1) / kTileRows;
+        total_blocks = (p.V + ROWS - 1) / ROWS;
         if (threadIdx.x == 0) flags[1] = (int)drawn;
         __syncthreads();
     } else {
@@ -379,7 +417,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
             for (int base = 0; base < count; base += kWave) {  // wave-uniform
                 const int r = base + lane;
                 const int g0 = r < count ? order[r] : 0;
-                const int nb = r < count ? (off_lds[g0 + 1] - off_lds[g0] + kTileRows - 1) / kTileRows : 0;
+                const int nb = r < count ? (off_lds[g0 + 1] - off_lds[g0] + ROWS - 1) / ROWS : 0;
                 const int incl = wave_scan_inclusive(nb);
                 if (r < count) {
                     ustart[r] = off_lds[g0];
@@ -405,12 +443,12 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     // first row and end of the block's group (row indices into p.rows, or vocabulary ids)
     auto locate = [&](int b, int& first, int& end, unsigned long long& bm) {
         if (dense) {
-            first = b * kTileRows;
+            first = b * ROWS;
             end = p.V;
             bm = all_tokens;
         } else {
             while (b >= uni(uprefix[u + 1])) ++u;      // blocks come in increasing order
-            first = uni(ustart[u]) + (b - uni(uprefix[u])) * kTileRows;
+            first = uni(ustart[u]) + (b - uni(uprefix[u])) * ROWS;
             end = uni(uend[u]);
             bm = uni64(umask[u]);
         }
@@ -434,7 +472,18 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         for (int o = 0; o < 4; ++o)
             wrow[o] = ((unsigned)rid[o] * (unsigned)p.n_vec + (GENERAL ? 0 : kq * 32 + line_load_chunk(lane))) * 16u;
     };
-    auto load_a = [&](int c, int sp, int o) { a[sp * 4 + o] = tile_load_w<GENERAL>(p, wrow[o], c, sp); };
+    auto load_a = [&](int c, int sp, int o) { a[sp * 4 + o] = tile_load_w<GENERAL, SPLIT>(p, wrow[o], c, sp); };
+    // the ring's slots at a block's start: the step pairs of the first chunk, or the one step pair
+    // of each of the first four (past the last chunk: clamped to the row's end, not used)
+    auto load_ring = [&]() {
+#pragma unroll
+        for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {
+                if constexpr (SPLIT == kTileSplit) load_a(0, sp, o);
+                else a[sp * 4 + o] = tile_load_w<GENERAL, SPLIT>(p, wrow[o], sp, 0);
+            }
+    };
 
     int b = uni(flags[1]);
     int first = 0, end = 0;
@@ -444,10 +493,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         locate(b, first, end, bm);
         my_rows(first, end, rid);
         set_rows(rid);
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int o = 0; o < 4; ++o) load_a(0, sp, o);
+        load_ring();
     }
     // General form: the running sums' rounding errors take the registers of two token tiles, so a
     // block serves 32 tokens at a time and comes round again for the next 32.
@@ -474,14 +520,14 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
             for (int ct = 0; ct < 4; ++ct) acc[t][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
         if constexpr (GENERAL) {
-            if (n_ct == 1) tile_k_loop<DT, 1, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);   // block-uniform
-            else tile_k_loop<DT, 2, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
+            if (n_ct == 1) tile_k_loop<DT, 1, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);   // block-uniform
+            else tile_k_loop<DT, 2, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
         } else {
             switch (n_ct) {                                // block-uniform
-                case 1: tile_k_loop<DT, 1, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
-                case 2: tile_k_loop<DT, 2, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
-                case 3: tile_k_loop<DT, 3, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
-                default: tile_k_loop<DT, 4, GENERAL>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+                case 1: tile_k_loop<DT, 1, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+                case 2: tile_k_loop<DT, 2, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+                case 3: tile_k_loop<DT, 3, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+                default: tile_k_loop<DT, 4, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
             }
         }
 
@@ -503,10 +549,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
                 my_rows(nfirst, nend, rid);
                 set_rows(rid);
             }
-#pragma unroll
-            for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-                for (int o = 0; o < 4; ++o) load_a(0, sp, o);
+            load_ring();
         }
 
         // half sums -> LDS (over the staging buffers, free after the last barrier).  A
@@ -529,19 +572,21 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         // kernel reads the logits only of blocks whose largest can matter.  Log-probability
         // mode: the sum of exp(z - largest) as well, the block's piece of the group's lse.
         for (int s = wave; s < n_t; s += kTileWaves) {
-            float* dst = p.z + ((size_t)b * M + (kPasses ? s0 : 0) + s) * kTileRows + lane;
-            float zs[2];
+            float* dst = p.z + ((size_t)b * M + (kPasses ? s0 : 0) + s) * ROWS + lane;
+            float zs[2] = {-INFINITY, -INFINITY};
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                const int tile = hf * 4 + (lane >> 4), row = lane & 15;   // row tile 0..7 of the block
+            for (int hf = 0; hf < (ROWS + kWave - 1) / kWave; ++hf) {
+                const int tile = hf * 4 + (lane >> 4), row = lane & 15;   // row tile of the block
                 const int e = (row >> 2) * 68 + (s & 15) * 4 + (row & 3);
-                const int w0 = (tile >> 1) * kTileSplit;                  // the row group's first wave
+                const int w0 = ((tile >> 1) * SPLIT) & (kTileWaves - 1);  // the row group's first wave
                 float z = 0.f;
 #pragma unroll
-                for (int q = 0; q < kTileSplit; ++q)
+                for (int q = 0; q < SPLIT; ++q)
                     z += red[(w0 + q) * kRedWave + (tile & 1) * kRedTile + (s >> 4) * kRedCt + e];
-                dst[hf * kWave] = z;
-                zs[hf] = first + hf * kWave + lane < end ? z : -INFINITY;
+                if (ROWS >= kWave || lane < ROWS) {    // (32-row blocks: the lanes above repeat the rows)
+                    dst[hf * kWave] = z;
+                    zs[hf] = first + hf * kWave + lane < end ? z : -INFINITY;
+                }
             }
             const float wm = wave_max(fmaxf(zs[0], zs[1]));
             float sum = 0.f;
@@ -776,12 +821,12 @@ struct TileSelectParams {
     float* topk_out;                        // [M, k]
     int M, V, g, k;
     int max_blocks;                         // capacity of the per-block arrays in LDS
+    int rows_shift;                         // log2 of k_tiles' rows per block
 };
 
 constexpr int kSelectThreads = 512;
 constexpr int kSelectWaves = kSelectThreads / kWave;
 constexpr int kSelectKeys = 8;                   // candidates per thread and chunk
-constexpr int kSelectChunkBlocks = kSelectKeys * kSelectThreads / kTileRows;
 constexpr int kKeptMax = kSelectKeys * kSelectThreads + kMaxK;   // a chunk's candidates and the list
 
 struct TileSelectLds {
@@ -843,6 +888,8 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int t = blockIdx.x, k = p.k;
+    const int rows_per_block = 1 << p.rows_shift;
+    const int chunk_blocks = kSelectKeys * kSelectThreads >> p.rows_shift;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         __hip_atomic_store(p.next_block, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (threadIdx.x == 0) {
@@ -857,7 +904,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
             g_rows[0] = p.V;
             g_fb[0] = 0;
             g_slot[0] = t;
-            g_nb[0] = (p.V + kTileRows - 1) / kTileRows;
+            g_nb[0] = (p.V + rows_per_block - 1) >> p.rows_shift;
             g_shift[0] = 0.f;
         }
     } else {
@@ -869,7 +916,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
             g_rows[j] = hi - lo;
             g_fb[j] = p.group_first_block[grp];
             g_slot[j] = __popcll(mk & ((1ull << t) - 1ull));
-            g_nb[j] = (hi - lo + kTileRows - 1) / kTileRows;
+            g_nb[j] = (hi - lo + rows_per_block - 1) >> p.rows_shift;
             g_shift[j] = 0.f;
         }
     }
@@ -965,7 +1012,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
             n_q = uni(n_qual);
             int* ti = src_i; src_i = dst_i; dst_i = ti;
             unsigned* tv = src_v; src_v = dst_v; dst_v = tv;
-            if (tight && n_q <= kSelectChunkBlocks) break;     // (else once more: the candidates of one chunk)
+            if (tight && n_q <= chunk_blocks) break;     // (else once more: the candidates of one chunk)
             __syncthreads();                           // (everyone has the count)
             if (threadIdx.x == 0) n_qual = 0;
         }
@@ -975,7 +1022,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
     // 5. their candidates, 16 blocks at a time, merged with the list so far (buf[0, have))
     int have = 0;                                      // entries of the list so far
     unsigned long long list_kth = 0ull;                // its k-th key once it has k entries
-    for (int base = 0; base < n_q; base += kSelectChunkBlocks) {       // block-uniform
+    for (int base = 0; base < n_q; base += chunk_blocks) {       // block-uniform
         unsigned long long key[kSelectKeys];
         {
             float zv[kSelectKeys];
@@ -984,13 +1031,13 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
 #pragma unroll
             for (int q = 0; q < kSelectKeys; ++q) {
                 const int e = q * kSelectThreads + threadIdx.x;
-                const int qb = base + (e >> 7), r = e & (kTileRows - 1);
+                const int qb = base + (e >> p.rows_shift), r = e & (rows_per_block - 1);
                 const int info = qblk[qb < n_q ? qb : n_q - 1];
                 const int j = info >> 16, lb = info & 0xffff;
-                const int row = lb * kTileRows + r, n_rows = g_rows[j];
+                const int row = (lb << p.rows_shift) + r, n_rows = g_rows[j];
                 valid[q] = qb < n_q && row < n_rows;
                 grp[q] = j;
-                zv[q] = p.z[((size_t)(g_fb[j] + lb) * p.M + g_slot[j]) * kTileRows + r];
+                zv[q] = p.z[(((size_t)(g_fb[j] + lb) * p.M + g_slot[j]) << p.rows_shift) + r];
                 idv[q] = DENSE ? row : p.rows[g_start[j] + (row < n_rows ? row : n_rows - 1)];
             }
 #pragma unroll
@@ -1053,7 +1100,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
         }
         __syncthreads();
         have = kept < k ? kept : k;
-        if (base + kSelectChunkBlocks >= n_q) break;   // block-uniform: that was the last chunk
+        if (base + chunk_blocks >= n_q) break;   // block-uniform: that was the last chunk
         if ((int)threadIdx.x < have) buf[threadIdx.x] = list[threadIdx.x];
         if (threadIdx.x == 0) n_kept = have;
         list_kth = have == k ? list[k - 1] : 0ull;

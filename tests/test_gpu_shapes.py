@@ -89,7 +89,9 @@ def test_equal_logits_in_the_single_launch_kernel(coral):
 # The general path's tile kernels: widths that leave the last 512-column (fp32: 256-column) chunk
 # partly filled, by one 16-byte vector up to one short of whole; one to four token tiles; fp32.
 GENERAL = [("bf16", 4104, 9), ("f16", 4160, 8), ("bf16", 5112, 33), ("bf16", 520, 64), ("f16", 1000, 50),
-           ("f32", 2052, 20), ("f32", 4092, 17), ("f32", 1024, 64), ("f32", 260, 64), ("f32", 4608, 3)]
+           ("f32", 2052, 20), ("f32", 4092, 17), ("f32", 1024, 64), ("f32", 260, 64), ("f32", 4608, 3),
+           # whole chunks, rows long and few enough for blocks of 32 rows
+           ("bf16", 4608, 20), ("f16", 8192, 11), ("bf16", 4096, 36)]
 
 
 @pytest.mark.parametrize("dtype,H,M", GENERAL)
