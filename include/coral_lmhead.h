@@ -178,7 +178,8 @@ coral_status coral_lmhead_grouped(const void *hidden, const void *gate_W,
  * of CORAL_NOALLOC_SCRATCH_BYTES inside the library, one copy per GPU, held until the
  * process ends.  The call allocates and frees nothing.
  *   - Shapes whose scratch need (coral_lmhead_workspace_bytes for the same sizes, without the
- *     log-probability mode's tables) exceeds CORAL_NOALLOC_SCRATCH_BYTES are refused with
+ *     log-probability mode's tables; rows beyond 8 KB: what the tile or general path needs for
+ *     them) exceeds CORAL_NOALLOC_SCRATCH_BYTES are refused with
  *     CORAL_ERR_WORKSPACE before anything is enqueued.  Every workload shape of Table 1 with up
  *     to 16 tokens fits.
  *   - All calls on one GPU share that GPU's array: calls that overlap on one GPU (two

@@ -12,9 +12,10 @@
 //   - the hidden vectors of the tokens that selected the group sit in LDS and are
 //     re-used for every row of the chunk; bf16 pairs go through v_dot2c_f32_bf16
 //     with fp32 accumulation;
-//   - each wavefront keeps its running k best per token in registers (lane i holds
-//     rank i), so the logits row never leaves the chip; workgroup partial lists are
-//     merged by rank counting, then a last small kernel merges per token.
+//   - where the hidden vectors fit on chip the logits row never leaves it: a workgroup collects
+//     its logits per token in LDS, publishes its k best, and the last workgroup merges all.
+//     With many tokens the matrix cores take over and the activated rows' logits go through
+//     memory to a ranking kernel.
 // A group selected by several tokens is read once for all of them (the union of the
 // tokens' groups that the appendix's tree-decoding paragraph activates).
 #include <hip/hip_runtime.h>
@@ -591,12 +592,13 @@ coral_status launch_tiles(bool dense, bool general, const void* hidden, const vo
     q.topk_out = topk_out;
     q.M = M; q.V = V; q.g = g; q.k = k;
     q.max_blocks = V / rows_per_block + g + 1;
-    q.rows_shift = small ? 5 : 7;
     static_assert(kTileRowsSmall == 1 << 5 && kTileRows == 1 << 7, "");
     const int select_lds = tile_select_lds_layout(dense ? 1 : g, q.max_blocks).total;
     typedef void (*select_fn)(TileSelectParams);
-    const select_fn sf = dense ? k_tile_select<true, false>
-                               : logprob ? k_tile_select<false, true> : k_tile_select<false, false>;
+    const select_fn sf =
+        dense     ? (small ? k_tile_select<true, false, 5> : k_tile_select<true, false, 7>)
+        : logprob ? (small ? k_tile_select<false, true, 5> : k_tile_select<false, true, 7>)
+                  : (small ? k_tile_select<false, false, 5> : k_tile_select<false, false, 7>);
     if (!allow_lds(reinterpret_cast<const void*>(sf), select_lds)) return CORAL_ERR_HIP;
     hipLaunchKernelGGL(sf, dim3(M), dim3(kSelectThreads), select_lds, stream, q);
     return launch_status();

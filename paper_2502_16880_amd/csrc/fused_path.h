@@ -46,7 +46,7 @@ __host__ __device__ constexpr int fused_rows(int segs) { return kFusedLoads / se
 inline int fused_segs(int jp) { return jp <= 2 ? 2 : jp <= 4 ? 4 : jp <= 8 ? 8 : 16; }
 __host__ __device__ constexpr int log2_small(int n) { return n <= 1 ? 0 : 1 + log2_small(n / 2); }
 constexpr int kLdsLimit = 160 * 1024;
-// Log-probability mode: a row pair's cost in a workgroup's time is its load latency plus
+// Log-probability mode: a batch's cost in a workgroup's time is its load latency plus
 // the dot products of every token that selected its group; measured in units of one
 // token's dot products the latency is about this much.
 constexpr int kLpBaseCost = 10;
@@ -643,14 +643,14 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         // Log-probability mode: every workgroup streams rows of one group only (it keeps one
         // list and one log-sum-exp state per token, Eq. 8 normalises per group), so the
         // workgroups are shared out among the count <= 64 activated groups in proportion to
-        // their cost, row pairs x (kLpBaseCost + tokens that selected the group): one each,
+        // their cost, batches x (kLpBaseCost + tokens that selected the group): one each,
         // the rest by the groups' shares rounded down, what is then left one more each to the
         // groups with the highest cost per workgroup.  The numbers add up to gridDim.x.
         // One wave's work (activated group u in lane u), after it has written the tables of 2c.
         auto share_out_workgroups = [&](int count, int all_pairs) {
             const int P = gridDim.x;
             const int nb_u = lane < count ? uprefix[lane + 1] - uprefix[lane] : 0;
-            // (row pairs scaled to 16 bits so that the products below stay in 31)
+            // (batches scaled to 16 bits so that the products below stay in 31)
             const int shift = max(0, 16 - __clz(all_pairs));
             const unsigned cost =
                 lane < count ? (unsigned)(nb_u >> shift) * (unsigned)(kLpBaseCost + __popcll(umask[lane])) : 0u;
@@ -777,7 +777,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
                     }
                     count += __popcll(b);
                 }
-                int carry = 0;                             // row pairs before each activated group
+                int carry = 0;                             // batches before each activated group
                 for (int base = 0; base < count; base += kWave) {
                     const int u = base + lane;
                     const int nb = u < count ? (uend[u] - ustart[u] + ROWS - 1) / ROWS : 0;

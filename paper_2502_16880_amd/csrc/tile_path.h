@@ -821,7 +821,6 @@ struct TileSelectParams {
     float* topk_out;                        // [M, k]
     int M, V, g, k;
     int max_blocks;                         // capacity of the per-block arrays in LDS
-    int rows_shift;                         // log2 of k_tiles' rows per block
 };
 
 constexpr int kSelectThreads = 512;
@@ -860,7 +859,8 @@ __host__ __device__ inline TileSelectLds tile_select_lds_layout(int n_groups, in
     return L;
 }
 
-template <bool DENSE, bool LP>
+// SHIFT: log2 of k_tiles' rows per block.
+template <bool DENSE, bool LP, int SHIFT>
 __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams p) {
     extern __shared__ uint4 smem[];
     char* lds = reinterpret_cast<char*>(smem);
@@ -888,8 +888,8 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int t = blockIdx.x, k = p.k;
-    const int rows_per_block = 1 << p.rows_shift;
-    const int chunk_blocks = kSelectKeys * kSelectThreads >> p.rows_shift;
+    constexpr int rows_per_block = 1 << SHIFT;
+    constexpr int chunk_blocks = kSelectKeys * kSelectThreads >> SHIFT;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         __hip_atomic_store(p.next_block, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (threadIdx.x == 0) {
@@ -904,7 +904,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
             g_rows[0] = p.V;
             g_fb[0] = 0;
             g_slot[0] = t;
-            g_nb[0] = (p.V + rows_per_block - 1) >> p.rows_shift;
+            g_nb[0] = (p.V + rows_per_block - 1) >> SHIFT;
             g_shift[0] = 0.f;
         }
     } else {
@@ -916,7 +916,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
             g_rows[j] = hi - lo;
             g_fb[j] = p.group_first_block[grp];
             g_slot[j] = __popcll(mk & ((1ull << t) - 1ull));
-            g_nb[j] = (hi - lo + rows_per_block - 1) >> p.rows_shift;
+            g_nb[j] = (hi - lo + rows_per_block - 1) >> SHIFT;
             g_shift[j] = 0.f;
         }
     }
@@ -1031,13 +1031,13 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
 #pragma unroll
             for (int q = 0; q < kSelectKeys; ++q) {
                 const int e = q * kSelectThreads + threadIdx.x;
-                const int qb = base + (e >> p.rows_shift), r = e & (rows_per_block - 1);
+                const int qb = base + (e >> SHIFT), r = e & (rows_per_block - 1);
                 const int info = qblk[qb < n_q ? qb : n_q - 1];
                 const int j = info >> 16, lb = info & 0xffff;
-                const int row = (lb << p.rows_shift) + r, n_rows = g_rows[j];
+                const int row = (lb << SHIFT) + r, n_rows = g_rows[j];
                 valid[q] = qb < n_q && row < n_rows;
                 grp[q] = j;
-                zv[q] = p.z[(((size_t)(g_fb[j] + lb) * p.M + g_slot[j]) << p.rows_shift) + r];
+                zv[q] = p.z[(((size_t)(g_fb[j] + lb) * p.M + g_slot[j]) << SHIFT) + r];
                 idv[q] = DENSE ? row : p.rows[g_start[j] + (row < n_rows ? row : n_rows - 1)];
             }
 #pragma unroll
