@@ -80,7 +80,7 @@ __device__ __forceinline__ void tree_pad(int n_real, int n_next, int lane, int32
 // Up to 64 nodes kept: one wave selects the n_next best of R * 64 >= N candidates, put(rank, key)
 // once per rank, key 0 past the last candidate: selection instead of ranking every candidate (64
 // x 16 candidates to 64 nodes took 9.7 us, every node's wave building the whole table and
-// searching it; now 8.6 us).  fetch(e) reads candidate e (all of them before the first is
+// searching it; now 6.5 us).  fetch(e) reads candidate e (all of them before the first is
 // used), key_of(raw, e) makes its key.  buf: 64 LDS words.
 constexpr int kTreeTopkMax = 16 * kWave;
 template <int R, class Fetch, class KeyOf, class Put>
