@@ -326,10 +326,16 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
         }
     }
     if (GENERAL) {
+        // (an infinite sum has no rounding error: the two-sum's is inf - inf, NaN)
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int ct = 0; ct < NCT; ++ct) acc[t][ct] += low[t][ct];
+            for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float sum = acc[t][ct][i] + low[t][ct][i];
+                    acc[t][ct][i] = __builtin_isfinite(sum) ? sum : acc[t][ct][i];
+                }
     }
 }
 

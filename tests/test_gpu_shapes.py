@@ -122,3 +122,75 @@ def test_tree_level_selection_and_ranking(coral, M, k, n_next):
                                   torch.from_numpy(logp).cuda(), n_next)
     for a, b in zip(want, got):
         assert np.array_equal(np.asarray(a), b.cpu().numpy())
+
+
+# Infinite logits (a vocabulary masked with -inf weights, sums beyond fp32): +-inf like any other
+# value, also where a running sum keeps its rounding error.  "general": the tile kernels' general
+# form, "small": its blocks of 32 rows, with whole and partly filled chunks of columns.
+INFINITE = [("general", "bf16", 520, 64), ("general", "f32", 1024, 64), ("general", "f16", 1000, 50),
+            ("general", "bf16", 5112, 33), ("small", "bf16", 8192, 12), ("small", "f16", 4608, 16),
+            ("single", "bf16", 4096, 4)]
+
+
+@pytest.mark.parametrize("form,dtype,H,M", INFINITE)
+def test_infinite_logits(coral, form, dtype, H, M):
+    sizes = [40, 130, 70, 300, 33, 64, 260, 128]
+    G, g, k, V = len(sizes), 3, 64, sum(sizes)
+    cfg = HeadConfig(f"inf_{form}", dtype, H, V, G, g, (M,), k, 980 + H + M, True)
+    head = ragged_head(cfg, sizes)
+    hidden = make_hidden(cfg, M, M)
+    inf = {"bf16": (0x7f80, 0xff80), "f16": (0x7c00, 0xfc00), "f32": (np.float32(np.inf), np.float32(-np.inf))}[dtype]
+    rng = np.random.default_rng(cfg.seed + 1)
+    # one infinite weight in every ninth row (the sign of the logit is then that of the weight times
+    # the token's value), everywhere from the first to the last column
+    at = rng.permutation(V)[:V // 9]
+    col = rng.integers(0, H, at.size)
+    col[0], col[1] = 0, H - 1
+    for n, (r, c) in enumerate(zip(at, col)):
+        head.lm_W[r, c] = inf[n % 2]
+    dh = DeviceHead(coral, head)
+    d_hidden = coral.device_tensor(hidden, dtype)
+    z = (d_hidden.double().cpu() @ dh.lm_W.double().cpu().t()).numpy()
+    assert not np.isnan(z).any() and np.isinf(z).sum() == M * at.size
+    group = np.empty(V, np.int64)
+    group[head.group_rows] = np.repeat(np.arange(G), sizes)
+
+    def best(values, groups=None):                     # the k best candidates, equal values by lower id
+        cand = np.arange(V) if groups is None else np.flatnonzero(np.isin(group, groups))
+        order = cand[np.lexsort((cand, -values[cand]))[:k]]
+        return order, values[order]
+
+    def agree(what, values, ids, val, sel=None):
+        for m in range(M):
+            print(f"{form} {dtype} H={H} {what}, token {m} of {M}", flush=True)
+            want_ids, want = best(values[m], None if sel is None else sel[m])
+            assert np.array_equal(np.isposinf(want), np.isposinf(val[m]))
+            assert np.array_equal(np.isneginf(want), np.isneginf(val[m]))
+            fin = np.isfinite(want)
+            assert np.array_equal(ids[m][~fin], want_ids[~fin])      # (infinite values tie exactly)
+            # 5e-5: the bound on log-probabilities of the parity tests, for values of this size
+            assert (np.abs(val[m][fin] - want[fin]) <= 5e-5).all()
+            assert (np.abs(val[m][fin] - values[m][ids[m][fin]]) <= 5e-5).all()
+
+    ids, val, sel = run_grouped(coral, dh, hidden, g, k)
+    agree("logits", z, ids, val, sel)
+    agree("dense", z, *run_dense(coral, dh, hidden, k))
+
+    # Masked rows: of every group all but the first 20, so that -inf reaches the list's end, in the
+    # groups' sums of exp as well (a +inf there leaves its group's log-probabilities undefined).
+    hid = np.abs(hidden) if dtype == "f32" else hidden & np.uint16(0x7fff)
+    for n in range(G):
+        masked = head.group_rows[head.group_offsets[n] + 20:head.group_offsets[n + 1]]
+        head.lm_W[masked, rng.integers(0, H, masked.size)] = inf[1]
+    head.lm_W[at, col] = inf[1]                        # (no +inf is left)
+    dh = DeviceHead(coral, head)
+    d_hid = coral.device_tensor(hid, dtype).double().cpu()
+    z = (d_hid @ dh.lm_W.double().cpu().t()).numpy()
+    s = (d_hid @ dh.gate_W.double().cpu().t()).numpy() + head.gate_bias
+    router = s - np.log(np.exp(s).sum(axis=1, keepdims=True))
+    lse = np.stack([np.log(np.exp(z[:, group == n]).sum(axis=1)) for n in range(G)], axis=1)
+    assert not np.isnan(z).any() and not np.isposinf(z).any() and np.isfinite(lse).all()
+    ids, val, sel = run_grouped(coral, dh, hid, g, k)
+    agree("masked logits", z, ids, val, sel)
+    ids, val, sel = run_logprob(coral, dh, hid, g, k)
+    agree("masked log-probabilities", z + (router - lse)[:, group], ids, val, sel)
