@@ -327,7 +327,7 @@ __device__ __forceinline__ void stream_chunk(const LogitsParams& p, const uint4*
                 if (t < nt) list_insert(lv[t], li[t], z, row_id[r], lane, p.k);
                 if (LP) {                              // wave-uniform values
                     const float nm = fmaxf(mx[t], z);
-                    sm[t] = sm[t] * expf(mx[t] - nm) + expf(z - nm);
+                    if (nm > -INFINITY) sm[t] = sm[t] * expf(mx[t] - nm) + expf(z - nm);   // (else nothing to sum yet)
                     mx[t] = nm;
                 }
             }

@@ -129,7 +129,7 @@ def test_tree_level_selection_and_ranking(coral, M, k, n_next):
 # form, "small": its blocks of 32 rows, with whole and partly filled chunks of columns.
 INFINITE = [("general", "bf16", 520, 64), ("general", "f32", 1024, 64), ("general", "f16", 1000, 50),
             ("general", "bf16", 5112, 33), ("small", "bf16", 8192, 12), ("small", "f16", 4608, 16),
-            ("single", "bf16", 4096, 4)]
+            ("staged", "f32", 4608, 3), ("single", "bf16", 4096, 4)]
 
 
 @pytest.mark.parametrize("form,dtype,H,M", INFINITE)
