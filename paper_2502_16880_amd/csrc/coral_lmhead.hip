@@ -448,6 +448,7 @@ struct PathPlan {
                          // token batch and lists do not fit LDS: rows beyond about 10 K values)
     int tile_umax, tile_lds;
     bool tile_kernels;   // paths 0 and 2: the tile kernels run (path 0: else the staged ones)
+    bool tile_small;     // ... with blocks of 32 rows
 };
 
 bool staged_fits(int M, int jp, int k) {
@@ -493,6 +494,19 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
     return pl;
 }
 
+// Blocks of 32 rows instead of 128, where the 128-row blocks would leave a third of the compute
+// units without work (`groups` activated groups of equal size, `rows` in all), a group's tokens fit
+// one token tile on average (every block stages them again, against a quarter of the weight
+// bytes) and a row is long (a block's start and end, about 4 us, against its chunks).
+// Measured, 128 rows against 32: dense f16 H = 7344, 14561 rows, 16 tokens 88 against 64 us; bf16
+// H = 7680, 12 groups of 1176 rows, 11 tokens 73 against 52; the other way round bf16 H = 1664, 13
+// groups of 2005 rows, 40 tokens 35 against 48; dense f16 H = 5632, 62 tokens 64 against 173.
+bool tile_small_blocks(int V, int g, long long rows, long long groups, long long group_tokens, int n_chunks) {
+    return rows / kTileRows + groups / 2 <= kMaxWorkgroups * 2 / 3 && group_tokens <= 16 && n_chunks >= 8 &&
+           V / kTileRowsSmall + g + 1 <= (1 << 16) &&
+           tile_select_lds_layout(g > 0 ? g : 1, V / kTileRowsSmall + g + 1).total <= kLdsLimit;
+}
+
 PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob = false) {
     PathPlan pl = plan_path_kind(dense, M, H, V, G, g, k, dt, logprob);
     // (One batch of tokens and fewer 128-row blocks than compute units: the staged kernels' 32-row
@@ -502,6 +516,11 @@ PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_d
     const bool few = M <= kTokBatch && rows < (long long)kMaxWorkgroups * kTileRows && staged_fits(M, (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave, k);
     pl.tile_kernels = pl.path == 2 || (pl.path == 0 && !few &&
                                        tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds));
+    const long long groups = dense ? 1 : max_union(M, G, g);
+    const int n_chunks = (H / (is_16bit(dt) ? 8 : 4) + kChunkVecs - 1) / kChunkVecs;
+    pl.tile_small = pl.tile_kernels && groups > 0 &&
+                    tile_small_blocks(V, dense ? 0 : g, rows, groups,
+                                      dense ? M : ((long long)M * g + groups - 1) / groups, n_chunks);
     return pl;
 }
 
@@ -520,25 +539,12 @@ Tiles layout_tiles(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
     return t;
 }
 
-// Blocks of 32 rows instead of 128, where the 128-row blocks would leave a third of the compute
-// units without work (`groups` activated groups of equal size, `rows` in all), a group's tokens fit
-// one token tile on average (every block stages them again, against a quarter of the weight
-// bytes) and a row is long (a block's start and end, about 4 us, against its chunks).
-// Measured, 128 rows against 32: dense f16 H = 7344, 14561 rows, 16 tokens 88 against 64 us; bf16
-// H = 7680, 12 groups of 1176 rows, 11 tokens 73 against 52; the other way round bf16 H = 1664, 13
-// groups of 2005 rows, 40 tokens 35 against 48; dense f16 H = 5632, 62 tokens 64 against 173.
-bool tile_small_blocks(int V, int g, long long rows, long long groups, long long group_tokens, int n_chunks) {
-    return rows / kTileRows + groups / 2 <= kMaxWorkgroups * 2 / 3 && group_tokens <= 16 && n_chunks >= 8 &&
-           V / kTileRowsSmall + g + 1 <= (1 << 16) &&
-           tile_select_lds_layout(g > 0 ? g : 1, V / kTileRowsSmall + g + 1).total <= kLdsLimit;
-}
-
 // Enqueues k_tiles and the ranking of the logits it leaves.  For the grouped head the gate
 // and selection kernel must already be enqueued (selection, the token tiles' masks; in the
 // log-probability mode log p_router of the selection too).
-coral_status launch_tiles(bool dense, bool general, const void* hidden, const void* lm_W,
+coral_status launch_tiles(bool dense, const PathPlan& plan, const void* hidden, const void* lm_W,
                           const coral_group_index* gi, int M, int H, int V,
-                          int G, int k, coral_dtype dt, int u_max, int lds, int32_t* topk_ids,
+                          int G, int k, coral_dtype dt, int32_t* topk_ids,
                           float* topk_out, char* ws, const Layout& L, hipStream_t stream,
                           void* ev_before, void* ev_after, const int32_t* sel = nullptr, int g = 0,
                           bool logprob = false) {
@@ -560,11 +566,10 @@ coral_status launch_tiles(bool dense, bool general, const void* hidden, const vo
     p.M = M; p.V = V; p.G = G;
     p.n_vec = H / (is_16bit(dt) ? 8 : 4);
     p.n_chunks = (p.n_vec + kChunkVecs - 1) / kChunkVecs;
-    p.u_max = u_max;
+    p.u_max = plan.tile_umax;
     typedef void (*tiles_fn)(TileParams, int);
-    const long long groups = dense ? 1 : max_union(M, G, g);
-    const bool small = tile_small_blocks(V, g, dense ? V : groups * V / G, groups,
-                                         dense ? M : ((long long)M * g + groups - 1) / groups, p.n_chunks);
+    const bool small = plan.tile_small, general = plan.path == 0;
+    const int lds = plan.tile_lds;
     const int rows_per_block = small ? kTileRowsSmall : kTileRows;
     const tiles_fn fn =
         small     ? CORAL_PICK_DT(dt, (k_tiles<kF32, true, kTileSplitSmall>), (k_tiles<kBF16, true, kTileSplitSmall>),
@@ -707,6 +712,19 @@ extern "C" coral_status coral_lmhead_workspace_init(void* workspace, size_t work
 
 namespace {
 
+// The tile kernels' arrays in the static scratch: for all M tokens, or for the most equal batches
+// of them that fit.
+Layout layout_in_batches(int M, int V, int G, int g, int k, Tiles tiles, int* tokens) {
+    Layout L = {};
+    for (int n = 1; n <= M; ++n) {
+        const int m = (M + n - 1) / n;
+        L = make_layout(m, V, G, g, k, Pieces{}, tiles, LayoutFor::kTiles);
+        *tokens = m;
+        if (L.total <= kStaticScratchBytes) break;
+    }
+    return L;
+}
+
 coral_status grouped_impl(const void* hidden, const void* gate_hidden, const void* gate_W,
                           const float* gate_bias, const void* lm_W, const coral_group_index* gi, int M, int H, int V,
                           int g, int k, coral_dtype dt, int32_t* topk_ids, float* topk_logits,
@@ -747,24 +765,24 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
     // (the static scratch serves the logit ranking only: no table of pieces, and of the arrays
     // only those of the path that this very call takes; rows beyond 8 KB are taken or refused by
     // what the multi-kernel path for them would need)
+    PathPlan plan = plan_path(false, M, H, V, G, g, k, dt, logprob);
     Layout L;
-    bool static_general = false;
+    int tile_tokens = M;                       // tokens that the tile kernels take at a time
     if (!static_workspace) {
         L = make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt), layout_tiles(M, H, V, G, g, k, dt));
     } else {
-        const PathPlan sp = plan_path(false, M, H, V, G, g, k, dt);
-        const bool long_rows = sp.path == 1 && (size_t)H * (is_16bit(dt) ? 2 : 4) > 8192;
+        const bool long_rows = plan.path == 1 && (size_t)H * (is_16bit(dt) ? 2 : 4) > 8192;
         int um, lds;
-        const bool tiles = sp.path == 2 || (long_rows && tiles_fit(M, H, V, G, g, k, dt, &um, &lds));
+        const bool tiles = plan.path == 2 || (long_rows && tiles_fit(M, H, V, G, g, k, dt, &um, &lds));
         L = make_layout(M, V, G, g, k, Pieces{}, tiles ? Tiles::kOwn : Tiles::kNone,
                         tiles ? LayoutFor::kTiles : LayoutFor::kWorkspace);
         if (long_rows && L.total <= kStaticScratchBytes)
             L = make_layout(M, V, G, g, k, Pieces{}, Tiles::kNone, LayoutFor::kSingleLaunch);
-        if (sp.path == 0 && sp.tile_kernels && L.total <= kStaticScratchBytes) {
-            const Layout T = make_layout(M, V, G, g, k, Pieces{}, Tiles::kGeneral, LayoutFor::kTiles);
-            static_general = T.total <= kStaticScratchBytes;      // else the staged kernels, whose lists are smaller
-            if (static_general) L = T;
-        }
+        // (the general path's tile kernels may need more than the staged lists it is accepted by: then
+        // they run for fewer tokens at a time, which leaves every bit of a token's result as it is;
+        // at least one token's logits fit, 4 V bytes with V limited by the ranking kernel's LDS)
+        if (plan.path == 0 && plan.tile_kernels && L.total <= kStaticScratchBytes)
+            L = layout_in_batches(M, V, G, g, k, Tiles::kGeneral, &tile_tokens);
     }
     if (static_workspace) {
         if (logprob || L.total > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;
@@ -774,13 +792,11 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
     }
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    PathPlan plan = plan_path(false, M, H, V, G, g, k, dt, logprob);
     if (logprob && plan.path == 1) {   // a device with few compute units: see fused_logprob_fits
         const int cu = compute_units();
         if (2 * max_union(M, G, g) > (cu < kMaxWorkgroups ? cu : kMaxWorkgroups))
             plan.path = staged_fits(M, ((H / (is_16bit(dt) ? 8 : 4)) + kWave - 1) / kWave, k) ? 0 : -1;
     }
-    if (static_workspace && plan.path == 0) plan.tile_kernels = static_general;
     if (plan.path < 0) return CORAL_ERR_UNSUPPORTED;       // before anything is enqueued
     if (static_workspace) {
         // this device's copy of the array; its control words are cleared by a fill kernel on
@@ -807,21 +823,27 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
     const uint4* ghid = static_cast<const uint4*>(gate_hidden);
     const uint4* gw = static_cast<const uint4*>(gate_W);
     if (plan.tile_kernels) {
-        GateSelParams q = {};
-        q.hidden = ghid; q.gate_W = gw; q.bias = gate_bias; q.s = s; q.sel = sel;
-        q.tile_mask = reinterpret_cast<unsigned long long*>(ws + L.tile_mask);
-        q.counters = reinterpret_cast<unsigned int*>(ws + L.ctrl) + coral_ctrl::kGateSelectArrival;
-        q.M = M; q.G = G; q.g = g; q.n_vec = n_vec;
-        if (logprob) q.logp_sel = reinterpret_cast<float*>(ws + L.logp_sel);
-        const int tiles = ((G + 15) / 16) * ((M + 15) / 16);
+        const int tiles_g = (G + 15) / 16;
         typedef void (*gate_select_fn)(GateSelParams);
         const gate_select_fn gs = CORAL_PICK_DT(dt, k_gate_select<kF32>, k_gate_select<kBF16>, k_gate_select<kF16>);
-        hipLaunchKernelGGL(gs, dim3(tiles, kGateParts), dim3(kFusedBlock), 0, stream, q);
-        if ((st = launch_status()) != CORAL_OK) return st;
-        st = launch_tiles(false, plan.path == 0, hidden, lm_W, gi, M, H, V, G, k, dt,
-                          plan.tile_umax, plan.tile_lds, topk_ids, topk_logits, ws, L, stream, ev_before,
-                          ev_after, sel, g, logprob);
-        if (st != CORAL_OK || !level) return st;
+        for (int m0 = 0; m0 < M; m0 += tile_tokens) {          // (one turn but for the static scratch)
+            const int m = M - m0 < tile_tokens ? M - m0 : tile_tokens;
+            int32_t* sel_m = sel_groups ? sel + (size_t)m0 * g : sel;
+            GateSelParams q = {};
+            q.hidden = ghid + (size_t)m0 * n_vec;
+            q.gate_W = gw; q.bias = gate_bias; q.s = s; q.sel = sel_m;
+            q.tile_mask = reinterpret_cast<unsigned long long*>(ws + L.tile_mask);
+            q.counters = reinterpret_cast<unsigned int*>(ws + L.ctrl) + coral_ctrl::kGateSelectArrival;
+            q.M = m; q.G = G; q.g = g; q.n_vec = n_vec;
+            if (logprob) q.logp_sel = reinterpret_cast<float*>(ws + L.logp_sel);
+            hipLaunchKernelGGL(gs, dim3(tiles_g * ((m + 15) / 16), kGateParts), dim3(kFusedBlock), 0, stream, q);
+            if ((st = launch_status()) != CORAL_OK) return st;
+            st = launch_tiles(false, plan, hid + (size_t)m0 * n_vec, lm_W, gi, m, H, V, G, k, dt,
+                              topk_ids + (size_t)m0 * k, topk_logits + (size_t)m0 * k, ws, L, stream, ev_before,
+                              ev_after, sel_m, g, logprob);
+            if (st != CORAL_OK) return st;
+        }
+        if (!level) return CORAL_OK;
         return launch_tree_expand(*level, topk_ids, topk_logits, M, k, stream);
     }
     typedef void (*gate_fn)(const uint4*, const uint4*, const float*, int, int, int, float*);
@@ -893,9 +915,8 @@ coral_status dense_impl(const void* hidden, const void* lm_W, int M, int H, int 
     if (plan.path < 0) return CORAL_ERR_UNSUPPORTED;
     // many tokens per row: the contraction is no longer cheap on the vector units
     if (plan.tile_kernels)
-        return launch_tiles(true, plan.path == 0, hidden, lm_W, nullptr, M, H, V, 0, k, dt,
-                            plan.tile_umax, plan.tile_lds, topk_ids, topk_logits, ws, L, stream,
-                            ev_before, ev_after);
+        return launch_tiles(true, plan, hidden, lm_W, nullptr, M, H, V, 0, k, dt, topk_ids, topk_logits, ws, L,
+                            stream, ev_before, ev_after);
     if (plan.path == 1)
         return launch_fused(true, hidden, nullptr, nullptr, nullptr, lm_W, nullptr, M, H, V, 0, 0, k, dt, topk_ids,
                             topk_logits, nullptr, ws, L, stream, ev_before, ev_after);

@@ -135,3 +135,22 @@ def test_noalloc_under_graph_capture(coral):
         torch.cuda.synchronize()
         for a, b in zip(want, (ids, z, sel)):
             assert torch.equal(a, b), rep
+
+
+# The general path's tile kernels (more than eight tokens): their arrays fit the scratch; or they do
+# not, while the staged lists by which the shape is accepted do, and the tokens go in batches.
+GENERAL = [("bf16", 1664, 6400, 16, 2, 10, 40), ("f16", 1000, 16000, 32, 3, 4, 64), ("f32", 2056, 4096, 16, 2, 8, 33),
+           ("bf16", 1664, 50272, 16, 2, 10, 40), ("bf16", 2568, 100352, 64, 4, 2, 33), ("f32", 2308, 50272, 16, 2, 3, 64)]
+
+
+@pytest.mark.parametrize("dtype,H,V,G,g,k,M", GENERAL)
+def test_noalloc_on_the_general_paths_tile_kernels(coral, dtype, H, V, G, g, k, M):
+    dt = {"f32": coral.CORAL_F32, "bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
+    cfg = HeadConfig(f"general{H}", dtype, H, V, G, g, (M,), k, 1000 + H, True, bias_std=0.5)
+    assert coral.coral_lmhead_path(False, M, H, V, G, g, k, dt) == 0
+    dev = upload(coral, make_head(cfg))
+    for m in (M, M - 7):
+        print(f"case {dtype} H={H} V={V} M={m}", flush=True)
+        want, got = both(coral, cfg, dev, m, g, k, batch=m)
+        for name, a, b in zip(("ids", "logits", "groups"), want, got):
+            assert torch.equal(a, b), f"{name} differ with {m} tokens"
