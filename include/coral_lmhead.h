@@ -177,11 +177,12 @@ coral_status coral_lmhead_grouped(const void *hidden, const void *gate_W,
  * lists, arrival counters, the staged path's hand-over arrays) lives in a static device array
  * of CORAL_NOALLOC_SCRATCH_BYTES inside the library, one copy per GPU, held until the
  * process ends.  The call allocates and frees nothing.
- *   - Shapes whose scratch need (coral_lmhead_workspace_bytes for the same sizes, without the
- *     log-probability mode's tables; rows beyond 8 KB: what the tile or general path needs for
- *     them) exceeds CORAL_NOALLOC_SCRATCH_BYTES are refused with
+ *   - Shapes whose published and staged lists (16-bit shapes with whole 512-column chunks that
+ *     are beyond the single-launch path, or have rows beyond 8 KB: the tile path's logits
+ *     buffer with 128-row blocks) exceed CORAL_NOALLOC_SCRATCH_BYTES are refused with
  *     CORAL_ERR_WORKSPACE before anything is enqueued.  Every workload shape of Table 1 with up
- *     to 16 tokens fits.
+ *     to 16 tokens fits.  Where the kernels that run a shape need more than it is counted by,
+ *     they take the tokens in batches, with the same results.
  *   - All calls on one GPU share that GPU's array: calls that overlap on one GPU (two
  *     streams, two threads) race and give unspecified results; calls on one stream, or
  *     otherwise ordered, are safe.  Each call first clears the array's control words with a

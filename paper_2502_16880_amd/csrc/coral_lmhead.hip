@@ -79,15 +79,20 @@ enum class LayoutFor { kWorkspace, kSingleLaunch, kTiles };
 
 // pieces: the log-probability mode's table of per-batch pieces (layout_pieces).  tiles: whether the
 // shape can take the tile kernels (their logits buffer and statistics are left out otherwise), as
-// the matrix-core path proper or on the general path.
+// the matrix-core path proper or on the general path, and whether with blocks of 32 rows.
 enum class Tiles { kNone, kGeneral, kOwn };
+struct TileArrays {
+    Tiles kind;
+    bool small;
+};
 struct Pieces {
     size_t entries;             // 0 if the single-launch kernel cannot run the mode
     bool shared;                // in the memory of the multi-kernel paths' arrays
 };
-Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, Tiles tiles,
+Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, TileArrays tile_arrays,
                    LayoutFor what = LayoutFor::kWorkspace) {
     Layout L;
+    const Tiles tiles = tile_arrays.kind;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         size_t at = off;
@@ -96,10 +101,11 @@ Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, Tiles tiles
     };
     L.ctrl = take(kCtrlBytes);
     const size_t single = what != LayoutFor::kTiles ? 1 : 0;
+    const size_t logprob = what == LayoutFor::kWorkspace ? 1 : 0;
     const size_t staged = what == LayoutFor::kWorkspace ? 1 : 0;
     L.fused_part = take(single * kMaxWorkgroups * M * k * sizeof(Cand));
-    L.fused_lse = take(single * kMaxWorkgroups * M * sizeof(unsigned long long));   // log-probability mode
-    L.fused_glist = take(single * M * (g ? g : 1) * k * sizeof(Cand));
+    L.fused_lse = take(logprob * kMaxWorkgroups * M * sizeof(unsigned long long));   // log-probability mode
+    L.fused_glist = take(logprob * M * (g ? g : 1) * k * sizeof(Cand));
     L.fused_pairs = off;
     const size_t pieces_end = align_up(off + pieces.entries * sizeof(unsigned long long), 256);
     if (!pieces.shared) off = pieces_end;
@@ -125,7 +131,8 @@ Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, Tiles tiles
     const size_t tile_blocks = (size_t)V / kTileRows + G + (tiles == Tiles::kOwn || G == 0 ? 1 : 0);
     L.tile_z = take(tiles != Tiles::kNone ? tile_blocks * M * kTileRows * sizeof(float) : 0);
     // (with blocks of 32 rows the logits take no more, their statistics V / 32 + G entries)
-    L.tile_stat = take(tiles != Tiles::kNone ? ((size_t)V / kTileRowsSmall + G + 1) * M * sizeof(float2) : 0);
+    const size_t stat_blocks = (size_t)V / (tile_arrays.small ? kTileRowsSmall : kTileRows) + G + 1;
+    L.tile_stat = take(tiles != Tiles::kNone ? stat_blocks * M * sizeof(float2) : 0);
     if (off < after) off = after;
     L.total = off > pieces_end ? off : pieces_end;
     return L;
@@ -526,15 +533,16 @@ PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_d
 
 // Whether a call with these sizes (grouped in either output mode, or dense when G = 0) can run
 // the tile kernels: the workspace then holds their logits buffer.
-Tiles layout_tiles(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
-    if (!dtype_ok(dt) || H % (is_16bit(dt) ? 8 : 4) != 0) return Tiles::kNone;
+TileArrays layout_tiles(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
+    if (!dtype_ok(dt) || H % (is_16bit(dt) ? 8 : 4) != 0) return {Tiles::kNone, false};
     const PathPlan plans[3] = {plan_path(true, M, H, V, 0, 0, k, dt),
                                G < 1 ? PathPlan{-1} : plan_path(false, M, H, V, G, g, k, dt),
                                G < 1 ? PathPlan{-1} : plan_path(false, M, H, V, G, g, k, dt, true)};
-    Tiles t = Tiles::kNone;
+    TileArrays t = {Tiles::kNone, false};
     for (const PathPlan& p : plans) {
-        if (p.path == 2) return Tiles::kOwn;
-        if (p.path == 0 && p.tile_kernels) t = Tiles::kGeneral;
+        if (p.path == 2) t.kind = Tiles::kOwn;
+        else if (p.path == 0 && p.tile_kernels && t.kind == Tiles::kNone) t.kind = Tiles::kGeneral;
+        t.small = t.small || p.tile_small;
     }
     return t;
 }
@@ -712,14 +720,38 @@ extern "C" coral_status coral_lmhead_workspace_init(void* workspace, size_t work
 
 namespace {
 
-// The tile kernels' arrays in the static scratch: for all M tokens, or for the most equal batches
-// of them that fit.
-Layout layout_in_batches(int M, int V, int G, int g, int k, Tiles tiles, int* tokens) {
+// The static scratch array (logit ranking only, no table of pieces).  Which shapes it takes is a
+// matter of sizes that callers rely on, and does not move with the kernels: the published and the
+// staged lists must fit, or, for shapes that the tile path runs with 128-row blocks, that path's
+// arrays.  The latter count too where the single-launch kernel has come to run such shapes since
+// (rows beyond 8 KB, and narrow heads with many candidates, since its merges need no 24 KB of their
+// own at the place of the hidden vectors).
+size_t static_counted_bytes(const PathPlan& plan, int M, int H, int V, int G, int g, int k, coral_dtype dt) {
+    bool tiles = plan.path == 2;
+    int um, lds;
+    if (plan.path == 1 && tiles_fit(M, H, V, G, g, k, dt, &um, &lds)) {
+        const int jp = (H / 8 + kWave - 1) / kWave;
+        const FusedLds F = fused_lds_layout(M, G, g, k, jp, false, fused_gate_mode(false, M, G, g, k, jp, dt));
+        const int hidden = M * hidden_lds_stride(jp) * (int)sizeof(uint4), merges = 24 * 1024;
+        tiles = jp > 8 || F.total - F.o_lists + (hidden > merges ? hidden : merges) > kLdsLimit;
+    }
+    return make_layout(M, V, G, g, k, Pieces{}, {tiles ? Tiles::kOwn : Tiles::kNone, false},
+                       tiles ? LayoutFor::kTiles : LayoutFor::kWorkspace).total;
+}
+
+// The arrays of the kernels that run a call, in the static scratch.  The tile kernels' may be more
+// than the call is counted by: then they run for the tokens in equal batches, which leaves every bit
+// of a token's result as it is (one token's arrays fit: 4 V bytes of logits, with V limited by the
+// ranking kernel's LDS).
+Layout static_layout(const PathPlan& plan, int M, int V, int G, int g, int k, int* batch) {
+    *batch = M;
+    if (plan.path == 1) return make_layout(M, V, G, g, k, Pieces{}, TileArrays{}, LayoutFor::kSingleLaunch);
+    if (!plan.tile_kernels) return make_layout(M, V, G, g, k, Pieces{}, TileArrays{});
     Layout L = {};
     for (int n = 1; n <= M; ++n) {
-        const int m = (M + n - 1) / n;
-        L = make_layout(m, V, G, g, k, Pieces{}, tiles, LayoutFor::kTiles);
-        *tokens = m;
+        *batch = (M + n - 1) / n;
+        L = make_layout(*batch, V, G, g, k, Pieces{}, {plan.path == 2 ? Tiles::kOwn : Tiles::kGeneral, plan.tile_small},
+                        LayoutFor::kTiles);
         if (L.total <= kStaticScratchBytes) break;
     }
     return L;
@@ -762,31 +794,15 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
         min_cand += smallest[i];
     }
     if ((long long)k > min_cand) return CORAL_ERR_SHAPE;
-    // (the static scratch serves the logit ranking only: no table of pieces, and of the arrays
-    // only those of the path that this very call takes; rows beyond 8 KB are taken or refused by
-    // what the multi-kernel path for them would need)
     PathPlan plan = plan_path(false, M, H, V, G, g, k, dt, logprob);
     Layout L;
     int tile_tokens = M;                       // tokens that the tile kernels take at a time
-    if (!static_workspace) {
-        L = make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt), layout_tiles(M, H, V, G, g, k, dt));
-    } else {
-        const bool long_rows = plan.path == 1 && (size_t)H * (is_16bit(dt) ? 2 : 4) > 8192;
-        int um, lds;
-        const bool tiles = plan.path == 2 || (long_rows && tiles_fit(M, H, V, G, g, k, dt, &um, &lds));
-        L = make_layout(M, V, G, g, k, Pieces{}, tiles ? Tiles::kOwn : Tiles::kNone,
-                        tiles ? LayoutFor::kTiles : LayoutFor::kWorkspace);
-        if (long_rows && L.total <= kStaticScratchBytes)
-            L = make_layout(M, V, G, g, k, Pieces{}, Tiles::kNone, LayoutFor::kSingleLaunch);
-        // (the general path's tile kernels may need more than the staged lists it is accepted by: then
-        // they run for fewer tokens at a time, which leaves every bit of a token's result as it is;
-        // at least one token's logits fit, 4 V bytes with V limited by the ranking kernel's LDS)
-        if (plan.path == 0 && plan.tile_kernels && L.total <= kStaticScratchBytes)
-            L = layout_in_batches(M, V, G, g, k, Tiles::kGeneral, &tile_tokens);
-    }
     if (static_workspace) {
-        if (logprob || L.total > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;
+        if (logprob || static_counted_bytes(plan, M, H, V, G, g, k, dt) > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;
+        L = static_layout(plan, M, V, G, g, k, &tile_tokens);
+        if (L.total > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;             // not reached
     } else {
+        L = make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt), layout_tiles(M, H, V, G, g, k, dt));
         st = check_workspace(workspace, workspace_bytes, L.total);
         if (st != CORAL_OK) return st;
     }

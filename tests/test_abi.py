@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2502_16880_amd as coral
 
@@ -281,3 +282,36 @@ def test_noalloc_entry_point_checks_arguments_and_size_before_touching_the_devic
     header = open(HEADER).read()
     m = re.search(r"#define\s+CORAL_NOALLOC_SCRATCH_BYTES\s+\((\d+)u\s*<<\s*(\d+)\)", header)
     assert m and int(m.group(1)) << int(m.group(2)) == coral.NOALLOC_SCRATCH_BYTES
+
+
+def noalloc_status(M, H, V, G, g, k, dt):
+    """Status of coral_lmhead_grouped_noalloc with made-up addresses.  Only without a GPU: a shape
+    that passes the size check then stops where the scratch array's address is looked up."""
+    off = (np.arange(G + 1, dtype=np.int64) * V // G).astype(np.int32)
+    gi = coral._GroupIndexStruct(G, off.ctypes.data, FAKE + 0x600000, FAKE + 0x700000)
+    return coral._L.coral_lmhead_grouped_noalloc(FAKE, FAKE + 0x100000, None, FAKE + 0x200000, ctypes.byref(gi), M, H,
+                                                 V, g, k, dt, FAKE + 0x300000, FAKE + 0x400000, None, None)
+
+
+# (H, V, G, g, k, storage) and the most tokens that the static scratch takes: counted by the tile
+# path's arrays (whole 512-column chunks, rows beyond 8 KB among them), by the staged lists (other
+# widths, fp32, what the single-launch kernel runs), and a narrow head with 64 candidates that counts
+# by the former although the latter kernel runs it
+NOALLOC_LIMITS = [((4096, 32000, 16, 2, 10, BF16), 60), ((4096, 32000, 16, 2, 10, 2), 60), ((4096, 32000, 32, 4, 10, BF16), 56),
+                  ((4096, 50257, 16, 2, 10, BF16), 39), ((2560, 50257, 48, 3, 20, BF16), 36), ((8192, 32000, 16, 2, 10, BF16), 60),
+                  ((5120, 128256, 32, 4, 10, BF16), 15), ((4096, 128256, 32, 4, 10, BF16), 16), ((3584, 152064, 32, 4, 10, BF16), 16),
+                  ((1664, 50272, 16, 2, 10, BF16), 51), ((2308, 50272, 16, 2, 10, F32), 51), ((256, 8192, 16, 2, 64, F32), 31)]
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the made-up addresses would be launched with")
+@pytest.mark.parametrize("shape,most", NOALLOC_LIMITS)
+def test_noalloc_takes_the_sizes_it_always_took(shape, most):
+    assert noalloc_status(most, *shape) == HIP
+    assert noalloc_status(most + 1, *shape) == WORKSPACE
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the made-up addresses would be launched with")
+def test_noalloc_sizes_of_a_narrow_head_with_many_candidates():
+    assert coral.coral_lmhead_path(False, 16, 512, 32000, 16, 2, 64, BF16) == 1
+    took = [m for m in range(1, 65) if noalloc_status(m, 512, 32000, 16, 2, 64, BF16) == HIP]
+    assert took == [*range(1, 13), *range(16, 61)]       # up to 12 by its lists, from 16 on by the tile path's arrays

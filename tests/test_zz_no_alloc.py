@@ -154,3 +154,30 @@ def test_noalloc_on_the_general_paths_tile_kernels(coral, dtype, H, V, G, g, k, 
         want, got = both(coral, cfg, dev, m, g, k, batch=m)
         for name, a, b in zip(("ids", "logits", "groups"), want, got):
             assert torch.equal(a, b), f"{name} differ with {m} tokens"
+
+
+# The most tokens that the scratch takes: tile path with 128-row blocks, with 32-row blocks (whose
+# statistics make the tokens go in batches), and a narrow head that the single-launch kernel runs.
+LIMITS = [("bf16", 4096, 32000, 16, 2, 10, 60, 2), ("f16", 4096, 32000, 32, 4, 10, 56, 2),
+          ("bf16", 4608, 56358, 93, 1, 4, 30, 2), ("bf16", 512, 32000, 16, 2, 64, 16, 1)]
+
+
+@pytest.mark.parametrize("dtype,H,V,G,g,k,M,path", LIMITS)
+def test_noalloc_at_the_limits_of_its_scratch(coral, dtype, H, V, G, g, k, M, path):
+    code = {"bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
+    assert coral.coral_lmhead_path(False, M, H, V, G, g, k, code) == path
+    print(f"case {dtype} H={H} V={V} M={M}", flush=True)
+    torch.manual_seed(H + M)
+    t = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    lm_W = (torch.randn(V, H, device="cuda", dtype=t)).mul_(0.02)
+    gate_W = (torch.randn(G, H, device="cuda", dtype=t)).mul_(0.02)
+    hidden = torch.randn(M, H, device="cuda", dtype=t)
+    gi = coral.GroupIndex((np.arange(G + 1) * (V // G)).astype(np.int32), np.random.default_rng(1).permutation(V))
+    want = coral.coral_lmhead_grouped(hidden, gate_W, None, lm_W, gi, g, k)
+    ids = torch.full((M, k), -5, dtype=torch.int32, device="cuda")
+    z = torch.full((M, k), float("nan"), device="cuda")
+    sel = torch.full((M, g), -5, dtype=torch.int32, device="cuda")
+    coral.coral_lmhead_grouped_noalloc(hidden, gate_W, None, lm_W, gi, g, k, ids, z, sel)
+    torch.cuda.synchronize()
+    for a, b in zip(want, (ids, z, sel)):
+        assert torch.equal(a, b)
