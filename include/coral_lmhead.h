@@ -88,7 +88,8 @@ coral_status coral_group_index_validate(const int32_t *host_offsets,
 /*
  * Bytes of device workspace that coral_lmhead_grouped / coral_lmhead_dense need
  * for these sizes (pass G = g = 0 for the dense head).  The bound holds for any
- * partition of V rows into G groups.  Returns 0 if the sizes are invalid.
+ * partition of V rows into G groups, for all the entry points that take these sizes, the
+ * dense head among them, and for fewer tokens.  Returns 0 if the sizes are invalid.
  */
 size_t coral_lmhead_workspace_bytes(int M, int H, int V, int G, int g, int k,
                                     coral_dtype dt);

@@ -314,21 +314,13 @@ coral_status launch_tree_expand(const LevelExpand& level, const int32_t* cand_id
 // The single-launch log-probability mode's table of pieces: one (max, sum) per (batch of rows of
 // a selected group, token that selected it); a token's g groups are distinct, so their batches
 // number V / rows + g at most.  Rows beyond 8 KB (one to a batch): the table shares the memory of
-// the multi-kernel paths' arrays, which no call uses with it, and is sized for the most tokens up
-// to M with which the mode runs in that kernel, so that a workspace for M tokens serves fewer.
+// the multi-kernel paths' arrays, which no call uses with it.
 Pieces layout_pieces(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
-    if (G < 1 || !dtype_ok(dt)) return {0, false};
+    if (G < 1 || !dtype_ok(dt) || M > kLogprobFusedMaxTokens) return {0, false};
     const int n_vec = H / (is_16bit(dt) ? 8 : 4);
     const int jp = (n_vec + kWave - 1) / kWave;
-    if (jp < 1 || !fused_rows_fit(jp)) return {0, false};
-    const bool shared = jp > 8;
-    const int in_lds = kLdsLimit / (int)(hidden_lds_stride(jp) * sizeof(uint4));       // hidden vectors alone
-    const int least = shared ? 1 : M;
-    const int most = in_lds < kLogprobFusedMaxTokens ? in_lds : kLogprobFusedMaxTokens;
-    for (int m = M < most ? M : most; m >= least; --m)
-        if (fused_logprob_fits(m, G, g, k, jp, dt, kMaxWorkgroups))
-            return {(size_t)m * ((size_t)V / fused_rows(fused_segs(jp)) + g), shared};
-    return {0, false};
+    if (jp < 1 || !fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups)) return {0, false};
+    return {(size_t)M * ((size_t)V / fused_rows(fused_segs(jp)) + g), jp > 8};
 }
 
 // Enqueues the single-launch path (the caller has checked with plan_path that it fits).
@@ -690,8 +682,14 @@ extern "C" coral_status coral_group_index_validate(const int32_t* host_offsets,
 extern "C" size_t coral_lmhead_workspace_bytes(int M, int H, int V, int G, int g, int k,
                                                coral_dtype dt) {
     if (!sizes_ok(M, H, V, G, g, k)) return 0;
-    return make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt),
-                       layout_tiles(M, H, V, G, g, k, dt)).total;
+    // (fewer tokens can need more, where they take a route with larger arrays)
+    size_t most = 0;
+    for (int m = M; m >= 1; m = m > kMaxM ? kMaxM : m - 1) {
+        const size_t need = make_layout(m, V, G, g, k, layout_pieces(m, H, V, G, g, k, dt),
+                                        layout_tiles(m, H, V, G, g, k, dt)).total;
+        if (need > most) most = need;
+    }
+    return most;
 }
 
 extern "C" int coral_lmhead_path(int dense, int M, int H, int V, int G, int g, int k,

@@ -315,3 +315,26 @@ def test_noalloc_sizes_of_a_narrow_head_with_many_candidates():
     assert coral.coral_lmhead_path(False, 16, 512, 32000, 16, 2, 64, BF16) == 1
     took = [m for m in range(1, 65) if noalloc_status(m, 512, 32000, 16, 2, 64, BF16) == HIP]
     assert took == [*range(1, 13), *range(16, 61)]       # up to 12 by its lists, from 16 on by the tile path's arrays
+
+
+# Heads whose calls with fewer tokens take a route with larger arrays: log-probabilities in the
+# single launch up to 32 tokens, the general path's tile kernels where the full count has no path.
+FEWER = [(36, 256, 152064, 48, 3, 20, F32), (33, 256, 9568, 16, 9, 16, F32), (48, 1024, 128256, 61, 8, 16, BF16),
+         (25, 3072, 128256, 16, 5, 10, BF16), (38, 5120, 50272, 300, 3, 1, F32), (64, 2048, 913944, 32, 9, 4, 2),
+         (64, 4096, 128256, 64, 8, 16, BF16)]
+
+
+@pytest.mark.parametrize("M,H,V,G,g,k,dt", FEWER)
+def test_a_workspace_serves_fewer_tokens(M, H, V, G, g, k, dt):
+    wb = coral.coral_lmhead_workspace_bytes
+    have = wb(M, H, V, G, g, k, dt)
+    assert all(wb(m, H, V, G, g, k, dt) <= have for m in range(1, M))
+    assert all(wb(m, H, V, 0, 0, k, dt) <= have for m in range(1, M + 1))       # the dense head too
+    if torch.cuda.is_available():
+        return                                         # (the made-up addresses would be launched with)
+    c = Call()
+    c.off = (np.arange(G + 1, dtype=np.int64) * V // G).astype(np.int32)
+    c.gi = coral._GroupIndexStruct(G, c.off.ctypes.data, FAKE + 0x600000, FAKE + 0x700000)
+    for m in range(1, M + 1):
+        kw = dict(M=m, H=H, V=V, g=g, k=k, dt=dt, ws_bytes=have)
+        assert c.grouped(**kw) in (HIP, UNSUPPORTED) and c.dense(**kw) in (HIP, UNSUPPORTED)

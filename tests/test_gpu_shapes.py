@@ -194,3 +194,23 @@ def test_infinite_logits(coral, form, dtype, H, M):
     agree("masked logits", z, ids, val, sel)
     ids, val, sel = run_logprob(coral, dh, hid, g, k)
     agree("masked log-probabilities", z + (router - lse)[:, group], ids, val, sel)
+
+
+@pytest.mark.parametrize("dtype,H,G,v,g,k,Ms", [("f32", 256, 16, 598, 9, 16, (33, 32, 7)), ("bf16", 1024, 60, 190, 8, 16, (48, 33, 32, 1)),
+                                                ("bf16", 8192, 32, 190, 4, 10, (20, 8, 9, 1)), ("f16", 1000, 20, 190, 2, 33, (64, 5, 40, 8))])
+def test_one_workspace_for_several_token_counts(coral, dtype, H, G, v, g, k, Ms):
+    """A workspace for the most tokens serves fewer, in any order and every output mode: the same
+    bits as with a workspace of the call's own."""
+    sizes = [v - 31 if n % 2 else v + 31 for n in range(G)]
+    cfg = HeadConfig(f"ws{H}", dtype, H, sum(sizes), G, g, Ms, k, 990 + H, True)
+    dh = DeviceHead(coral, ragged_head(cfg, sizes))
+    code = {"bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16, "f32": coral.CORAL_F32}[dtype]
+    ws = coral.alloc_workspace(max(Ms), H, cfg.V, G, g, k, code)
+    for M in Ms:
+        h = coral.device_tensor(make_hidden(cfg, M, M), dtype)
+        for call in (lambda w: coral.coral_lmhead_grouped(h, dh.gate_W, dh.bias, dh.lm_W, dh.gi, g, k, workspace=w),
+                     lambda w: coral.coral_lmhead_grouped_logprob(h, dh.gate_W, dh.bias, dh.lm_W, dh.gi, g, k, workspace=w),
+                     lambda w: coral.coral_lmhead_dense(h, dh.lm_W, k, workspace=w)):
+            print(f"case {dtype} H={H} M={M}", flush=True)
+            for a, b in zip(call(None), call(ws)):
+                assert torch.equal(a, b)
