@@ -287,6 +287,31 @@ bool fused_logprob_fits(int M, int G, int g, int k, int jp, coral_dtype dt, int 
                .total <= kLdsLimit;
 }
 
+// Tile kernels: weights below 4 GiB, LDS plan within the limit.
+bool tile_kernels_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_max_out, int* lds_out) {
+    if (k > kMaxK || M > 64) return false;
+    if ((unsigned long long)V * H * (is_16bit(dt) ? 2ull : 4ull) >= (1ull << 32)) return false;   // 32-bit weight offsets
+    long long um = (long long)M * g < G ? (long long)M * g : G;
+    if (um < 1) um = 1;
+    const TileLds T = tile_lds_layout((int)um);
+    if (T.total > kLdsLimit) return false;
+    // the ranking kernel keeps a few words per block of a token's groups in LDS
+    if ((long long)V / kTileRows + g + 1 > (1 << 16)) return false;
+    if (tile_select_lds_layout(g > 0 ? g : 1, V / kTileRows + g + 1).total > kLdsLimit) return false;
+    *u_max_out = (int)um;
+    *lds_out = T.total;
+    return true;
+}
+
+// Log-probability mode: whether the single-launch kernel runs a call.  (Beyond 32 tokens only where
+// the tile kernels cannot: 256-wide head, V = 900000, 36 tokens, 2 of 32 groups 180 us here, 707 us
+// with the staged kernels, which are left then.)
+bool logprob_takes_fused(int M, int H, int V, int G, int g, int k, int jp, coral_dtype dt) {
+    int um, lds;
+    return fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups) &&
+           (M <= kLogprobFusedMaxTokens || !tile_kernels_fit(M, H, V, G, g, k, dt, &um, &lds));
+}
+
 // What a draft-level call adds to the log-probability head: the expansion of the tree level
 // whose nodes are the call's tokens.
 struct LevelExpand {
@@ -316,10 +341,10 @@ coral_status launch_tree_expand(const LevelExpand& level, const int32_t* cand_id
 // number V / rows + g at most.  Rows beyond 8 KB (one to a batch): the table shares the memory of
 // the multi-kernel paths' arrays, which no call uses with it.
 Pieces layout_pieces(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
-    if (G < 1 || !dtype_ok(dt) || M > kLogprobFusedMaxTokens) return {0, false};
+    if (G < 1 || !dtype_ok(dt)) return {0, false};
     const int n_vec = H / (is_16bit(dt) ? 8 : 4);
     const int jp = (n_vec + kWave - 1) / kWave;
-    if (jp < 1 || !fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups)) return {0, false};
+    if (jp < 1 || !logprob_takes_fused(M, H, V, G, g, k, jp, dt)) return {0, false};
     return {(size_t)M * ((size_t)V / fused_rows(fused_segs(jp)) + g), jp > 8};
 }
 
@@ -420,22 +445,6 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
 // dominate and the vector path is faster).
 bool dense_prefers_tiles(int M, int V) { return M >= 8 && V >= 2 * kMaxWorkgroups * kTileRows; }
 
-// Tile kernels: weights below 4 GiB, LDS plan within the limit.
-bool tile_kernels_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_max_out, int* lds_out) {
-    if (k > kMaxK || M > 64) return false;
-    if ((unsigned long long)V * H * (is_16bit(dt) ? 2ull : 4ull) >= (1ull << 32)) return false;   // 32-bit weight offsets
-    long long um = (long long)M * g < G ? (long long)M * g : G;
-    if (um < 1) um = 1;
-    const TileLds T = tile_lds_layout((int)um);
-    if (T.total > kLdsLimit) return false;
-    // the ranking kernel keeps a few words per block of a token's groups in LDS
-    if ((long long)V / kTileRows + g + 1 > (1 << 16)) return false;
-    if (tile_select_lds_layout(g > 0 ? g : 1, V / kTileRows + g + 1).total > kLdsLimit) return false;
-    *u_max_out = (int)um;
-    *lds_out = T.total;
-    return true;
-}
-
 // Matrix-core path proper: 16-bit storage and whole 512-column chunks as well.
 bool tiles_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_max_out, int* lds_out) {
     return is_16bit(dt) && H % (kChunkVecs * 8) == 0 && tile_kernels_fit(M, H, V, G, g, k, dt, u_max_out, lds_out);
@@ -469,7 +478,7 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
     if (logprob) {     // the single-launch kernel where it fits, else the tile path, else the staged path
         pl.path = staged_fits(M, jp, k) ? 0 : -1;
         if (dense) return pl;
-        if (M <= kLogprobFusedMaxTokens && fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups)) {
+        if (logprob_takes_fused(M, H, V, G, g, k, jp, dt)) {
             pl.path = 1;
         } else if (tiles_fit(M, H, V, G, g, k, dt, &pl.tile_umax, &pl.tile_lds) && G <= kWave) {
             pl.path = 2;                    // (k_gate_select leaves log p_router for up to 64 groups)

@@ -338,3 +338,13 @@ def test_a_workspace_serves_fewer_tokens(M, H, V, G, g, k, dt):
     for m in range(1, M + 1):
         kw = dict(M=m, H=H, V=V, g=g, k=k, dt=dt, ws_bytes=have)
         assert c.grouped(**kw) in (HIP, UNSUPPORTED) and c.dense(**kw) in (HIP, UNSUPPORTED)
+
+
+def test_log_probabilities_beyond_32_tokens_stay_in_one_launch_where_the_tile_kernels_do_not_fit():
+    """The ranking kernel's tables in LDS end at about 660 000 vocabulary rows."""
+    lp = coral.coral_lmhead_logprob_path
+    assert lp(32, 256, 128256, 32, 2, 8, BF16) == 1 and lp(33, 256, 128256, 32, 2, 8, BF16) == 0
+    assert lp(33, 512, 128256, 32, 2, 8, BF16) == 2
+    for M in (32, 33, 48):
+        assert lp(M, 256, 700_000, 32, 2, 8, BF16) == 1
+        assert lp(M, 512, 700_000, 32, 2, 8, BF16) == 1

@@ -214,3 +214,12 @@ def test_one_workspace_for_several_token_counts(coral, dtype, H, G, v, g, k, Ms)
             print(f"case {dtype} H={H} M={M}", flush=True)
             for a, b in zip(call(None), call(ws)):
                 assert torch.equal(a, b)
+
+
+def test_log_probabilities_of_many_tokens_over_a_vocabulary_beyond_the_ranking_kernel(coral):
+    """More than 32 tokens in the single launch: two passes of hidden vectors, pieces in memory."""
+    cfg = HeadConfig("lpbig", "bf16", 64, 700_000, 16, 2, (40,), 8, 995, True)
+    assert coral.coral_lmhead_logprob_path(40, 64, 700_000, 16, 2, 8, coral.CORAL_BF16) == 1
+    dh = DeviceHead(coral, ragged_head(cfg, [43_750] * 16))
+    hidden = make_hidden(cfg, 40, 1)
+    check_logprob(dh, hidden, 2, 8, run_logprob(coral, dh, hidden, 2, 8))
