@@ -515,14 +515,33 @@ bool tile_small_blocks(int V, int g, long long rows, long long groups, long long
            tile_select_lds_layout(g > 0 ? g : 1, V / kTileRowsSmall + g + 1).total <= kLdsLimit;
 }
 
+// The general path's steps that the staged kernels run faster than the tile kernels (`rows`: rows of
+// the activated groups at most):
+//   - one batch of tokens and fewer 128-row blocks than compute units, as their 32-row chunks spread
+//     over more of these: fp32 H = 2304, one token, one group of 710 rows 32 us staged, 54 tiles;
+//   - rows beyond 8 KB and hardly more than one token per group.  The tile kernels' time goes by
+//     whole rounds of blocks, whatever the tokens; the staged kernels stream rows as they come, at a
+//     cost per token, and their gate and selection grow with tokens x groups (fp32 most: H = 2304,
+//     128 groups, 8 tokens 141, 108; 300 groups, 48 tokens 193, 110).  us, staged against tiles:
+//     bf16 H = 4104, 128256 rows, 32 groups, 4 tokens 103, 125, 8 tokens 156, 183, 14 tokens 225,
+//     210, 33 tokens 383, 275; 16 groups, 14 tokens 220, 209; H = 4360, 14 tokens 236, 260; H = 8200,
+//     3 tokens 152, 228; 128 groups, 10 tokens 177, 224, but with 50176 rows in all, 14 tokens 130,
+//     118; dense H = 8200, 50257 rows, one token 178, 226, 3 tokens 197, 226, 4 tokens 230, 226;
+//     dense H = 4104, 2 tokens 121, 120, 4 tokens 143, 118.
+bool staged_preferred(bool dense, int M, int H, int G, int g, int k, coral_dtype dt, long long rows) {
+    const int jp = (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave;
+    if (!staged_fits(M, jp, k)) return false;
+    const long long round = (long long)kMaxWorkgroups * kTileRows;
+    if (M <= kTokBatch && rows < round) return true;
+    if (jp <= 8) return false;
+    if (dense) return M <= (jp > 16 ? 3 : 2);
+    return 4 * M * g <= 7 * max_union(M, G, g) && M * G <= (is_16bit(dt) ? 3072 : 512) && 6 * rows > 7 * round;
+}
+
 PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob = false) {
     PathPlan pl = plan_path_kind(dense, M, H, V, G, g, k, dt, logprob);
-    // (One batch of tokens and fewer 128-row blocks than compute units: the staged kernels' 32-row
-    // chunks spread over more of them.  fp32 H = 2304, one token, one group of 710 rows: 32 us
-    // staged, 54 us with the tile kernels.)
     const long long rows = dense ? V : max_union(M, G, g) * V / (G > 0 ? G : 1);
-    const bool few = M <= kTokBatch && rows < (long long)kMaxWorkgroups * kTileRows && staged_fits(M, (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave, k);
-    pl.tile_kernels = pl.path == 2 || (pl.path == 0 && !few &&
+    pl.tile_kernels = pl.path == 2 || (pl.path == 0 && !staged_preferred(dense, M, H, G, g, k, dt, rows) &&
                                        tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds));
     const long long groups = dense ? 1 : max_union(M, G, g);
     const int n_chunks = (H / (is_16bit(dt) ? 8 : 4) + kChunkVecs - 1) / kChunkVecs;

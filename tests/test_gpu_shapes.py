@@ -223,3 +223,19 @@ def test_log_probabilities_of_many_tokens_over_a_vocabulary_beyond_the_ranking_k
     dh = DeviceHead(coral, ragged_head(cfg, [43_750] * 16))
     hidden = make_hidden(cfg, 40, 1)
     check_logprob(dh, hidden, 2, 8, run_logprob(coral, dh, hidden, 2, 8))
+
+
+def test_general_path_few_tokens_per_group(coral):
+    """Rows beyond 8 KB: hardly more than one token per group (staged kernels), then two (tile
+    kernels); the dense head with two tokens and three."""
+    cfg = HeadConfig("few", "bf16", 4104, 45_056, 32, 4, (12, 16), 10, 996, True)
+    assert coral.coral_lmhead_path(False, 12, cfg.H, cfg.V, cfg.G, cfg.g, cfg.k, coral.CORAL_BF16) == 0
+    dh = DeviceHead(coral, ragged_head(cfg, [1408 + (n % 2 * 2 - 1) * 17 * (n // 2) for n in range(32)]))
+    for M in (12, 16):
+        hidden = make_hidden(cfg, M, M)
+        print(f"case {cfg.name} M={M}", flush=True)
+        check_grouped(dh, hidden, cfg.g, cfg.k, run_grouped(coral, dh, hidden, cfg.g, cfg.k))
+        check_logprob(dh, hidden, cfg.g, cfg.k, run_logprob(coral, dh, hidden, cfg.g, cfg.k))
+    for M in (2, 3):
+        hidden = make_hidden(cfg, M, M)
+        check_dense(dh, hidden, cfg.k, run_dense(coral, dh, hidden, cfg.k))
