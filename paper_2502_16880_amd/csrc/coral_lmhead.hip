@@ -303,12 +303,46 @@ bool tile_kernels_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, 
     return true;
 }
 
+// Matrix-core path proper: 16-bit storage and whole 512-column chunks as well.
+bool tiles_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_max_out, int* lds_out) {
+    return is_16bit(dt) && H % (kChunkVecs * 8) == 0 && tile_kernels_fit(M, H, V, G, g, k, dt, u_max_out, lds_out);
+}
+
+// 128-row blocks of the groups that M tokens activate if each draws its g of G by lot.
+double expected_blocks(int M, int V, int G, int g) {
+    double out = 1.0;                          // chance that a group stays out
+    for (int m = 0; m < M; ++m) out *= 1.0 - (double)g / G;
+    return G * (1.0 - out) * ((V / G + kTileRows - 1) / kTileRows);
+}
+
+// Rows beyond 8 KB, whose gate every workgroup of the single launch computes by itself from more
+// bytes than L2 serves quickly: taken while groups and tokens are few, or where the matrix-core path
+// is the other choice, whose launches cost more with few tokens.  us, the multi-kernel paths against
+// the single launch (two of G groups each):
+//   bf16 H = 4616, V = 128100, one token, G = 128 40, 30, G = 300 38, 46; 3 tokens, 100 45, 41, 200
+//   41, 52; 6 tokens, 80 72, 62, 100 57, 67, 300 46, 103; 9 tokens, 80 106, 77, 200 68, 86;
+//   fp32 H = 4096, V = 64000, one token, 128 40, 34, 200 39, 43; 6 tokens, 80 72, 61, 128 54, 66;
+//   log-probabilities (three groups each), H = 4616, one token, 64 35, 34, 128 35, 37; 6 tokens, 32
+//   119, 99, 64 79, 80, 100 75, 84; H = 6664, V = 99984, two of 48 groups, 4 tokens 59, 64;
+//   matrix-core path: H = 5120, one token, 64 44, 25, 6 tokens, 32 97, 83.  Only where its blocks
+//   fill a good part of one round over the compute units it is ahead: 6 tokens, 48 66, 73; 9 tokens,
+//   64 67, 76; log-probabilities, H = 8192, 6 tokens, 64 101, 120.
+bool long_rows_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob) {
+    int um, lds;
+    if (tiles_fit(M, H, V, G, g, k, dt, &um, &lds) && (!logprob || G <= kWave)) {
+        const double blocks = expected_blocks(M, V, G, g);
+        return M < 4 || blocks <= (logprob ? 110 : 130) || blocks > kMaxWorkgroups + 6;
+    }
+    return G + 6 * M <= (logprob ? 70 : 135);
+}
+
 // Log-probability mode: whether the single-launch kernel runs a call.  (Beyond 32 tokens only where
 // the tile kernels cannot: 256-wide head, V = 900000, 36 tokens, 2 of 32 groups 180 us here, 707 us
 // with the staged kernels, which are left then.)
 bool logprob_takes_fused(int M, int H, int V, int G, int g, int k, int jp, coral_dtype dt) {
     int um, lds;
     return fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups) &&
+           (jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, true)) &&
            (M <= kLogprobFusedMaxTokens || !tile_kernels_fit(M, H, V, G, g, k, dt, &um, &lds));
 }
 
@@ -445,11 +479,6 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
 // dominate and the vector path is faster).
 bool dense_prefers_tiles(int M, int V) { return M >= 8 && V >= 2 * kMaxWorkgroups * kTileRows; }
 
-// Matrix-core path proper: 16-bit storage and whole 512-column chunks as well.
-bool tiles_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_max_out, int* lds_out) {
-    return is_16bit(dt) && H % (kChunkVecs * 8) == 0 && tile_kernels_fit(M, H, V, G, g, k, dt, u_max_out, lds_out);
-}
-
 // Which path a call takes, decided in one place for the entry points and the path query.
 struct PathPlan {
     int path;            // 0 general, 1 single launch, 2 tiles, -1 none (the staged kernels'
@@ -486,7 +515,7 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
         return pl;
     }
     const bool fused_ok =
-        fused_rows_fit(jp) &&
+        fused_rows_fit(jp) && (dense || jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, false)) &&
         fused_lds_layout(M, dense ? 0 : G, dense ? 0 : g, k, jp, dense,
                          fused_gate_mode(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp, dt)).total <= kLdsLimit;
     const bool tiles_ok =
@@ -525,23 +554,23 @@ bool tile_small_blocks(int V, int g, long long rows, long long groups, long long
 //     128 groups, 8 tokens 141, 108; 300 groups, 48 tokens 193, 110).  us, staged against tiles:
 //     bf16 H = 4104, 128256 rows, 32 groups, 4 tokens 103, 125, 8 tokens 156, 183, 14 tokens 225,
 //     210, 33 tokens 383, 275; 16 groups, 14 tokens 220, 209; H = 4360, 14 tokens 236, 260; H = 8200,
-//     3 tokens 152, 228; 128 groups, 10 tokens 177, 224, but with 50176 rows in all, 14 tokens 130,
-//     118; dense H = 8200, 50257 rows, one token 178, 226, 3 tokens 197, 226, 4 tokens 230, 226;
+//     3 tokens 152, 228; 128 groups, 10 tokens 177, 224, but with 50176 rows in all (one round),
+//     14 tokens 130, 118; fp32 H = 3332, V = 99984, 2 of 48 groups, 9 tokens 134, 188; dense H = 8200, 50257 rows, one token 178, 226, 3 tokens 197, 226, 4 tokens 230, 226;
 //     dense H = 4104, 2 tokens 121, 120, 4 tokens 143, 118.
-bool staged_preferred(bool dense, int M, int H, int G, int g, int k, coral_dtype dt, long long rows) {
+bool staged_preferred(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt, long long rows) {
     const int jp = (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave;
     if (!staged_fits(M, jp, k)) return false;
-    const long long round = (long long)kMaxWorkgroups * kTileRows;
-    if (M <= kTokBatch && rows < round) return true;
+    if (M <= kTokBatch && rows < (long long)kMaxWorkgroups * kTileRows) return true;
     if (jp <= 8) return false;
     if (dense) return M <= (jp > 16 ? 3 : 2);
-    return 4 * M * g <= 7 * max_union(M, G, g) && M * G <= (is_16bit(dt) ? 3072 : 512) && 6 * rows > 7 * round;
+    return 4 * M * g <= 7 * max_union(M, G, g) && M * G <= (is_16bit(dt) ? 3072 : 800) &&
+           expected_blocks(M, V, G, g) > kMaxWorkgroups;
 }
 
 PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob = false) {
     PathPlan pl = plan_path_kind(dense, M, H, V, G, g, k, dt, logprob);
     const long long rows = dense ? V : max_union(M, G, g) * V / (G > 0 ? G : 1);
-    pl.tile_kernels = pl.path == 2 || (pl.path == 0 && !staged_preferred(dense, M, H, G, g, k, dt, rows) &&
+    pl.tile_kernels = pl.path == 2 || (pl.path == 0 && !staged_preferred(dense, M, H, V, G, g, k, dt, rows) &&
                                        tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds));
     const long long groups = dense ? 1 : max_union(M, G, g);
     const int n_chunks = (H / (is_16bit(dt) ? 8 : 4) + kChunkVecs - 1) / kChunkVecs;
