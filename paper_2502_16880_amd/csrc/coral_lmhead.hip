@@ -531,16 +531,16 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
     return pl;
 }
 
-// Blocks of 32 rows instead of 128, where the 128-row blocks would leave a third of the compute
-// units without work (`groups` activated groups of equal size, `rows` in all), a group's tokens fit
-// one token tile on average (every block stages them again, against a quarter of the weight
-// bytes) and a row is long (a block's start and end, about 4 us, against its chunks).
-// Measured, 128 rows against 32: dense f16 H = 7344, 14561 rows, 16 tokens 88 against 64 us; bf16
-// H = 7680, 12 groups of 1176 rows, 11 tokens 73 against 52; the other way round bf16 H = 1664, 13
-// groups of 2005 rows, 40 tokens 35 against 48; dense f16 H = 5632, 62 tokens 64 against 173.
-bool tile_small_blocks(int V, int g, long long rows, long long groups, long long group_tokens, int n_chunks) {
-    return rows / kTileRows + groups / 2 <= kMaxWorkgroups * 2 / 3 && group_tokens <= 16 && n_chunks >= 8 &&
-           V / kTileRowsSmall + g + 1 <= (1 << 16) &&
+// Blocks of 32 rows instead of 128, where the 128-row blocks of the groups that the tokens activate
+// would leave nearly half of the compute units without work, a group's tokens fit one token tile on
+// average (every block stages them again, against a quarter of the weight bytes) and a row is long (a
+// block's start and end, about 4 us, against its chunks).  Measured, 128 rows against 32, by 128-row
+// blocks: bf16 H = 4608, 16 tokens, dense 32 blocks 35 against 23 us, 141 blocks 43 against 52; over
+// 730 heads with 8 to 18 chunks the mean ratio is 0.7 up to 80 blocks, 0.9 from 80 to 138 and 1.1 beyond.
+// The other way round bf16 H = 1664, 13 groups of 2005 rows, 40 tokens 35 against 48; dense f16 H =
+// 5632, 62 tokens 64 against 173.
+bool tile_small_blocks(int V, int g, double blocks, long long group_tokens, int n_chunks) {
+    return blocks < 138 && group_tokens <= 16 && n_chunks >= 8 && V / kTileRowsSmall + g + 1 <= (1 << 16) &&
            tile_select_lds_layout(g > 0 ? g : 1, V / kTileRowsSmall + g + 1).total <= kLdsLimit;
 }
 
@@ -575,7 +575,7 @@ PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_d
     const long long groups = dense ? 1 : max_union(M, G, g);
     const int n_chunks = (H / (is_16bit(dt) ? 8 : 4) + kChunkVecs - 1) / kChunkVecs;
     pl.tile_small = pl.tile_kernels && groups > 0 &&
-                    tile_small_blocks(V, dense ? 0 : g, rows, groups,
+                    tile_small_blocks(V, dense ? 0 : g, dense ? expected_blocks(1, V, 1, 1) : expected_blocks(M, V, G, g),
                                       dense ? M : ((long long)M * g + groups - 1) / groups, n_chunks);
     return pl;
 }

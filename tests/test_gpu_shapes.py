@@ -239,3 +239,19 @@ def test_general_path_few_tokens_per_group(coral):
     for M in (2, 3):
         hidden = make_hidden(cfg, M, M)
         check_dense(dh, hidden, cfg.k, run_dense(coral, dh, hidden, cfg.k))
+
+
+@pytest.mark.parametrize("dtype,H,M", [("bf16", 4608, 40), ("f16", 5120, 64), ("f32", 2304, 33)])
+def test_small_blocks_of_a_group_with_two_passes_of_tokens(coral, dtype, H, M):
+    """Blocks of 32 rows are chosen by the tokens per group on average; here every token chooses the
+    same group, so its blocks come round twice, 32 tokens each."""
+    sizes = [100, 70, 95, 161, 64, 33, 120, 96, 130]
+    cfg = HeadConfig(f"pass{H}", dtype, H, sum(sizes), len(sizes), 1, (M,), 12, 997 + H, True)
+    head = ragged_head(cfg, sizes)
+    head.gate_bias[3] += 100.0
+    dh = DeviceHead(coral, head)
+    hidden = make_hidden(cfg, M, M)
+    out = run_grouped(coral, dh, hidden, 1, 12)
+    assert (out[2] == 3).all()
+    check_grouped(dh, hidden, 1, 12, out)
+    check_logprob(dh, hidden, 1, 12, run_logprob(coral, dh, hidden, 1, 12))
