@@ -308,11 +308,14 @@ bool tiles_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_
     return is_16bit(dt) && H % (kChunkVecs * 8) == 0 && tile_kernels_fit(M, H, V, G, g, k, dt, u_max_out, lds_out);
 }
 
-// 128-row blocks of the groups that M tokens activate if each draws its g of G by lot.
-double expected_blocks(int M, int V, int G, int g) {
+// Groups that M tokens activate if each draws its g of G by lot, and their 128-row blocks.
+double expected_groups(int M, int G, int g) {
     double out = 1.0;                          // chance that a group stays out
     for (int m = 0; m < M; ++m) out *= 1.0 - (double)g / G;
-    return G * (1.0 - out) * ((V / G + kTileRows - 1) / kTileRows);
+    return G * (1.0 - out);
+}
+double expected_blocks(int M, int V, int G, int g) {
+    return expected_groups(M, G, g) * ((V / G + kTileRows - 1) / kTileRows);
 }
 
 // Rows beyond 8 KB, whose gate every workgroup of the single launch computes by itself from more
@@ -382,6 +385,31 @@ Pieces layout_pieces(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
     return {(size_t)M * ((size_t)V / fused_rows(fused_segs(jp)) + g), jp > 8};
 }
 
+// Collected candidates instead of per-wave lists, where a workgroup is sure to meet at
+// most kCollectMax rows per token: it takes D consecutive batches out of every D P of the
+// concatenated activated groups, so of any group (a run of at most n batches) it meets no
+// more than D * (n / D P) + min(D, n % D P), and a token has g groups.  D = kDealFew (the
+// bound for the smaller D that the kernel uses as well is never larger), or, where buffers
+// that size do not fit, D = 1 throughout (512-wide head, 55 tokens, 7 of 61 groups: 64
+// entries per token instead of 448, 148 us with lists, 57 with buffers).  Returns the entries
+// per token, 0 for lists.
+int collect_cap(bool dense, int M, int G, int g, int k, int jp, int gate, int group_rows, int P, bool* deal_single) {
+    const int rows = fused_rows(fused_segs(jp));
+    for (int deal = kDealFew; deal >= 1; deal -= kDealFew - 1) {
+        const long long period = (long long)deal * P;
+        const long long n = ((long long)group_rows + rows - 1) / rows;
+        const long long rest = n % period;
+        const long long per_group = deal * (n / period) + (rest < deal ? rest : deal);
+        const long long bound = (rows * per_group * (dense ? 1 : g) + kWave - 1) / kWave * kWave;
+        *deal_single = deal == 1;
+        if (bound > 0 && bound <= kCollectMax &&
+            fused_lds_layout(M, G, g, k, jp, dense, gate, false, (int)bound).total <= kLdsLimit)
+            return (int)bound;
+    }
+    *deal_single = false;
+    return 0;
+}
+
 // Enqueues the single-launch path (the caller has checked with plan_path that it fits).
 coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidden, const void* gate_W,
                const float* gate_bias,
@@ -395,28 +423,11 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
     int P = compute_units();
     if (P < 1) return CORAL_ERR_HIP;
     if (P > kMaxWorkgroups) P = kMaxWorkgroups;
-    // Collected candidates instead of per-wave lists, where a workgroup is sure to meet at
-    // most kCollectMax rows per token: it takes D consecutive batches out of every D P of the
-    // concatenated activated groups, so of any group (a run of at most n batches) it meets no
-    // more than D * (n / D P) + min(D, n % D P), and a token has g groups.  D = kDealFew (the
-    // bound for the smaller D that the kernel uses as well is never larger), or, where buffers
-    // that size do not fit, D = 1 throughout (512-wide head, 55 tokens, 7 of 61 groups: 64
-    // entries per token instead of 448, 187 us with lists, 58 with buffers).
-    const int segs = fused_segs(jp), rows = fused_rows(segs);
+    const int segs = fused_segs(jp);
     int cap = 0;
     bool deal_single = false;
     if (!logprob) {
-        for (int deal = kDealFew; deal >= 1 && !cap; deal -= kDealFew - 1) {
-            const long long period = (long long)deal * P;
-            const long long n = ((long long)(dense ? V : max_group_rows) + rows - 1) / rows;
-            const long long rest = n % period;
-            const long long per_group = deal * (n / period) + (rest < deal ? rest : deal);
-            const long long bound = (rows * per_group * (dense ? 1 : g) + kWave - 1) / kWave * kWave;
-            if (bound > 0 && bound <= kCollectMax &&
-                fused_lds_layout(M, G, g, k, jp, dense, gate, false, (int)bound).total <= kLdsLimit)
-                cap = (int)bound;
-            deal_single = cap && deal == 1;
-        }
+        cap = collect_cap(dense, M, G, g, k, jp, gate, dense ? V : max_group_rows, P, &deal_single);
     } else {
         // a workgroup's rows depend on the selection: buffers as large as fit beside the pieces,
         // used by the workgroups whose rows they hold
@@ -520,8 +531,16 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
                          fused_gate_mode(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp, dt)).total <= kLdsLimit;
     const bool tiles_ok =
         tiles_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds);
-    if (dense && dense_prefers_tiles(M, V) && tiles_ok)
+    // (Dense head with many tokens: also where the single launch could not collect its candidates
+    // and would keep sorted lists, every logit of every token against them: bf16 H = 1024, V =
+    // 58000, 40 tokens 323 us, tile kernels 37; H = 4096, 16 tokens 164, 91.)
+    bool single;
+    const bool lists = dense && M >= 16 && fused_ok &&
+                       !collect_cap(true, M, 0, 0, k, jp, kGateVector, V, kMaxWorkgroups, &single);
+    if (dense && (dense_prefers_tiles(M, V) || lists) && tiles_ok)
         pl.path = 2;
+    else if (lists && tile_kernels_fit(M, H, V, 0, 0, k, dt, &pl.tile_umax, &pl.tile_lds))
+        pl.path = 0;
     else if (fused_ok)
         pl.path = 1;
     else if (tiles_ok)
@@ -548,6 +567,8 @@ bool tile_small_blocks(int V, int g, double blocks, long long group_tokens, int 
 // the activated groups at most):
 //   - one batch of tokens and fewer 128-row blocks than compute units, as their 32-row chunks spread
 //     over more of these: fp32 H = 2304, one token, one group of 710 rows 32 us staged, 54 tiles;
+//   - a few (token, group) pairs, hardly any of them in the same group: fp32 H = 2304, 9 tokens, one
+//     of 300 groups each 28, 37; but one of 32 groups of 187 rows each 41, 32;
 //   - rows beyond 8 KB and hardly more than one token per group.  The tile kernels' time goes by
 //     whole rounds of blocks, whatever the tokens; the staged kernels stream rows as they come, at a
 //     cost per token, and their gate and selection grow with tokens x groups (fp32 most: H = 2304,
@@ -561,10 +582,11 @@ bool staged_preferred(bool dense, int M, int H, int V, int G, int g, int k, cora
     const int jp = (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave;
     if (!staged_fits(M, jp, k)) return false;
     if (M <= kTokBatch && rows < (long long)kMaxWorkgroups * kTileRows) return true;
+    if (!dense && M * g <= 12 && M * g <= 1.1 * expected_groups(M, G, g)) return true;
     if (jp <= 8) return false;
     if (dense) return M <= (jp > 16 ? 3 : 2);
     return 4 * M * g <= 7 * max_union(M, G, g) && M * G <= (is_16bit(dt) ? 3072 : 800) &&
-           expected_blocks(M, V, G, g) > kMaxWorkgroups;
+           expected_blocks(M, V, G, g) > kMaxWorkgroups - 6;
 }
 
 PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob = false) {
