@@ -531,15 +531,18 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
                          fused_gate_mode(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp, dt)).total <= kLdsLimit;
     const bool tiles_ok =
         tiles_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds);
-    // (Dense head with many tokens: also where the single launch could not collect its candidates
-    // and would keep sorted lists, every logit of every token against them: bf16 H = 1024, V =
-    // 58000, 40 tokens 323 us, tile kernels 37; H = 4096, 16 tokens 164, 91.)
+    // (Many tokens: also where the single launch could not collect its candidates and would keep
+    // sorted lists, every logit of every token against them: dense bf16 H = 1024, V = 58000, 40
+    // tokens 323 us, tile kernels 37; H = 4096, 16 tokens 164, 91; grouped bf16 H = 512, V = 128256,
+    // 64 tokens, 2 of 4 groups 435, 52.  Equal groups: what is decided here depends on sizes only.)
     bool single;
-    const bool lists = dense && M >= 16 && fused_ok &&
-                       !collect_cap(true, M, 0, 0, k, jp, kGateVector, V, kMaxWorkgroups, &single);
-    if (dense && (dense_prefers_tiles(M, V) || lists) && tiles_ok)
+    const bool lists = M >= (dense ? 16 : 32) && fused_ok &&
+                       !collect_cap(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp,
+                                    fused_gate_mode(dense, M, G, g, k, jp, dt), dense ? V : (V + G - 1) / G,
+                                    kMaxWorkgroups, &single);
+    if (((dense && dense_prefers_tiles(M, V)) || lists) && tiles_ok)
         pl.path = 2;
-    else if (lists && tile_kernels_fit(M, H, V, 0, 0, k, dt, &pl.tile_umax, &pl.tile_lds))
+    else if (lists && tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds))
         pl.path = 0;
     else if (fused_ok)
         pl.path = 1;
@@ -798,19 +801,18 @@ extern "C" coral_status coral_lmhead_workspace_init(void* workspace, size_t work
 namespace {
 
 // The static scratch array (logit ranking only, no table of pieces).  Which shapes it takes is a
-// matter of sizes that callers rely on, and does not move with the kernels: the published and the
-// staged lists must fit, or, for shapes that the tile path runs with 128-row blocks, that path's
-// arrays.  The latter count too where the single-launch kernel has come to run such shapes since
-// (rows beyond 8 KB, and narrow heads with many candidates, since its merges need no 24 KB of their
-// own at the place of the hidden vectors).
-size_t static_counted_bytes(const PathPlan& plan, int M, int H, int V, int G, int g, int k, coral_dtype dt) {
-    bool tiles = plan.path == 2;
+// matter of sizes that callers rely on, and does not move with the kernels that run them: the
+// published and the staged lists must fit; or, for 16-bit heads of whole 512-column chunks whose rows
+// are beyond 8 KB or whose tokens and lists do not share the LDS of a workgroup with 24 KB for
+// merges, the tile path's arrays with 128-row blocks.
+size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
     int um, lds;
-    if (plan.path == 1 && tiles_fit(M, H, V, G, g, k, dt, &um, &lds)) {
-        const int jp = (H / 8 + kWave - 1) / kWave;
+    bool tiles = tiles_fit(M, H, V, G, g, k, dt, &um, &lds);
+    const int jp = (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave;
+    if (tiles && jp <= 8) {
         const FusedLds F = fused_lds_layout(M, G, g, k, jp, false, fused_gate_mode(false, M, G, g, k, jp, dt));
         const int hidden = M * hidden_lds_stride(jp) * (int)sizeof(uint4), merges = 24 * 1024;
-        tiles = jp > 8 || F.total - F.o_lists + (hidden > merges ? hidden : merges) > kLdsLimit;
+        tiles = F.total - F.o_lists + (hidden > merges ? hidden : merges) > kLdsLimit;
     }
     return make_layout(M, V, G, g, k, Pieces{}, {tiles ? Tiles::kOwn : Tiles::kNone, false},
                        tiles ? LayoutFor::kTiles : LayoutFor::kWorkspace).total;
@@ -875,7 +877,7 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
     Layout L;
     int tile_tokens = M;                       // tokens that the tile kernels take at a time
     if (static_workspace) {
-        if (logprob || static_counted_bytes(plan, M, H, V, G, g, k, dt) > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;
+        if (logprob || static_counted_bytes(M, H, V, G, g, k, dt) > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;
         L = static_layout(plan, M, V, G, g, k, &tile_tokens);
         if (L.total > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;             // not reached
     } else {

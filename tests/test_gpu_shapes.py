@@ -255,3 +255,17 @@ def test_small_blocks_of_a_group_with_two_passes_of_tokens(coral, dtype, H, M):
     assert (out[2] == 3).all()
     check_grouped(dh, hidden, 1, 12, out)
     check_logprob(dh, hidden, 1, 12, run_logprob(coral, dh, hidden, 1, 12))
+
+
+def test_tile_kernels_instead_of_lists(coral):
+    """Many tokens whose candidates the single launch could not collect, dense and grouped."""
+    cfg = HeadConfig("lists_f32", "f32", 232, 104_160, 20, 7, (62,), 10, 999, True)
+    assert coral.coral_lmhead_path(False, 62, 232, cfg.V, 20, 7, 10, coral.CORAL_F32) == 0
+    dh = DeviceHead(coral, ragged_head(cfg, [5208 + (n % 2 * 2 - 1) * n // 2 * 10 for n in range(20)]))
+    hidden = make_hidden(cfg, 62, 1)
+    check_grouped(dh, hidden, 7, 10, run_grouped(coral, dh, hidden, 7, 10))
+    cfg = HeadConfig("lists_bf16", "bf16", 512, 40_000, 4, 2, (64,), 10, 1001, True)
+    assert coral.coral_lmhead_path(True, 64, 512, cfg.V, 0, 0, 10, coral.CORAL_BF16) == 2
+    dh = DeviceHead(coral, ragged_head(cfg, [10_000] * 4))
+    hidden = make_hidden(cfg, 64, 1)
+    check_dense(dh, hidden, 10, run_dense(coral, dh, hidden, 10))

@@ -140,7 +140,8 @@ def test_noalloc_under_graph_capture(coral):
 # The general path's tile kernels (more than eight tokens): their arrays fit the scratch; or they do
 # not, while the staged lists by which the shape is accepted do, and the tokens go in batches.
 GENERAL = [("bf16", 1664, 6400, 16, 2, 10, 40), ("f16", 1000, 16000, 32, 3, 4, 64), ("f32", 2056, 4096, 16, 2, 8, 33),
-           ("bf16", 1664, 50272, 16, 2, 10, 40), ("bf16", 2568, 100352, 64, 4, 2, 33), ("f32", 2308, 50272, 16, 2, 3, 64)]
+           ("bf16", 1664, 50272, 16, 2, 10, 40), ("bf16", 2568, 100352, 64, 4, 2, 33), ("f32", 2308, 50272, 16, 2, 3, 64),
+           ("f32", 232, 104160, 20, 7, 3, 62)]
 
 
 @pytest.mark.parametrize("dtype,H,V,G,g,k,M", GENERAL)
