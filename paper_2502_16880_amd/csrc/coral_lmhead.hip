@@ -310,8 +310,10 @@ bool tiles_fit(int M, int H, int V, int G, int g, int k, coral_dtype dt, int* u_
 
 // Groups that M tokens activate if each draws its g of G by lot, and their 128-row blocks.
 double expected_groups(int M, int G, int g) {
-    double out = 1.0;                          // chance that a group stays out
-    for (int m = 0; m < M; ++m) out *= 1.0 - (double)g / G;
+    double out = 1.0;                          // chance that a group stays out: (1 - g / G) ^ M
+    double power = 1.0 - (double)g / G;
+    for (int m = M; m; m >>= 1, power *= power)
+        if (m & 1) out *= power;
     return G * (1.0 - out);
 }
 double expected_blocks(int M, int V, int G, int g) {
@@ -326,7 +328,9 @@ double expected_blocks(int M, int V, int G, int g) {
 //   41, 52; 6 tokens, 80 72, 62, 100 57, 67, 300 46, 103; 9 tokens, 80 106, 77, 200 68, 86;
 //   fp32 H = 4096, V = 64000, one token, 128 40, 34, 200 39, 43; 6 tokens, 80 72, 61, 128 54, 66;
 //   log-probabilities (three groups each), H = 4616, one token, 64 35, 34, 128 35, 37; 6 tokens, 32
-//   119, 99, 64 79, 80, 100 75, 84; H = 6664, V = 99984, two of 48 groups, 4 tokens 59, 64;
+//   119, 99, 64 79, 80, 100 75, 84; H = 6664, V = 99984, two of 48 groups, 4 tokens 59, 64; up to 40
+//   groups and 6 to 14 tokens, 18 heads of each pair, 0.55 to 0.88 of the time on average;
+//   k = 33 (the staged merges go by whole lists), fp32 H = 2564, five of 65 groups, 8 tokens 220, 98;
 //   matrix-core path: H = 5120, one token, 64 44, 25, 6 tokens, 32 97, 83.  Only where its blocks
 //   fill a good part of one round over the compute units it is ahead: 6 tokens, 48 66, 73; 9 tokens,
 //   64 67, 76; log-probabilities, H = 8192, 6 tokens, 64 101, 120.
@@ -334,9 +338,9 @@ bool long_rows_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype 
     int um, lds;
     if (tiles_fit(M, H, V, G, g, k, dt, &um, &lds) && (!logprob || G <= kWave)) {
         const double blocks = expected_blocks(M, V, G, g);
-        return M < 4 || blocks <= (logprob ? 110 : 130) || blocks > kMaxWorkgroups + 6;
+        return M < 4 || k > 10 || blocks <= (logprob ? 110 : 145) || blocks > kMaxWorkgroups + 6;
     }
-    return G + 6 * M <= (logprob ? 70 : 135);
+    return G <= (!logprob ? 64 : M >= 7 ? 60 : 40) || G + 6 * M <= (logprob ? 80 : 135) + (k > 10 ? 8 * (k - 10) : 0);
 }
 
 // Log-probability mode: whether the single-launch kernel runs a call.  (Beyond 32 tokens only where
@@ -553,16 +557,18 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
     return pl;
 }
 
-// Blocks of 32 rows instead of 128, where the 128-row blocks of the groups that the tokens activate
-// would leave nearly half of the compute units without work, a group's tokens fit one token tile on
-// average (every block stages them again, against a quarter of the weight bytes) and a row is long (a
-// block's start and end, about 4 us, against its chunks).  Measured, 128 rows against 32, by 128-row
-// blocks: bf16 H = 4608, 16 tokens, dense 32 blocks 35 against 23 us, 141 blocks 43 against 52; over
-// 730 heads with 8 to 18 chunks the mean ratio is 0.7 up to 80 blocks, 0.9 from 80 to 138 and 1.1 beyond.
-// The other way round bf16 H = 1664, 13 groups of 2005 rows, 40 tokens 35 against 48; dense f16 H =
-// 5632, 62 tokens 64 against 173.
-bool tile_small_blocks(int V, int g, double blocks, long long group_tokens, int n_chunks) {
-    return blocks < 138 && group_tokens <= 16 && n_chunks >= 8 && V / kTileRowsSmall + g + 1 <= (1 << 16) &&
+// Blocks of 32 rows instead of 128, where the rows of the groups that the tokens activate fill fewer
+// 128-row blocks than half of the compute units, a group's tokens fit one token tile on average
+// (every block stages them again, against a quarter of the weight bytes) and a row is long (a block's
+// start and end, about 4 us, against its chunks).  Measured, 128 rows against 32: bf16 H = 4608, 16
+// tokens, dense 4000 rows 35 against 23 us, 16000 rows 44 against 42, 18000 rows 43 against 52; over
+// 730 heads with 8 to 18 chunks the mean ratio is 0.7 up to 80 blocks, 0.9 from there on and 1.1
+// beyond 138.  Groups far from a multiple of 128 rows leave larger blocks empty: fp32 H = 2432, 76
+// groups of 133 rows, 48 tokens 121 against 61.  The other way round bf16 H = 1664, 13 groups of 2005
+// rows, 40 tokens 35 against 48; dense f16 H = 5632, 62 tokens 64 against 173.
+bool tile_small_blocks(int V, int g, double rows, long long group_tokens, int n_chunks) {
+    return rows < kMaxWorkgroups / 2 * kTileRows && group_tokens <= 16 && n_chunks >= 8 &&
+           V / kTileRowsSmall + g + 1 <= (1 << 16) &&
            tile_select_lds_layout(g > 0 ? g : 1, V / kTileRowsSmall + g + 1).total <= kLdsLimit;
 }
 
@@ -570,25 +576,29 @@ bool tile_small_blocks(int V, int g, double blocks, long long group_tokens, int 
 // the activated groups at most):
 //   - one batch of tokens and fewer 128-row blocks than compute units, as their 32-row chunks spread
 //     over more of these: fp32 H = 2304, one token, one group of 710 rows 32 us staged, 54 tiles;
-//   - a few (token, group) pairs, hardly any of them in the same group: fp32 H = 2304, 9 tokens, one
+//   - k <= 16 (their merges go by whole lists: dense bf16 H = 4136, one token, k = 64 720, 370) and a
+//     few (token, group) pairs, hardly any of them in the same group: fp32 H = 2304, 9 tokens, one
 //     of 300 groups each 28, 37; but one of 32 groups of 187 rows each 41, 32;
-//   - rows beyond 8 KB and hardly more than one token per group.  The tile kernels' time goes by
-//     whole rounds of blocks, whatever the tokens; the staged kernels stream rows as they come, at a
-//     cost per token, and their gate and selection grow with tokens x groups (fp32 most: H = 2304,
-//     128 groups, 8 tokens 141, 108; 300 groups, 48 tokens 193, 110).  us, staged against tiles:
-//     bf16 H = 4104, 128256 rows, 32 groups, 4 tokens 103, 125, 8 tokens 156, 183, 14 tokens 225,
-//     210, 33 tokens 383, 275; 16 groups, 14 tokens 220, 209; H = 4360, 14 tokens 236, 260; H = 8200,
-//     3 tokens 152, 228; 128 groups, 10 tokens 177, 224, but with 50176 rows in all (one round),
-//     14 tokens 130, 118; fp32 H = 3332, V = 99984, 2 of 48 groups, 9 tokens 134, 188; dense H = 8200, 50257 rows, one token 178, 226, 3 tokens 197, 226, 4 tokens 230, 226;
-//     dense H = 4104, 2 tokens 121, 120, 4 tokens 143, 118.
+//   - rows beyond 8 KB that leave a chunk partly filled (whole ones: fp32 H = 4352, 12 groups of 7223
+//     rows, 12 tokens 242, 170), up to two tokens per group, more than one round of blocks, k <= 10
+//     (k = 16: H = 4352, 7 groups, 3 tokens 144, 101).  The tile kernels' time goes by whole rounds of
+//     blocks, whatever the tokens; the staged kernels stream rows as they come, at a cost per token,
+//     and their gate and selection grow with tokens x groups (fp32 most: H = 2304, 128 groups, 8
+//     tokens 141, 108; 300 groups, 48 tokens 193, 110).  us, staged against tiles, bf16: H = 4104,
+//     128256 rows, 32 groups, 4 tokens 103, 125, 8 tokens 156, 183, 14 tokens 225, 210, 33 tokens 383,
+//     275; H = 4360, 16 groups, 14 tokens 236, 260; H = 8200, 3 tokens 152, 228; 128 groups, 10 tokens
+//     177, 224, but with 50176 rows in all (one round), 14 tokens 130, 118; fp32 H = 3332, V = 99984,
+//     2 of 48 groups, 9 tokens 134, 188; dense H = 8200, 50257 rows, one token 178, 226, 3 tokens
+//     197, 226, 4 tokens 230, 226; dense H = 4104, 2 tokens 121, 120, 4 tokens 143, 118.
 bool staged_preferred(bool dense, int M, int H, int V, int G, int g, int k, coral_dtype dt, long long rows) {
     const int jp = (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave;
     if (!staged_fits(M, jp, k)) return false;
     if (M <= kTokBatch && rows < (long long)kMaxWorkgroups * kTileRows) return true;
+    if (k > 16) return false;
     if (!dense && M * g <= 12 && M * g <= 1.1 * expected_groups(M, G, g)) return true;
-    if (jp <= 8) return false;
+    if (jp <= 8 || H % (kChunkVecs * (is_16bit(dt) ? 8 : 4)) == 0) return false;
     if (dense) return M <= (jp > 16 ? 3 : 2);
-    return 4 * M * g <= 7 * max_union(M, G, g) && M * G <= (is_16bit(dt) ? 3072 : 800) &&
+    return k <= 10 && M <= 24 && M * g <= 2.1 * expected_groups(M, G, g) && M * G <= (is_16bit(dt) ? 3072 : 800) &&
            expected_blocks(M, V, G, g) > kMaxWorkgroups - 6;
 }
 
@@ -600,7 +610,7 @@ PathPlan plan_path(bool dense, int M, int H, int V, int G, int g, int k, coral_d
     const long long groups = dense ? 1 : max_union(M, G, g);
     const int n_chunks = (H / (is_16bit(dt) ? 8 : 4) + kChunkVecs - 1) / kChunkVecs;
     pl.tile_small = pl.tile_kernels && groups > 0 &&
-                    tile_small_blocks(V, dense ? 0 : g, dense ? expected_blocks(1, V, 1, 1) : expected_blocks(M, V, G, g),
+                    tile_small_blocks(V, dense ? 0 : g, dense ? V : expected_groups(M, G, g) * V / G,
                                       dense ? M : ((long long)M * g + groups - 1) / groups, n_chunks);
     return pl;
 }

@@ -269,3 +269,12 @@ def test_tile_kernels_instead_of_lists(coral):
     dh = DeviceHead(coral, ragged_head(cfg, [10_000] * 4))
     hidden = make_hidden(cfg, 64, 1)
     check_dense(dh, hidden, 10, run_dense(coral, dh, hidden, 10))
+
+
+@pytest.mark.parametrize("dtype,H,G,Ms", [("bf16", 4616, 200, (1, 6)), ("f32", 2564, 150, (2, 9)), ("f16", 8192, 100, (1, 9)),
+                                          ("bf16", 5120, 48, (3, 6)), ("f32", 4096, 70, (1, 4))])
+def test_rows_beyond_8_kb_with_many_groups(coral, dtype, H, G, Ms):
+    """Both sides of the rule that keeps such rows in the single launch: groups and tokens."""
+    sizes = [9 + (11 * n) % 50 for n in range(G)]
+    cfg = HeadConfig(f"longgroups{H}", dtype, H, sum(sizes), G, 2, Ms, 8, 1003 + H, True)
+    check_all(coral, cfg, sizes, Ms, dense=False)
