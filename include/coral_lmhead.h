@@ -97,12 +97,14 @@ size_t coral_lmhead_workspace_bytes(int M, int H, int V, int G, int g, int k,
 /*
  * Which kernels a call with these sizes will use (dense != 0: coral_lmhead_dense):
  * 0 = general path (one launch per stage: the tile path's kernels in a form for any storage
- * type and width, or staged kernels on the vector units where these do not fit), 1 =
- * single-launch path (gate, selection, row streaming and top-k of section 3.3 in one persistent
- * kernel: rows of up to 8 KB, or of 10 to 16 KB, whose token batch fits on chip),
- * 2 = matrix-core tile path (bf16, H a multiple of 512, weights below 4 GiB: groups
- * shared by many tokens, the appendix's tree-decoding case, when the hidden vectors do
- * not fit on chip; dense head with 8 or more tokens and at least 65536 rows),
+ * type and width, or staged kernels on the vector units where these do not fit or are
+ * slower), 1 = single-launch path (gate, selection, row streaming and top-k of section 3.3 in
+ * one persistent kernel: rows of up to 8 KB whose token batch fits on chip, or of 10 to 16 KB
+ * with few groups and tokens; not 16 tokens and more dense, 32 grouped, whose candidates do
+ * not fit beside them), 2 = matrix-core tile path (bf16 or fp16, H a multiple of 512, weights
+ * below 4 GiB: groups shared by many tokens, the appendix's tree-decoding case, when the
+ * hidden vectors do not fit on chip; dense head with 8 or more tokens and at least 65536
+ * rows),
  * -1 = sizes not supported (outside the limits above, or a shape only the general path
  * could take whose token batch does not fit LDS: rows beyond about 10 000 values with 8 or
  * more tokens).  Host-only, no device work; for tests and benchmark reports.
@@ -111,8 +113,10 @@ int coral_lmhead_path(int dense, int M, int H, int V, int G, int g, int k, coral
 
 /*
  * The same for coral_lmhead_grouped_logprob (Eq. 8's output): 1 = single-launch kernel
- * (at most 64 activated groups, min(M*g, G) <= 64, g <= 16, and its LDS plan fits),
- * 2 = matrix-core tile path (where that path's conditions hold and G <= 64),
+ * (at most 64 activated groups, min(M*g, G) <= 64, g <= 16, and its LDS plan fits; beyond 32
+ * tokens only where the tile kernels do not fit; rows of 10 to 16 KB as above),
+ * 2 = matrix-core tile path (where that path's conditions hold and G <= 64; more groups go to
+ * the general path's form of the same kernels),
  * 0 = general path, -1 = sizes not supported.  Host-only.
  */
 int coral_lmhead_logprob_path(int M, int H, int V, int G, int g, int k, coral_dtype dt);
@@ -213,7 +217,7 @@ coral_status coral_lmhead_grouped_noalloc(const void *hidden, const void *gate_W
  * selected groups have probability zero (Eq. 8) and are never returned.
  *   topk_logprob [device] out [M,k] fp32 log-probabilities (natural logarithm)
  * All other arguments, limits and errors as for coral_lmhead_grouped.  Runs in the
- * single-launch kernel, on the tile path or on the staged path (coral_lmhead_logprob_path
+ * single-launch kernel, on the tile path or on the general path (coral_lmhead_logprob_path
  * tells which).
  */
 coral_status coral_lmhead_grouped_logprob(const void *hidden, const void *gate_W,
@@ -290,7 +294,7 @@ coral_status coral_tree_expand(const float *parent_score, const int32_t *cand_id
  * (cand_ids = topk_ids, cand_logp = topk_logprob).  Where the head runs in the single-launch
  * kernel (coral_lmhead_logprob_path == 1) the workgroup that writes the head's result also
  * expands the level, so the call is one launch; otherwise the expansion is one more launch
- * behind those of the tile or staged path.  Results are identical to the two calls made one
+ * behind those of the tile or general path.  Results are identical to the two calls made one
  * after the other.
  *   parent_score [device] [M] fp32 or NULL, n_next, next_parent / next_token / next_score
  *   [device] out [n_next]: as for coral_tree_expand.  topk_ids, topk_logprob, sel_groups:

@@ -181,7 +181,7 @@ def coral_lmhead_workspace_bytes(M: int, H: int, V: int, G: int, g: int, k: int,
     return int(_L.coral_lmhead_workspace_bytes(M, H, V, G, g, k, dt))
 
 
-PATH_NAMES = {0: "staged", 1: "single-launch", 2: "tiles", -1: "unsupported"}
+PATH_NAMES = {0: "general", 1: "single-launch", 2: "tiles", -1: "unsupported"}
 
 
 def coral_lmhead_path(dense: bool, M: int, H: int, V: int, G: int, g: int, k: int, dt: int) -> int:

@@ -519,13 +519,14 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
     PathPlan pl = {};
     const int n_vec = H / (is_16bit(dt) ? 8 : 4);
     const int jp = (n_vec + kWave - 1) / kWave;
-    if (logprob) {     // the single-launch kernel where it fits, else the tile path, else the staged path
+    if (logprob) {     // the single-launch kernel, else the tile path, else the general path
         pl.path = staged_fits(M, jp, k) ? 0 : -1;
         if (dense) return pl;
         if (logprob_takes_fused(M, H, V, G, g, k, jp, dt)) {
             pl.path = 1;
         } else if (tiles_fit(M, H, V, G, g, k, dt, &pl.tile_umax, &pl.tile_lds) && G <= kWave) {
-            pl.path = 2;                    // (k_gate_select leaves log p_router for up to 64 groups)
+            pl.path = 2;                    // (more than 64 groups: the general path, whose form of the
+                                            // same kernels serves any number; not measured in this one)
         }
         return pl;
     }

@@ -59,7 +59,7 @@ struct TileParams {
     const unsigned long long* tile_mask;    // [token tiles, G] (grouped) what k_gate_select left
     unsigned long long* group_mask;         // [G] out (grouped): tokens that selected the group
     int32_t* group_first_block;             // [G] out (grouped): first block of an activated group
-    float* z;                               // [blocks, M, 128] out: logits of (block, token slot)
+    float* z;                               // [blocks, M, rows of a block] out: logits of (block, token slot)
     float2* stat;                           // [blocks, M] out: the slot's largest logit, and in the
                                             // log-probability mode the sum of exp(z - largest)
     int want_lse;
@@ -814,7 +814,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_gate_select(GateSelParams p) {
 // the (largest, sum of exp) pieces k_tiles left per block, combined in block order, and
 // bounds and keys are formed from z + (log p_router(n) - lse_n).
 struct TileSelectParams {
-    const float* z;                         // [blocks, M, 128] what k_tiles left
+    const float* z;                         // [blocks, M, rows of a block] what k_tiles left
     const float2* stat;                     // [blocks, M]
     const int32_t* sel;                     // [M, g] selected groups (grouped)
     const int32_t* offsets;                 // [G+1]
@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
         qblk = src_i;                                  // the blocks whose largest reaches the bound
     }
 
-    // 5. their candidates, 16 blocks at a time, merged with the list so far (buf[0, have))
+    // 5. their candidates, 4096 at a time, merged with the list so far (buf[0, have))
     int have = 0;                                      // entries of the list so far
     unsigned long long list_kth = 0ull;                // its k-th key once it has k entries
     for (int base = 0; base < n_q; base += chunk_blocks) {       // block-uniform
