@@ -348,3 +348,19 @@ def test_log_probabilities_beyond_32_tokens_stay_in_one_launch_where_the_tile_ke
     for M in (32, 33, 48):
         assert lp(M, 256, 700_000, 32, 2, 8, BF16) == 1
         assert lp(M, 512, 700_000, 32, 2, 8, BF16) == 1
+
+
+def test_routes_on_both_sides_of_the_dispatch_rules():
+    path, lp = coral.coral_lmhead_path, coral.coral_lmhead_logprob_path
+    # rows beyond 8 KB: the single launch with few groups and tokens, more of both with many candidates
+    assert path(False, 1, 4616, 128_000, 128, 2, 10, BF16) == 1 and path(False, 1, 4616, 128_100, 300, 2, 10, BF16) == 0
+    assert path(False, 6, 4616, 128_000, 80, 2, 10, BF16) == 1 and path(False, 6, 4616, 128_000, 128, 2, 10, BF16) == 0
+    assert path(False, 6, 4616, 128_000, 128, 2, 33, BF16) == 1
+    assert lp(8, 5888, 42_200, 25, 2, 4, BF16) == 1 and lp(6, 4616, 128_000, 100, 3, 10, BF16) == 0
+    assert path(False, 1, 8192, 128_100, 300, 2, 10, BF16) == 1    # the other choice is the matrix-core path
+    assert path(False, 6, 5120, 128_256, 48, 2, 10, BF16) == 2     # its blocks fill most of one round
+    assert path(False, 6, 5120, 128_256, 32, 2, 10, BF16) == 1     # ... a second one, mostly empty
+    # many tokens whose candidates would have to be kept in lists
+    assert path(True, 15, 4096, 60_000, 0, 0, 10, BF16) == 1 and path(True, 16, 4096, 60_000, 0, 0, 10, BF16) == 2
+    assert path(False, 31, 256, 1_000_000, 4, 2, 10, BF16) == 1 and path(False, 64, 512, 128_256, 4, 2, 10, BF16) == 2
+    assert path(False, 62, 232, 104_160, 20, 7, 10, F32) == 0
