@@ -807,9 +807,9 @@ __global__ __launch_bounds__(kFusedBlock) void k_gate_select(GateSelParams p) {
 // out of 128 (wide draft tree) or a thousand (dense).  Their logits, 32 blocks (4096
 // candidates, eight per thread) at a time, are filtered by the bound and by the k-th entry
 // of the list so far, collected in LDS with the list, and ranked by counting (64-bit
-// ordering keys, all distinct).  Should more than 512 pass (equal logits, adversarial
-// inputs), the k-th largest of each wave's lanes' best keys and the largest of these eight
-// is a second bound that leaves at most 8 (8 (k - 1) + 1).
+// ordering keys, all distinct).  Should more than 256 pass (k beyond 32, few blocks), a bound
+// taken from the threads' best candidates as from the blocks' maxima comes first; should still
+// more than 512 pass (equal logits), the same by whole keys, which are distinct.
 // Log-probability mode (Eq. 8): log p(x) = log p_router(n) + z[x] - lse_n; lse_n comes from
 // the (largest, sum of exp) pieces k_tiles left per block, combined in block order, and
 // bounds and keys are formed from z + (log p_router(n) - lse_n).
@@ -832,6 +832,7 @@ struct TileSelectParams {
 constexpr int kSelectThreads = 512;
 constexpr int kSelectWaves = kSelectThreads / kWave;
 constexpr int kSelectKeys = 8;                   // candidates per thread and chunk
+constexpr int kSelectFew = 4 * kWave;            // so many are ranked as they are
 constexpr int kKeptMax = kSelectKeys * kSelectThreads + kMaxK;   // a chunk's candidates and the list
 
 struct TileSelectLds {
@@ -887,8 +888,8 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
     int* qblk = reinterpret_cast<int*>(lds + lay.o_qblk);
     unsigned* bval = reinterpret_cast<unsigned*>(lds + lay.o_bval);
     unsigned* qval = reinterpret_cast<unsigned*>(lds + lay.o_qval);
-    __shared__ unsigned long long bound_w[kSelectWaves];
-    __shared__ unsigned tau_w[kSelectWaves];
+    __shared__ unsigned long long bound_w[kSelectWaves], bound_all_w[kSelectWaves];
+    __shared__ unsigned tau_w[kSelectWaves], tau_all_w[kSelectWaves];
     __shared__ int n_kept, n_qual;
 
     const int lane = threadIdx.x & (kWave - 1);
@@ -973,18 +974,38 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
         __syncthreads();
     }
 
-    // 3. the bound: a value that k block maxima reach.  A thread's best over its candidates
-    // (every 256th), the k-th largest of a wave's 64 bests (k threads, so k blocks reach it;
-    // 0 if fewer than k threads have one), the largest of the waves' values; blocks that
-    // reach it are the next round's candidates.  With one candidate per thread the bound
-    // leaves between k and 4 k blocks; with more (the dense head's thousand blocks) a second
-    // and third round tighten it.
+    // 3. the bound: a value that k block maxima reach.  Of the workgroup's threads, each with its
+    // best of the candidates, two samples say one: the k-th largest of a wave's 64 (k threads of
+    // that wave reach it; the largest of the waves' values counts, 0 if fewer than k threads of
+    // each have a candidate), and the (k / 8)-th largest of every wave's (so many of each wave
+    // reach the smallest of the eight values).  The first is exact for up to 64 candidates and the
+    // tighter one for k of about 10; beyond k = 32 it says next to nothing of more (ranking 64 of
+    // 3000 candidates took 80 us with it alone, 10 with the second as well).  Blocks that reach the
+    // bound are the next round's candidates: 1188 blocks come down to 13 with k = 4, 34 with 10, 77
+    // with 64.
     if (LP) {
         for (int i = threadIdx.x; i < n_blocks; i += kSelectThreads)
             bval[i] = ord32(bst[i].x + g_shift[binfo[i] >> 16]);
         __syncthreads();
     }
     unsigned* keys32 = reinterpret_cast<unsigned*>(wkeys) + wave * kWave;
+    const int k_wave = (k + kSelectWaves - 1) / kSelectWaves;
+    // what the waves' samples say together; every thread of the workgroup calls it
+    auto bound_of = [&](unsigned best) {
+        const TwoKeys kth = wave_kth_keys(keys32, best, k, k_wave, lane);
+        if (lane == 0) {
+            tau_w[wave] = kth.first;
+            tau_all_w[wave] = kth.second;
+        }
+        __syncthreads();
+        unsigned one = tau_w[0], all = tau_all_w[0];
+#pragma unroll
+        for (int w = 1; w < kSelectWaves; ++w) {
+            one = tau_w[w] > one ? tau_w[w] : one;
+            all = tau_all_w[w] < all ? tau_all_w[w] : all;
+        }
+        return one > all ? one : all;
+    };
     unsigned tau = 0u;
     int n_q = n_blocks;
     {
@@ -994,13 +1015,14 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
         unsigned* dst_v = qval;
         for (int round = 0; round < 3; ++round) {      // block-uniform
             unsigned best = 0u;
-            for (int i = threadIdx.x; i < n_q; i += kSelectThreads) best = src_v[i] > best ? src_v[i] : best;
-            const unsigned kth = wave_kth_key(keys32, best, k, lane);
-            if (lane == 0) tau_w[wave] = kth;
-            __syncthreads();
-            tau = tau_w[0];
-#pragma unroll
-            for (int w = 1; w < kSelectWaves; ++w) tau = tau_w[w] > tau ? tau_w[w] : tau;
+            if (n_q <= kSelectThreads && n_q > 2 * kWave && k > 10) {      // an equal share for every wave
+                const int per = (n_q + kSelectWaves - 1) / kSelectWaves;
+                const int i = wave * per + lane;
+                if (lane < per && i < n_q) best = src_v[i];
+            } else {
+                for (int i = threadIdx.x; i < n_q; i += kSelectThreads) best = src_v[i] > best ? src_v[i] : best;
+            }
+            tau = bound_of(best);
             for (int base = 0; base < n_q; base += kSelectThreads) {   // block-uniform
                 const int i = base + threadIdx.x;
                 const bool on = i < n_q && src_v[i] >= tau;
@@ -1014,11 +1036,12 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
                 }
             }
             __syncthreads();
-            const bool tight = n_q <= kSelectThreads;
+            const int before = n_q;
             n_q = uni(n_qual);
             int* ti = src_i; src_i = dst_i; dst_i = ti;
             unsigned* tv = src_v; src_v = dst_v; dst_v = tv;
-            if (tight && n_q <= chunk_blocks) break;     // (else once more: the candidates of one chunk)
+            // done once the candidates fit one chunk, or hardly fewer are left than before
+            if (before <= kSelectThreads && (n_q <= chunk_blocks || 4 * n_q > 3 * before)) break;
             __syncthreads();                           // (everyone has the count)
             if (threadIdx.x == 0) n_qual = 0;
         }
@@ -1067,30 +1090,48 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
         };
         int at = reserve(0ull);                        // (n_kept = have: the list comes first)
         __syncthreads();
-        const int passed = uni(n_kept) - have;
-        if (passed > kSelectThreads) {                 // block-uniform: too many for one key per thread
+        int passed = uni(n_kept) - have;
+        auto again = [&](unsigned long long bnd) {
+            __syncthreads();                           // (every wave has read the count by now)
+            if (threadIdx.x == 0) n_kept = have;
+            __syncthreads();
+            at = reserve(bnd);
+            __syncthreads();
+            passed = uni(n_kept) - have;
+        };
+        if (passed > kSelectFew) {                     // block-uniform: the candidates' own bound
+            unsigned best = 0u;
+#pragma unroll
+            for (int q = 0; q < kSelectKeys; ++q) best = (unsigned)(key[q] >> 32) > best ? (unsigned)(key[q] >> 32) : best;
+            again((unsigned long long)bound_of(best) << 32);
+        }
+        if (passed > kSelectThreads) {                 // block-uniform: equal values; the same by whole keys
             unsigned long long best = key[0];
 #pragma unroll
             for (int q = 1; q < kSelectKeys; ++q) best = key[q] > best ? key[q] : best;
             unsigned long long* wk = wkeys + wave * kWave;
             wk[lane] = best;
             const int above = count_above(wk, kWave, best);
-            const unsigned long long hit = __ballot(best != 0ull && above == k - 1);   // one lane or none
-            unsigned long long bnd = 0ull;
-            if (hit) {
+            auto ranked = [&](int rank) {              // the key of that rank, 0 if there is none
+                const unsigned long long hit = __ballot(best != 0ull && above == rank);
+                if (!hit) return 0ull;
                 const int src = __ffsll((long long)hit) - 1;
-                bnd = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(best >> 32), src) << 32) |
-                      (unsigned)__builtin_amdgcn_readlane((int)(unsigned)best, src);
+                return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(best >> 32), src) << 32) |
+                       (unsigned)__builtin_amdgcn_readlane((int)(unsigned)best, src);
+            };
+            const unsigned long long one = ranked(k - 1), all = ranked(k_wave - 1);
+            if (lane == 0) {
+                bound_w[wave] = one;
+                bound_all_w[wave] = all;
             }
-            if (lane == 0) bound_w[wave] = bnd;
-            __syncthreads();                           // (every wave has read the count by now)
-            if (threadIdx.x == 0) n_kept = have;
             __syncthreads();
-            bnd = bound_w[0];
+            unsigned long long bnd = bound_w[0], least = bound_all_w[0];
 #pragma unroll
-            for (int w = 1; w < kSelectWaves; ++w) bnd = bound_w[w] > bnd ? bound_w[w] : bnd;
-            at = reserve(bnd);
-            __syncthreads();
+            for (int w = 1; w < kSelectWaves; ++w) {
+                bnd = bound_w[w] > bnd ? bound_w[w] : bnd;
+                least = bound_all_w[w] < least ? bound_all_w[w] : least;
+            }
+            again(bnd > least ? bnd : least);
         }
 #pragma unroll
         for (int q = 0; q < kSelectKeys; ++q) {

@@ -123,6 +123,20 @@ __device__ __forceinline__ unsigned wave_kth_key(unsigned* keys32, unsigned key,
     }
     return wave_min_u32(above < k ? key : 0xffffffffu);
 }
+// The same for two ranks at once.
+struct TwoKeys {
+    unsigned first, second;
+};
+__device__ __forceinline__ TwoKeys wave_kth_keys(unsigned* keys32, unsigned key, int k1, int k2, int lane) {
+    keys32[lane] = key;
+    int above = 0;
+#pragma unroll 4
+    for (int j = 0; j < kWave / 4; ++j) {
+        const uint4 q = reinterpret_cast<const uint4*>(keys32)[j];
+        above += (q.x > key ? 1 : 0) + (q.y > key ? 1 : 0) + (q.z > key ? 1 : 0) + (q.w > key ? 1 : 0);
+    }
+    return {wave_min_u32(above < k1 ? key : 0xffffffffu), wave_min_u32(above < k2 ? key : 0xffffffffu)};
+}
 
 // A bound that at least `want` and at most `most` (>= want) of the wave's keys reach; 1 (every
 // key reaches it) if there are no more than `most`, or fewer than `want`.  First the want-th

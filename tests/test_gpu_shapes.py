@@ -278,3 +278,21 @@ def test_rows_beyond_8_kb_with_many_groups(coral, dtype, H, G, Ms):
     sizes = [9 + (11 * n) % 50 for n in range(G)]
     cfg = HeadConfig(f"longgroups{H}", dtype, H, sum(sizes), G, 2, Ms, 8, 1003 + H, True)
     check_all(coral, cfg, sizes, Ms, dense=False)
+
+
+@pytest.mark.parametrize("k", [10, 11, 33, 64])
+@pytest.mark.parametrize("rows", [200, 3000, 9000, 17000])
+def test_ranking_kernel_samples(coral, rows, k):
+    """The ranking behind the tile kernels: 4 to 270 blocks per token (dense: up to 535) and every form
+    of the bound; then equal logits, which no bound by value divides."""
+    sizes = [rows + 61 * (n - 1) for n in range(4)]
+    cfg = HeadConfig(f"rank{rows}", "bf16", 512, sum(sizes), 4, 2, (33,), k, 1010 + rows + k, True)
+    assert coral.coral_lmhead_logprob_path(33, 512, cfg.V, 4, 2, k, coral.CORAL_BF16) == 2
+    dh = DeviceHead(coral, ragged_head(cfg, sizes))
+    hidden = make_hidden(cfg, 33, 1)
+    check_grouped(dh, hidden, 2, k, run_grouped(coral, dh, hidden, 2, k))
+    check_logprob(dh, hidden, 2, k, run_logprob(coral, dh, hidden, 2, k))
+    check_dense(dh, hidden, k, run_dense(coral, dh, hidden, k))
+    hidden = np.zeros((33, 512), np.uint16)
+    check_dense(dh, hidden, k, run_dense(coral, dh, hidden, k))
+    check_logprob(dh, hidden, 2, k, run_logprob(coral, dh, hidden, 2, k))
