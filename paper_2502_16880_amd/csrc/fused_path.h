@@ -50,6 +50,10 @@ constexpr int kLdsLimit = 160 * 1024;
 // the dot products of every token that selected its group; measured in units of one
 // token's dot products the latency is about this much.
 constexpr int kLpBaseCost = 10;
+// Batches of a workgroup where there are few: fewer workgroups then leave fewer lists to merge (three
+// groups of 101 rows, one token: 24.8 us with all 256, 22.0 with four batches each, 22.4 with 16; six
+// tokens over 9500 rows 29.1, 29.0, 39.4).
+constexpr int kLpFewBatches = 4;
 constexpr int kLpPiecesMax = 16 * 1024;    // LDS for a workgroup's log-sum-exp pieces, at most
 // Collected candidates: where a workgroup meets few rows per token (the configured shapes:
 // g * v / 256, about 63), the waves append every logit to one buffer per token instead of
@@ -221,9 +225,7 @@ __device__ __forceinline__ void lse_take(float& m, float& s, unsigned long long 
 // Combines the (max, sum) states of all lanes (absent: (-inf, 0)) into log(sum of exp); -inf
 // if there is nothing to sum.
 __device__ __forceinline__ float lse_finish(float m, float s) {
-    float wm = m;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) wm = fmaxf(wm, __shfl_xor(wm, off));
+    const float wm = wave_max(m);
     const float ws = wave_sum(wm > -INFINITY ? s * expf(m - wm) : 0.f);
     return wm + logf(ws);
 }
@@ -648,20 +650,21 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         // groups with the highest cost per workgroup.  The numbers add up to gridDim.x.
         // One wave's work (activated group u in lane u), after it has written the tables of 2c.
         auto share_out_workgroups = [&](int count, int all_pairs) {
-            const int P = gridDim.x;
+            const int P = min((int)gridDim.x, max(count, (all_pairs + kLpFewBatches - 1) / kLpFewBatches));
             const int nb_u = lane < count ? uprefix[lane + 1] - uprefix[lane] : 0;
             // (batches scaled to 16 bits so that the products below stay in 31)
             const int shift = max(0, 16 - __clz(all_pairs));
             const unsigned cost =
                 lane < count ? (unsigned)(nb_u >> shift) * (unsigned)(kLpBaseCost + __popcll(umask[lane])) : 0u;
             const unsigned total = (unsigned)__builtin_amdgcn_readlane(wave_scan_inclusive((int)cost), 63);
-            int n_wg = lane < count ? 1 + (int)(cost * (unsigned)(P - count) / (total ? total : 1u)) : 0;
+            // (the reciprocal rounded down, so that the shares never add up to more than there are)
+            const float scale = (float)(P - count) * __builtin_amdgcn_rcpf((float)(total ? total : 1u)) * (1.f - 0x1p-20f);
+            int n_wg = lane < count ? 1 + (int)((float)cost * scale) : 0;
             const int left = P - __builtin_amdgcn_readlane(wave_scan_inclusive(n_wg), 63);
             if (left > 0) {                            // wave-uniform
                 unsigned long long* rank_keys =
                     reinterpret_cast<unsigned long long*>(lds + lay.o_keys) + (size_t)wave * kWave;
-                const int rank = wave_rank(rank_keys, lane < count ? (float)cost / (float)n_wg : -INFINITY,
-                                           lane, kWave, lane);
+                const int rank = wave_rank(rank_keys, (float)cost * __builtin_amdgcn_rcpf((float)n_wg), lane, count, lane);
                 if (lane < count && rank < left) ++n_wg;
             }
             const int incl_wg = wave_scan_inclusive(n_wg);
@@ -818,16 +821,21 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     // serves faster takes more of them and all waves finish together.  D = 1 shares the
     // batches out evenly, D = 8 keeps neighbouring rows in one workgroup.  Measured (us):
     // two rounds (Llama3 shape, M = 1) D = 8 33.0, D = 1 33.5; ten (M = 10) 131.0, 130.1; 15
-    // (dense) 159.0, 156.4; a tenth of a round (256-wide head) D = 1, 2, 4, 8, 16: 14.2, 14.0,
-    // 13.3, 13.8, 15.5 (few workgroups with several waves each leave fewer lists to merge).
+    // (dense) 159.0, 156.4; a fifth of a round (1024-wide head, 8 tokens) D = 4 20.9, D = 8 22.4; a
+    // tenth, one token 11.7, 11.3.  Few enough batches for all lists to be fetched in one trip with
+    // D = 8 (256-wide head, 4 tokens): 14.3, 13.6; not quite (2 tokens, k = 20): 14.4, 14.7.
     // (Log-probability mode: the workgroup's share is a contiguous range of one group's
     // batches instead, the j-th of the equal parts its group's workgroups cut the group into.)
     const int round = gridDim.x * kFusedWaves;
+    const bool one_trip = M <= 4 && total_batches * k <= kDealFew * 8 * kWave;   // (see wave_merge_lists)
     const int deal = total_batches >= 4 * round || p.deal_single ? 0
-                     : total_batches >= round ? log2_small(kDealFew) : log2_small(kDealFew / 2);
+                     : total_batches >= round || one_trip ? log2_small(kDealFew) : log2_small(kDealFew / 2);
     auto dealt = [&](int i) {
         return (int)(((i >> deal) * gridDim.x + blockIdx.x) << deal) + (i & ((1 << deal) - 1));
     };
+    // Workgroups without a batch leave here; the last merge goes by the others' lists.
+    const int P_act = LP ? uni(wgstart[uni(flags[0])]) : min((int)gridDim.x, (total_batches + (1 << deal) - 1) >> deal);
+    if ((int)blockIdx.x >= P_act) return;              // block-uniform
     int u = 0;
     int lp_lo = 0, lp_nwg = 0;
     // The (max, sum of exp) pieces are kept per batch and summed in batch order at the end: a
@@ -1011,10 +1019,16 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     if (LP) {
         __syncthreads();
         // the tokens of this workgroup's group only: their lists, ranked by logit (inside
-        // a group that is the order of log p as well), and their log-sum-exp pieces
+        // a group that is the order of log p as well), and their log-sum-exp pieces.  Up to eight
+        // tokens: two waves each, one for the list and one for the pieces (a wave alone on its SIMD
+        // issues a dependent instruction every eight to ten cycles: one after the other 3.7 us
+        // from the last row to the list in memory at the Llama3 shape).
         unsigned long long rem = uni64(umask[u]);
+        const int split = 2 * __popcll(rem) <= kFusedWaves ? 1 : 0;
         for (int idx = 0; rem; ++idx, rem &= rem - 1ull) {     // block-uniform
-            if ((idx & (kFusedWaves - 1)) != wave) continue;
+            const bool lists = ((idx << split) & (kFusedWaves - 1)) == wave;
+            const bool pieces = (((idx << split) + split) & (kFusedWaves - 1)) == wave;
+            if (!lists && !pieces) continue;           // wave-uniform
             const int t = __ffsll(rem) - 1;
             // the pieces of this workgroup's batches for token slot idx, summed in batch order;
             // the first 256 are requested before the ranking, which hides their latency
@@ -1028,17 +1042,17 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 early[c] = 0xff800000ull;              // (-inf, 0)
-                if (q0 + c * kWave < q_end) early[c] = piece_at(q0 + c * kWave);
+                if (pieces && q0 + c * kWave < q_end) early[c] = piece_at(q0 + c * kWave);
             }
-            publish_token(t);
+            if (lists) publish_token(t);
+            if (!pieces) continue;
             // (the maximum first, then every piece scaled to it: independent exponentials)
             float late_m = -INFINITY, late_s = 0.f;    // batches beyond the first 256, if any
             for (int q = q0 + 4 * kWave; q < q_end; q += kWave) lse_take(late_m, late_s, piece_at(q));
             float wm = late_m;
 #pragma unroll
             for (int c = 0; c < 4; ++c) wm = fmaxf(wm, __uint_as_float((unsigned)(early[c] & 0xffffffffull)));
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) wm = fmaxf(wm, __shfl_xor(wm, off));
+            wm = wave_max(wm);
             float mine_s = 0.f;
             if (wm > -INFINITY) {
 #pragma unroll
@@ -1058,47 +1072,61 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     if (LP) {
         __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the published lists are out
         __syncthreads();
-        // Eq. 8: log p(x) = log p_router(n) + z[x] - lse_n.  finish(t, gu) is one wave's work
-        // for token t and its selected group ugroup[gu]: it combines the log-sum-exp pieces
-        // of the group's workgroups, takes the router's log-softmax over all G scores, merges
-        // the group's published lists by logit and leaves the k best, offset added, in its
-        // lanes (lane r = rank r).
-        auto finish = [&](int t, int gu) {
+        // Eq. 8: log p(x) = log p_router(n) + z[x] - lse_n.  finish(t, gu) is the work for token t and
+        // its selected group ugroup[gu], of one wave or shared by a wave and the next one (lists: this
+        // wave's part is to merge the group's published lists by logit; shifts: to combine the
+        // log-sum-exp pieces of the group's workgroups and take the router's log-softmax over all
+        // G scores).  Leaves the k best, offset added, in the lanes (lane r = rank r) of the wave
+        // that merges.  With `split` it is called by every wave, `on` or not, up to the barrier.
+        auto finish = [&](bool on, bool lists, bool shifts, bool split, int t, int gu) {
             const int n = uni(ugroup[gu]);
             const int w0 = uni(wgstart[gu]);
             const int n_wg = uni(wgstart[gu + 1]) - w0;
+            float shift = 0.f;
             // the pieces are requested first and used after the merge, whose own loads
             // then share their trip to memory
             unsigned long long piece[4];
+            if (on && shifts) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int l = c * kWave + lane;
-                piece[c] = 0xff800000ull;              // (-inf, 0)
-                if (l < n_wg)
-                    piece[c] = __hip_atomic_load(p.lse_part + (size_t)t * P + w0 + l, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
+                for (int c = 0; c < 4; ++c) {
+                    const int l = c * kWave + lane;
+                    piece[c] = 0xff800000ull;          // (-inf, 0)
+                    if (l < n_wg)
+                        piece[c] = __hip_atomic_load(p.lse_part + (size_t)t * P + w0 + l, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
-            const Cand* src = p.part + (size_t)t * k * P + w0;
-            wave_merge_lists(
-                n_wg, k, lane, ms, [&](int l, int e) { return fetch_cand(src + (size_t)e * P + l); },
-                [&](int r, unsigned long long key) { ms->out[r] = key_cand(key); });
-            float bm = -INFINITY, bs = 0.f;
+            if (on && lists) {
+                const Cand* src = p.part + (size_t)t * k * P + w0;
+                wave_merge_lists(
+                    n_wg, k, lane, ms, [&](int l, int e) { return fetch_cand(src + (size_t)e * P + l); },
+                    [&](int r, unsigned long long key) { ms->out[r] = key_cand(key); });
+            }
+            if (on && shifts) {
+                float rm = -INFINITY, rs = 0.f, s_n = 0.f;
+                for (int o = lane; o < p.G; o += kWave) {
+                    float v = s_lds[t * p.G + o];
+                    if (!(v == v)) v = -INFINITY;
+                    if (o == n) s_n = v;
+                    const float nm = fmaxf(rm, v);
+                    if (nm > -INFINITY) rs = rs * expf(rm - nm) + expf(v - nm);
+                    rm = nm;
+                }
+                s_n = wave_sum(s_n);                   // one lane holds it, the others zero
+                const float logp = s_n - lse_finish(rm, rs);
+                float bm = -INFINITY, bs = 0.f;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) lse_take(bm, bs, piece[c]);   // ascending workgroup order
-            const float lse_n = lse_finish(bm, bs);
-            float rm = -INFINITY, rs = 0.f, s_n = 0.f;
-            for (int o = lane; o < p.G; o += kWave) {
-                float v = s_lds[t * p.G + o];
-                if (!(v == v)) v = -INFINITY;
-                if (o == n) s_n = v;
-                const float nm = fmaxf(rm, v);
-                if (nm > -INFINITY) rs = rs * expf(rm - nm) + expf(v - nm);
-                rm = nm;
+                for (int c = 0; c < 4; ++c)            // ascending workgroup order
+                    if (c * kWave < n_wg) lse_take(bm, bs, piece[c]);   // uniform
+                shift = logp - lse_finish(bm, bs);
             }
-            s_n = wave_sum(s_n);                       // one lane holds it, the others zero
-            const float shift = (s_n - lse_finish(rm, rs)) - lse_n;
+            if (split) {                               // block-uniform
+                if (on && shifts && lane == 0) ms->out[0].v = shift;
+                __syncthreads();
+                if (on && lists) shift = ms[1].out[0].v;
+            }
             Cand c = sentinel();
-            if (lane < k) c = ms->out[lane];
+            if (on && lists && lane < k) c = ms->out[lane];
             if (is_real(c)) c.v += shift;
             return c;
         };
@@ -1162,17 +1190,19 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             if (threadIdx.x == 0) {
                 const unsigned int old = __hip_atomic_fetch_add(p.counter, 1u, __ATOMIC_RELAXED,
                                                                 __HIP_MEMORY_SCOPE_AGENT);
-                flags[1] = old == gridDim.x - 1 ? 1 : 0;
+                flags[1] = old == (unsigned)P_act - 1u ? 1 : 0;
             }
             __syncthreads();
             if (!uni(flags[1])) return;                // block-uniform
             const int count = uni(flags[0]);
             Cand* glists = reinterpret_cast<Cand*>(lds + lay.o_keys);   // [M * g, k], <= 16 x 64 entries
-            if (wave < M * p.g) {
-                const int n = uni(sel_lds[wave]);
+            {
+                const int pair = wave >> 1;            // two waves each
+                const bool on = pair < M * p.g, lists = !(wave & 1);
+                const int n = uni(sel_lds[on ? pair : 0]);
                 const int gu = __ffsll(__ballot(lane < count && ugroup[lane] == n)) - 1;
-                const Cand c = finish(wave / p.g, gu);
-                if (lane < k) glists[wave * k + lane] = c;
+                const Cand c = finish(on, lists, !lists, true, on ? pair / p.g : 0, gu);
+                if (on && lists && lane < k) glists[pair * k + lane] = c;
             }
             __syncthreads();
             if (wave < M) {
@@ -1203,12 +1233,22 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             __hip_atomic_store(group_counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int n = uni(ugroup[u]);
         unsigned long long rem = uni64(umask[u]);
-        for (int idx = 0; rem; ++idx, rem &= rem - 1ull) {     // block-uniform
-            if ((idx & (kFusedWaves - 1)) != wave) continue;
-            const int t = __ffsll(rem) - 1;
+        while (rem) {                                  // block-uniform: 8 tokens or up to 16 at a time
+            const int todo = __popcll(rem);
+            const bool split = 2 * todo <= kFusedWaves;
+            const int mine = split ? wave >> 1 : wave;
+            const bool on = mine < todo;
+            unsigned long long at = rem;               // this wave's token: the mine-th of those left
+            for (int i = 0; i < kFusedWaves && i < todo; ++i) {
+                if (on && i < mine) at &= at - 1ull;
+                if (!split) rem &= rem - 1ull;
+            }
+            if (split) rem = 0ull;
+            const int t = __ffsll(at) - 1;
+            const bool lists = !split || !(wave & 1), shifts = !split || (wave & 1);
             const int i = __ffsll(__ballot(lane < p.g && sel_lds[t * p.g + lane] == n)) - 1;
-            const Cand c = finish(t, u);
-            if (lane < k) publish_cand(p.glist + ((size_t)t * p.g + i) * k + lane, c.v, c.id);
+            const Cand c = finish(on, lists, shifts, split, t, u);
+            if (on && lists && lane < k) publish_cand(p.glist + ((size_t)t * p.g + i) * k + lane, c.v, c.id);
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the group's lists are out
         __syncthreads();
@@ -1237,7 +1277,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     if (threadIdx.x == 0) {
         const unsigned int old = __hip_atomic_fetch_add(p.counter, 1u, __ATOMIC_RELAXED,
                                                         __HIP_MEMORY_SCOPE_AGENT);
-        flags[1] = old == gridDim.x - 1 ? 1 : 0;
+        flags[1] = old == (unsigned)P_act - 1u ? 1 : 0;
     }
     __syncthreads();
     if (!uni(flags[1])) return;                        // block-uniform
@@ -1246,7 +1286,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     for (int t = wave; t < M; t += kFusedWaves) {
         const Cand* src = p.part + (size_t)t * k * P;
         wave_merge_lists(
-            P, k, lane, ms,
+            P_act, k, lane, ms,
             [&](int l, int i) { return fetch_cand(src + (size_t)i * P + l); },
             [&](int r, unsigned long long key) {
                 const Cand c = key_cand(key);

@@ -261,20 +261,30 @@ __device__ __forceinline__ void wave_merge_lists(int n_lists, int k, int lane, M
     // afterwards: in a guarded fetch the compiler starts the conversion to a key inside the guard,
     // which waits for that fetch before the next one is issued. Three such fetches in a row cost
     // 1.2 us more than one.)
-    Cand c[4];
-    if (n_e <= 4 * kWave) {
+    auto fetch_all = [&](auto regs) {                          // all entries in one trip
+        constexpr int N = decltype(regs)::value;
+        Cand c[N];
+        unsigned long long key[N];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < N; ++u) {
             int e = u * kWave + lane;
             e = e < n_e ? e : n_e - 1;
             const int l = div_small(e, inv_k);
             c[u] = get(l, e - l * k);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) key[u] = u * kWave + lane < n_e ? real_key(c[u]) : 0ull;
-        wave_topk<4>(key, k, lane, ms->keys, put);
+        for (int u = 0; u < N; ++u) key[u] = u * kWave + lane < n_e ? real_key(c[u]) : 0ull;
+        wave_topk<N>(key, k, lane, ms->keys, put);
+    };
+    if (n_e <= 4 * kWave) {
+        fetch_all(std::integral_constant<int, 4>());
         return;
     }
+    if (n_e <= 8 * kWave) {
+        fetch_all(std::integral_constant<int, 8>());
+        return;
+    }
+    Cand c[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int l = u * kWave + lane;

@@ -296,3 +296,31 @@ def test_ranking_kernel_samples(coral, rows, k):
     hidden = np.zeros((33, 512), np.uint16)
     check_dense(dh, hidden, k, run_dense(coral, dh, hidden, k))
     check_logprob(dh, hidden, 2, k, run_logprob(coral, dh, hidden, 2, k))
+
+
+@pytest.mark.parametrize("M", [8, 9, 16, 17, 24, 25, 32])
+def test_log_probabilities_where_many_tokens_share_a_group(coral, M):
+    """The single launch's end in log-probability mode: two waves per (token, group) up to eight tokens
+    of a group, one beyond, sixteen at a time."""
+    sizes = [700, 90, 333, 64, 210, 8]
+    cfg = HeadConfig(f"share{M}", "bf16", 512, sum(sizes), len(sizes), 2, (M,), 20, 1300 + M, True)
+    head = ragged_head(cfg, sizes)
+    head.gate_bias[2] += 100.0                         # in every token's selection
+    dh = DeviceHead(coral, head)
+    assert coral.coral_lmhead_logprob_path(M, 512, cfg.V, cfg.G, 2, 20, coral.CORAL_BF16) == 1
+    hidden = make_hidden(cfg, M, M)
+    out = run_logprob(coral, dh, hidden, 2, 20)
+    assert (out[2] == 2).any(axis=1).all()
+    check_logprob(dh, hidden, 2, 20, out)
+    assert all(np.array_equal(x, y) for x, y in zip(out, run_logprob(coral, dh, hidden, 2, 20)))
+
+
+@pytest.mark.parametrize("k", [1, 15, 16, 17, 31, 32, 33, 64])
+@pytest.mark.parametrize("M", [1, 4, 5])
+def test_few_batches_and_lists_fetched_in_one_trip(coral, M, k):
+    """A small head: workgroups without a batch leave early, and the lists of the others are merged in
+    one trip up to 512 entries."""
+    cfg = HeadConfig(f"trip{k}", "f32", 256, 3510, 7, 1, (M,), k, 1400 + M + k, True)
+    sizes = [495 + 2 * n for n in range(7)]
+    sizes[-1] += 3510 - sum(sizes)
+    check_all(coral, cfg, sizes, (M,))
