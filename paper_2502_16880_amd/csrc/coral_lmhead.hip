@@ -40,7 +40,10 @@
 // caller-provided workspace.  One copy per GPU the library runs on, held until the process
 // ends; in host code the name is only a handle for hipGetSymbolAddress, never an address.
 constexpr size_t kStaticScratchBytes = (size_t)CORAL_NOALLOC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// The array is larger than what calls are counted by (static_counted_bytes): the statistics of blocks
+// processed in halves, 128 blocks of 64 tokens at most.
+constexpr size_t kStaticArrayBytes = kStaticScratchBytes + 128 * 64 * 8;
+static __device__ __align__(256) unsigned char scratch[kStaticArrayBytes];
 
 namespace {
 
@@ -63,7 +66,7 @@ static_assert(coral_ctrl::kLpGroupArrivalWords >= kWave, "one arrival counter pe
 static_assert(coral_ctrl::kGateSelectArrivalWords * 16 >= kMaxM, "one arrival counter per token tile");
 
 struct Layout {
-    size_t ctrl, fused_part, fused_lse, fused_glist, fused_pairs, s, sel, mask, union_list, n_union, chunk_base, slot_count, part, lse_part, logp_sel, tile_mask, tile_first_block, tile_z, tile_stat, total;
+    size_t ctrl, fused_part, fused_lse, fused_glist, fused_pairs, s, sel, mask, union_list, n_union, chunk_base, slot_count, part, lse_part, logp_sel, tile_mask, tile_first_block, tile_z, tile_stat, tile_upper, total;
     int part_stride;
 };
 
@@ -74,8 +77,8 @@ bool sizes_ok(int M, int H, int V, int G, int g, int k) {
 }
 
 // Which paths' arrays a layout holds: all that calls with these sizes can take (a workspace), or
-// those of one path only (the static scratch array).
-enum class LayoutFor { kWorkspace, kSingleLaunch, kTiles };
+// those of one path only (the static scratch array; kCounted: what its calls are counted by).
+enum class LayoutFor { kWorkspace, kSingleLaunch, kTiles, kCounted };
 
 // pieces: the log-probability mode's table of per-batch pieces (layout_pieces).  tiles: whether the
 // shape can take the tile kernels (their logits buffer and statistics are left out otherwise), as
@@ -100,7 +103,7 @@ Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, TileArrays 
         return at;
     };
     L.ctrl = take(kCtrlBytes);
-    const size_t single = what != LayoutFor::kTiles ? 1 : 0;
+    const size_t single = what != LayoutFor::kTiles && what != LayoutFor::kCounted ? 1 : 0;
     const size_t logprob = what == LayoutFor::kWorkspace ? 1 : 0;
     const size_t staged = what == LayoutFor::kWorkspace ? 1 : 0;
     L.fused_part = take(single * kMaxWorkgroups * M * k * sizeof(Cand));
@@ -133,6 +136,8 @@ Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, TileArrays 
     // (with blocks of 32 rows the logits take no more, their statistics V / 32 + G entries)
     const size_t stat_blocks = (size_t)V / (tile_arrays.small ? kTileRowsSmall : kTileRows) + G + 1;
     L.tile_stat = take(tiles != Tiles::kNone ? stat_blocks * M * sizeof(float2) : 0);
+    // of blocks processed in halves (half of the workgroups have one at most)
+    L.tile_upper = take(tiles == Tiles::kOwn && what != LayoutFor::kCounted ? kMaxWorkgroups / 2 * M * sizeof(float2) : 0);
     if (off < after) off = after;
     L.total = off > pieces_end ? off : pieces_end;
     return L;
@@ -654,6 +659,8 @@ coral_status launch_tiles(bool dense, const PathPlan& plan, const void* hidden, 
     p.group_first_block = reinterpret_cast<int32_t*>(ws + L.tile_first_block);
     p.z = reinterpret_cast<float*>(ws + L.tile_z);
     p.stat = reinterpret_cast<float2*>(ws + L.tile_stat);
+    p.stat_upper = reinterpret_cast<float2*>(ws + L.tile_upper);
+    p.split_from = reinterpret_cast<int32_t*>(ws + L.n_union);
     p.want_lse = logprob ? 1 : 0;
     p.next_block = reinterpret_cast<unsigned int*>(ws + L.ctrl) + coral_ctrl::kTileQueue;
     p.M = M; p.V = V; p.G = G;
@@ -679,6 +686,8 @@ coral_status launch_tiles(bool dense, const PathPlan& plan, const void* hidden, 
     TileSelectParams q = {};
     q.z = p.z;
     q.stat = p.stat;
+    q.stat_upper = p.stat_upper;
+    q.split_from = p.split_from;
     q.sel = sel;
     q.offsets = p.offsets;
     q.rows = p.rows;
@@ -826,7 +835,7 @@ size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtyp
         tiles = F.total - F.o_lists + (hidden > merges ? hidden : merges) > kLdsLimit;
     }
     return make_layout(M, V, G, g, k, Pieces{}, {tiles ? Tiles::kOwn : Tiles::kNone, false},
-                       tiles ? LayoutFor::kTiles : LayoutFor::kWorkspace).total;
+                       tiles ? LayoutFor::kCounted : LayoutFor::kWorkspace).total;
 }
 
 // The arrays of the kernels that run a call, in the static scratch.  The tile kernels' may be more
@@ -842,7 +851,7 @@ Layout static_layout(const PathPlan& plan, int M, int V, int G, int g, int k, in
         *batch = (M + n - 1) / n;
         L = make_layout(*batch, V, G, g, k, Pieces{}, {plan.path == 2 ? Tiles::kOwn : Tiles::kGeneral, plan.tile_small},
                         LayoutFor::kTiles);
-        if (L.total <= kStaticScratchBytes) break;
+        if (L.total <= kStaticArrayBytes) break;
     }
     return L;
 }
@@ -890,7 +899,7 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
     if (static_workspace) {
         if (logprob || static_counted_bytes(M, H, V, G, g, k, dt) > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;
         L = static_layout(plan, M, V, G, g, k, &tile_tokens);
-        if (L.total > kStaticScratchBytes) return CORAL_ERR_WORKSPACE;             // not reached
+        if (L.total > kStaticArrayBytes) return CORAL_ERR_WORKSPACE;               // not reached
     } else {
         L = make_layout(M, V, G, g, k, layout_pieces(M, H, V, G, g, k, dt), layout_tiles(M, H, V, G, g, k, dt));
         st = check_workspace(workspace, workspace_bytes, L.total);

@@ -32,15 +32,17 @@ constexpr int kTileWaves = 8;
 // Waves that share a row group of 32 rows (split of a chunk's columns): two, a block then being
 // 128 rows, or all eight with blocks of 32 rows, for steps whose 128-row blocks would leave
 // compute units without work (see tile_small_blocks in coral_lmhead.hip).
-constexpr int kTileSplit = 2, kTileSplitSmall = 8;
+constexpr int kTileSplit = 2, kTileSplitHalf = 4, kTileSplitSmall = 8;
 __host__ __device__ constexpr int tile_rows(int split) { return 32 * kTileWaves / split; }
+constexpr int kTileHalfTokens = 32;              // tokens of a group whose blocks can be processed in halves
 constexpr int kTileBlock = kTileWaves * kWave;
 constexpr int kTileRows = tile_rows(kTileSplit);          // weight rows per block (4 row groups of 32)
 constexpr int kTileRowsSmall = tile_rows(kTileSplitSmall);
+static_assert(tile_rows(kTileSplitHalf) * 2 == kTileRows && tile_rows(kTileSplitHalf) == kWave, "");
 constexpr int kChunkVecs = 64;                   // 16-byte vectors per 512-column chunk
 constexpr int kHbStride = kChunkVecs + 1;        // LDS row stride in vectors (pad: no bank conflicts)
 constexpr int kHbBufVecs = 64 * kHbStride;       // one staging buffer: 64 token slots
-constexpr int kRing = 16;                        // weight loads of a wave per chunk = ring size
+constexpr int kRing = 16;                        // weight loads of a wave in flight
 constexpr int kGateParts = 2;                    // workgroups that share the columns of a gate tile
 // Strides (floats) of the accumulator tiles parked in LDS for the epilogue: token tile,
 // row tile of a wave, wave.  Modulo the 64 banks they are 16, 16 and 48.
@@ -62,6 +64,8 @@ struct TileParams {
     float* z;                               // [blocks, M, rows of a block] out: logits of (block, token slot)
     float2* stat;                           // [blocks, M] out: the slot's largest logit, and in the
                                             // log-probability mode the sum of exp(z - largest)
+    float2* stat_upper;                     // [blocks from split_from on, M] out: the same of rows 64 to 127
+    int32_t* split_from;                    // out: the first block processed in halves
     int want_lse;
     unsigned int* next_block;               // block queue: zero before the launch
     int M, V, G;
@@ -173,16 +177,15 @@ __device__ __forceinline__ uint4 tile_load_w(const TileParams& p, unsigned row, 
 // Step pair SP of a chunk: the two 32-column steps whose weight lines sit in ring slots
 // 4 SLOT .. 4 SLOT + 3.  A wave has 8 / SPLIT step pairs of a chunk, so the ring's four cover
 // SPLIT / 2 chunks and are refilled that far ahead.
-template <int DT, int NCT, bool REFILL, int SP, bool GENERAL, int SPLIT, int SLOT>
+template <int DT, int NCT, bool REFILL, bool STORE, int SP, bool GENERAL, int SPLIT, int SLOT, int AHEAD>
 __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4 (&a)[kRing],
                                                f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
                                                const unsigned (&wrow)[4],
-                                               uint4* hbuf, TileStage& hst, uint4* my_slice) {
-    const int lane = threadIdx.x & (kWave - 1);
+                                               uint4* hbuf, TileStage& hst, uint4* my_slice, int lane) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int r16 = lane & 15, q4 = lane >> 4;
     const int kq = wave % SPLIT;
-    constexpr int kAhead = SPLIT / 2, kSteps = 16 / SPLIT;
+    constexpr int kSteps = 16 / SPLIT;
     const uint4* hb = hbuf + (size_t)(c & 1) * kHbBufVecs;
     if (GENERAL && (!REFILL || SPLIT == kTileSplitSmall)) {    // the last chunk: nothing past the row's end
         const unsigned in = tile_lane_vec<SPLIT>(c, SP) < p.n_vec ? 0xffffffffu : 0u;
@@ -196,12 +199,12 @@ __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4
         mfma_operands_from_lines(a[SLOT * 4 + 2 * t], a[SLOT * 4 + 2 * t + 1], lane, my_slice, op[t][0],
                                  op[t][1]);
         if (REFILL) {                                  // refill the two slots just consumed
-            a[SLOT * 4 + 2 * t] = tile_load_w<GENERAL, SPLIT>(p, wrow[2 * t], c + kAhead, SP);
-            a[SLOT * 4 + 2 * t + 1] = tile_load_w<GENERAL, SPLIT>(p, wrow[2 * t + 1], c + kAhead, SP);
+            a[SLOT * 4 + 2 * t] = tile_load_w<GENERAL, SPLIT>(p, wrow[2 * t], c + AHEAD, SP);
+            a[SLOT * 4 + 2 * t + 1] = tile_load_w<GENERAL, SPLIT>(p, wrow[2 * t + 1], c + AHEAD, SP);
         }
     }
     if (REFILL) keep_memory_order();
-    if (REFILL && SP == 3 && SPLIT == kTileSplit) {    // the other buffer is free since the last barrier
+    if (STORE) {                                       // the other buffer is free since the last barrier
         tile_store_hidden<NCT, GENERAL>(p.n_vec, hst, hbuf, c + 1, lane, wave);
         keep_memory_order();
     }
@@ -251,23 +254,46 @@ __device__ __forceinline__ void tile_chunk(const TileParams& p, int c, uint4 (&a
                                            const unsigned (&wrow)[4],
                                            uint4* hbuf, const int* tokslot, int n_t, uint4* my_slice) {
     TileStage hst;
+    const int lane = threadIdx.x & (kWave - 1);
     // (the scheduling barriers keep the compiler from sinking the loads to where their
     // registers are first needed, which would undo the ordering)
     // (general form with two token tiles: after the first step pair, fp32 after the second, there
     // are no registers for them before)
     constexpr int kFetchAt = !GENERAL || NCT == 1 ? 0 : DT == kF32 ? 2 : 1;
     auto fetch = [&]() {
-        tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, hst, c + 1, threadIdx.x & (kWave - 1),
+        tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, hst, c + 1, lane,
                                         __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
         keep_memory_order();
     };
     if (REFILL && kFetchAt == 0) fetch();
-    tile_step_pair<DT, NCT, REFILL, 0, GENERAL, kTileSplit, 0>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    tile_step_pair<DT, NCT, REFILL, false, 0, GENERAL, kTileSplit, 0, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
     if (REFILL && kFetchAt == 1) fetch();
-    tile_step_pair<DT, NCT, REFILL, 1, GENERAL, kTileSplit, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    tile_step_pair<DT, NCT, REFILL, false, 1, GENERAL, kTileSplit, 1, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
     if (REFILL && kFetchAt == 2) fetch();
-    tile_step_pair<DT, NCT, REFILL, 2, GENERAL, kTileSplit, 2>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
-    tile_step_pair<DT, NCT, REFILL, 3, GENERAL, kTileSplit, 3>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    tile_step_pair<DT, NCT, REFILL, false, 2, GENERAL, kTileSplit, 2, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
+    tile_step_pair<DT, NCT, REFILL, REFILL, 3, GENERAL, kTileSplit, 3, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
+    __syncthreads();
+}
+
+// The same with four waves on a row group (halves of 64 rows): two step pairs of a chunk per wave, so
+// that the ring holds two chunks.  Hidden vectors are requested two chunks ahead as well: a chunk ahead
+// they would be younger than all of the next chunk's weight lines, and waiting for them would drain
+// the ring.  PH = c % 2.  `fetched` takes those of chunk c + 2 (REFILL: there is one), `held` are those
+// of chunk c + 1 (STORE).
+template <int DT, int NCT, bool REFILL, bool STORE, int PH>
+__device__ __forceinline__ void tile_chunk_half(const TileParams& p, int c, uint4 (&a)[kRing],
+                                                f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
+                                                const unsigned (&wrow)[4], uint4* hbuf, const int* tokslot, int n_t,
+                                                uint4* my_slice, TileStage& fetched, TileStage& held) {
+    int lane = threadIdx.x & (kWave - 1);
+    asm volatile("" : "+v"(lane));
+    if (REFILL) {
+        tile_fetch_hidden<NCT, false>(p, tokslot, n_t, fetched, c + 2, lane,
+                                      __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+        keep_memory_order();
+    }
+    tile_step_pair<DT, NCT, REFILL, false, 0, false, kTileSplitHalf, PH * 2, 2>(p, c, a, acc, low, wrow, hbuf, held, my_slice, lane);
+    tile_step_pair<DT, NCT, REFILL, STORE, 1, false, kTileSplitHalf, PH * 2 + 1, 2>(p, c, a, acc, low, wrow, hbuf, held, my_slice, lane);
     __syncthreads();
 }
 
@@ -288,7 +314,7 @@ __device__ __forceinline__ void tile_chunk_small(const TileParams& p, int c, uin
     }
     // (past the last chunk the refills read the row's last vector, which nothing uses: a form
     // without them beside this one costs more registers than there are)
-    tile_step_pair<DT, NCT, true, 0, true, kTileSplitSmall, PH>(p, c, a, acc, low, wrow, hbuf, hst, my_slice);
+    tile_step_pair<DT, NCT, true, false, 0, true, kTileSplitSmall, PH, 4>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, threadIdx.x & (kWave - 1));
     if (more) tile_store_hidden<NCT, true>(p.n_vec, hst, hbuf, c + 1, lane, wave);
     __syncthreads();
 }
@@ -302,18 +328,35 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
                                             const int* tokslot, uint4* my_slice, int n_t) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    {
-        TileStage hst;
-        tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, hst, 0, lane, wave);
-        tile_store_hidden<NCT, GENERAL>(p.n_vec, hst, hbuf, 0, lane, wave);
+    TileStage even, odd;                               // (blocks of 64 rows) hidden vectors of the next even and odd chunk
+    tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, even, 0, lane, wave);
+    if constexpr (SPLIT == kTileSplitHalf) {
+        tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, odd, 1, lane, wave);
+        keep_memory_order();
     }
+    tile_store_hidden<NCT, GENERAL>(p.n_vec, even, hbuf, 0, lane, wave);
     __syncthreads();
     f32x4_t low[2][4];                                 // (general form) what the running sums have rounded off
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct) low[t][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    if constexpr (SPLIT == kTileSplit) {
+    if constexpr (SPLIT == kTileSplitHalf) {
+        const int n = p.n_chunks;                      // at least two
+        int c = 0;
+        for (; c + 3 < n; c += 2) {                    // uniform
+            tile_chunk_half<DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
+            tile_chunk_half<DT, NCT, true, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
+        }
+        if (c + 2 < n) {                               // three left
+            tile_chunk_half<DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
+            tile_chunk_half<DT, NCT, false, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
+            tile_chunk_half<DT, NCT, false, false, 0>(p, c + 2, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
+        } else {
+            tile_chunk_half<DT, NCT, false, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
+            tile_chunk_half<DT, NCT, false, false, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
+        }
+    } else if constexpr (SPLIT == kTileSplit) {
         for (int c = 0; c + 1 < p.n_chunks; ++c)
             tile_chunk<DT, NCT, true, GENERAL>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
         tile_chunk<DT, NCT, false, GENERAL>(p, p.n_chunks - 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
@@ -346,6 +389,7 @@ template <int DT, bool GENERAL, int SPLIT>
 __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     static_assert(SPLIT == kTileSplit || GENERAL, "blocks of 32 rows exist in the general form");
     constexpr int ROWS = tile_rows(SPLIT);
+    constexpr bool HALVES = !GENERAL;                  // blocks can be processed in halves (see split_from)
     extern __shared__ uint4 smem[];
     char* lds = reinterpret_cast<char*>(smem);
     const TileLds lay = tile_lds_layout(p.u_max);
@@ -359,7 +403,6 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int rg = wave / SPLIT, kq = wave % SPLIT;
     const int M = p.M;
     uint4* my_slice = reinterpret_cast<uint4*>(lds + lay.o_scratch) + (size_t)wave * kLinePairSlots;
 
@@ -371,7 +414,10 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     int total_blocks;
     if (dense) {
         total_blocks = (p.V + ROWS - 1) / ROWS;
-        if (threadIdx.x == 0) flags[1] = (int)drawn;
+        if (threadIdx.x == 0) {
+            flags[1] = (int)drawn;
+            flags[2] = M > kTileHalfTokens ? total_blocks : 0;
+        }
         __syncthreads();
     } else {
         // The activated groups in the order the workgroups go through them: most token
@@ -419,7 +465,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
                 // (many groups: ascending id; the order only balances the load)
                 for (int r = lane; r < count; r += kWave) order[r] = ulist[r];
             }
-            int carry = 0;
+            int carry = 0, many_end = 0;
             for (int base = 0; base < count; base += kWave) {  // wave-uniform
                 const int r = base + lane;
                 const int g0 = r < count ? order[r] : 0;
@@ -432,11 +478,14 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
                     umask[r] = gmask[g0];
                     if (blockIdx.x == 0) p.group_first_block[g0] = carry + incl - nb;
                 }
+                const unsigned long long many = __ballot(r < count && __popcll(gmask[g0]) > kTileHalfTokens);
+                if (many) many_end = carry + __builtin_amdgcn_readlane(incl, 63 - __clzll((long long)many));
                 carry += __builtin_amdgcn_readlane(incl, 63);
             }
             if (lane == 0) {                           // LDS is in order within a wave
                 uprefix[count] = carry;
                 flags[0] = count;
+                flags[2] = many_end;
                 flags[1] = (int)drawn;
             }
         }
@@ -445,77 +494,101 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     }
 
     const unsigned long long all_tokens = M >= 64 ? ~0ull : ((1ull << M) - 1ull);
+    // Where the last round of blocks would occupy no more than half of the workgroups, its blocks are
+    // handed out in halves of 64 rows (four waves on a row group): one workgroup alone reads a block
+    // at 50 GB/s, and 32 blocks in a third round held up the wide tree's step by 20 us (136.6 us a call,
+    // 126.5 with halves, by how many blocks are left over); heads with fewer blocks than that in all likewise.  Not those of groups with
+    // more than 32 tokens (behind flags[2] there is none): the hidden vectors of the next two chunks
+    // do not fit the registers beside three or four token tiles, and a form that waits for them a chunk
+    // ahead made the whole kernel slower (wide tree 126 -> 134 us, by the registers it takes).
+    const int P = gridDim.x;
+    const int over = total_blocks % P;
+    const int split_from = HALVES && p.n_chunks > 1 && 2 * over <= P ? max(total_blocks - over, uni(flags[2])) : total_blocks;
+    const int total_units = 2 * total_blocks - split_from;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *p.split_from = split_from;
     int u = 0;
-    // first row and end of the block's group (row indices into p.rows, or vocabulary ids)
-    auto locate = [&](int b, int& first, int& end, unsigned long long& bm) {
-        if (dense) {
-            first = b * ROWS;
-            end = p.V;
-            bm = all_tokens;
-        } else {
-            while (b >= uni(uprefix[u + 1])) ++u;      // blocks come in increasing order
-            first = uni(ustart[u]) + (b - uni(uprefix[u])) * ROWS;
-            end = uni(uend[u]);
-            bm = uni64(umask[u]);
+    // A unit of the queue: block b, of it all rows or those of one half; its first row and the end of
+    // its group (row indices into p.rows, or vocabulary ids).
+    struct Unit {
+        int b, half;                                   // half: -1 all rows, 0 the first 64, 1 the others
+        int first, end;
+        unsigned long long bm;
+    };
+    auto locate = [&](int at) {
+        Unit x;
+        x.b = at;
+        x.half = -1;
+        if (HALVES && at >= split_from) {
+            x.b = split_from + ((at - split_from) >> 1);
+            x.half = (at - split_from) & 1;
         }
+        if (dense) {
+            x.first = x.b * ROWS;
+            x.end = p.V;
+            x.bm = all_tokens;
+        } else {
+            while (x.b >= uni(uprefix[u + 1])) ++u;    // blocks come in increasing order
+            x.first = uni(ustart[u]) + (x.b - uni(uprefix[u])) * ROWS;
+            x.end = uni(uend[u]);
+            x.bm = uni64(umask[u]);
+        }
+        if (HALVES && x.half == 1) x.first += ROWS / 2;
+        return x;
     };
     // This lane's four weight rows: row (lane / 8) of each 8-row octet o of the wave's 32
-    // rows (clamped inside the group; the logits of the duplicates are never read).
-    auto my_rows = [&](int first, int end, int (&rid)[4]) {
+    // rows (clamped inside the group; the logits of the duplicates are never read), as byte offsets
+    // of its place in a chunk; and the ring's first slots.  Slot sp * 4 + o holds octet o's 128-byte
+    // line of step pair sp of the first chunk, or (halves) of pair sp % 2 of chunk sp / 2, or (all
+    // waves on one row group) of the one step pair of chunk sp (past the last chunk: clamped to the
+    // row's end, not used).
+    uint4 a[kRing];
+    unsigned wrow[4];
+    auto start_unit = [&](const Unit& x, int lane) {
+        const int split = HALVES && x.half >= 0 ? kTileSplitHalf : SPLIT;      // uniform
+        const int rg = wave / split, kq = wave % split;
 #pragma unroll
         for (int o = 0; o < 4; ++o) {
-            int idx = first + rg * 32 + o * 8 + line_load_row(lane);
-            if (idx >= end) idx = end - 1;
-            rid[o] = dense ? idx : p.rows[idx];
+            int idx = x.first + rg * 32 + o * 8 + line_load_row(lane);
+            if (idx >= x.end) idx = x.end - 1;
+            const int rid = dense ? idx : p.rows[idx];
+            wrow[o] = ((unsigned)rid * (unsigned)p.n_vec + (GENERAL ? 0 : kq * (kChunkVecs / split) + line_load_chunk(lane))) * 16u;
+        }
+#pragma unroll
+        for (int sp = 0; sp < 4; ++sp) {
+            int c = SPLIT == kTileSplit ? 0 : sp, pair = SPLIT == kTileSplit ? sp : 0;
+            if (HALVES && x.half >= 0) {               // uniform
+                c = sp >> 1;
+                pair = sp & 1;
+            }
+#pragma unroll
+            for (int o = 0; o < 4; ++o) a[sp * 4 + o] = tile_load_w<GENERAL, SPLIT>(p, wrow[o], c, pair);
         }
     };
-    // Ring slot sp * 4 + o holds, of the current chunk, octet o's 128-byte line of the step
-    // pair sp (steps kq * 8 + 2 sp and + 1 of the chunk).
-    uint4 a[kRing];
-    unsigned wrow[4];                                  // byte offsets of this lane's rows at its place in a chunk
-    auto set_rows = [&](const int (&rid)[4]) {
-#pragma unroll
-        for (int o = 0; o < 4; ++o)
-            wrow[o] = ((unsigned)rid[o] * (unsigned)p.n_vec + (GENERAL ? 0 : kq * 32 + line_load_chunk(lane))) * 16u;
-    };
-    auto load_a = [&](int c, int sp, int o) { a[sp * 4 + o] = tile_load_w<GENERAL, SPLIT>(p, wrow[o], c, sp); };
-    // the ring's slots at a block's start: the step pairs of the first chunk, or the one step pair
-    // of each of the first four (past the last chunk: clamped to the row's end, not used)
-    auto load_ring = [&]() {
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int o = 0; o < 4; ++o) {
-                if constexpr (SPLIT == kTileSplit) load_a(0, sp, o);
-                else a[sp * 4 + o] = tile_load_w<GENERAL, SPLIT>(p, wrow[o], sp, 0);
-            }
-    };
 
-    int b = uni(flags[1]);
-    int first = 0, end = 0;
-    unsigned long long bm = 0ull;
-    int rid[4] = {0, 0, 0, 0};
-    if (b < total_blocks) {
-        locate(b, first, end, bm);
-        my_rows(first, end, rid);
-        set_rows(rid);
-        load_ring();
+    int at = uni(flags[1]);
+    Unit now = {0, -1, 0, 0, 0ull};
+    if (at < total_units) {
+        now = locate(at);
+        start_unit(now, lane);
     }
     // General form: the running sums' rounding errors take the registers of two token tiles, so a
     // block serves 32 tokens at a time and comes round again for the next 32.
     constexpr bool kPasses = GENERAL;
     constexpr int kPassTokens = kPasses ? 32 : kMaxM;
     int s0 = 0;                                        // first token slot of this pass
-    while (b < total_blocks) {                         // block-uniform
+    while (at < total_units) {                         // block-uniform
+        int ln = lane;                                 // (what is derived from it is not kept from block to block:
+        asm volatile("" : "+v"(ln));                   // there are no registers for that)
+        const unsigned long long bm = now.bm;
         const bool last_pass = !kPasses || s0 + kPassTokens >= __popcll(bm);
         if (threadIdx.x == 0 && last_pass)             // the draw returns long before the K loop ends
             drawn = __hip_atomic_fetch_add(p.next_block, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int n_t = kPasses ? min(__popcll(bm) - s0, kPassTokens) : __popcll(bm);
         const int n_ct = (n_t + 15) >> 4;
         if (wave == 0) {                               // token of every slot
-            const bool on = (bm >> lane) & 1ull;
-            const int slot = __popcll(bm & ((1ull << lane) - 1ull)) - (kPasses ? s0 : 0);
-            if (on && (!kPasses || slot >= 0)) tokslot[slot] = lane;   // (slots past this pass's are not read)
+            const bool on = (bm >> ln) & 1ull;
+            const int slot = __popcll(bm & ((1ull << ln) - 1ull)) - (kPasses ? s0 : 0);
+            if (on && (!kPasses || slot >= 0)) tokslot[slot] = ln;   // (slots past this pass's are not read)
         }
         __syncthreads();
 
@@ -529,11 +602,17 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
             if (n_ct == 1) tile_k_loop<DT, 1, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);   // block-uniform
             else tile_k_loop<DT, 2, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
         } else {
+            auto run = [&](auto tiles) {
+                constexpr int NCT = decltype(tiles)::value;
+                if constexpr (NCT <= 2)
+                    if (now.half >= 0) return tile_k_loop<DT, NCT, GENERAL, kTileSplitHalf>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
+                tile_k_loop<DT, NCT, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
+            };
             switch (n_ct) {                                // block-uniform
-                case 1: tile_k_loop<DT, 1, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
-                case 2: tile_k_loop<DT, 2, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
-                case 3: tile_k_loop<DT, 3, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
-                default: tile_k_loop<DT, 4, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t); break;
+                case 1: run(std::integral_constant<int, 1>()); break;
+                case 2: run(std::integral_constant<int, 2>()); break;
+                case 3: run(std::integral_constant<int, 3>()); break;
+                default: run(std::integral_constant<int, 4>()); break;
             }
         }
 
@@ -541,29 +620,19 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         // (flags[1] was last read before this block's barriers)
         if (threadIdx.x == 0 && last_pass) flags[1] = (int)drawn;
         __syncthreads();
-        const int nb = last_pass ? uni(flags[1]) : b;
-        int nfirst = 0, nend = 0;
-        unsigned long long nbm = 0ull;
-        if (kPasses && !last_pass) {
-            nfirst = first;
-            nend = end;
-            nbm = bm;
-        }
-        if (nb < total_blocks) {
-            if (last_pass) {
-                locate(nb, nfirst, nend, nbm);
-                my_rows(nfirst, nend, rid);
-                set_rows(rid);
-            }
-            load_ring();
+        const int next_at = last_pass ? uni(flags[1]) : at;
+        Unit next = now;
+        if (next_at < total_units) {
+            if (last_pass) next = locate(next_at);
+            start_unit(next, ln);
         }
 
         // half sums -> LDS (over the staging buffers, free after the last barrier).  A
-        // tile's accumulators sit at lane * 4 plus 4 floats of padding per 16 lanes, and the
+        // tile's accumulators sit at ln * 4 plus 4 floats of padding per 16 lanes, and the
         // strides between tiles are chosen so that the reads below, whose 64 lanes want one
         // column of four different tiles, fall on 64 different banks.
         float* red = reinterpret_cast<float*>(hbuf);
-        const int red_lane = lane * 4 + (lane >> 4) * 4;
+        const int red_lane = ln * 4 + (ln >> 4) * 4;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -572,40 +641,49 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
                     *reinterpret_cast<f32x4_t*>(red + wave * kRedWave + t * kRedTile + ct * kRedCt + red_lane) =
                         acc[t][ct];
         __syncthreads();
-        // one wave per token slot, the block's rows in two halves of 64: lane = (row tile,
+        // one wave per token slot, the block's rows in two halves of 64: ln = (row tile,
         // row) -> 64 logits of the slot, 256 consecutive bytes of the block's logits
         // and the slot's largest logit (rows past the group's end do not count): the ranking
         // kernel reads the logits only of blocks whose largest can matter.  Log-probability
         // mode: the sum of exp(z - largest) as well, the block's piece of the group's lse.
         for (int s = wave; s < n_t; s += kTileWaves) {
-            float* dst = p.z + ((size_t)b * M + (kPasses ? s0 : 0) + s) * ROWS + lane;
+            const size_t entry = (size_t)now.b * M + (kPasses ? s0 : 0) + s;
+            const bool half = HALVES && now.half >= 0; // uniform
+            float* dst = p.z + entry * ROWS + (half ? now.half * kWave : 0) + ln;
             float zs[2] = {-INFINITY, -INFINITY};
 #pragma unroll
             for (int hf = 0; hf < (ROWS + kWave - 1) / kWave; ++hf) {
-                const int tile = hf * 4 + (lane >> 4), row = lane & 15;   // row tile of the block
+                if (hf == 1 && half) break;            // uniform
+                const int tile = hf * 4 + (ln >> 4), row = ln & 15;   // row tile of the unit
                 const int e = (row >> 2) * 68 + (s & 15) * 4 + (row & 3);
-                const int w0 = ((tile >> 1) * SPLIT) & (kTileWaves - 1);  // the row group's first wave
+                const int w0 = ((tile >> 1) * (half ? kTileSplitHalf : SPLIT)) & (kTileWaves - 1);    // the row group's first wave
+                auto part = [&](int q) { return red[(w0 + q) * kRedWave + (tile & 1) * kRedTile + (s >> 4) * kRedCt + e]; };
                 float z = 0.f;
 #pragma unroll
-                for (int q = 0; q < SPLIT; ++q)
-                    z += red[(w0 + q) * kRedWave + (tile & 1) * kRedTile + (s >> 4) * kRedCt + e];
-                if (ROWS >= kWave || lane < ROWS) {    // (32-row blocks: the lanes above repeat the rows)
+                for (int q = 0; q < SPLIT; ++q) z += part(q);
+                if (half) {
+#pragma unroll
+                    for (int q = SPLIT; q < kTileSplitHalf; ++q) z += part(q);
+                }
+                if (ROWS >= kWave || ln < ROWS) {      // (32-row blocks: the lanes above repeat the rows)
                     dst[hf * kWave] = z;
-                    zs[hf] = first + hf * kWave + lane < end ? z : -INFINITY;
+                    zs[hf] = now.first + hf * kWave + ln < now.end ? z : -INFINITY;
                 }
             }
             const float wm = wave_max(fmaxf(zs[0], zs[1]));
             float sum = 0.f;
             if (p.want_lse)                            // block-uniform
                 sum = wave_sum(wm > -INFINITY ? expf(zs[0] - wm) + expf(zs[1] - wm) : 0.f);
-            if (lane == 0) p.stat[(size_t)b * M + (kPasses ? s0 : 0) + s] = make_float2(wm, sum);
+            if (ln == 0) {
+                float2* st = p.stat + entry;
+                if (half && now.half == 1) st = p.stat_upper + (entry - (size_t)split_from * M);
+                *st = make_float2(wm, sum);
+            }
         }
         __syncthreads();
         if (kPasses) s0 = last_pass ? 0 : s0 + kPassTokens;
-        b = nb;
-        first = nfirst;
-        end = nend;
-        bm = nbm;
+        at = next_at;
+        now = next;
     }
 }
 
@@ -816,6 +894,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_gate_select(GateSelParams p) {
 struct TileSelectParams {
     const float* z;                         // [blocks, M, rows of a block] what k_tiles left
     const float2* stat;                     // [blocks, M]
+    const float2* stat_upper;
+    const int32_t* split_from;
     const int32_t* sel;                     // [M, g] selected groups (grouped)
     const int32_t* offsets;                 // [G+1]
     const int32_t* rows;                    // [V]
@@ -897,6 +977,7 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
     const int t = blockIdx.x, k = p.k;
     constexpr int rows_per_block = 1 << SHIFT;
     constexpr int chunk_blocks = kSelectKeys * kSelectThreads >> SHIFT;
+    const int split_from = rows_per_block == kTileRows ? *p.split_from : 0;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         __hip_atomic_store(p.next_block, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (threadIdx.x == 0) {
@@ -951,7 +1032,14 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
         }
         const int lb = i - g_pre[lo];
         binfo[i] = (lo << 16) | lb;
-        const float2 st = p.stat[(size_t)(g_fb[lo] + lb) * p.M + g_slot[lo]];
+        const size_t entry = (size_t)(g_fb[lo] + lb) * p.M + g_slot[lo];
+        float2 st = p.stat[entry];
+        if (rows_per_block == kTileRows && g_fb[lo] + lb >= split_from) {      // processed in halves
+            const float2 up = p.stat_upper[entry - (size_t)split_from * p.M];
+            const float most = fmaxf(st.x, up.x);
+            if (LP && most > -INFINITY) st.y = st.y * expf(st.x - most) + up.y * expf(up.x - most);
+            st.x = most;
+        }
         if (LP) bst[i] = st;
         else bval[i] = ord32(st.x);                    // (no offsets: the block's largest logit as it is)
     }
@@ -992,7 +1080,8 @@ __global__ __launch_bounds__(kSelectThreads) void k_tile_select(TileSelectParams
     const int k_wave = (k + kSelectWaves - 1) / kSelectWaves;
     // what the waves' samples say together; every thread of the workgroup calls it
     auto bound_of = [&](unsigned best) {
-        const TwoKeys kth = wave_kth_keys(keys32, best, k, k_wave, lane);
+        const TwoKeys kth = k <= 10 ? TwoKeys{wave_kth_key(keys32, best, k, lane), 0u}         // uniform
+                                    : wave_kth_keys(keys32, best, k, k_wave, lane);
         if (lane == 0) {
             tau_w[wave] = kth.first;
             tau_all_w[wave] = kth.second;

@@ -298,6 +298,35 @@ def test_ranking_kernel_samples(coral, rows, k):
     check_logprob(dh, hidden, 2, k, run_logprob(coral, dh, hidden, 2, k))
 
 
+@pytest.mark.parametrize("dtype,H,M", [("bf16", 512, 34), ("f16", 1024, 40), ("bf16", 1536, 33), ("bf16", 2048, 64), ("f16", 2560, 48),
+                                       ("bf16", 3072, 40)])
+def test_blocks_in_halves(coral, dtype, H, M):
+    """The tile path's last round of blocks in halves of 64 rows: one chunk of columns (never halved)
+    to six, groups that end in either half, one of them with too many tokens; then all of one round and
+    a rest in halves, grouped and dense."""
+    sizes = [64, 65, 1, 127, 128, 129, 300, 192, 193, 90, 410, 260]
+    cfg = HeadConfig(f"half{H}", dtype, H, sum(sizes), len(sizes), 2, (M,), 12, 1100 + H, True)
+    head = ragged_head(cfg, sizes)
+    head.gate_bias[6] += 2.0
+    dh = DeviceHead(coral, head)
+    hidden = make_hidden(cfg, M, M)
+    assert coral.coral_lmhead_logprob_path(M, H, cfg.V, cfg.G, 2, 12, coral.CORAL_BF16) == 2
+    check_grouped(dh, hidden, 2, 12, run_grouped(coral, dh, hidden, 2, 12))
+    out = run_logprob(coral, dh, hidden, 2, 12)
+    check_logprob(dh, hidden, 2, 12, out)
+    assert all(np.array_equal(x, y) for x, y in zip(out, run_logprob(coral, dh, hidden, 2, 12)))
+
+
+def test_a_whole_round_of_blocks_and_a_rest_in_halves(coral):
+    cfg = HeadConfig("rest", "bf16", 1024, 40_100, 16, 4, (40,), 10, 1200, True)
+    sizes = [2500] * 15 + [2600]
+    dh = DeviceHead(coral, ragged_head(cfg, sizes))
+    for M in (40, 32):
+        hidden = make_hidden(cfg, M, M)
+        check_logprob(dh, hidden, 4, 10, run_logprob(coral, dh, hidden, 4, 10))
+        check_dense(dh, hidden, 10, run_dense(coral, dh, hidden, 10))
+
+
 @pytest.mark.parametrize("M", [8, 9, 16, 17, 24, 25, 32])
 def test_log_probabilities_where_many_tokens_share_a_group(coral, M):
     """The single launch's end in log-probability mode: two waves per (token, group) up to eight tokens
