@@ -1144,8 +1144,10 @@ extern "C" coral_status coral_router_premix(const void* hidden, const void* W1, 
     p.n_vec = H / (w16 ? 8 : 4);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     typedef void (*premix_fn)(PremixParams);
+    // Which kernel, us (k_premix_wide, k_premix_blocks): H = 2560, 8 tokens 6.3, 6.6, 15 6.3, 7.0; H =
+    // 4096, 8 tokens 9.9, 9.5, 15 9.8, 10.0, 40 12.6, 13.8.
     if (w16 && M >= 4 && M <= 64 && H % (kPremixChunkVecs * 8) == 0 &&
-        H / (kPremixChunkVecs * 8) <= kPremixMaxChunks) {     // matrix cores, tokens staged in chunks
+        H / (kPremixChunkVecs * 8) <= kPremixMaxChunks && (M > 8 || H <= 3072)) {     // matrix cores, tokens staged in chunks
         typedef void (*wide_fn)(PremixParams);
         const int n_ct = (M + 15) / 16;
         const bool f16 = dt == CORAL_F16;
@@ -1164,17 +1166,21 @@ extern "C" coral_status coral_router_premix(const void* hidden, const void* W1, 
         hipLaunchKernelGGL(wf, dim3(H / 16), dim3(kPremixWideBlock), lds, stream, p);
         return launch_status();
     }
-    if (w16 && H % 64 == 0 && M >= 4) {                       // matrix cores
-        int tok = M < kPremixTileTok ? M : kPremixTileTok;
-        while (tok > 4 && premix_mfma_lds_bytes(tok, p.n_vec) > (size_t)kLdsLimit) --tok;
-        const size_t lds = premix_mfma_lds_bytes(tok, p.n_vec);
-        if (lds <= (size_t)kLdsLimit) {
-            p.tok_per_wg = tok;
-            const premix_fn mf = dt == CORAL_F16 ? k_premix_mfma<kF16> : k_premix_mfma<kBF16>;
-            if (!allow_lds(reinterpret_cast<const void*>(mf), (int)lds)) return CORAL_ERR_HIP;
-            hipLaunchKernelGGL(mf, dim3(H / 16, (M + tok - 1) / tok), dim3(kBlock), lds, stream, p);
-            return launch_status();
-        }
+    // ... (k_premix, k_premix_blocks): 16 bits, H = 512, one token 4.6, 3.6, H = 5120 14.1, 13.3, H =
+    // 6016 15.3, 16.2, 2 tokens 17.1, 16.1; H = 8192, 1 to 4 tokens 24.9, 27.9, 25.8, 27.7, 27.1, 27.5,
+    // 34.0, 27.4; fp32, H = 1536, 4 tokens 7.4, 7.5, 8 tokens 10.0, 7.5; H = 4096, one token 15.2, 19.0, 4
+    // tokens 16.9, 19.1, 8 tokens 31.4, 19.0.  (fp32 rows of less than 6 KB: the vector units' sums are the
+    // more exact ones, 3.45e-8 against 3.6e-8 at H = 512; 5.7e-8 against 5.3e-8 at 1536.)
+    if (w16 ? M >= 4 || H <= 5632 || (M >= 2 && H <= 7680) : M >= 5 && H >= 1536) {
+        const int n_ct = M <= 16 ? 1 : M <= 32 ? 2 : M <= 48 ? 3 : 4;
+        // (as many blocks ahead as the registers hold)
+        const premix_fn fn =
+            n_ct == 1   ? CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 1, 2>), (k_premix_blocks<kBF16, 1, 3>), (k_premix_blocks<kF16, 1, 3>))
+            : n_ct == 2 ? CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 2, 3>), (k_premix_blocks<kBF16, 2, 3>), (k_premix_blocks<kF16, 2, 3>))
+            : n_ct == 3 ? CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 3, 2>), (k_premix_blocks<kBF16, 3, 2>), (k_premix_blocks<kF16, 3, 2>))
+                        : CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 4, 1>), (k_premix_blocks<kBF16, 4, 2>), (k_premix_blocks<kF16, 4, 2>));
+        hipLaunchKernelGGL(fn, dim3((H + 15) / 16, (M + n_ct * 16 - 1) / (n_ct * 16)), dim3(kPremixBlockThreads), 0, stream, p);
+        return launch_status();
     }
     int tok = (int)((size_t)kLdsLimit / 2 / row_bytes);       // two workgroups per compute unit
     if (tok < 1) tok = 1;

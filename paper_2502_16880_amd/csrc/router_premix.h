@@ -6,10 +6,9 @@
 // flight at d = 4096), dotted with every token's vector (fp32 accumulation), and lane t
 // finishes token t: activation, residual, rounding to the storage type.
 //
-// From four tokens on the vector units would bound the kernel (a bf16 dot instruction per two
-// products of every token), so the contraction goes to the matrix cores: a workgroup owns 16
-// output features, its four waves split their columns, and each wave holds 16 whole 128-byte
-// lines of each of the 16 rows (32 loads, 32 KB) in registers at once.
+// From a few tokens on the vector units would bound the kernel (a bf16 dot instruction per two
+// products of every token), so the contraction goes to the matrix cores: k_premix_wide and
+// k_premix_blocks.
 #pragma once
 #include "device_utils.h"
 #include "fused_path.h"
@@ -129,108 +128,8 @@ __global__ __launch_bounds__(kBlock) void k_premix(PremixParams p) {
     }
 }
 
-constexpr int kPremixTileTok = 16;               // tokens of a workgroup on the matrix cores
-constexpr int kPremixLines = 16;                 // 128-byte lines of a row a wave holds at once
-constexpr int kPremixTileStage = 32;             // 16-byte vectors a thread stages through registers
-
-__host__ __device__ inline size_t premix_mfma_lds_bytes(int tok, int n_vec) {
-    return ((size_t)tok * (n_vec + 1) + (size_t)kWavesPerBlock * kLinePairSlots) * sizeof(uint4) +
-           (size_t)kWavesPerBlock * 256 * sizeof(float);
-}
-
-// bf16, H a multiple of 64 (whole 128-byte lines).  Tile of 16 output features x 16 tokens:
-// A operand = rows of W1, B operand = hidden vectors from LDS (row stride padded by one
-// vector: conflict-free); lane l of the result holds features 4*(l/16)..+4 of token l%16.
-template <int DT>
-__global__ __launch_bounds__(kBlock) void k_premix_mfma(PremixParams p) {
-    extern __shared__ uint4 smem[];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int r16 = lane & 15, q4 = lane >> 4;
-    const int stride = p.n_vec + 1;
-    uint4* hs = smem;                                              // [tok_per_wg][stride]
-    uint4* my_slice = smem + (size_t)p.tok_per_wg * stride + (size_t)wave * kLinePairSlots;
-    float* red = reinterpret_cast<float*>(smem + (size_t)p.tok_per_wg * stride +
-                                          (size_t)kWavesPerBlock * kLinePairSlots);   // [4][256]
-    const int m0 = blockIdx.y * p.tok_per_wg;
-    const int tb = p.M - m0 < p.tok_per_wg ? p.M - m0 : p.tok_per_wg;
-    const int r0 = blockIdx.x * 16;                                // H is a multiple of 16 here
-    const int n_lines = p.n_vec / 8;
-    // line L of the rows belongs to wave L % 4; a wave takes 16 of its lines per batch
-    uint4 lo[kPremixLines], hi[kPremixLines];
-    const uint4* wlo = p.W1 + (size_t)(r0 + line_load_row(lane)) * p.n_vec + line_load_chunk(lane);
-    const uint4* whi = wlo + (size_t)8 * p.n_vec;
-    auto load_batch = [&](int b) {
-#pragma unroll
-        for (int i = 0; i < kPremixLines; ++i) {
-            const int L = (b * kPremixLines + i) * kWavesPerBlock + wave;
-            lo[i] = make_uint4(0, 0, 0, 0);
-            hi[i] = make_uint4(0, 0, 0, 0);
-            if (L < n_lines) {                                     // wave-uniform
-                lo[i] = load_stream(wlo + L * 8);
-                hi[i] = load_stream(whi + L * 8);
-            }
-        }
-    };
-    // The tokens' vectors are requested before the weight lines and written to LDS after
-    // those have been requested too: loads complete in order, so the tokens do not wait for
-    // the 32 KB of weight lines per wave behind them, and the lines stream meanwhile.
-    const int total = tb * p.n_vec;
-    const uint4* hsrc = p.hidden + (size_t)m0 * p.n_vec;
-    auto hs_slot = [&](int i) {
-        const int t = i / p.n_vec;
-        return hs + (size_t)t * stride + (i - t * p.n_vec);
-    };
-    uint4 st[kPremixTileStage];
-#pragma unroll
-    for (int j = 0; j < kPremixTileStage; ++j) {
-        const int i = threadIdx.x + j * kBlock;
-        if (i < total) st[j] = load_vec(hsrc + i);
-    }
-    for (int i = threadIdx.x + kPremixTileStage * kBlock; i < total; i += kBlock) *hs_slot(i) = hsrc[i];
-    asm volatile("" ::: "memory");                                 // (keeps the order)
-    load_batch(0);
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int j = 0; j < kPremixTileStage; ++j) {
-        const int i = threadIdx.x + j * kBlock;
-        if (i < total) store_vec(hs_slot(i), st[j]);
-    }
-    __syncthreads();
-    f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    const uint4* hb = hs + (size_t)(r16 < tb ? r16 : tb - 1) * stride + q4;   // columns past tb are not stored
-    for (int b = 0; b * kPremixLines * kWavesPerBlock < n_lines; ++b) {       // block-uniform
-        if (b) load_batch(b);
-#pragma unroll
-        for (int i = 0; i < kPremixLines; ++i) {
-            const int L = (b * kPremixLines + i) * kWavesPerBlock + wave;
-            if (L < n_lines) {                                     // wave-uniform
-                uint4 s0, s1;
-                mfma_operands_from_lines(lo[i], hi[i], lane, my_slice, s0, s1);
-                const uint4 b0 = hb[L * 8], b1 = hb[L * 8 + 4];
-                acc = mfma_tile<DT>(s0, b0, acc);
-                acc = mfma_tile<DT>(s1, b1, acc);
-            }
-        }
-    }
-    *reinterpret_cast<f32x4_t*>(red + wave * 256 + lane * 4) = acc;
-    __syncthreads();
-    {
-        const int e = threadIdx.x, l = e >> 2, i = e & 3;
-        const int row = r0 + (l >> 4) * 4 + i, tok = l & 15;
-        float y = 0.f;
-#pragma unroll
-        for (int w = 0; w < kWavesPerBlock; ++w) y += red[w * 256 + e];    // wave order
-        if (tok < tb) {
-            const unsigned short* hrow = reinterpret_cast<const unsigned short*>(hs + (size_t)tok * stride);
-            static_cast<unsigned short*>(p.out)[(size_t)(m0 + tok) * p.H + row] =
-                narrow16<DT>(premix_act(y, p.act) + widen16<DT>(hrow[row]));
-        }
-    }
-}
-
-// More than 16 tokens: the token vectors no longer fit LDS whole, so they are staged in
-// 512-column chunks for all token tiles at once (two buffers), and a workgroup of eight waves
+// Rows of up to 8 KB in whole 512-column chunks, four tokens and more: the token vectors are staged in
+// such chunks for all token tiles at once, and a workgroup of eight waves
 // owns 16 output features: wave w takes the 64 columns w*64.. of every chunk, i.e. one
 // 128-byte line of each of the 16 rows per chunk, and requests all its lines up front (the
 // whole of W1 is in flight in one round).  A line pair's operands serve every token tile.
@@ -470,6 +369,127 @@ __global__ __launch_bounds__(kPremixWideBlock) void k_premix_wide(PremixParams p
         if (tok < p.M)
             static_cast<unsigned short*>(p.out)[(size_t)tok * p.H + row] =
                 narrow16<DT>(premix_act(y, p.act) + widen16<DT>(h_res[j]));
+    }
+}
+
+// Any width and storage type: a workgroup of eight waves owns 16 output features, its waves share
+// the columns in blocks of 256 bytes (every eighth), and both operands of a block are loaded four
+// rows x 256 bytes per wave load and transposed in registers: no staging of the tokens, no barrier
+// before the sums at the end, two workgroups per compute unit.  The tokens come out of the L2, D
+// blocks ahead like the weights (loads return in order: tokens requested later than the next
+// block's weights would wait for them).  Bound by the weights' stream and, from two token tiles on,
+// the tokens' out of the L2.  us, against the forms it replaces (four waves holding 16 lines of every
+// row, one token tile at a time; the vector units): bf16 H = 6016, 15 tokens 38.2 -> 18.5, 64 tokens
+// 112.6 -> 38.3 (bytes at 6.8 TB/s: 10.6), H = 2568, 15 tokens 12.8 -> 8.0; fp32 H = 4096, 15 tokens
+// 47.0 -> 19.7, error against float64 1.1e-7 -> 0.75e-7.
+constexpr int kPremixBlockWaves = 8;
+constexpr int kPremixBlockThreads = kPremixBlockWaves * kWave;
+template <int DT, int NCT, int D>
+__global__ __launch_bounds__(kPremixBlockThreads, NCT == 1 ? 4 : 2) void k_premix_blocks(PremixParams p) {
+    __shared__ __attribute__((aligned(16))) float red[kPremixBlockWaves * NCT * 256];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int q4 = lane >> 4, a4 = (lane >> 2) & 3, c4 = lane & 3;
+    const int r0 = blockIdx.x * 16, m0 = blockIdx.y * NCT * 16;
+    const int tb = p.M - m0;                                       // tokens from m0 on
+    const uint4* hidden = p.hidden + (size_t)m0 * p.n_vec;
+    // the residual of the results this thread will write, as in k_premix_wide
+    constexpr int kOutPerThread = (NCT * 256 + kPremixBlockThreads - 1) / kPremixBlockThreads;
+    float h_res[kOutPerThread];
+#pragma unroll
+    for (int j = 0; j < kOutPerThread; ++j) {
+        const int e = threadIdx.x + j * kPremixBlockThreads;
+        const int l = (e & 255) >> 2, row = r0 + (l >> 4) * 4 + (e & 3), tok = (e >> 8) * 16 + (l & 15);
+        h_res[j] = 0.f;
+        if (e < NCT * 256 && tok < tb && row < p.H) {
+            const size_t at = (size_t)tok * p.H + row;
+            if (DT == kF32) h_res[j] = reinterpret_cast<const float*>(hidden)[at];
+            else h_res[j] = widen16<DT>(reinterpret_cast<const unsigned short*>(hidden)[at]);
+        }
+    }
+    const int n_blk = (p.n_vec + 15) / 16;
+    const int n = (n_blk - wave + kPremixBlockWaves - 1) / kPremixBlockWaves;      // this wave's blocks
+    uint4 a[D][4], b[D][NCT][4];
+    auto load = [&](int i, int slot) {
+        const int vec = (wave + i * kPremixBlockWaves) * 16 + q4 * 4 + c4;
+        const bool in = vec < p.n_vec;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int row = r0 + a4 * 4 + t;
+            a[slot][t] = make_uint4(0, 0, 0, 0);
+            if (in && row < p.H) a[slot][t] = load_stream(p.W1 + (size_t)row * p.n_vec + vec);
+        }
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int m = ct * 16 + a4 * 4 + t;
+                b[slot][ct][t] = make_uint4(0, 0, 0, 0);
+                if (in && m < tb) b[slot][ct][t] = load_vec(hidden + (size_t)m * p.n_vec + vec);
+            }
+    };
+#pragma unroll
+    for (int k = 0; k < D; ++k)
+        if (k < n) load(k, k);                                     // wave-uniform
+    f32x4_t acc[NCT][2];
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) acc[ct][0] = acc[ct][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < n; i += D) {                               // wave-uniform
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            if (i + k < n) {
+                mfma_operands_from_quad_rows(a[k][0], a[k][1], a[k][2], a[k][3], lane);
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct) {
+                    mfma_operands_from_quad_rows(b[k][ct][0], b[k][ct][1], b[k][ct][2], b[k][ct][3], lane);
+                    if (DT == kF32) {
+                        // a block's products start from zero and are added with the rounding error
+                        // kept (two-sum), as in k_tiles' general form: one running sum was 2e-7
+                        // off at 4000 columns, the vector units' lane-split sums 1.1e-7
+                        const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                        const f32x4_t x = (mfma_tile<DT>(a[k][0], b[k][ct][0], zero) + mfma_tile<DT>(a[k][1], b[k][ct][1], zero)) +
+                                          (mfma_tile<DT>(a[k][2], b[k][ct][2], zero) + mfma_tile<DT>(a[k][3], b[k][ct][3], zero));
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float hi = acc[ct][0][q], sum = hi + x[q], back = sum - hi;
+                            acc[ct][1][q] += (hi - (sum - back)) + (x[q] - back);
+                            acc[ct][0][q] = sum;
+                        }
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) acc[ct][0] = mfma_tile<DT>(a[k][c], b[k][ct][c], acc[ct][0]);
+                    }
+                }
+                if (i + k + D < n) load(i + k + D, k);
+            }
+        }
+    }
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+        if (DT == kF32) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {              // (an infinite sum's error is NaN)
+                const float sum = acc[ct][0][q] + acc[ct][1][q];
+                acc[ct][0][q] = __builtin_isfinite(sum) ? sum : acc[ct][0][q];
+            }
+        }
+        *reinterpret_cast<f32x4_t*>(red + ((size_t)wave * NCT + ct) * 256 + lane * 4) = acc[ct][0];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kOutPerThread; ++j) {
+        const int e = threadIdx.x + j * kPremixBlockThreads;
+        if (e >= NCT * 256) break;
+        const int ct = e >> 8, l = (e & 255) >> 2, row = r0 + (l >> 4) * 4 + (e & 3), tok = ct * 16 + (l & 15);
+        auto part = [&](int w) { return red[((size_t)w * NCT + ct) * 256 + (e & 255)]; };
+        static_assert(kPremixBlockWaves == 8, "");
+        const float y = ((part(0) + part(1)) + (part(2) + part(3))) + ((part(4) + part(5)) + (part(6) + part(7)));
+        if (tok < tb && row < p.H) {
+            const float u = premix_act(y, p.act) + h_res[j];
+            const size_t at = (size_t)(m0 + tok) * p.H + row;
+            if (DT == kF32) static_cast<float*>(p.out)[at] = u;
+            else static_cast<unsigned short*>(p.out)[at] = narrow16<DT>(u);
+        }
     }
 }
 

@@ -353,3 +353,21 @@ def test_few_batches_and_lists_fetched_in_one_trip(coral, M, k):
     sizes = [495 + 2 * n for n in range(7)]
     sizes[-1] += 3510 - sum(sizes)
     check_all(coral, cfg, sizes, (M,))
+
+
+@pytest.mark.parametrize("dtype,H,M", [("bf16", 8, 1), ("f16", 136, 2), ("bf16", 264, 15), ("f16", 1000, 16), ("bf16", 2568, 17), ("f16", 1160, 33),
+                                       ("bf16", 1032, 49), ("f16", 520, 65), ("bf16", 5120, 3), ("bf16", 6016, 1), ("f16", 6016, 2),
+                                       ("bf16", 7680, 1), ("f16", 8192, 3), ("bf16", 8192, 4), ("bf16", 3072, 8), ("bf16", 3584, 8), ("f16", 3584, 9),
+                                       ("f32", 4, 1), ("f32", 1532, 5), ("f32", 1536, 4), ("f32", 1540, 5), ("f32", 1796, 32),
+                                       ("f32", 1544, 40), ("f32", 1536, 64), ("f32", 1620, 130)])
+def test_premix_of_any_width(coral, dtype, H, M):
+    """The kernel for any width: the last 256-byte block and the last 16 features partly filled, fewer
+    blocks than waves, one to four token tiles and several times 64 tokens, either side of its rule."""
+    from coral_inputs import make_router_W1
+    from oracle import compare
+    cfg = HeadConfig(f"premix_any_{dtype}_{H}", dtype, H, 64, 2, 1, (M,), 4, 1500 + M, True)
+    W1, hidden = make_router_W1(cfg), make_hidden(cfg, M, 0)
+    print(f"case premix {dtype} H={H} M={M}", flush=True)
+    u = coral.coral_router_premix(coral.device_tensor(hidden, dtype), coral.device_tensor(W1, dtype), "silu")
+    raw = u.cpu().numpy() if dtype == "f32" else u.view(torch.int16).cpu().numpy().view(np.uint16)
+    assert compare.check_premix(hidden, W1, dtype, "silu", raw).tokens == M
