@@ -161,8 +161,8 @@ __device__ __forceinline__ int tile_lane_vec(int c, int sp) {
 // The 128-byte line of step pair sp of chunk c in the lane's row at byte offset `row` of
 // the weight matrix (offsets are 32-bit: the path takes matrices below 4 GiB).  GENERAL: `row` is
 // the row's start, and lanes past its end read its last vector (dropped in tile_step_pair);
-// otherwise the lane's place in a chunk is part of `row`.
-template <bool GENERAL, int SPLIT>
+// otherwise the lane's place in a chunk is part of `row`.  STREAM: non-temporal (see tile_streams).
+template <bool STREAM, bool GENERAL, int SPLIT>
 __device__ __forceinline__ uint4 tile_load_w(const TileParams& p, unsigned row, int c, int sp) {
     unsigned off;
     if (GENERAL) {
@@ -171,13 +171,14 @@ __device__ __forceinline__ uint4 tile_load_w(const TileParams& p, unsigned row, 
     } else {
         off = row + (unsigned)(c * kChunkVecs + sp * 8) * 16u;
     }
-    return load_stream(reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(p.lm_W) + off));
+    const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(p.lm_W) + off);
+    return STREAM ? load_stream(src) : load_vec(src);
 }
 
 // Step pair SP of a chunk: the two 32-column steps whose weight lines sit in ring slots
 // 4 SLOT .. 4 SLOT + 3.  A wave has 8 / SPLIT step pairs of a chunk, so the ring's four cover
 // SPLIT / 2 chunks and are refilled that far ahead.
-template <int DT, int NCT, bool REFILL, bool STORE, int SP, bool GENERAL, int SPLIT, int SLOT, int AHEAD>
+template <bool STREAM, int DT, int NCT, bool REFILL, bool STORE, int SP, bool GENERAL, int SPLIT, int SLOT, int AHEAD>
 __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4 (&a)[kRing],
                                                f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
                                                const unsigned (&wrow)[4],
@@ -199,8 +200,8 @@ __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4
         mfma_operands_from_lines(a[SLOT * 4 + 2 * t], a[SLOT * 4 + 2 * t + 1], lane, my_slice, op[t][0],
                                  op[t][1]);
         if (REFILL) {                                  // refill the two slots just consumed
-            a[SLOT * 4 + 2 * t] = tile_load_w<GENERAL, SPLIT>(p, wrow[2 * t], c + AHEAD, SP);
-            a[SLOT * 4 + 2 * t + 1] = tile_load_w<GENERAL, SPLIT>(p, wrow[2 * t + 1], c + AHEAD, SP);
+            a[SLOT * 4 + 2 * t] = tile_load_w<STREAM, GENERAL, SPLIT>(p, wrow[2 * t], c + AHEAD, SP);
+            a[SLOT * 4 + 2 * t + 1] = tile_load_w<STREAM, GENERAL, SPLIT>(p, wrow[2 * t + 1], c + AHEAD, SP);
         }
     }
     if (REFILL) keep_memory_order();
@@ -248,7 +249,7 @@ __device__ __forceinline__ void tile_step_pair(const TileParams& p, int c, uint4
     }
 }
 
-template <int DT, int NCT, bool REFILL, bool GENERAL>
+template <bool STREAM, int DT, int NCT, bool REFILL, bool GENERAL>
 __device__ __forceinline__ void tile_chunk(const TileParams& p, int c, uint4 (&a)[kRing],
                                            f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
                                            const unsigned (&wrow)[4],
@@ -266,12 +267,12 @@ __device__ __forceinline__ void tile_chunk(const TileParams& p, int c, uint4 (&a
         keep_memory_order();
     };
     if (REFILL && kFetchAt == 0) fetch();
-    tile_step_pair<DT, NCT, REFILL, false, 0, GENERAL, kTileSplit, 0, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
+    tile_step_pair<STREAM, DT, NCT, REFILL, false, 0, GENERAL, kTileSplit, 0, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
     if (REFILL && kFetchAt == 1) fetch();
-    tile_step_pair<DT, NCT, REFILL, false, 1, GENERAL, kTileSplit, 1, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
+    tile_step_pair<STREAM, DT, NCT, REFILL, false, 1, GENERAL, kTileSplit, 1, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
     if (REFILL && kFetchAt == 2) fetch();
-    tile_step_pair<DT, NCT, REFILL, false, 2, GENERAL, kTileSplit, 2, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
-    tile_step_pair<DT, NCT, REFILL, REFILL, 3, GENERAL, kTileSplit, 3, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
+    tile_step_pair<STREAM, DT, NCT, REFILL, false, 2, GENERAL, kTileSplit, 2, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
+    tile_step_pair<STREAM, DT, NCT, REFILL, REFILL, 3, GENERAL, kTileSplit, 3, 1>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, lane);
     __syncthreads();
 }
 
@@ -280,7 +281,7 @@ __device__ __forceinline__ void tile_chunk(const TileParams& p, int c, uint4 (&a
 // they would be younger than all of the next chunk's weight lines, and waiting for them would drain
 // the ring.  PH = c % 2.  `fetched` takes those of chunk c + 2 (REFILL: there is one), `held` are those
 // of chunk c + 1 (STORE).
-template <int DT, int NCT, bool REFILL, bool STORE, int PH>
+template <bool STREAM, int DT, int NCT, bool REFILL, bool STORE, int PH>
 __device__ __forceinline__ void tile_chunk_half(const TileParams& p, int c, uint4 (&a)[kRing],
                                                 f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
                                                 const unsigned (&wrow)[4], uint4* hbuf, const int* tokslot, int n_t,
@@ -292,14 +293,14 @@ __device__ __forceinline__ void tile_chunk_half(const TileParams& p, int c, uint
                                       __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
         keep_memory_order();
     }
-    tile_step_pair<DT, NCT, REFILL, false, 0, false, kTileSplitHalf, PH * 2, 2>(p, c, a, acc, low, wrow, hbuf, held, my_slice, lane);
-    tile_step_pair<DT, NCT, REFILL, STORE, 1, false, kTileSplitHalf, PH * 2 + 1, 2>(p, c, a, acc, low, wrow, hbuf, held, my_slice, lane);
+    tile_step_pair<STREAM, DT, NCT, REFILL, false, 0, false, kTileSplitHalf, PH * 2, 2>(p, c, a, acc, low, wrow, hbuf, held, my_slice, lane);
+    tile_step_pair<STREAM, DT, NCT, REFILL, STORE, 1, false, kTileSplitHalf, PH * 2 + 1, 2>(p, c, a, acc, low, wrow, hbuf, held, my_slice, lane);
     __syncthreads();
 }
 
 // The same with all eight waves on one row group (general form): one step pair of the chunk per
 // wave, from ring slot PH = c % 4.
-template <int DT, int NCT, int PH>
+template <bool STREAM, int DT, int NCT, int PH>
 __device__ __forceinline__ void tile_chunk_small(const TileParams& p, int c, uint4 (&a)[kRing],
                                                  f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
                                                  const unsigned (&wrow)[4],
@@ -314,7 +315,7 @@ __device__ __forceinline__ void tile_chunk_small(const TileParams& p, int c, uin
     }
     // (past the last chunk the refills read the row's last vector, which nothing uses: a form
     // without them beside this one costs more registers than there are)
-    tile_step_pair<DT, NCT, true, false, 0, true, kTileSplitSmall, PH, 4>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, threadIdx.x & (kWave - 1));
+    tile_step_pair<STREAM, DT, NCT, true, false, 0, true, kTileSplitSmall, PH, 4>(p, c, a, acc, low, wrow, hbuf, hst, my_slice, threadIdx.x & (kWave - 1));
     if (more) tile_store_hidden<NCT, true>(p.n_vec, hst, hbuf, c + 1, lane, wave);
     __syncthreads();
 }
@@ -322,7 +323,7 @@ __device__ __forceinline__ void tile_chunk_small(const TileParams& p, int c, uin
 // The K loop of one block.  Hidden chunk staging: slots wave, wave + 8, ... below 16 NCT;
 // lane = vector inside the chunk; slots past the group's tokens repeat its last token
 // (their columns of the tiles are never read back).
-template <int DT, int NCT, bool GENERAL, int SPLIT>
+template <bool STREAM, int DT, int NCT, bool GENERAL, int SPLIT>
 __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRing], f32x4_t (&acc)[2][4],
                                             const unsigned (&wrow)[4], uint4* hbuf,
                                             const int* tokslot, uint4* my_slice, int n_t) {
@@ -345,27 +346,27 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
         const int n = p.n_chunks;                      // at least two
         int c = 0;
         for (; c + 3 < n; c += 2) {                    // uniform
-            tile_chunk_half<DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
-            tile_chunk_half<DT, NCT, true, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
+            tile_chunk_half<STREAM, DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
+            tile_chunk_half<STREAM, DT, NCT, true, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
         }
         if (c + 2 < n) {                               // three left
-            tile_chunk_half<DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
-            tile_chunk_half<DT, NCT, false, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
-            tile_chunk_half<DT, NCT, false, false, 0>(p, c + 2, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
+            tile_chunk_half<STREAM, DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
+            tile_chunk_half<STREAM, DT, NCT, false, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
+            tile_chunk_half<STREAM, DT, NCT, false, false, 0>(p, c + 2, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
         } else {
-            tile_chunk_half<DT, NCT, false, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
-            tile_chunk_half<DT, NCT, false, false, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
+            tile_chunk_half<STREAM, DT, NCT, false, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
+            tile_chunk_half<STREAM, DT, NCT, false, false, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
         }
     } else if constexpr (SPLIT == kTileSplit) {
         for (int c = 0; c + 1 < p.n_chunks; ++c)
-            tile_chunk<DT, NCT, true, GENERAL>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
-        tile_chunk<DT, NCT, false, GENERAL>(p, p.n_chunks - 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            tile_chunk<STREAM, DT, NCT, true, GENERAL>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+        tile_chunk<STREAM, DT, NCT, false, GENERAL>(p, p.n_chunks - 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
     } else {
         for (int c = 0; c < p.n_chunks; c += 4) {      // uniform
-            tile_chunk_small<DT, NCT, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
-            if (c + 1 < p.n_chunks) tile_chunk_small<DT, NCT, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
-            if (c + 2 < p.n_chunks) tile_chunk_small<DT, NCT, 2>(p, c + 2, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
-            if (c + 3 < p.n_chunks) tile_chunk_small<DT, NCT, 3>(p, c + 3, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            tile_chunk_small<STREAM, DT, NCT, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            if (c + 1 < p.n_chunks) tile_chunk_small<STREAM, DT, NCT, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            if (c + 2 < p.n_chunks) tile_chunk_small<STREAM, DT, NCT, 2>(p, c + 2, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            if (c + 3 < p.n_chunks) tile_chunk_small<STREAM, DT, NCT, 3>(p, c + 3, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
         }
     }
     if (GENERAL) {
@@ -385,7 +386,7 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
 // GENERAL: the general path's form: any storage type, rows of any number of 16-byte vectors (the
 // last chunk partly filled, loads and operands past a row's end guarded) and sums as exact as the
 // staged kernels'.  Otherwise 16-bit storage and whole chunks.
-template <int DT, bool GENERAL, int SPLIT>
+template <bool STREAM, int DT, bool GENERAL, int SPLIT>
 __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     static_assert(SPLIT == kTileSplit || GENERAL, "blocks of 32 rows exist in the general form");
     constexpr int ROWS = tile_rows(SPLIT);
@@ -561,7 +562,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
                 pair = sp & 1;
             }
 #pragma unroll
-            for (int o = 0; o < 4; ++o) a[sp * 4 + o] = tile_load_w<GENERAL, SPLIT>(p, wrow[o], c, pair);
+            for (int o = 0; o < 4; ++o) a[sp * 4 + o] = tile_load_w<STREAM, GENERAL, SPLIT>(p, wrow[o], c, pair);
         }
     };
 
@@ -599,14 +600,14 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
             for (int ct = 0; ct < 4; ++ct) acc[t][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
         if constexpr (GENERAL) {
-            if (n_ct == 1) tile_k_loop<DT, 1, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);   // block-uniform
-            else tile_k_loop<DT, 2, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
+            if (n_ct == 1) tile_k_loop<STREAM, DT, 1, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);   // block-uniform
+            else tile_k_loop<STREAM, DT, 2, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
         } else {
             auto run = [&](auto tiles) {
                 constexpr int NCT = decltype(tiles)::value;
                 if constexpr (NCT <= 2)
-                    if (now.half >= 0) return tile_k_loop<DT, NCT, GENERAL, kTileSplitHalf>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
-                tile_k_loop<DT, NCT, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
+                    if (now.half >= 0) return tile_k_loop<STREAM, DT, NCT, GENERAL, kTileSplitHalf>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
+                tile_k_loop<STREAM, DT, NCT, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
             };
             switch (n_ct) {                                // block-uniform
                 case 1: run(std::integral_constant<int, 1>()); break;
