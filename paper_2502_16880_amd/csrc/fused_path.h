@@ -973,6 +973,10 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             else rank_lists(std::integral_constant<int, 16>());
         }
     };
+    // Where two waves share a task (log-probability mode): wave i < 8 and this one.  The four SIMDs
+    // have every fourth wave each, so the first waves spread over them, and so do the second ones.
+    auto second_wave = [](int i) { return kFusedWaves / 2 + ((i + 2) & (kFusedWaves / 2 - 1)); };
+    auto shared_task = [](int w) { return w < kFusedWaves / 2 ? w : (w - 2) & (kFusedWaves / 2 - 1); };
     auto publish_all = [&]() {                         // logit mode, every wave of the workgroup
         if (out.cap && out.cap <= 2 * kWave && M <= kFusedWaves / 2) {
             // Fewer tokens than waves and at most two candidates per lane: S waves share a token,
@@ -1024,10 +1028,10 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         // issues a dependent instruction every eight to ten cycles: one after the other 3.7 us
         // from the last row to the list in memory at the Llama3 shape).
         unsigned long long rem = uni64(umask[u]);
-        const int split = 2 * __popcll(rem) <= kFusedWaves ? 1 : 0;
+        const bool split = 2 * __popcll(rem) <= kFusedWaves;
         for (int idx = 0; rem; ++idx, rem &= rem - 1ull) {     // block-uniform
-            const bool lists = ((idx << split) & (kFusedWaves - 1)) == wave;
-            const bool pieces = (((idx << split) + split) & (kFusedWaves - 1)) == wave;
+            const bool lists = (idx & (kFusedWaves - 1)) == wave;
+            const bool pieces = split ? second_wave(idx) == wave : lists;
             if (!lists && !pieces) continue;           // wave-uniform
             const int t = __ffsll(rem) - 1;
             // the pieces of this workgroup's batches for token slot idx, summed in batch order;
@@ -1073,7 +1077,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): the published lists are out
         __syncthreads();
         // Eq. 8: log p(x) = log p_router(n) + z[x] - lse_n.  finish(t, gu) is the work for token t and
-        // its selected group ugroup[gu], of one wave or shared by a wave and the next one (lists: this
+        // its selected group ugroup[gu], of one wave or shared by two (lists: this
         // wave's part is to merge the group's published lists by logit; shifts: to combine the
         // log-sum-exp pieces of the group's workgroups and take the router's log-softmax over all
         // G scores).  Leaves the k best, offset added, in the lanes (lane r = rank r) of the wave
@@ -1123,7 +1127,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             if (split) {                               // block-uniform
                 if (on && shifts && lane == 0) ms->out[0].v = shift;
                 __syncthreads();
-                if (on && lists) shift = ms[1].out[0].v;
+                if (on && lists) shift = (ms - wave + second_wave(wave))->out[0].v;
             }
             Cand c = sentinel();
             if (on && lists && lane < k) c = ms->out[lane];
@@ -1197,8 +1201,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             const int count = uni(flags[0]);
             Cand* glists = reinterpret_cast<Cand*>(lds + lay.o_keys);   // [M * g, k], <= 16 x 64 entries
             {
-                const int pair = wave >> 1;            // two waves each
-                const bool on = pair < M * p.g, lists = !(wave & 1);
+                const int pair = shared_task(wave);    // two waves each
+                const bool on = pair < M * p.g, lists = wave < kFusedWaves / 2;
                 const int n = uni(sel_lds[on ? pair : 0]);
                 const int gu = __ffsll(__ballot(lane < count && ugroup[lane] == n)) - 1;
                 const Cand c = finish(on, lists, !lists, true, on ? pair / p.g : 0, gu);
@@ -1236,7 +1240,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         while (rem) {                                  // block-uniform: 8 tokens or up to 16 at a time
             const int todo = __popcll(rem);
             const bool split = 2 * todo <= kFusedWaves;
-            const int mine = split ? wave >> 1 : wave;
+            const int mine = split ? shared_task(wave) : wave;
             const bool on = mine < todo;
             unsigned long long at = rem;               // this wave's token: the mine-th of those left
             for (int i = 0; i < kFusedWaves && i < todo; ++i) {
@@ -1245,7 +1249,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             }
             if (split) rem = 0ull;
             const int t = __ffsll(at) - 1;
-            const bool lists = !split || !(wave & 1), shifts = !split || (wave & 1);
+            const bool lists = !split || wave < kFusedWaves / 2, shifts = !split || wave >= kFusedWaves / 2;
             const int i = __ffsll(__ballot(lane < p.g && sel_lds[t * p.g + lane] == n)) - 1;
             const Cand c = finish(on, lists, shifts, split, t, u);
             if (on && lists && lane < k) publish_cand(p.glist + ((size_t)t * p.g + i) * k + lane, c.v, c.id);
