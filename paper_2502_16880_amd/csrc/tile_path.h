@@ -74,7 +74,7 @@ struct TileParams {
 };
 
 struct TileLds {
-    int o_hbuf, o_tokslot, o_scratch, o_ustart, o_uend, o_uprefix, o_umask, o_flags, total;
+    int o_hbuf, o_scratch, o_ustart, o_uend, o_uprefix, o_umask, o_flags, total;
 };
 
 __host__ __device__ inline TileLds tile_lds_layout(int u_max) {
@@ -86,14 +86,15 @@ __host__ __device__ inline TileLds tile_lds_layout(int u_max) {
         return at;
     };
     L.o_hbuf = take((size_t)2 * kHbBufVecs * sizeof(uint4));
-    L.o_tokslot = take(64 * sizeof(int));
     L.o_scratch = take((size_t)kTileWaves * kLinePairSlots * sizeof(uint4));
     L.o_ustart = take((size_t)u_max * sizeof(int));
     L.o_uend = take((size_t)u_max * sizeof(int));
     L.o_uprefix = take((size_t)(u_max + 1) * sizeof(int));
     L.o_umask = take((size_t)u_max * sizeof(unsigned long long));
     L.o_flags = take(16);
-    L.total = off;
+    // (256 bytes more than are used: which shapes fit, and with them the route and the size checks of
+    // calls, stays as it was when the kernel kept its tokens here)
+    L.total = off + 256;
     return L;
 }
 
@@ -109,26 +110,55 @@ struct TileStage {                                     // staging registers, 2 N
     uint4 r0, r1, r2, r3, r4, r5, r6, r7;
 };
 
+// The tokens of a wave's staging slots wave, wave + 8, ... (wave-uniform), slots past the unit's tokens
+// repeating its last one.
+struct TileTokens {
+    int t0, t1, t2, t3, t4, t5, t6, t7;
+};
+// ... of a unit of n_t tokens, those of the mask from the first-th on.
+__device__ __forceinline__ TileTokens tile_tokens(unsigned long long mask, int first, int n_t, int lane, int wave) {
+    const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u)) - first;
+    const int mine = (mask >> lane) & 1ull ? below : -1;   // this lane's token's slot
+    auto tok = [&](int i) {
+        const int s = wave + i * kTileWaves;
+        return __ffsll(__ballot(mine == (s < n_t ? s : n_t - 1))) - 1;
+    };
+    return {tok(0), tok(1), tok(2), tok(3), tok(4), tok(5), tok(6), tok(7)};
+}
+
 template <int NCT, bool GENERAL>
-__device__ __forceinline__ void tile_fetch_hidden(const TileParams& p, const int* tokslot, int n_t,
-                                                  TileStage& hst, int c, int lane, int wave) {
+__device__ __forceinline__ void tile_fetch_hidden(const TileParams& p, const TileTokens& tok, TileStage& hst, int c, int lane) {
     constexpr int kN = 2 * NCT;
     // (past the row's end, in the last chunk: the row's last vector, stored as zero)
     const int last = p.n_vec - 1 - c * kChunkVecs;
     const uint4* src = p.hidden + c * kChunkVecs + (GENERAL && lane > last ? last : lane);
-    // token of slot wave + 8 i (wave-uniform); slots past the group's tokens repeat its last
-    auto tok = [&](int i) {
-        const int s = wave + i * kTileWaves;
-        return (size_t)uni(tokslot[s < n_t ? s : n_t - 1]);
-    };
-    if (kN > 0) hst.r0 = load_vec(src + tok(0) * p.n_vec);
-    if (kN > 1) hst.r1 = load_vec(src + tok(1) * p.n_vec);
-    if (kN > 2) hst.r2 = load_vec(src + tok(2) * p.n_vec);
-    if (kN > 3) hst.r3 = load_vec(src + tok(3) * p.n_vec);
-    if (kN > 4) hst.r4 = load_vec(src + tok(4) * p.n_vec);
-    if (kN > 5) hst.r5 = load_vec(src + tok(5) * p.n_vec);
-    if (kN > 6) hst.r6 = load_vec(src + tok(6) * p.n_vec);
-    if (kN > 7) hst.r7 = load_vec(src + tok(7) * p.n_vec);
+    int n_vec = p.n_vec;
+    asm volatile("" : "+s"(n_vec));                    // (the rows' offsets are not kept from chunk to chunk)
+    auto load = [&](int t) { return load_vec(src + (size_t)t * n_vec); };
+    if (kN > 0) hst.r0 = load(tok.t0);
+    if (kN > 1) hst.r1 = load(tok.t1);
+    if (kN > 2) hst.r2 = load(tok.t2);
+    if (kN > 3) hst.r3 = load(tok.t3);
+    if (kN > 4) hst.r4 = load(tok.t4);
+    if (kN > 5) hst.r5 = load(tok.t5);
+    if (kN > 6) hst.r6 = load(tok.t6);
+    if (kN > 7) hst.r7 = load(tok.t7);
+}
+// The first chunk's hidden vectors of a unit with up to two token tiles (with more there are no registers
+// for them beside the parked tiles), n2 = 2 or 4 staging slots per wave, in r0 ... r3; of a half with one
+// tile the second chunk's behind them.
+template <bool GENERAL>
+__device__ __forceinline__ void tile_fetch_first(const TileParams& p, const TileTokens& tok, TileStage& hst, int n2, bool half, int lane) {
+    if (n2 > 4) return;                                // (all conditions are uniform)
+    const uint4* src = p.hidden + (GENERAL && lane > p.n_vec - 1 ? p.n_vec - 1 : lane);
+    auto load = [&](int t, int c) { return load_vec(src + c * kChunkVecs + (size_t)t * p.n_vec); };
+    hst.r0 = load(tok.t0, 0);
+    hst.r1 = load(tok.t1, 0);
+    if (n2 == 4 || half) {
+        hst.r2 = load(n2 == 4 ? tok.t2 : tok.t0, n2 == 4 ? 0 : 1);
+        hst.r3 = load(n2 == 4 ? tok.t3 : tok.t1, n2 == 4 ? 0 : 1);
+    }
+    keep_memory_order();
 }
 template <int NCT, bool GENERAL>
 __device__ __forceinline__ void tile_store_hidden(int n_vec, const TileStage& hst, uint4* hbuf, int c, int lane,
@@ -253,17 +283,17 @@ template <bool STREAM, int DT, int NCT, bool REFILL, bool GENERAL>
 __device__ __forceinline__ void tile_chunk(const TileParams& p, int c, uint4 (&a)[kRing],
                                            f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
                                            const unsigned (&wrow)[4],
-                                           uint4* hbuf, const int* tokslot, int n_t, uint4* my_slice) {
+                                           uint4* hbuf, const TileTokens& tok, uint4* my_slice) {
     TileStage hst;
-    const int lane = threadIdx.x & (kWave - 1);
+    int lane = threadIdx.x & (kWave - 1);
+    asm volatile("" : "+v"(lane));                     // (what is derived from it is not kept from chunk to chunk)
     // (the scheduling barriers keep the compiler from sinking the loads to where their
     // registers are first needed, which would undo the ordering)
     // (general form with two token tiles: after the first step pair, fp32 after the second, there
     // are no registers for them before)
     constexpr int kFetchAt = !GENERAL || NCT == 1 ? 0 : DT == kF32 ? 2 : 1;
     auto fetch = [&]() {
-        tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, hst, c + 1, lane,
-                                        __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+        tile_fetch_hidden<NCT, GENERAL>(p, tok, hst, c + 1, lane);
         keep_memory_order();
     };
     if (REFILL && kFetchAt == 0) fetch();
@@ -284,13 +314,12 @@ __device__ __forceinline__ void tile_chunk(const TileParams& p, int c, uint4 (&a
 template <bool STREAM, int DT, int NCT, bool REFILL, bool STORE, int PH>
 __device__ __forceinline__ void tile_chunk_half(const TileParams& p, int c, uint4 (&a)[kRing],
                                                 f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
-                                                const unsigned (&wrow)[4], uint4* hbuf, const int* tokslot, int n_t,
+                                                const unsigned (&wrow)[4], uint4* hbuf, const TileTokens& tok,
                                                 uint4* my_slice, TileStage& fetched, TileStage& held) {
     int lane = threadIdx.x & (kWave - 1);
     asm volatile("" : "+v"(lane));
     if (REFILL) {
-        tile_fetch_hidden<NCT, false>(p, tokslot, n_t, fetched, c + 2, lane,
-                                      __builtin_amdgcn_readfirstlane(threadIdx.x / kWave));
+        tile_fetch_hidden<NCT, false>(p, tok, fetched, c + 2, lane);
         keep_memory_order();
     }
     tile_step_pair<STREAM, DT, NCT, REFILL, false, 0, false, kTileSplitHalf, PH * 2, 2>(p, c, a, acc, low, wrow, hbuf, held, my_slice, lane);
@@ -304,13 +333,13 @@ template <bool STREAM, int DT, int NCT, int PH>
 __device__ __forceinline__ void tile_chunk_small(const TileParams& p, int c, uint4 (&a)[kRing],
                                                  f32x4_t (&acc)[2][4], f32x4_t (&low)[2][4],
                                                  const unsigned (&wrow)[4],
-                                                 uint4* hbuf, const int* tokslot, int n_t, uint4* my_slice) {
+                                                 uint4* hbuf, const TileTokens& tok, uint4* my_slice) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const bool more = c + 1 < p.n_chunks;              // uniform
     TileStage hst;
     if (more) {
-        tile_fetch_hidden<NCT, true>(p, tokslot, n_t, hst, c + 1, lane, wave);
+        tile_fetch_hidden<NCT, true>(p, tok, hst, c + 1, lane);
         keep_memory_order();
     }
     // (past the last chunk the refills read the row's last vector, which nothing uses: a form
@@ -326,16 +355,21 @@ __device__ __forceinline__ void tile_chunk_small(const TileParams& p, int c, uin
 template <bool STREAM, int DT, int NCT, bool GENERAL, int SPLIT>
 __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRing], f32x4_t (&acc)[2][4],
                                             const unsigned (&wrow)[4], uint4* hbuf,
-                                            const int* tokslot, uint4* my_slice, int n_t) {
-    const int lane = threadIdx.x & (kWave - 1);
+                                            const TileTokens& tok, const TileStage& first, uint4* my_slice) {
+    int lane = threadIdx.x & (kWave - 1);
+    asm volatile("" : "+v"(lane));
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    TileStage even, odd;                               // (blocks of 64 rows) hidden vectors of the next even and odd chunk
-    tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, even, 0, lane, wave);
-    if constexpr (SPLIT == kTileSplitHalf) {
-        tile_fetch_hidden<NCT, GENERAL>(p, tokslot, n_t, odd, 1, lane, wave);
+    TileStage even, odd;                               // (halves) hidden vectors of the next even and odd chunk
+    if (SPLIT == kTileSplitHalf && NCT == 1) {         // (see tile_fetch_first)
+        odd.r0 = first.r2;
+        odd.r1 = first.r3;
+    }
+    if (SPLIT == kTileSplitHalf && NCT == 2) {
+        tile_fetch_hidden<NCT, GENERAL>(p, tok, odd, 1, lane);
         keep_memory_order();
     }
-    tile_store_hidden<NCT, GENERAL>(p.n_vec, even, hbuf, 0, lane, wave);
+    if (NCT > 2) tile_fetch_hidden<NCT, GENERAL>(p, tok, even, 0, lane);
+    tile_store_hidden<NCT, GENERAL>(p.n_vec, NCT > 2 ? even : first, hbuf, 0, lane, wave);
     __syncthreads();
     f32x4_t low[2][4];                                 // (general form) what the running sums have rounded off
 #pragma unroll
@@ -346,27 +380,27 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
         const int n = p.n_chunks;                      // at least two
         int c = 0;
         for (; c + 3 < n; c += 2) {                    // uniform
-            tile_chunk_half<STREAM, DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
-            tile_chunk_half<STREAM, DT, NCT, true, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
+            tile_chunk_half<STREAM, DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tok, my_slice, even, odd);
+            tile_chunk_half<STREAM, DT, NCT, true, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tok, my_slice, odd, even);
         }
         if (c + 2 < n) {                               // three left
-            tile_chunk_half<STREAM, DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
-            tile_chunk_half<STREAM, DT, NCT, false, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
-            tile_chunk_half<STREAM, DT, NCT, false, false, 0>(p, c + 2, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
+            tile_chunk_half<STREAM, DT, NCT, true, true, 0>(p, c, a, acc, low, wrow, hbuf, tok, my_slice, even, odd);
+            tile_chunk_half<STREAM, DT, NCT, false, true, 1>(p, c + 1, a, acc, low, wrow, hbuf, tok, my_slice, odd, even);
+            tile_chunk_half<STREAM, DT, NCT, false, false, 0>(p, c + 2, a, acc, low, wrow, hbuf, tok, my_slice, even, odd);
         } else {
-            tile_chunk_half<STREAM, DT, NCT, false, true, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, even, odd);
-            tile_chunk_half<STREAM, DT, NCT, false, false, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice, odd, even);
+            tile_chunk_half<STREAM, DT, NCT, false, true, 0>(p, c, a, acc, low, wrow, hbuf, tok, my_slice, even, odd);
+            tile_chunk_half<STREAM, DT, NCT, false, false, 1>(p, c + 1, a, acc, low, wrow, hbuf, tok, my_slice, odd, even);
         }
     } else if constexpr (SPLIT == kTileSplit) {
         for (int c = 0; c + 1 < p.n_chunks; ++c)
-            tile_chunk<STREAM, DT, NCT, true, GENERAL>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
-        tile_chunk<STREAM, DT, NCT, false, GENERAL>(p, p.n_chunks - 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            tile_chunk<STREAM, DT, NCT, true, GENERAL>(p, c, a, acc, low, wrow, hbuf, tok, my_slice);
+        tile_chunk<STREAM, DT, NCT, false, GENERAL>(p, p.n_chunks - 1, a, acc, low, wrow, hbuf, tok, my_slice);
     } else {
         for (int c = 0; c < p.n_chunks; c += 4) {      // uniform
-            tile_chunk_small<STREAM, DT, NCT, 0>(p, c, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
-            if (c + 1 < p.n_chunks) tile_chunk_small<STREAM, DT, NCT, 1>(p, c + 1, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
-            if (c + 2 < p.n_chunks) tile_chunk_small<STREAM, DT, NCT, 2>(p, c + 2, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
-            if (c + 3 < p.n_chunks) tile_chunk_small<STREAM, DT, NCT, 3>(p, c + 3, a, acc, low, wrow, hbuf, tokslot, n_t, my_slice);
+            tile_chunk_small<STREAM, DT, NCT, 0>(p, c, a, acc, low, wrow, hbuf, tok, my_slice);
+            if (c + 1 < p.n_chunks) tile_chunk_small<STREAM, DT, NCT, 1>(p, c + 1, a, acc, low, wrow, hbuf, tok, my_slice);
+            if (c + 2 < p.n_chunks) tile_chunk_small<STREAM, DT, NCT, 2>(p, c + 2, a, acc, low, wrow, hbuf, tok, my_slice);
+            if (c + 3 < p.n_chunks) tile_chunk_small<STREAM, DT, NCT, 3>(p, c + 3, a, acc, low, wrow, hbuf, tok, my_slice);
         }
     }
     if (GENERAL) {
@@ -395,7 +429,6 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     char* lds = reinterpret_cast<char*>(smem);
     const TileLds lay = tile_lds_layout(p.u_max);
     uint4* hbuf = reinterpret_cast<uint4*>(lds + lay.o_hbuf);
-    int* tokslot = reinterpret_cast<int*>(lds + lay.o_tokslot);
     int* ustart = reinterpret_cast<int*>(lds + lay.o_ustart);
     int* uend = reinterpret_cast<int*>(lds + lay.o_uend);
     int* uprefix = reinterpret_cast<int*>(lds + lay.o_uprefix);
@@ -542,18 +575,38 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     // line of step pair sp of the first chunk, or (halves) of pair sp % 2 of chunk sp / 2, or (all
     // waves on one row group) of the one step pair of chunk sp (past the last chunk: clamped to the
     // row's end, not used).
+    // The hidden vectors of the first chunk (halves: two) are requested before them: behind them they
+    // would arrive after the last line, and the K loop's first refills with them.
     uint4 a[kRing];
     unsigned wrow[4];
-    auto start_unit = [&](const Unit& x, int lane) {
-        const int split = HALVES && x.half >= 0 ? kTileSplitHalf : SPLIT;      // uniform
+    TileTokens tok;
+    TileStage first;
+    // General form: the running sums' rounding errors take the registers of two token tiles, so a
+    // block serves 32 tokens at a time and comes round again for the next 32.
+    constexpr bool kPasses = GENERAL;
+    constexpr int kPassTokens = kPasses ? 32 : kMaxM;
+    // tokens of a unit's pass from slot s0 on
+    auto pass_tokens = [&](unsigned long long bm, int s0) {
+        const int left = __popcll(bm) - (kPasses ? s0 : 0);
+        return kPasses && left > kPassTokens ? kPassTokens : left;
+    };
+    auto start_unit = [&](const Unit& x, int s0, int lane) {
+        const bool half = HALVES && x.half >= 0;       // uniform
+        const int split = half ? kTileSplitHalf : SPLIT;
         const int rg = wave / split, kq = wave % split;
+        int rid[4];
 #pragma unroll
         for (int o = 0; o < 4; ++o) {
             int idx = x.first + rg * 32 + o * 8 + line_load_row(lane);
             if (idx >= x.end) idx = x.end - 1;
-            const int rid = dense ? idx : p.rows[idx];
-            wrow[o] = ((unsigned)rid * (unsigned)p.n_vec + (GENERAL ? 0 : kq * (kChunkVecs / split) + line_load_chunk(lane))) * 16u;
+            rid[o] = dense ? idx : p.rows[idx];
         }
+        const int n_t = pass_tokens(x.bm, s0);
+        tok = tile_tokens(x.bm, s0, n_t, lane, wave);
+        tile_fetch_first<GENERAL>(p, tok, first, 2 * ((n_t + 15) >> 4), half, lane);
+#pragma unroll
+        for (int o = 0; o < 4; ++o)
+            wrow[o] = ((unsigned)rid[o] * (unsigned)p.n_vec + (GENERAL ? 0 : kq * (kChunkVecs / split) + line_load_chunk(lane))) * 16u;
 #pragma unroll
         for (int sp = 0; sp < 4; ++sp) {
             int c = SPLIT == kTileSplit ? 0 : sp, pair = SPLIT == kTileSplit ? sp : 0;
@@ -570,12 +623,8 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     Unit now = {0, -1, 0, 0, 0ull};
     if (at < total_units) {
         now = locate(at);
-        start_unit(now, lane);
+        start_unit(now, 0, lane);
     }
-    // General form: the running sums' rounding errors take the registers of two token tiles, so a
-    // block serves 32 tokens at a time and comes round again for the next 32.
-    constexpr bool kPasses = GENERAL;
-    constexpr int kPassTokens = kPasses ? 32 : kMaxM;
     int s0 = 0;                                        // first token slot of this pass
     while (at < total_units) {                         // block-uniform
         int ln = lane;                                 // (what is derived from it is not kept from block to block:
@@ -584,14 +633,8 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         const bool last_pass = !kPasses || s0 + kPassTokens >= __popcll(bm);
         if (threadIdx.x == 0 && last_pass)             // the draw returns long before the K loop ends
             drawn = __hip_atomic_fetch_add(p.next_block, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int n_t = kPasses ? min(__popcll(bm) - s0, kPassTokens) : __popcll(bm);
+        const int n_t = pass_tokens(bm, s0);
         const int n_ct = (n_t + 15) >> 4;
-        if (wave == 0) {                               // token of every slot
-            const bool on = (bm >> ln) & 1ull;
-            const int slot = __popcll(bm & ((1ull << ln) - 1ull)) - (kPasses ? s0 : 0);
-            if (on && (!kPasses || slot >= 0)) tokslot[slot] = ln;   // (slots past this pass's are not read)
-        }
-        __syncthreads();
 
         f32x4_t acc[2][4];
 #pragma unroll
@@ -600,14 +643,14 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
             for (int ct = 0; ct < 4; ++ct) acc[t][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
         if constexpr (GENERAL) {
-            if (n_ct == 1) tile_k_loop<STREAM, DT, 1, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);   // block-uniform
-            else tile_k_loop<STREAM, DT, 2, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
+            if (n_ct == 1) tile_k_loop<STREAM, DT, 1, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tok, first, my_slice);   // block-uniform
+            else tile_k_loop<STREAM, DT, 2, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tok, first, my_slice);
         } else {
             auto run = [&](auto tiles) {
                 constexpr int NCT = decltype(tiles)::value;
                 if constexpr (NCT <= 2)
-                    if (now.half >= 0) return tile_k_loop<STREAM, DT, NCT, GENERAL, kTileSplitHalf>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
-                tile_k_loop<STREAM, DT, NCT, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tokslot, my_slice, n_t);
+                    if (now.half >= 0) return tile_k_loop<STREAM, DT, NCT, GENERAL, kTileSplitHalf>(p, a, acc, wrow, hbuf, tok, first, my_slice);
+                tile_k_loop<STREAM, DT, NCT, GENERAL, SPLIT>(p, a, acc, wrow, hbuf, tok, first, my_slice);
             };
             switch (n_ct) {                                // block-uniform
                 case 1: run(std::integral_constant<int, 1>()); break;
@@ -625,7 +668,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         Unit next = now;
         if (next_at < total_units) {
             if (last_pass) next = locate(next_at);
-            start_unit(next, ln);
+            start_unit(next, last_pass ? 0 : s0 + kPassTokens, ln);
         }
 
         // half sums -> LDS (over the staging buffers, free after the last barrier).  A
