@@ -550,9 +550,16 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
                        !collect_cap(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp,
                                     fused_gate_mode(dense, M, G, g, k, jp, dt), dense ? V : (V + G - 1) / G,
                                     kMaxWorkgroups, &single);
+    // (Dense heads of 8192 rows and more from 16 tokens on, fp32 24, in any case: every row is dotted with
+    // every token, which the vector units do at their own rate, not the memory's.  In the general form,
+    // whose sums are as exact as theirs: 3.4e-8 against 4.4e-8 off.  us, single launch against tiles: bf16
+    // H = 1024, V = 38654, 26 tokens 54, 28; H = 2560, V = 14060, 16 tokens 33, 24; f16 H = 872, V = 141882,
+    // 18 tokens 95, 83; over 20 heads 1.5 times as fast, 1.1 at least; 13 and 12 tokens 55, 52, 29, 31; fp32
+    // H = 352, V = 21065, 30 tokens 34, 28, 16 tokens 19, 20.  Fewer rows were not measured.)
+    const bool many = dense && fused_ok && V >= 8192 && M >= (is_16bit(dt) ? 16 : 24);
     if (((dense && dense_prefers_tiles(M, V)) || lists) && tiles_ok)
         pl.path = 2;
-    else if (lists && tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds))
+    else if ((lists || many) && tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds))
         pl.path = 0;
     else if (fused_ok)
         pl.path = 1;
@@ -650,7 +657,7 @@ bool tile_streams(bool dense, bool general, bool small, int M, int V, int G, int
     const double groups = dense ? 1.0 : expected_groups(M, G, g) * (biased ? 0.5 : 1.0);
     const double rows = dense ? V : groups * V / G;
     if (n_vec % 8 != 0) return false;
-    if (small) return true;
+    if (small || (dense && !general)) return true;     // (consecutive rows, H = 3584, 10 K of them, 51 tokens 42.1, 43.7)
     if (general && (dense ? M : M * g / groups) > 32.0) return false;
     return rows * n_vec * 16.0 > 128e6;
 }

@@ -364,3 +364,12 @@ def test_routes_on_both_sides_of_the_dispatch_rules():
     assert path(True, 15, 4096, 60_000, 0, 0, 10, BF16) == 1 and path(True, 16, 4096, 60_000, 0, 0, 10, BF16) == 2
     assert path(False, 31, 256, 1_000_000, 4, 2, 10, BF16) == 1 and path(False, 64, 512, 128_256, 4, 2, 10, BF16) == 2
     assert path(False, 62, 232, 104_160, 20, 7, 10, F32) == 0
+
+
+def test_dense_heads_with_many_tokens_take_the_tile_kernels():
+    """Either side of the rule: tokens, rows, storage type."""
+    BF16, F32 = coral.CORAL_BF16, coral.CORAL_F32
+    path = coral.coral_lmhead_path
+    assert path(True, 15, 1024, 38_654, 0, 0, 10, BF16) == 1 and path(True, 16, 1024, 38_654, 0, 0, 10, BF16) in (0, 2)
+    assert path(True, 16, 1000, 9_000, 0, 0, 1, BF16) == 0 and path(True, 16, 1000, 8_191, 0, 0, 1, BF16) == 1
+    assert path(True, 23, 512, 9_000, 0, 0, 1, F32) == 1 and path(True, 24, 512, 9_000, 0, 0, 1, F32) == 0
