@@ -530,11 +530,12 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     const unsigned long long all_tokens = M >= 64 ? ~0ull : ((1ull << M) - 1ull);
     // Where the last round of blocks would occupy no more than half of the workgroups, its blocks are
     // handed out in halves of 64 rows (four waves on a row group): one workgroup alone reads a block
-    // at 50 GB/s, and 32 blocks in a third round held up the wide tree's step by 20 us (136.6 us a call,
-    // 126.5 with halves, by how many blocks are left over); heads with fewer blocks than that in all likewise.  Not those of groups with
-    // more than 32 tokens (behind flags[2] there is none): the hidden vectors of the next two chunks
-    // do not fit the registers beside three or four token tiles, and a form that waits for them a chunk
-    // ahead made the whole kernel slower (wide tree 126 -> 134 us, by the registers it takes).
+    // at 50 GB/s, and 32 blocks in a third round held up the wide tree's step by 20 us (136.6 us a
+    // call, 126.5 with halves; 2.5 % on average over inputs); heads with fewer blocks than that in all
+    // likewise (ragged head, 24 tokens 42.2, 37.5).  Not those of groups with more than 32 tokens
+    // (behind flags[2] there is none): the hidden vectors of the next two chunks do not fit the
+    // registers beside three or four token tiles, and a form that waits for them a chunk ahead made
+    // the whole kernel slower (wide tree 126 -> 134 us, by the registers it takes).
     const int P = gridDim.x;
     const int over = total_blocks % P;
     const int split_from = HALVES && p.n_chunks > 1 && 2 * over <= P ? max(total_blocks - over, uni(flags[2])) : total_blocks;
