@@ -670,7 +670,7 @@ coral_status launch_tiles(bool dense, const PathPlan& plan, const void* hidden, 
                           int G, int k, coral_dtype dt, int32_t* topk_ids,
                           float* topk_out, char* ws, const Layout& L, hipStream_t stream,
                           void* ev_before, void* ev_after, const int32_t* sel = nullptr, int g = 0,
-                          bool logprob = false, bool biased = false) {
+                          bool logprob = false, bool biased = false, bool halves = true) {
     int P = compute_units();
     if (P < 1) return CORAL_ERR_HIP;
     if (P > kMaxWorkgroups) P = kMaxWorkgroups;
@@ -686,6 +686,7 @@ coral_status launch_tiles(bool dense, const PathPlan& plan, const void* hidden, 
     p.stat = reinterpret_cast<float2*>(ws + L.tile_stat);
     p.stat_upper = reinterpret_cast<float2*>(ws + L.tile_upper);
     p.split_from = reinterpret_cast<int32_t*>(ws + L.n_union);
+    p.halves = halves ? 1 : 0;
     p.want_lse = logprob ? 1 : 0;
     p.next_block = reinterpret_cast<unsigned int*>(ws + L.ctrl) + coral_ctrl::kTileQueue;
     p.M = M; p.V = V; p.G = G;
@@ -866,10 +867,16 @@ size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtyp
                        tiles ? LayoutFor::kCounted : LayoutFor::kWorkspace).total;
 }
 
+// The tile kernels' arrays for M tokens in the static scratch.
+Layout static_tiles_layout(const PathPlan& plan, int M, int V, int G, int g, int k) {
+    return make_layout(M, V, G, g, k, Pieces{}, {plan.path == 2 ? Tiles::kOwn : Tiles::kGeneral, plan.tile_small},
+                       LayoutFor::kTiles);
+}
+
 // The arrays of the kernels that run a call, in the static scratch.  The tile kernels' may be more
 // than the call is counted by: then they run for the tokens in equal batches, which leaves every bit
-// of a token's result as it is (one token's arrays fit: 4 V bytes of logits, with V limited by the
-// ranking kernel's LDS).
+// of a token's result as it is where no block is processed in halves (one token's arrays fit: 4 V bytes
+// of logits, with V limited by the ranking kernel's LDS).
 Layout static_layout(const PathPlan& plan, int M, int V, int G, int g, int k, int* batch) {
     *batch = M;
     if (plan.path == 1) return make_layout(M, V, G, g, k, Pieces{}, TileArrays{}, LayoutFor::kSingleLaunch);
@@ -877,11 +884,20 @@ Layout static_layout(const PathPlan& plan, int M, int V, int G, int g, int k, in
     Layout L = {};
     for (int n = 1; n <= M; ++n) {
         *batch = (M + n - 1) / n;
-        L = make_layout(*batch, V, G, g, k, Pieces{}, {plan.path == 2 ? Tiles::kOwn : Tiles::kGeneral, plan.tile_small},
-                        LayoutFor::kTiles);
+        L = static_tiles_layout(plan, *batch, V, G, g, k);
         if (L.total <= kStaticArrayBytes) break;
     }
     return L;
+}
+
+// Whether the grouped head's blocks may be processed in halves.  A half's columns are summed in four
+// parts instead of two, so its logits round differently, and which blocks are halved goes by the groups
+// of all tokens of a launch.  Shapes whose tokens go in batches in the static scratch are therefore never
+// halved, there and with a workspace, and give the same bits either way.  (bf16 H = 1024, V = 100000, two
+// of eight groups, 64 tokens in four batches; the log-probability mode has no static form.)
+bool tiles_take_halves(const PathPlan& plan, int M, int H, int V, int G, int g, int k, coral_dtype dt) {
+    return plan.path != 2 || static_tiles_layout(plan, M, V, G, g, k).total <= kStaticArrayBytes ||
+           static_counted_bytes(M, H, V, G, g, k, dt) > kStaticScratchBytes;
 }
 
 coral_status grouped_impl(const void* hidden, const void* gate_hidden, const void* gate_W,
@@ -969,6 +985,7 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
         const int tiles_g = (G + 15) / 16;
         typedef void (*gate_select_fn)(GateSelParams);
         const gate_select_fn gs = CORAL_PICK_DT(dt, k_gate_select<kF32>, k_gate_select<kBF16>, k_gate_select<kF16>);
+        const bool halves = logprob || tiles_take_halves(plan, M, H, V, G, g, k, dt);
         for (int m0 = 0; m0 < M; m0 += tile_tokens) {          // (one turn but for the static scratch)
             const int m = M - m0 < tile_tokens ? M - m0 : tile_tokens;
             int32_t* sel_m = sel_groups ? sel + (size_t)m0 * g : sel;
@@ -983,7 +1000,7 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
             if ((st = launch_status()) != CORAL_OK) return st;
             st = launch_tiles(false, plan, hid + (size_t)m0 * n_vec, lm_W, gi, m, H, V, G, k, dt,
                               topk_ids + (size_t)m0 * k, topk_logits + (size_t)m0 * k, ws, L, stream, ev_before,
-                              ev_after, sel_m, g, logprob, gate_bias != nullptr);
+                              ev_after, sel_m, g, logprob, gate_bias != nullptr, halves);
             if (st != CORAL_OK) return st;
         }
         if (!level) return CORAL_OK;

@@ -66,6 +66,7 @@ struct TileParams {
                                             // log-probability mode the sum of exp(z - largest)
     float2* stat_upper;                     // [blocks from split_from on, M] out: the same of rows 64 to 127
     int32_t* split_from;                    // out: the first block processed in halves
+    int halves;                             // whether blocks may be (see tiles_take_halves in coral_lmhead.hip)
     int want_lse;
     unsigned int* next_block;               // block queue: zero before the launch
     int M, V, G;
@@ -538,7 +539,7 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     // the whole kernel slower (wide tree 126 -> 134 us, by the registers it takes).
     const int P = gridDim.x;
     const int over = total_blocks % P;
-    const int split_from = HALVES && p.n_chunks > 1 && 2 * over <= P ? max(total_blocks - over, uni(flags[2])) : total_blocks;
+    const int split_from = HALVES && p.halves && p.n_chunks > 1 && 2 * over <= P ? max(total_blocks - over, uni(flags[2])) : total_blocks;
     const int total_units = 2 * total_blocks - split_from;
     if (blockIdx.x == 0 && threadIdx.x == 0) *p.split_from = split_from;
     int u = 0;

@@ -182,3 +182,35 @@ def test_noalloc_at_the_limits_of_its_scratch(coral, dtype, H, V, G, g, k, M, pa
     torch.cuda.synchronize()
     for a, b in zip(want, (ids, z, sel)):
         assert torch.equal(a, b)
+
+
+# Plain tile path, more tokens than the scratch takes at once (its logits), groups of uneven size and
+# popularity: which blocks the last round holds differs from batch to batch.
+BATCHED = [("bf16", 1024, 66000, 4, 2, 8, 48), ("f16", 1024, 100000, 8, 3, 4, 48), ("bf16", 1536, 100000, 4, 2, 8, 33)]
+
+
+@pytest.mark.parametrize("dtype,H,V,G,g,k,M", BATCHED)
+def test_noalloc_in_batches_on_the_tile_path(coral, dtype, H, V, G, g, k, M):
+    code = {"bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
+    assert coral.coral_lmhead_path(False, M, H, V, G, g, k, code) == 2
+    assert M * V * 4 > coral.NOALLOC_SCRATCH_BYTES
+    torch.manual_seed(H + M)
+    t = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    lm_W = (torch.randn(V, H, device="cuda", dtype=t)).mul_(0.02)
+    gate_W = (torch.randn(G, H, device="cuda", dtype=t)).mul_(0.02)
+    bias = torch.zeros(G, device="cuda")
+    bias[G - 1] = 1.5
+    cuts = np.arange(G + 1) * (V // G)
+    cuts[1:-1:2] += 200
+    gi = coral.GroupIndex(cuts.astype(np.int32), np.random.default_rng(1).permutation(V).astype(np.int32))
+    for call in range(3):
+        print(f"case {dtype} H={H} V={V} M={M} call {call}", flush=True)
+        hidden = torch.randn(M, H, device="cuda", dtype=t)
+        want = coral.coral_lmhead_grouped(hidden, gate_W, bias, lm_W, gi, g, k)
+        ids = torch.full((M, k), -5, dtype=torch.int32, device="cuda")
+        z = torch.full((M, k), float("nan"), device="cuda")
+        sel = torch.full((M, g), -5, dtype=torch.int32, device="cuda")
+        coral.coral_lmhead_grouped_noalloc(hidden, gate_W, bias, lm_W, gi, g, k, ids, z, sel)
+        torch.cuda.synchronize()
+        for name, a, b in zip(("ids", "logits", "groups"), want, (ids, z, sel)):
+            assert torch.equal(a, b), name
