@@ -1190,7 +1190,7 @@ extern "C" coral_status coral_router_premix(const void* hidden, const void* W1, 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     typedef void (*premix_fn)(PremixParams);
     // Which kernel, us (k_premix_wide, k_premix_blocks): H = 2560, 8 tokens 6.3, 6.6, 15 6.3, 7.0; H =
-    // 4096, 8 tokens 9.9, 9.5, 15 9.8, 10.0, 40 12.6, 13.8.
+    // 3584, 8 tokens 8.3, 8.3; H = 4096, 1 to 8 tokens 9.4, 9.0, 15 9.8, 10.0, 40 12.6, 13.8.
     if (w16 && M >= 4 && M <= 64 && H % (kPremixChunkVecs * 8) == 0 &&
         H / (kPremixChunkVecs * 8) <= kPremixMaxChunks && (M > 8 || H <= 3072)) {     // matrix cores, tokens staged in chunks
         typedef void (*wide_fn)(PremixParams);
@@ -1220,10 +1220,10 @@ extern "C" coral_status coral_router_premix(const void* hidden, const void* W1, 
         const int n_ct = M <= 16 ? 1 : M <= 32 ? 2 : M <= 48 ? 3 : 4;
         // (as many blocks ahead as the registers hold)
         const premix_fn fn =
-            n_ct == 1   ? CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 1, 2>), (k_premix_blocks<kBF16, 1, 3>), (k_premix_blocks<kF16, 1, 3>))
-            : n_ct == 2 ? CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 2, 3>), (k_premix_blocks<kBF16, 2, 3>), (k_premix_blocks<kF16, 2, 3>))
-            : n_ct == 3 ? CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 3, 2>), (k_premix_blocks<kBF16, 3, 2>), (k_premix_blocks<kF16, 3, 2>))
-                        : CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 4, 1>), (k_premix_blocks<kBF16, 4, 2>), (k_premix_blocks<kF16, 4, 2>));
+            n_ct == 1   ? CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 1, 2>), (k_premix_blocks<kBF16, 1, 2>), (k_premix_blocks<kF16, 1, 2>))
+            : n_ct == 2 ? CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 2, 3>), (k_premix_blocks<kBF16, 2, 2>), (k_premix_blocks<kF16, 2, 2>))
+            : n_ct == 3 ? CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 3, 2>), (k_premix_blocks<kBF16, 3, 1>), (k_premix_blocks<kF16, 3, 1>))
+                        : CORAL_PICK_DT(dt, (k_premix_blocks<kF32, 4, 1>), (k_premix_blocks<kBF16, 4, 1>), (k_premix_blocks<kF16, 4, 1>));
         hipLaunchKernelGGL(fn, dim3((H + 15) / 16, (M + n_ct * 16 - 1) / (n_ct * 16)), dim3(kPremixBlockThreads), 0, stream, p);
         return launch_status();
     }

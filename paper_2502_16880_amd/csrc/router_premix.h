@@ -128,13 +128,14 @@ __global__ __launch_bounds__(kBlock) void k_premix(PremixParams p) {
     }
 }
 
-// Rows of up to 8 KB in whole 512-column chunks, four tokens and more: the token vectors are staged in
-// such chunks for all token tiles at once, and a workgroup of eight waves
+// Rows of up to 8 KB in whole 512-column chunks: the token vectors are staged in such chunks for all token
+// tiles at once, and a workgroup of eight waves
 // owns 16 output features: wave w takes the 64 columns w*64.. of every chunk, i.e. one
 // 128-byte line of each of the 16 rows per chunk, and requests all its lines up front (the
 // whole of W1 is in flight in one round).  A line pair's operands serve every token tile.
 // A later chunk's token vectors are requested at the top of a chunk and written to a free
-// buffer at its end.  From four tokens on; bf16 / fp16, H a multiple of 512, at most 8 chunks.
+// buffer at its end.  bf16 / fp16, H a multiple of 512, at most 8 chunks, four tokens and more (H beyond
+// 3072: nine and more, see coral_router_premix).
 constexpr int kPremixWideWaves = 8;
 constexpr int kPremixWideBlock = kPremixWideWaves * kWave;
 constexpr int kPremixChunkVecs = 64;             // 16-byte vectors per 512-column chunk
@@ -378,10 +379,16 @@ __global__ __launch_bounds__(kPremixWideBlock) void k_premix_wide(PremixParams p
 // before the sums at the end, two workgroups per compute unit.  The tokens come out of the L2, D
 // blocks ahead like the weights (loads return in order: tokens requested later than the next
 // block's weights would wait for them).  Bound by the weights' stream and, from two token tiles on,
-// the tokens' out of the L2.  us, against the forms it replaces (four waves holding 16 lines of every
-// row, one token tile at a time; the vector units): bf16 H = 6016, 15 tokens 38.2 -> 18.5, 64 tokens
-// 112.6 -> 38.3 (bytes at 6.8 TB/s: 10.6), H = 2568, 15 tokens 12.8 -> 8.0; fp32 H = 4096, 15 tokens
-// 47.0 -> 19.7, error against float64 1.1e-7 -> 0.75e-7.
+// the tokens' out of the L2.  us a call, against the forms it replaces (four waves holding 16 lines of
+// every row, one token tile at a time; the vector units): bf16 H = 6016, 16 tokens 40.3 -> 20.2, 64 tokens
+// 112.5 -> 37.4 (bytes at 6.8 TB/s: 10.6), H = 2568, 16 tokens 13.9 -> 7.3; fp32 H = 4096, 16 tokens
+// 60.4 -> 18.3.
+// Sums no less exact than theirs: a wave keeps one per 32 columns of a block for at most four blocks (16
+// bits), or a block's products with the rounding error kept (fp32).  Values of u that fall on the other
+// side of a rounding boundary, vector units / one running sum per wave / this: bf16 H = 4096 6.1e-5, 8.8e-5,
+// 6.0e-5 of them, H = 7168 7.2e-5, 1.29e-4, 6.9e-5, H = 10248 8.6e-5, 1.59e-4, 7.5e-5; fp32 H = 4096,
+// relative error 1.1e-7, 2e-7, 0.75e-7.  (Every block's sum added with its rounding error, 16 bits: 5.4e-5
+// at H = 4096, but 5 to 10 % slower.)
 constexpr int kPremixBlockWaves = 8;
 constexpr int kPremixBlockThreads = kPremixBlockWaves * kWave;
 template <int DT, int NCT, int D>
@@ -389,6 +396,7 @@ __global__ __launch_bounds__(kPremixBlockThreads, NCT == 1 ? 4 : 2) void k_premi
     __shared__ __attribute__((aligned(16))) float red[kPremixBlockWaves * NCT * 256];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    static_assert(4 % D == 0 || DT == kF32, "the sums are gathered between trips");
     const int q4 = lane >> 4, a4 = (lane >> 2) & 3, c4 = lane & 3;
     const int r0 = blockIdx.x * 16, m0 = blockIdx.y * NCT * 16;
     const int tb = p.M - m0;                                       // tokens from m0 on
@@ -431,10 +439,25 @@ __global__ __launch_bounds__(kPremixBlockThreads, NCT == 1 ? 4 : 2) void k_premi
 #pragma unroll
     for (int k = 0; k < D; ++k)
         if (k < n) load(k, k);                                     // wave-uniform
-    f32x4_t acc[NCT][2];
+    // Sums: 16 bits, one per 32 columns of a block, gathered in `total` every four blocks; fp32, acc[0]
+    // with its rounding errors in acc[1].
+    f32x4_t acc[NCT][4], total[NCT];
+    auto gather = [&]() {
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) acc[ct][0] = acc[ct][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < NCT; ++ct) {
+            total[ct] += (acc[ct][0] + acc[ct][1]) + (acc[ct][2] + acc[ct][3]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[ct][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+#pragma unroll
+    for (int ct = 0; ct < NCT; ++ct) {
+        total[ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[ct][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
     for (int i = 0; i < n; i += D) {                               // wave-uniform
+        if (DT != kF32 && i > 0 && i % 4 == 0) gather();
 #pragma unroll
         for (int k = 0; k < D; ++k) {
             if (i + k < n) {
@@ -444,8 +467,7 @@ __global__ __launch_bounds__(kPremixBlockThreads, NCT == 1 ? 4 : 2) void k_premi
                     mfma_operands_from_quad_rows(b[k][ct][0], b[k][ct][1], b[k][ct][2], b[k][ct][3], lane);
                     if (DT == kF32) {
                         // a block's products start from zero and are added with the rounding error
-                        // kept (two-sum), as in k_tiles' general form: one running sum was 2e-7
-                        // off at 4000 columns, the vector units' lane-split sums 1.1e-7
+                        // kept (two-sum), as in k_tiles' general form
                         const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
                         const f32x4_t x = (mfma_tile<DT>(a[k][0], b[k][ct][0], zero) + mfma_tile<DT>(a[k][1], b[k][ct][1], zero)) +
                                           (mfma_tile<DT>(a[k][2], b[k][ct][2], zero) + mfma_tile<DT>(a[k][3], b[k][ct][3], zero));
@@ -457,23 +479,24 @@ __global__ __launch_bounds__(kPremixBlockThreads, NCT == 1 ? 4 : 2) void k_premi
                         }
                     } else {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) acc[ct][0] = mfma_tile<DT>(a[k][c], b[k][ct][c], acc[ct][0]);
+                        for (int c = 0; c < 4; ++c) acc[ct][c] = mfma_tile<DT>(a[k][c], b[k][ct][c], acc[ct][c]);
                     }
                 }
                 if (i + k + D < n) load(i + k + D, k);
             }
         }
     }
+    if (DT != kF32) gather();
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) {
         if (DT == kF32) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {              // (an infinite sum's error is NaN)
                 const float sum = acc[ct][0][q] + acc[ct][1][q];
-                acc[ct][0][q] = __builtin_isfinite(sum) ? sum : acc[ct][0][q];
+                total[ct][q] = __builtin_isfinite(sum) ? sum : acc[ct][0][q];
             }
         }
-        *reinterpret_cast<f32x4_t*>(red + ((size_t)wave * NCT + ct) * 256 + lane * 4) = acc[ct][0];
+        *reinterpret_cast<f32x4_t*>(red + ((size_t)wave * NCT + ct) * 256 + lane * 4) = total[ct];
     }
     __syncthreads();
 #pragma unroll
