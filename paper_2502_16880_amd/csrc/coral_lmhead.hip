@@ -644,22 +644,25 @@ TileArrays layout_tiles(int M, int H, int V, int G, int g, int k, coral_dtype dt
     return t;
 }
 
-// Whether k_tiles reads the weights past the caches (non-temporal).  Large steps do: 398 to 660 MB of
-// rows are 5 to 10 % faster so (bf16 H = 3584, 1090 MB 180 us against 194 with ordinary loads, H = 6016
-// 58.9, 63.2).  Ordinary loads where the rows are no whole 128-byte lines (a line is then wanted by two
-// loads of a wave, the second of which should find it: dense H = 5680, 22 tokens 165 us past the caches,
-// 146 through them, H = 2280, 13 tokens 32.0, 22.5), where the rows are few (64 MB 26.4, 22.9; 109 MB
-// 33.1, 30.2; 162 MB 38.4, 40.6), and where blocks come round again for the next 32 tokens (fp32 H =
-// 1536, 43 tokens, 484 MB 245, 228).  Blocks of 32 rows, whose waves read longer runs of a row, gain
-// nothing (H = 5120, 35 tokens 53.5, 56.2).  A router's bias makes its tokens agree: about half of the groups
-// that they would draw by lot (48 groups, 24 tokens 203 MB by lot, 64 MB with a bias of N(0, 2^2)).
-bool tile_streams(bool dense, bool general, bool small, int M, int V, int G, int g, int n_vec, bool biased) {
-    const double groups = dense ? 1.0 : expected_groups(M, G, g) * (biased ? 0.5 : 1.0);
-    const double rows = dense ? V : groups * V / G;
-    if (n_vec % 8 != 0) return false;
-    if (small || (dense && !general)) return true;     // (consecutive rows, H = 3584, 10 K of them, 51 tokens 42.1, 43.7)
-    if (general && (dense ? M : M * g / groups) > 32.0) return false;
-    return rows * n_vec * 16.0 > 128e6;
+// From how many activated rows on k_tiles reads the weights past the caches (non-temporal): 0 always,
+// INT_MAX never.  Few rows are read through them, as a draft loop's next step may find them in the
+// last-level cache; that costs where it does not, from 128 MB on more than it gives where it does.  us,
+// through the caches against past them, new weights in every step and the same: two of 32 groups, H = 5120, 95
+// MB 46.1, 43.8 and 35.4, 41.1, 177 MB 60.1, 55.9 and 54.7, 58.1; three of 48, H = 2560, 80 MB 41.0, 39.6
+// and 38.5, 40.7, 165 MB 57.6, 52.9 and 51.0, 53.3, 238 MB 70.7, 64.2 and 59.6, 63.6; H = 8192, 410 MB
+// 111.7, 100.1 and 106.2, 93.1.  The kernel counts the rows (what tokens activate goes by the scores: with
+// a router's bias of N(0, 2^2) 80 MB of the 197 that they would draw by lot).  In any case through the
+// caches: rows that are no whole 128-byte lines (a line is then wanted by two loads of a wave, the second of
+// which should find it: dense H = 5680, 22 tokens 165 us past the caches, 146 through them, H = 2280, 13
+// tokens 32.0, 22.5), and blocks that come round again for the next 32 tokens (fp32 H = 1536, 43 tokens,
+// 484 MB 245, 228).  In any case past them: blocks of 32 rows, whose waves read longer runs of a row (H =
+// 5120, 35 tokens 53.5, 56.2), and the dense head's consecutive rows of whole chunks (new weights in every
+// step, 24 tokens, H = 1536, 201 MB 51.6, 47.0, H = 512, 67 MB 30.6, 29.1).
+int tile_stream_rows(bool dense, bool general, bool small, int M, int G, int g, int n_vec) {
+    if (n_vec % 8 != 0) return INT_MAX;
+    if (small || (dense && !general)) return 0;
+    if (general && (dense ? M : M * g / expected_groups(M, G, g)) > 32.0) return INT_MAX;
+    return (int)(128000000 / (n_vec * 16)) + 1;
 }
 
 // Enqueues k_tiles and the ranking of the logits it leaves.  For the grouped head the gate
@@ -670,7 +673,7 @@ coral_status launch_tiles(bool dense, const PathPlan& plan, const void* hidden, 
                           int G, int k, coral_dtype dt, int32_t* topk_ids,
                           float* topk_out, char* ws, const Layout& L, hipStream_t stream,
                           void* ev_before, void* ev_after, const int32_t* sel = nullptr, int g = 0,
-                          bool logprob = false, bool biased = false, bool halves = true) {
+                          bool logprob = false, bool halves = true) {
     int P = compute_units();
     if (P < 1) return CORAL_ERR_HIP;
     if (P > kMaxWorkgroups) P = kMaxWorkgroups;
@@ -697,15 +700,11 @@ coral_status launch_tiles(bool dense, const PathPlan& plan, const void* hidden, 
     const bool small = plan.tile_small, general = plan.path == 0;
     const int lds = plan.tile_lds;
     const int rows_per_block = small ? kTileRowsSmall : kTileRows;
-    const auto pick = [&](auto stream) -> tiles_fn {
-        constexpr bool S = decltype(stream)::value;
-        if (small) return CORAL_PICK_DT(dt, (k_tiles<S, kF32, true, kTileSplitSmall>), (k_tiles<S, kBF16, true, kTileSplitSmall>),
-                                        (k_tiles<S, kF16, true, kTileSplitSmall>));
-        if (general) return CORAL_PICK_DT(dt, (k_tiles<S, kF32, true, kTileSplit>), (k_tiles<S, kBF16, true, kTileSplit>),
-                                          (k_tiles<S, kF16, true, kTileSplit>));
-        return dt == CORAL_F16 ? k_tiles<S, kF16, false, kTileSplit> : k_tiles<S, kBF16, false, kTileSplit>;
-    };
-    const tiles_fn fn = tile_streams(dense, general, small, M, V, G, g, p.n_vec, biased) ? pick(std::true_type()) : pick(std::false_type());
+    p.stream_rows = tile_stream_rows(dense, general, small, M, G, g, p.n_vec);
+    const tiles_fn fn =
+        small     ? CORAL_PICK_DT(dt, (k_tiles<kF32, true, kTileSplitSmall>), (k_tiles<kBF16, true, kTileSplitSmall>), (k_tiles<kF16, true, kTileSplitSmall>))
+        : general ? CORAL_PICK_DT(dt, (k_tiles<kF32, true, kTileSplit>), (k_tiles<kBF16, true, kTileSplit>), (k_tiles<kF16, true, kTileSplit>))
+        : dt == CORAL_F16 ? k_tiles<kF16, false, kTileSplit> : k_tiles<kBF16, false, kTileSplit>;
     if (!allow_lds(reinterpret_cast<const void*>(fn), lds)) return CORAL_ERR_HIP;
     coral_status st;
     if ((st = launch_timed(fn, dim3(P), dim3(kTileBlock), lds, stream, ev_before, ev_after, p, dense ? 1 : 0)) !=
@@ -1000,7 +999,7 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
             if ((st = launch_status()) != CORAL_OK) return st;
             st = launch_tiles(false, plan, hid + (size_t)m0 * n_vec, lm_W, gi, m, H, V, G, k, dt,
                               topk_ids + (size_t)m0 * k, topk_logits + (size_t)m0 * k, ws, L, stream, ev_before,
-                              ev_after, sel_m, g, logprob, gate_bias != nullptr, halves);
+                              ev_after, sel_m, g, logprob, halves);
             if (st != CORAL_OK) return st;
         }
         if (!level) return CORAL_OK;

@@ -67,6 +67,7 @@ struct TileParams {
     float2* stat_upper;                     // [blocks from split_from on, M] out: the same of rows 64 to 127
     int32_t* split_from;                    // out: the first block processed in halves
     int halves;                             // whether blocks may be (see tiles_take_halves in coral_lmhead.hip)
+    int stream_rows;                        // weights past the caches from so many activated rows on (tile_stream_rows)
     int want_lse;
     unsigned int* next_block;               // block queue: zero before the launch
     int M, V, G;
@@ -192,7 +193,7 @@ __device__ __forceinline__ int tile_lane_vec(int c, int sp) {
 // The 128-byte line of step pair sp of chunk c in the lane's row at byte offset `row` of
 // the weight matrix (offsets are 32-bit: the path takes matrices below 4 GiB).  GENERAL: `row` is
 // the row's start, and lanes past its end read its last vector (dropped in tile_step_pair);
-// otherwise the lane's place in a chunk is part of `row`.  STREAM: non-temporal (see tile_streams).
+// otherwise the lane's place in a chunk is part of `row`.  STREAM: non-temporal (see tile_stream_rows).
 template <bool STREAM, bool GENERAL, int SPLIT>
 __device__ __forceinline__ uint4 tile_load_w(const TileParams& p, unsigned row, int c, int sp) {
     unsigned off;
@@ -421,113 +422,22 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
 // GENERAL: the general path's form: any storage type, rows of any number of 16-byte vectors (the
 // last chunk partly filled, loads and operands past a row's end guarded) and sums as exact as the
 // staged kernels'.  Otherwise 16-bit storage and whole chunks.
+// The blocks of a launch, drawn from the queue one by one: `at` is the workgroup's first.
 template <bool STREAM, int DT, bool GENERAL, int SPLIT>
-__global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
-    static_assert(SPLIT == kTileSplit || GENERAL, "blocks of 32 rows exist in the general form");
+__device__ __forceinline__ void tile_units(const TileParams& p, bool dense, int at, int total_blocks, const TileLds& lay, char* lds) {
     constexpr int ROWS = tile_rows(SPLIT);
     constexpr bool HALVES = !GENERAL;                  // blocks can be processed in halves (see split_from)
-    extern __shared__ uint4 smem[];
-    char* lds = reinterpret_cast<char*>(smem);
-    const TileLds lay = tile_lds_layout(p.u_max);
     uint4* hbuf = reinterpret_cast<uint4*>(lds + lay.o_hbuf);
     int* ustart = reinterpret_cast<int*>(lds + lay.o_ustart);
     int* uend = reinterpret_cast<int*>(lds + lay.o_uend);
     int* uprefix = reinterpret_cast<int*>(lds + lay.o_uprefix);
     unsigned long long* umask = reinterpret_cast<unsigned long long*>(lds + lay.o_umask);
     int* flags = reinterpret_cast<int*>(lds + lay.o_flags);
-
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int M = p.M;
     uint4* my_slice = reinterpret_cast<uint4*>(lds + lay.o_scratch) + (size_t)wave * kLinePairSlots;
-
-    // Blocks cost different amounts (one to four token tiles), so they are handed out from
-    // a queue, most expensive groups first, rather than dealt round robin.
     unsigned int drawn = 0u;
-    if (threadIdx.x == 0)
-        drawn = __hip_atomic_fetch_add(p.next_block, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    int total_blocks;
-    if (dense) {
-        total_blocks = (p.V + ROWS - 1) / ROWS;
-        if (threadIdx.x == 0) {
-            flags[1] = (int)drawn;
-            flags[2] = M > kTileHalfTokens ? total_blocks : 0;
-        }
-        __syncthreads();
-    } else {
-        // The activated groups in the order the workgroups go through them: most token
-        // tiles first (a block costs more the more tokens it serves), then ascending group id;
-        // each with its row range, token mask and the number of blocks before it.  Every
-        // workgroup builds the same table; the scratch arrays lie over the staging buffers,
-        // which are free until the first K loop.
-        unsigned long long* gmask = reinterpret_cast<unsigned long long*>(hbuf);      // [G]
-        int* off_lds = reinterpret_cast<int*>(gmask + p.G);                            // [G + 1]
-        int* ulist = off_lds + p.G + 1;                                                // [G]
-        int* order = ulist + p.G;                                                      // [G]
-        const int n_tt = (M + 15) / 16;
-        for (int g0 = threadIdx.x; g0 <= p.G; g0 += kTileBlock) {
-            off_lds[g0] = p.offsets[g0];
-            if (g0 < p.G) {
-                unsigned long long mk = 0ull;
-                for (int c = 0; c < n_tt; ++c) mk |= p.tile_mask[(size_t)c * p.G + g0];
-                gmask[g0] = mk;
-                if (blockIdx.x == 0) p.group_mask[g0] = mk;
-            }
-        }
-        __syncthreads();
-        if (wave == 0) {
-            int count = 0;
-            for (int base = 0; base < p.G; base += kWave) {    // wave-uniform
-                const int g0 = base + lane;
-                const bool on = g0 < p.G && gmask[g0] != 0ull;
-                const unsigned long long bal = __ballot(on);
-                if (on) ulist[count + __popcll(bal & ((1ull << lane) - 1ull))] = g0;
-                count += __popcll(bal);
-            }
-            if (count <= kWave) {
-                // a group has one to four token tiles (M <= 64): four ballots place it
-                const int g0 = lane < count ? ulist[lane] : 0;
-                const int w0 = lane < count ? (__popcll(gmask[g0]) + 15) >> 4 : 0;
-                int rank = 0;
-#pragma unroll
-                for (int w = 4; w >= 1; --w) {
-                    const unsigned long long bal = __ballot(w0 == w);
-                    if (w0 < w) rank += __popcll(bal);
-                    if (w0 == w) rank += __popcll(bal & ((1ull << lane) - 1ull));
-                }
-                if (lane < count) order[rank] = g0;
-            } else {
-                // (many groups: ascending id; the order only balances the load)
-                for (int r = lane; r < count; r += kWave) order[r] = ulist[r];
-            }
-            int carry = 0, many_end = 0;
-            for (int base = 0; base < count; base += kWave) {  // wave-uniform
-                const int r = base + lane;
-                const int g0 = r < count ? order[r] : 0;
-                const int nb = r < count ? (off_lds[g0 + 1] - off_lds[g0] + ROWS - 1) / ROWS : 0;
-                const int incl = wave_scan_inclusive(nb);
-                if (r < count) {
-                    ustart[r] = off_lds[g0];
-                    uend[r] = off_lds[g0 + 1];
-                    uprefix[r] = carry + incl - nb;
-                    umask[r] = gmask[g0];
-                    if (blockIdx.x == 0) p.group_first_block[g0] = carry + incl - nb;
-                }
-                const unsigned long long many = __ballot(r < count && __popcll(gmask[g0]) > kTileHalfTokens);
-                if (many) many_end = carry + __builtin_amdgcn_readlane(incl, 63 - __clzll((long long)many));
-                carry += __builtin_amdgcn_readlane(incl, 63);
-            }
-            if (lane == 0) {                           // LDS is in order within a wave
-                uprefix[count] = carry;
-                flags[0] = count;
-                flags[2] = many_end;
-                flags[1] = (int)drawn;
-            }
-        }
-        __syncthreads();
-        total_blocks = uni(uprefix[uni(flags[0])]);
-    }
-
     const unsigned long long all_tokens = M >= 64 ? ~0ull : ((1ull << M) - 1ull);
     // Where the last round of blocks would occupy no more than half of the workgroups, its blocks are
     // handed out in halves of 64 rows (four waves on a row group): one workgroup alone reads a block
@@ -621,7 +531,6 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         }
     };
 
-    int at = uni(flags[1]);
     Unit now = {0, -1, 0, 0, 0ull};
     if (at < total_units) {
         now = locate(at);
@@ -731,6 +640,119 @@ __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
         at = next_at;
         now = next;
     }
+}
+
+template <int DT, bool GENERAL, int SPLIT>
+__global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
+    static_assert(SPLIT == kTileSplit || GENERAL, "blocks of 32 rows exist in the general form");
+    constexpr int ROWS = tile_rows(SPLIT);
+    extern __shared__ uint4 smem[];
+    char* lds = reinterpret_cast<char*>(smem);
+    const TileLds lay = tile_lds_layout(p.u_max);
+    uint4* hbuf = reinterpret_cast<uint4*>(lds + lay.o_hbuf);
+    int* ustart = reinterpret_cast<int*>(lds + lay.o_ustart);
+    int* uend = reinterpret_cast<int*>(lds + lay.o_uend);
+    int* uprefix = reinterpret_cast<int*>(lds + lay.o_uprefix);
+    unsigned long long* umask = reinterpret_cast<unsigned long long*>(lds + lay.o_umask);
+    int* flags = reinterpret_cast<int*>(lds + lay.o_flags);
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int M = p.M;
+
+    // Blocks cost different amounts (one to four token tiles), so they are handed out from
+    // a queue, most expensive groups first, rather than dealt round robin.
+    unsigned int drawn = 0u;
+    if (threadIdx.x == 0)
+        drawn = __hip_atomic_fetch_add(p.next_block, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int total_blocks, rows = p.V;                      // blocks and weight rows of the launch
+    if (dense) {
+        total_blocks = (p.V + ROWS - 1) / ROWS;
+        if (threadIdx.x == 0) {
+            flags[1] = (int)drawn;
+            flags[2] = M > kTileHalfTokens ? total_blocks : 0;
+        }
+        __syncthreads();
+    } else {
+        // The activated groups in the order the workgroups go through them: most token
+        // tiles first (a block costs more the more tokens it serves), then ascending group id;
+        // each with its row range, token mask and the number of blocks before it.  Every
+        // workgroup builds the same table; the scratch arrays lie over the staging buffers,
+        // which are free until the first K loop.
+        unsigned long long* gmask = reinterpret_cast<unsigned long long*>(hbuf);      // [G]
+        int* off_lds = reinterpret_cast<int*>(gmask + p.G);                            // [G + 1]
+        int* ulist = off_lds + p.G + 1;                                                // [G]
+        int* order = ulist + p.G;                                                      // [G]
+        const int n_tt = (M + 15) / 16;
+        for (int g0 = threadIdx.x; g0 <= p.G; g0 += kTileBlock) {
+            off_lds[g0] = p.offsets[g0];
+            if (g0 < p.G) {
+                unsigned long long mk = 0ull;
+                for (int c = 0; c < n_tt; ++c) mk |= p.tile_mask[(size_t)c * p.G + g0];
+                gmask[g0] = mk;
+                if (blockIdx.x == 0) p.group_mask[g0] = mk;
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            int count = 0;
+            for (int base = 0; base < p.G; base += kWave) {    // wave-uniform
+                const int g0 = base + lane;
+                const bool on = g0 < p.G && gmask[g0] != 0ull;
+                const unsigned long long bal = __ballot(on);
+                if (on) ulist[count + __popcll(bal & ((1ull << lane) - 1ull))] = g0;
+                count += __popcll(bal);
+            }
+            if (count <= kWave) {
+                // a group has one to four token tiles (M <= 64): four ballots place it
+                const int g0 = lane < count ? ulist[lane] : 0;
+                const int w0 = lane < count ? (__popcll(gmask[g0]) + 15) >> 4 : 0;
+                int rank = 0;
+#pragma unroll
+                for (int w = 4; w >= 1; --w) {
+                    const unsigned long long bal = __ballot(w0 == w);
+                    if (w0 < w) rank += __popcll(bal);
+                    if (w0 == w) rank += __popcll(bal & ((1ull << lane) - 1ull));
+                }
+                if (lane < count) order[rank] = g0;
+            } else {
+                // (many groups: ascending id; the order only balances the load)
+                for (int r = lane; r < count; r += kWave) order[r] = ulist[r];
+            }
+            int carry = 0, many_end = 0, row_sum = 0;
+            for (int base = 0; base < count; base += kWave) {  // wave-uniform
+                const int r = base + lane;
+                const int g0 = r < count ? order[r] : 0;
+                const int n_rows = r < count ? off_lds[g0 + 1] - off_lds[g0] : 0;
+                const int nb = (n_rows + ROWS - 1) / ROWS;
+                const int incl = wave_scan_inclusive(nb);
+                row_sum += __builtin_amdgcn_readlane(wave_scan_inclusive(n_rows), 63);
+                if (r < count) {
+                    ustart[r] = off_lds[g0];
+                    uend[r] = off_lds[g0 + 1];
+                    uprefix[r] = carry + incl - nb;
+                    umask[r] = gmask[g0];
+                    if (blockIdx.x == 0) p.group_first_block[g0] = carry + incl - nb;
+                }
+                const unsigned long long many = __ballot(r < count && __popcll(gmask[g0]) > kTileHalfTokens);
+                if (many) many_end = carry + __builtin_amdgcn_readlane(incl, 63 - __clzll((long long)many));
+                carry += __builtin_amdgcn_readlane(incl, 63);
+            }
+            if (lane == 0) {                           // LDS is in order within a wave
+                uprefix[count] = carry;
+                flags[0] = count;
+                flags[2] = many_end;
+                flags[3] = row_sum;
+                flags[1] = (int)drawn;
+            }
+        }
+        __syncthreads();
+        total_blocks = uni(uprefix[uni(flags[0])]);
+        rows = uni(flags[3]);
+    }
+    const int at = uni(flags[1]);
+    if (rows >= p.stream_rows) tile_units<true, DT, GENERAL, SPLIT>(p, dense, at, total_blocks, lay, lds);
+    else tile_units<false, DT, GENERAL, SPLIT>(p, dense, at, total_blocks, lay, lds);
 }
 
 // Gate and selection for the tile path (Eq. 7's W2 projection, then top-g): one workgroup

@@ -404,3 +404,22 @@ def test_premix_sums_on_the_matrix_cores(coral, H, M):
         total += u.numel()
     print(f"  {wrong} of {total}: {wrong / total:.2e}")
     assert wrong < 8e-5 * total
+
+
+@pytest.mark.parametrize("dtype,H,V,M,path", [("bf16", 4096, 20000, 40, 2), ("f16", 4160, 20000, 24, 0), ("f32", 1536, 24000, 24, 0)])
+def test_tile_kernels_past_the_caches_and_through_them(coral, dtype, H, V, M, path):
+    """The tile kernels choose their loads by the rows that the tokens activate: more than 128 MB of all
+    groups, then less of the two that a strong bias leaves."""
+    cfg = HeadConfig(f"loads{H}", dtype, H, V, 8, 2, (M,), 10, 1700 + H, True)
+    head = ragged_head(cfg, [V // 8] * 8)
+    dt = {"f32": coral.CORAL_F32, "bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
+    assert coral.coral_lmhead_path(False, M, H, V, 8, 2, 10, dt) == path
+    hidden = make_hidden(cfg, M, M)
+    for strong in (0.0, 100.0):
+        head.gate_bias[2:4] += strong
+        dh = DeviceHead(coral, head)
+        out = run_grouped(coral, dh, hidden, 2, 10)
+        check_grouped(dh, hidden, 2, 10, out)
+        row_bytes = H * (4 if dtype == "f32" else 2)
+        activated = np.unique(out[2]).size * (V // 8) * row_bytes
+        assert (activated < 128e6) == (strong > 0)
