@@ -180,7 +180,7 @@ coral_status coral_lmhead_grouped(const void *hidden, const void *gate_W,
  * allocation.  Same operation, arguments, results (bit for bit) and errors as
  * coral_lmhead_grouped, with no workspace argument: the kernels' scratch (published partial
  * lists, arrival counters, the staged path's hand-over arrays) lives in a static device array
- * of about CORAL_NOALLOC_SCRATCH_BYTES inside the library, one copy per GPU, held until the
+ * of CORAL_NOALLOC_SCRATCH_BYTES and 64 KB inside the library, one copy per GPU, held until the
  * process ends.  The call allocates and frees nothing.
  *   - Shapes whose published and staged lists (16-bit shapes with whole 512-column chunks that
  *     are beyond the single-launch path, or have rows beyond 8 KB: the tile path's logits

@@ -41,8 +41,10 @@
 // ends; in host code the name is only a handle for hipGetSymbolAddress, never an address.
 constexpr size_t kStaticScratchBytes = (size_t)CORAL_NOALLOC_SCRATCH_BYTES;
 // The array is larger than what calls are counted by (static_counted_bytes): the statistics of blocks
-// processed in halves, 128 blocks of 64 tokens at most.
-constexpr size_t kStaticArrayBytes = kStaticScratchBytes + 128 * 64 * 8;
+// processed in halves, of which half of the workgroups have one at most.
+constexpr int kMaxWorkgroups = 256;    // upper bound of the persistent kernels' grids
+constexpr size_t upper_stat_bytes(int M) { return (size_t)(kMaxWorkgroups / 2) * M * sizeof(float2); }
+constexpr size_t kStaticArrayBytes = kStaticScratchBytes + upper_stat_bytes(kMaxM);
 static __device__ __align__(256) unsigned char scratch[kStaticArrayBytes];
 
 namespace {
@@ -60,7 +62,6 @@ inline bool is_16bit(coral_dtype dt) { return dt != CORAL_F32; }
 // One of three instantiations by storage type (kernels without an fp32 form pass nullptr).
 #define CORAL_PICK_DT(dt, f32, bf16, f16) ((dt) == CORAL_F32 ? (f32) : (dt) == CORAL_BF16 ? (bf16) : (f16))
 
-constexpr int kMaxWorkgroups = 256;    // upper bound of the single-launch path's grid
 constexpr size_t kCtrlBytes = coral_ctrl::kWords * sizeof(unsigned int);   // control words at the start of the workspace
 static_assert(coral_ctrl::kLpGroupArrivalWords >= kWave, "one arrival counter per activated group");
 static_assert(coral_ctrl::kGateSelectArrivalWords * 16 >= kMaxM, "one arrival counter per token tile");
@@ -136,8 +137,7 @@ Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, TileArrays 
     // (with blocks of 32 rows the logits take no more, their statistics V / 32 + G entries)
     const size_t stat_blocks = (size_t)V / (tile_arrays.small ? kTileRowsSmall : kTileRows) + G + 1;
     L.tile_stat = take(tiles != Tiles::kNone ? stat_blocks * M * sizeof(float2) : 0);
-    // of blocks processed in halves (half of the workgroups have one at most)
-    L.tile_upper = take(tiles == Tiles::kOwn && what != LayoutFor::kCounted ? kMaxWorkgroups / 2 * M * sizeof(float2) : 0);
+    L.tile_upper = take(tiles == Tiles::kOwn && what != LayoutFor::kCounted ? upper_stat_bytes(M) : 0);   // of blocks in halves
     if (off < after) off = after;
     L.total = off > pieces_end ? off : pieces_end;
     return L;
