@@ -512,6 +512,35 @@ bool staged_fits(int M, int jp, int k) {
     return logits_lds_bytes(M < kTokBatch ? M : kTokBatch, jp, k) <= (size_t)kLdsLimit;
 }
 
+// Dense heads that fit the single launch: whether the tile kernels' general form takes less time, by
+// estimates in us fitted to 1200 heads of 8 to 152 K rows and 64 to 4096 columns, 16 to 31 tokens (fp32: 24
+// to 32), new weights in every call (root mean square error 4 to 5 %).  The single launch dots every row
+// with every token on the vector units (rows padded to its segments of 64 vectors); the tile kernels take
+// whole rounds of 128-row blocks, chunk by chunk, whatever the tokens, less with one token tile, and their
+// weights' stream is slower where rows are no whole 128-byte lines.  (fp32: few blocks take less than
+// estimated, hence the form of the line.)  Over these heads times are 0.75 of the single launch's (fp32 0.88),
+// 5 and 9 of them more than 2 % above it, the worst 1.09 and 1.11; with all of them on the tile kernels 37 and
+// 68 were, the worst 1.28 and 1.50.  bf16 H = 1024, V = 38654, 26 tokens 54 on the single launch, 28 on the
+// tiles; H = 1736, V = 11449, 18 tokens, k = 33 29, 37 (90 blocks); H = 2320, V = 33780, 19 tokens 61, 67 (264
+// blocks, a second round for eight); fp32 H = 944, V = 33304, 26 tokens 54, 70.  The general form's sums
+// are as exact as the vector units': 3.4e-8 against 4.4e-8 off.
+// Fewer than 8192 rows or 16 tokens (fp32 24) stay on the single launch: up to there such calls have been
+// moved, which is not where the two cross.  Measured on the other side, all on the tile kernels: 16 bits, 12
+// tokens 0.97 of the single launch's time on average, 0.75 to 1.32, 14 tokens 0.88, 0.66 to 1.35; below 8192
+// rows 16 tokens 1.07, 24 tokens 0.88; fp32 16 tokens 1.10, 23 tokens 0.96; below 8192 rows 24 tokens 1.34.
+bool general_tiles_faster(int M, int V, int n_vec, int k, coral_dtype dt) {
+    const int blocks = (V + kTileRows - 1) / kTileRows;
+    const double chunks = (n_vec + kChunkVecs - 1) / kChunkVecs;
+    const double steps = (blocks + kMaxWorkgroups - 1) / kMaxWorkgroups * chunks;      // chunks of a workgroup
+    const double mb = (double)V * n_vec * 16e-6, odd_mb = n_vec % 8 != 0 ? mb : 0.0;
+    const double rows = (double)M * V * 1e-6, dots = rows * 1e-3 * chunks * kWave;
+    if (is_16bit(dt))
+        return 10.4 + (M <= 16 ? 2.05 : 3.0) * steps + 3.3 * blocks / kMaxWorkgroups + 0.074 * mb + 0.043 * odd_mb + 0.164 * k <
+               0.97 * (8.0 + 0.39 * M + 133.0 * dots + 10.4 * rows + 0.051 * mb + 0.097 * k);
+    return 11.0 + 5.4 * steps + 4.1 * blocks / kMaxWorkgroups + 0.066 * mb + 0.03 * odd_mb + 0.15 * k <
+           4.0 + 0.9 * (7.7 + 0.42 * M + 98.0 * dots + 7.3 * rows + 0.041 * mb + 0.097 * k);
+}
+
 // The general path takes what the other two do not: fp32 rows beyond the single-launch kernel,
 // widths that are no multiple of 512, more than 64 groups with log-probabilities.  It runs the
 // tile kernels too, whose column tail is then guarded and whose fp32 form multiplies in full fp32
@@ -550,13 +579,7 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
                        !collect_cap(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp,
                                     fused_gate_mode(dense, M, G, g, k, jp, dt), dense ? V : (V + G - 1) / G,
                                     kMaxWorkgroups, &single);
-    // (Dense heads of 8192 rows and more from 16 tokens on, fp32 24, in any case: every row is dotted with
-    // every token, which the vector units do at their own rate, not the memory's.  In the general form,
-    // whose sums are as exact as theirs: 3.4e-8 against 4.4e-8 off.  us, single launch against tiles: bf16
-    // H = 1024, V = 38654, 26 tokens 54, 28; H = 2560, V = 14060, 16 tokens 33, 24; f16 H = 872, V = 141882,
-    // 18 tokens 95, 83; over 20 heads 1.5 times as fast, 1.1 at least; 13 and 12 tokens 55, 52, 29, 31; fp32
-    // H = 352, V = 21065, 30 tokens 34, 28, 16 tokens 19, 20.  Fewer rows were not measured.)
-    const bool many = dense && fused_ok && V >= 8192 && M >= (is_16bit(dt) ? 16 : 24);
+    const bool many = dense && fused_ok && V >= 8192 && M >= (is_16bit(dt) ? 16 : 24) && general_tiles_faster(M, V, n_vec, k, dt);
     if (((dense && dense_prefers_tiles(M, V)) || lists) && tiles_ok)
         pl.path = 2;
     else if ((lists || many) && tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds))

@@ -370,6 +370,12 @@ def test_dense_heads_with_many_tokens_take_the_tile_kernels():
     """Either side of the rule: tokens, rows, storage type."""
     BF16, F32 = coral.CORAL_BF16, coral.CORAL_F32
     path = coral.coral_lmhead_path
-    assert path(True, 15, 1024, 38_654, 0, 0, 10, BF16) == 1 and path(True, 16, 1024, 38_654, 0, 0, 10, BF16) in (0, 2)
+    assert path(True, 15, 1024, 38_654, 0, 0, 10, BF16) == 1 and path(True, 16, 1024, 38_654, 0, 0, 10, BF16) == 0
     assert path(True, 16, 1000, 9_000, 0, 0, 1, BF16) == 0 and path(True, 16, 1000, 8_191, 0, 0, 1, BF16) == 1
     assert path(True, 23, 512, 9_000, 0, 0, 1, F32) == 1 and path(True, 24, 512, 9_000, 0, 0, 1, F32) == 0
+    # few blocks, a second round for a few of them, fp32 whose rounds take as long as the vector units: the single launch
+    assert path(True, 18, 1736, 11_449, 0, 0, 33, BF16) == 1 and path(True, 24, 1736, 32_000, 0, 0, 33, BF16) == 0
+    assert path(True, 19, 2320, 33_780, 0, 0, 1, BF16) == 1 and path(True, 19, 2320, 32_700, 0, 0, 1, BF16) == 0
+    assert path(True, 26, 944, 33_304, 0, 0, 10, F32) == 1 and path(True, 26, 944, 32_700, 0, 0, 10, F32) == 0
+    # the plain form where a workgroup would keep sorted lists, and where the vocabulary is large
+    assert path(True, 16, 4096, 60_000, 0, 0, 10, BF16) == 2 and path(True, 8, 1024, 65_536, 0, 0, 10, BF16) == 2

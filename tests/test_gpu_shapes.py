@@ -374,7 +374,8 @@ def test_premix_of_any_width(coral, dtype, H, M):
 
 
 @pytest.mark.parametrize("dtype,H,V,M,k", [("bf16", 512, 8192, 16, 10), ("f16", 1000, 8300, 17, 1), ("bf16", 264, 9001, 33, 20), ("f32", 512, 8193, 24, 10),
-                                           ("bf16", 1024, 8200, 15, 10), ("bf16", 512, 8191, 40, 10), ("f32", 516, 8250, 23, 4)])
+                                           ("bf16", 1024, 8200, 15, 10), ("bf16", 512, 8191, 40, 10), ("f32", 516, 8250, 23, 4),
+                                           ("f16", 1000, 9000, 24, 1), ("f32", 512, 9000, 24, 1), ("f32", 328, 8202, 32, 20)])
 def test_dense_heads_with_many_tokens(coral, dtype, H, V, M, k):
     """Dense heads on either side of the line between the single launch and the tile kernels."""
     cfg = HeadConfig(f"dense{H}", dtype, H, V, 2, 1, (M,), k, 1600 + M, True)
