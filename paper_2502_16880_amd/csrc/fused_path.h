@@ -52,7 +52,7 @@ constexpr int kLdsLimit = 160 * 1024;
 constexpr int kLpBaseCost = 10;
 // Batches of a workgroup where there are few: fewer workgroups then leave fewer lists to merge (three
 // groups of 101 rows, one token: 24.8 us with all 256, 22.0 with four batches each, 22.4 with 16; six
-// tokens over 9500 rows 29.1, 29.0, 39.4).
+// tokens over 9500 rows 29.1, 29.0, 39.4; over small heads 4 % with 5 to 7 tokens, 1 % with 10 to 17).
 constexpr int kLpFewBatches = 4;
 constexpr int kLpPiecesMax = 16 * 1024;    // LDS for a workgroup's log-sum-exp pieces, at most
 // Collected candidates: where a workgroup meets few rows per token (the configured shapes:
@@ -647,10 +647,11 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         // workgroups are shared out among the count <= 64 activated groups in proportion to
         // their cost, batches x (kLpBaseCost + tokens that selected the group): one each,
         // the rest by the groups' shares rounded down, what is then left one more each to the
-        // groups with the highest cost per workgroup.  The numbers add up to gridDim.x.
+        // groups with the highest cost per workgroup.  The numbers add up to n_share: gridDim.x, or
+        // fewer where there are few batches (the workgroups behind leave before the stream: P_act).
         // One wave's work (activated group u in lane u), after it has written the tables of 2c.
         auto share_out_workgroups = [&](int count, int all_pairs) {
-            const int P = min((int)gridDim.x, max(count, (all_pairs + kLpFewBatches - 1) / kLpFewBatches));
+            const int n_share = min((int)gridDim.x, max(count, (all_pairs + kLpFewBatches - 1) / kLpFewBatches));
             const int nb_u = lane < count ? uprefix[lane + 1] - uprefix[lane] : 0;
             // (batches scaled to 16 bits so that the products below stay in 31)
             const int shift = max(0, 16 - __clz(all_pairs));
@@ -658,9 +659,9 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
                 lane < count ? (unsigned)(nb_u >> shift) * (unsigned)(kLpBaseCost + __popcll(umask[lane])) : 0u;
             const unsigned total = (unsigned)__builtin_amdgcn_readlane(wave_scan_inclusive((int)cost), 63);
             // (the reciprocal rounded down, so that the shares never add up to more than there are)
-            const float scale = (float)(P - count) * __builtin_amdgcn_rcpf((float)(total ? total : 1u)) * (1.f - 0x1p-20f);
+            const float scale = (float)(n_share - count) * __builtin_amdgcn_rcpf((float)(total ? total : 1u)) * (1.f - 0x1p-20f);
             int n_wg = lane < count ? 1 + (int)((float)cost * scale) : 0;
-            const int left = P - __builtin_amdgcn_readlane(wave_scan_inclusive(n_wg), 63);
+            const int left = n_share - __builtin_amdgcn_readlane(wave_scan_inclusive(n_wg), 63);
             if (left > 0) {                            // wave-uniform
                 unsigned long long* rank_keys =
                     reinterpret_cast<unsigned long long*>(lds + lay.o_keys) + (size_t)wave * kWave;
@@ -669,7 +670,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             }
             const int incl_wg = wave_scan_inclusive(n_wg);
             if (lane < count) wgstart[lane] = incl_wg - n_wg;
-            if (lane == 0) wgstart[count] = P;
+            if (lane == 0) wgstart[count] = n_share;
         };
         // ---- 2b. per-token top-g by rank counting: group n of token m is selected iff
         // fewer than g groups beat it (larger score first, then lower group id); its rank
@@ -823,7 +824,9 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     // two rounds (Llama3 shape, M = 1) D = 8 33.0, D = 1 33.5; ten (M = 10) 131.0, 130.1; 15
     // (dense) 159.0, 156.4; a fifth of a round (1024-wide head, 8 tokens) D = 4 20.9, D = 8 22.4; a
     // tenth, one token 11.7, 11.3.  Few enough batches for all lists to be fetched in one trip with
-    // D = 8 (256-wide head, 4 tokens): 14.3, 13.6; not quite (2 tokens, k = 20): 14.4, 14.7.
+    // D = 8 (256-wide head, 4 tokens): 14.3, 13.6; not quite (2 tokens, k = 20): 14.4, 14.7.  (Up to four
+    // tokens: with more the fewer workgroups have too many products each.  Time with D = 8 over D = 4, 14 to 17
+    // small heads each: 5 tokens 1.015, 6 1.03, 7 1.035, 8 1.015.)
     // (Log-probability mode: the workgroup's share is a contiguous range of one group's
     // batches instead, the j-th of the equal parts its group's workgroups cut the group into.)
     const int round = gridDim.x * kFusedWaves;
@@ -1188,8 +1191,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             }
         };
         if (2 * M * p.g <= kFusedWaves) {
-            // Few (token, group) pairs: the workgroup that arrives last takes them all, one
-            // wave each, and merges every token's g lists through LDS (two hand-overs through
+            // Few (token, group) pairs: the workgroup that arrives last takes them all, two
+            // waves each, and merges every token's g lists through LDS (two hand-overs through
             // memory fewer than below; from about 16 pairs on the scheme below is faster).
             if (threadIdx.x == 0) {
                 const unsigned int old = __hip_atomic_fetch_add(p.counter, 1u, __ATOMIC_RELAXED,
@@ -1220,8 +1223,9 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
                 __hip_atomic_store(p.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return;
         }
-        // More pairs than waves: the workgroup of a group that arrives last (a counter per
-        // activated group) finishes the group, one wave per token that selected it, and
+        // More pairs than half of the waves: the workgroup of a group that arrives last (a counter per
+        // activated group) finishes the group, two waves per token that selected it up to eight tokens,
+        // one beyond, and
         // publishes the lists; the group that finishes last (one more counter) merges every
         // token's g lists.  The groups' last workgroups work side by side, most of them
         // while other groups still stream.
@@ -1286,7 +1290,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     __syncthreads();
     if (!uni(flags[1])) return;                        // block-uniform
 
-    // Last workgroup: one wave per token merges the P published lists.
+    // Last workgroup: one wave per token merges the published lists, one per workgroup with batches.
     for (int t = wave; t < M; t += kFusedWaves) {
         const Cand* src = p.part + (size_t)t * k * P;
         wave_merge_lists(
