@@ -422,10 +422,8 @@ __device__ __forceinline__ void tile_k_loop(const TileParams& p, uint4 (&a)[kRin
     }
 }
 
-// GENERAL: the general path's form: any storage type, rows of any number of 16-byte vectors (the
-// last chunk partly filled, loads and operands past a row's end guarded) and sums as exact as the
-// staged kernels'.  Otherwise 16-bit storage and whole chunks.
-// The blocks of a launch, drawn from the queue one by one: `at` is the workgroup's first.
+// The workgroup's blocks, drawn from the queue one by one (`at`: its first draw), once the table of the
+// activated groups is in LDS.
 template <bool STREAM, int DT, bool GENERAL, int SPLIT>
 __device__ __forceinline__ void tile_units(const TileParams& p, bool dense, int at, int total_blocks, const TileLds& lay, char* lds) {
     constexpr int ROWS = tile_rows(SPLIT);
@@ -653,6 +651,10 @@ __device__ __forceinline__ void tile_units(const TileParams& p, bool dense, int 
     }
 }
 
+// The table of the activated groups, then the blocks with the loads that suit the table's rows.
+// GENERAL: the general path's form: any storage type, rows of any number of 16-byte vectors (the
+// last chunk partly filled, loads and operands past a row's end guarded) and sums as exact as the
+// staged kernels'.  Otherwise 16-bit storage and whole chunks.
 template <int DT, bool GENERAL, int SPLIT>
 __global__ __launch_bounds__(kTileBlock) void k_tiles(TileParams p, int dense) {
     static_assert(SPLIT == kTileSplit || GENERAL, "blocks of 32 rows exist in the general form");
