@@ -128,8 +128,9 @@ int coral_lmhead_logprob_path(int M, int H, int V, int G, int g, int k, coral_dt
  * workspace; every completed call leaves the control words ready for the next one.
  * The control words count the workgroups that have published their partial top-k
  * lists, so that the last one can merge them (the per-token top-k of the appendix's
- * "Tree decoding" paragraph) without a further launch, and hand out blocks of weight
- * rows to the workgroups of the tile path.  A call that fails with CORAL_ERR_HIP may
+ * "Tree decoding" paragraph) without a further launch, hand out blocks of weight
+ * rows to the workgroups of the tile path, and hold the gate's scores where the
+ * workgroups of the single launch share the gate.  A call that fails with CORAL_ERR_HIP may
  * leave them non-zero: prepare the workspace again before reusing it.
  *   workspace [device], 256-byte aligned, at least 256 bytes.
  */

@@ -13,19 +13,24 @@ struct Entry {
     int n_words;
 };
 
-constexpr int kWords = 128;                 // size of the control area in words (512 bytes)
+constexpr int kWords = 128 + 4096;          // size of the control area in words (16.5 KB)
 constexpr int kFusedArrival = 0;            // single-launch path: workgroups that have published
 constexpr int kGateSelectArrival = 8;       // tile path: per token tile, k_gate_select workgroups that
 constexpr int kGateSelectArrivalWords = 4;  //   have stored their scores (at most 4 token tiles)
 constexpr int kTileQueue = 4;               // tile path: next block of k_tiles
 constexpr int kLpGroupArrival = 64;         // log-probability mode: one counter per activated
 constexpr int kLpGroupArrivalWords = 64;    //   group (at most 64 in the single-launch kernel)
+constexpr int kGateDone = 1;                // single-launch path, shared gate: workgroups that have read the
+constexpr int kGateScores = 128;            //   scores, and the scores' bit patterns (0: not there yet),
+constexpr int kGateScoreWords = 4096;       //   group by group
 
 constexpr Entry kMap[] = {
     {"fused_arrival", kFusedArrival, 1},
     {"gate_select_arrival", kGateSelectArrival, kGateSelectArrivalWords},
     {"tile_queue", kTileQueue, 1},
     {"logprob_group_arrival", kLpGroupArrival, kLpGroupArrivalWords},
+    {"gate_done", kGateDone, 1},
+    {"gate_scores", kGateScores, kGateScoreWords},
 };
 constexpr int kMapEntries = sizeof(kMap) / sizeof(kMap[0]);
 

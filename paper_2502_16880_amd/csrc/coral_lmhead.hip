@@ -41,10 +41,14 @@
 // ends; in host code the name is only a handle for hipGetSymbolAddress, never an address.
 constexpr size_t kStaticScratchBytes = (size_t)CORAL_NOALLOC_SCRATCH_BYTES;
 // The array is larger than what calls are counted by (static_counted_bytes): the statistics of blocks
-// processed in halves, of which half of the workgroups have one at most.
+// processed in halves, of which half of the workgroups have one at most, and the control words beyond the
+// 512 bytes that were counted when calls' sizes became what callers rely on.
 constexpr int kMaxWorkgroups = 256;    // upper bound of the persistent kernels' grids
 constexpr size_t upper_stat_bytes(int M) { return (size_t)(kMaxWorkgroups / 2) * M * sizeof(float2); }
-constexpr size_t kStaticArrayBytes = kStaticScratchBytes + upper_stat_bytes(kMaxM);
+constexpr size_t kCtrlBytes = coral_ctrl::kWords * sizeof(unsigned int);   // control words at the start of the workspace
+constexpr size_t kCountedCtrlBytes = 512;
+static_assert(kCtrlBytes % 256 == 0, "");
+constexpr size_t kStaticArrayBytes = kStaticScratchBytes + upper_stat_bytes(kMaxM) + kCtrlBytes - kCountedCtrlBytes;
 static __device__ __align__(256) unsigned char scratch[kStaticArrayBytes];
 
 namespace {
@@ -62,7 +66,6 @@ inline bool is_16bit(coral_dtype dt) { return dt != CORAL_F32; }
 // One of three instantiations by storage type (kernels without an fp32 form pass nullptr).
 #define CORAL_PICK_DT(dt, f32, bf16, f16) ((dt) == CORAL_F32 ? (f32) : (dt) == CORAL_BF16 ? (bf16) : (f16))
 
-constexpr size_t kCtrlBytes = coral_ctrl::kWords * sizeof(unsigned int);   // control words at the start of the workspace
 static_assert(coral_ctrl::kLpGroupArrivalWords >= kWave, "one arrival counter per activated group");
 static_assert(coral_ctrl::kGateSelectArrivalWords * 16 >= kMaxM, "one arrival counter per token tile");
 
@@ -261,12 +264,31 @@ bool allow_lds(const void* fn, int bytes) {
     return true;
 }
 
-// Gate of the single-launch path: from four tokens on it goes through the matrix cores (16-bit
+// Gate of the single-launch path where every workgroup computes it, and what the LDS plan goes by: from four tokens on it goes through the matrix cores (16-bit
 // storage only; measured at the Llama3 shape: two tokens 52.1 against 50.8 us on the vector
 // units, three equal, four 81.0 against 81.5).
 int fused_gate_mode(bool dense, int M, int G, int g, int k, int jp, coral_dtype dt, bool logprob = false) {
     (void)G; (void)g; (void)k; (void)jp; (void)logprob;
     return dense || !is_16bit(dt) || M <= 3 ? kGateVector : kGateMfma;
+}
+
+// Whether the single launch's gate is shared between the workgroups (kGateShared): where it would take
+// every workgroup by itself longer than the hand-over, about 4 us.  Estimates in us of the former: on the
+// matrix cores by passes of 32 groups, on the vector units of 16 groups and two tokens, each with the bytes
+// of its rows.  Fitted to 2 x 343 heads (512 to 8192 columns, 8 to 120 groups, 1 to 32 tokens, bf16 and fp32,
+// 24000 rows): 1.08 times as fast on average (log-probabilities 1.05), hardly below the faster of the two
+// each time.  us, own gate against shared: bf16, 8 tokens, H = 8192, 8 groups 59, 55, 120 groups 74, 43;
+// H = 4096, 16 groups 27.8, 26.5, 64 groups 36, 28; H = 2048, 32 groups 22.0, 22.2; H = 512, 120 groups
+// 22.8, 20.6, 32 groups 16.4, 18.5; fp32, 16 tokens, H = 1024, 16 groups 33, 29, 4 tokens, H = 4096, 16
+// groups 30.4, 29.1, 64 groups 43, 30.  With few tokens the own gate starts early, and it matters whether
+// the gate's rows come from the caches: one token, 64 groups, H = 4096, 24000 rows 19.6, 20.0, 128256 rows
+// 28.9, 28.0; H = 8192, 32 groups 22.0, 22.5, 57.5, 56.4; H = 4096, 32 groups 16.8, 18.8, 34.7, 35.9.
+bool fused_gate_shared(int M, int G, int n_vec, coral_dtype dt) {
+    if (M * G > coral_ctrl::kGateScoreWords) return false;
+    const double kb = n_vec / 64.0;                        // of a gate row
+    const double own = is_16bit(dt) && M >= 4 ? (G + 31) / 32 * (0.4 + 0.68 * kb)
+                                              : (G + 15) / 16 * 0.5 * (0.3 + 0.05 * M + (0.1 + 0.11 * M) * kb);
+    return own > 3.5;
 }
 
 // Rows the single-launch kernel takes: up to 8 KB, and from 10 to 16 KB.  (Nine of sixteen
@@ -488,7 +510,7 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
     const auto getter = CORAL_PICK_DT(dt, short_rows ? coral_fused_short_f32 : coral_fused_long_f32,
                                       short_rows ? coral_fused_short_bf16 : coral_fused_long_bf16,
                                       short_rows ? coral_fused_short_f16 : coral_fused_long_f16);
-    const void* fn = getter(dense, gate, routed, logprob, segs);
+    const void* fn = getter(dense, !dense && fused_gate_shared(M, G, n_vec, dt) ? (int)kGateShared : gate, routed, logprob, segs);
     if (!allow_lds(fn, F.total)) return CORAL_ERR_HIP;
     void* args[] = {&p};
     return launch_timed(fn, dim3(P), dim3(kFusedBlock), F.total, stream, ev_before, ev_after, args);
@@ -861,11 +883,12 @@ extern "C" int coral_lmhead_logprob_path(int M, int H, int V, int G, int g, int 
 
 extern "C" coral_status coral_lmhead_workspace_init(void* workspace, size_t workspace_bytes,
                                                     void* hip_stream) {
-    coral_status st = check_workspace(workspace, workspace_bytes, kCtrlBytes);
+    // (a workspace that a call takes holds all control words)
+    coral_status st = check_workspace(workspace, workspace_bytes, kCountedCtrlBytes);
     if (st != CORAL_OK) return st;
-    hipLaunchKernelGGL(k_zero_words, dim3((kCtrlBytes / 4 + 255) / 256), dim3(256), 0,
-                       static_cast<hipStream_t>(hip_stream), static_cast<unsigned int*>(workspace),
-                       (int)(kCtrlBytes / 4));
+    const int words = (int)((workspace_bytes < kCtrlBytes ? workspace_bytes : kCtrlBytes) / 4);
+    hipLaunchKernelGGL(k_zero_words, dim3((words + 255) / 256), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
+                       static_cast<unsigned int*>(workspace), words);
     return launch_status();
 }
 
@@ -886,7 +909,7 @@ size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtyp
         tiles = F.total - F.o_lists + (hidden > merges ? hidden : merges) > kLdsLimit;
     }
     return make_layout(M, V, G, g, k, Pieces{}, {tiles ? Tiles::kOwn : Tiles::kNone, false},
-                       tiles ? LayoutFor::kCounted : LayoutFor::kWorkspace).total;
+                       tiles ? LayoutFor::kCounted : LayoutFor::kWorkspace).total - (kCtrlBytes - kCountedCtrlBytes);
 }
 
 // The tile kernels' arrays for M tokens in the static scratch.

@@ -10,6 +10,9 @@ template <int DT, int SEGS>
 const void* fused_instance(bool dense, int gate, bool routed, bool logprob) {
 #define CORAL_FUSED(...) reinterpret_cast<const void*>(&k_fused<DT, __VA_ARGS__, SEGS>)
     if (dense) return CORAL_FUSED(true, kGateVector, false, false);
+    if (gate == kGateShared)
+        return logprob ? (routed ? CORAL_FUSED(false, kGateShared, true, true) : CORAL_FUSED(false, kGateShared, false, true))
+                       : (routed ? CORAL_FUSED(false, kGateShared, true, false) : CORAL_FUSED(false, kGateShared, false, false));
     if constexpr (DT != kF32) {
         if (gate == kGateMfma)
             return logprob ? (routed ? CORAL_FUSED(false, kGateMfma, true, true) : CORAL_FUSED(false, kGateMfma, false, true))

@@ -2,10 +2,10 @@
 //
 // One persistent workgroup of 16 waves per compute unit.  Every workgroup
 //   1. stages the M hidden vectors in LDS,
-//   2. computes the whole gate s[M,G] itself from the L2-resident gate matrix (Eq. 7's
-//      W2 projection; redundant per workgroup, which costs less than a grid-wide
-//      synchronisation would), selects the g best groups per token and builds the list
-//      of activated groups with their token masks,
+//   2. gets the gate s[M,G] (Eq. 7's W2 projection): computes all of it from the L2-resident
+//      gate matrix, or, where that takes longer than a hand-over between the workgroups, its
+//      share of the groups, and reads the others' scores (kGateShared); selects the g best
+//      groups per token and builds the list of activated groups with their token masks,
 //   3. streams its share of the activated rows: a wave takes a batch of consecutive rows of
 //      one group at a time, sixteen 1 KB non-temporal loads whatever the rows' length (SEGS
 //      loads per row, 16 / SEGS rows: one row of 16 KB up to eight rows of 2 KB), and dots
@@ -17,7 +17,8 @@
 //      logit beats the wave's current k-th,
 //   5. publishes its k best per token; the workgroup that arrives last merges all
 //      workgroups' lists and writes the result.
-// The logits row never exists in memory.  No workgroup ever waits for another.
+// The logits row never exists in memory.  No workgroup depends on another's progress: the only wait,
+// for the shared gate's scores, is bounded, and who gives up computes them.
 //
 // Log-probability mode (LP, Eq. 8: log p(x) = log p_router(n) + z[x] - lse_n, the softmax
 // taken inside each selected group): a workgroup streams rows of one group only, the
@@ -64,9 +65,16 @@ constexpr int kCollectMax = kTopkLdsMax;       // entries per token, at most
 // collected rows is that for D = 8, which the others do not exceed.
 constexpr int kDealFew = 8;
 constexpr int kLpGroupCounters = coral_ctrl::kLpGroupArrival - coral_ctrl::kFusedArrival;   // from p.counter
-// How the gate (step 2a) is computed: on the vector units, or on the matrix cores (16-bit
-// storage, four tokens or more).
-enum GateMode { kGateVector = 0, kGateMfma = 1 };
+// How the gate (step 2a) is computed: by every workgroup for itself, on the vector units or on the matrix
+// cores (16-bit storage, four tokens or more), or shared between the workgroups (see fused_gate_shared in
+// coral_lmhead.hip).  The LDS plan goes by the first two whichever runs.
+enum GateMode { kGateVector = 0, kGateMfma = 1, kGateShared = 2 };
+// Shared gate: its words behind FusedParams::counter, and how often a score is asked for (about 1 us each)
+// before the workgroup computes the gate itself.
+constexpr int kGateScoresAt = coral_ctrl::kGateScores - coral_ctrl::kFusedArrival;
+constexpr int kGateDoneAt = coral_ctrl::kGateDone - coral_ctrl::kFusedArrival;
+constexpr int kGatePolls = 48;
+static_assert(coral_ctrl::kGateScoreWords <= kFusedBlock * 4, "a thread reads four scores");
 constexpr int kGateTileFloats = 256;          // a wave's partial 16 x 16 tile
 
 struct FusedParams {
@@ -90,7 +98,8 @@ struct FusedParams {
     float* next_score;          // [n_next]
     int n_next;
     unsigned int* counter;      // arrival counter, zero between calls; the log-probability
-                                // mode also uses words kLpGroupCounters .. + 63, zero as well
+                                // mode also uses words kLpGroupCounters .. + 63, the shared gate
+                                // kGateDoneAt and kGateScoresAt .. + M G - 1, zero as well
     int32_t* topk_ids;          // [M, k]
     float* topk_logits;         // [M, k]
     int M, V, G, g, k;
@@ -364,7 +373,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     constexpr int ROWS = fused_rows(SEGS);
     extern __shared__ uint4 smem[];
     char* lds = reinterpret_cast<char*>(smem);
-    const FusedLds lay = fused_lds_layout(p.M, p.G, p.g, p.k, p.jp, DENSE, GATE, LP, p.cap);
+    const FusedLds lay = fused_lds_layout(p.M, p.G, p.g, p.k, p.jp, DENSE, GATE != kGateShared ? GATE : DT == kF32 || p.M <= 3 ? kGateVector : kGateMfma, LP, p.cap);
     uint4* hs = reinterpret_cast<uint4*>(lds + lay.o_hidden);
     Cand* lists = reinterpret_cast<Cand*>(lds + lay.o_lists);
     float* s_lds = reinterpret_cast<float*>(lds + lay.o_s);
@@ -388,7 +397,10 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     const int M = p.M, k = p.k;
 
     // batch counter, see step 3: a wave's first batch is fixed (i = wave), the others are drawn
-    if (threadIdx.x == 0) flags[2] = LP ? 0 : p.stream_waves;
+    if (threadIdx.x == 0) {
+        flags[2] = LP ? 0 : p.stream_waves;
+        flags[3] = 0;                                  // shared gate: whether a score did not come in time
+    }
     if ((LP || p.cap) && (int)threadIdx.x < p.M) collect_count[threadIdx.x] = 0;     // (seen by all after the gate's barriers)
     // ---- 1. hidden vectors: requested first, written to LDS only after the grouped
     // variants have requested their first gate rows as well (loads return in order, so the
@@ -451,7 +463,87 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         __syncthreads();
     } else {
         for (int n = threadIdx.x; n < p.G; n += kFusedBlock) mask_lds[n] = 0ull;
-        if (GATE != kGateVector) {
+        if (GATE == kGateShared) {
+            // ---- 2a. every workgroup computes the scores of its share of the groups (blockIdx, blockIdx +
+            // #workgroups, ...; one wave a (group, token) pair at a time, the row's first request in flight
+            // with the hidden vectors), publishes them and reads everyone's.  A word is its own flag: it is
+            // zero between calls, and a score of +0 is published as -0.  They are read with
+            // 16-byte loads past the caches, a wave's 256 words in one request; four scores of one group
+            // are neighbours, so that a workgroup's stores touch one line: with a word per
+            // load and stores scattered over the lines of all groups the hand-over took 4 us longer
+            // than with these (256 workgroups ask for the same lines while the stores are on their way).
+            // Bounded: the workgroups before this one may not be running yet where other kernels
+            // hold the compute units.  After kGatePolls requests the workgroup computes all scores itself,
+            // in the same loop, hence with the same bits.
+            uint4 ga[SEGS];
+            auto load_gate_row = [&](int n) {
+                int left = p.n_vec - lane;
+                asm volatile("" : "+v"(left));
+#pragma unroll
+                for (int j = 0; j < SEGS; ++j) {
+                    ga[j] = make_uint4(0, 0, 0, 0);
+                    if (j * kWave < left) ga[j] = p.gate_W[(size_t)n * p.n_vec + j * kWave + lane];
+                }
+            };
+            int first_n = blockIdx.x, step_n = gridDim.x;
+            int pairs = (int)blockIdx.x < p.G ? ((p.G - 1 - (int)blockIdx.x) / (int)gridDim.x + 1) * M : 0;
+            if (wave < pairs) load_gate_row(first_n + wave / M * step_n);
+            hidden_commit(0);
+            small_commit();
+            hidden_rest();
+            __syncthreads();
+            unsigned* words = p.counter + kGateScoresAt;       // [G][M]
+            const int n_words = M * p.G;
+#pragma unroll 1
+            for (bool alone = false;; alone = true) {
+                for (int q = wave; q < pairs; q += kFusedWaves) {      // wave-uniform
+                    const int i = q / M, m = q - i * M, n = first_n + i * step_n;
+                    if (alone || q != wave) load_gate_row(n);
+                    float s = 0.f;
+#pragma unroll
+                    for (int j = 0; j < SEGS; ++j)
+                        if (j < p.jp) s = dot_vec<DT>(ga[j], hs[m * hs_stride + j * kWave + lane], s);
+                    s = wave_sum(s) + bias_lds[n];
+                    if (lane == 0) s_lds[m * p.G + n] = s == 0.f ? -0.f : s;
+                }
+                __syncthreads();
+                if (alone) break;
+                if (wave == 0)                             // (one wave: gate_through waits for its stores)
+                    for (int q = lane; q < pairs; q += kWave) {
+                        const int i = q / M, m = q - i * M, n = first_n + i * step_n;
+                        __hip_atomic_store(words + n * M + m, __float_as_uint(s_lds[m * p.G + n]), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                if (wave * 4 * kWave < n_words) {          // wave-uniform
+                    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(words, 0, n_words * (int)sizeof(unsigned), 0x00027000);
+                    int ln = lane;
+                    asm volatile("" : "+v"(ln));
+                    const int e0 = (wave * kWave + ln) * 4;
+                    u32x4_t v;
+                    bool all = false;
+                    for (int i = 0; i < kGatePolls; ++i) {
+                        v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, e0 * (int)sizeof(unsigned), 0, 16 /* sc1: from memory */);
+                        asm volatile("" ::: "memory");     // (the request is made again)
+                        all = true;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) all = all && (e0 + c >= n_words || v[c] != 0u);
+                        if (__ballot(!all) == 0ull) break;
+                        __builtin_amdgcn_s_sleep(2);
+                    }
+                    if (!all) flags[3] = 1;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int e = e0 + c, n = e / M;
+                        if (e < n_words) s_lds[(e - n * M) * p.G + n] = __uint_as_float(v[c]);
+                    }
+                }
+                __syncthreads();
+                if (!uni(flags[3])) break;                 // block-uniform
+                first_n = 0;
+                step_n = 1;
+                pairs = n_words;
+            }
+        } else if (GATE == kGateMfma) {
             // ---- 2a. gate on the matrix cores: s[16 groups x 16 tokens] tiles, the H
             // columns split over the 16 waves in steps of 32 (v_mfma_f32_16x16x32_bf16:
             // lane l feeds row l%16, columns 8*(l/16)..+8 of both operands and receives
@@ -838,7 +930,26 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     };
     // Workgroups without a batch leave here; the last merge goes by the others' lists.
     const int P_act = LP ? uni(wgstart[uni(flags[0])]) : min((int)gridDim.x, (total_batches + (1 << deal) - 1) >> deal);
-    if ((int)blockIdx.x >= P_act) return;              // block-uniform
+    // Shared gate: the workgroup has read the scores and its own are in memory; the last of all
+    // workgroups that gets here, those without a batch among them, leaves the words at zero for the next call.
+    auto gate_through = [&]() {
+        if (GATE != kGateShared || wave != 0) return;
+        __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wave's stores are out
+        int through = 0;
+        if (lane == 0)
+            through = (int)__hip_atomic_fetch_add(p.counter + kGateDoneAt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (uni(through) != (int)gridDim.x - 1) return;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));                   // (see wave_merge_lists)
+        for (int e = ln; e < M * p.G; e += kWave)
+            __hip_atomic_store(p.counter + kGateScoresAt + e, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0)
+            __hip_atomic_store(p.counter + kGateDoneAt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if ((int)blockIdx.x >= P_act) {                    // block-uniform
+        gate_through();
+        return;
+    }
     int u = 0;
     int lp_lo = 0, lp_nwg = 0;
     // The (max, sum of exp) pieces are kept per batch and summed in batch order at the end: a
@@ -943,6 +1054,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         bm = nbm;
     }
 
+    gate_through();
     // ---- 5. rank the workgroup's candidates, publish, last workgroup merges all
     // the hidden vectors are no longer needed: their LDS is the ranking scratch
     unsigned long long* rank_buf = reinterpret_cast<unsigned long long*>(lds + lay.o_hidden) + (size_t)wave * kWave;

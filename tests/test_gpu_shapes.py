@@ -424,3 +424,42 @@ def test_tile_kernels_past_the_caches_and_through_them(coral, dtype, H, V, M, pa
         row_bytes = H * (4 if dtype == "f32" else 2)
         activated = np.unique(out[2]).size * (V // 8) * row_bytes
         assert (activated < 128e6) == (strong > 0)
+
+
+# H, groups, tokens where the single launch's gate is shared between the workgroups: both sides of a workgroup
+# per group (256) and of the scores' words (4096), one (group, token) pair per workgroup to four per wave,
+# rows of one to sixteen wave loads; the last two tokens counts of a line: shared and own on one workspace
+SHARED_GATE = [("bf16", 8192, 8, (4, 1)), ("f16", 4096, 65, (1, 5, 16)), ("bf16", 4096, 300, (1, 3, 13, 14)),
+               ("f32", 4096, 17, (5, 1)), ("f32", 1000, 64, (16, 20, 2)), ("bf16", 520, 128, (4, 32, 33)), ("f16", 6664, 40, (4, 2))]
+
+
+@pytest.mark.parametrize("dtype,H,G,Ms", SHARED_GATE)
+def test_gate_shared_between_workgroups(coral, dtype, H, G, Ms):
+    sizes = [9 + (7 * n) % 11 for n in range(G)]
+    V, g, k = sum(sizes), 3, 6
+    cfg = HeadConfig(f"gate{G}", dtype, H, V, G, g, (1,), k, 900 + G, True)
+    dh = DeviceHead(coral, ragged_head(cfg, sizes))
+    code = {"f32": coral.CORAL_F32, "bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
+    ws = coral.alloc_workspace(max(Ms), H, V, G, g, k, code)
+    for M in Ms + Ms:
+        hidden = make_hidden(cfg, M, M)
+        print(f"case {cfg.name} {dtype} H={H} M={M}", flush=True)
+        assert coral.coral_lmhead_path(False, M, H, V, G, g, k, code) == 1
+        d_hidden = coral.device_tensor(hidden, dtype)
+        for logprob, check in ((False, check_grouped), (True, check_logprob)):
+            out = coral.coral_lmhead_grouped(d_hidden, dh.gate_W, dh.bias, dh.lm_W, dh.gi, g, k, workspace=ws, logprob=logprob)
+            torch.cuda.synchronize()
+            check(dh, hidden, g, k, tuple(x.cpu().numpy() for x in out))
+
+
+def test_shared_gate_with_scores_of_zero(coral):
+    """All-zero hidden vectors: every score is +0, the word that stands for none; the lower groups win."""
+    sizes = [40] * 48
+    cfg = HeadConfig("gate0", "bf16", 8192, sum(sizes), 48, 4, (1,), 5, 930, True)
+    head = ragged_head(cfg, sizes)
+    head.gate_bias[:] = 0.0
+    dh = DeviceHead(coral, head)
+    for _ in range(2):
+        ids, logits, sel = run_grouped(coral, dh, np.zeros((6, 8192), np.uint16), 4, 5)
+        assert np.array_equal(sel, np.tile(np.arange(4), (6, 1))) and not logits.any()
+        assert np.array_equal(ids, np.tile(np.sort(head.group_rows[:160])[:5], (6, 1)))
