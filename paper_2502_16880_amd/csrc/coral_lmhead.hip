@@ -347,28 +347,15 @@ double expected_blocks(int M, int V, int G, int g) {
     return expected_groups(M, G, g) * ((V / G + kTileRows - 1) / kTileRows);
 }
 
-// Rows beyond 8 KB, whose gate every workgroup of the single launch computes by itself from more
-// bytes than L2 serves quickly: taken while groups and tokens are few, or where the matrix-core path
-// is the other choice, whose launches cost more with few tokens.  us, the multi-kernel paths against
-// the single launch (two of G groups each):
-//   bf16 H = 4616, V = 128100, one token, G = 128 40, 30, G = 300 38, 46; 3 tokens, 100 45, 41, 200
-//   41, 52; 6 tokens, 80 72, 62, 100 57, 67, 300 46, 103; 9 tokens, 80 106, 77, 200 68, 86;
-//   fp32 H = 4096, V = 64000, one token, 128 40, 34, 200 39, 43; 6 tokens, 80 72, 61, 128 54, 66;
-//   log-probabilities (three groups each), H = 4616, one token, 64 35, 34, 128 35, 37; 6 tokens, 32
-//   119, 99, 64 79, 80, 100 75, 84; H = 6664, V = 99984, two of 48 groups, 4 tokens 59, 64; up to 40
-//   groups and 6 to 14 tokens, 18 heads of each pair, 0.55 to 0.88 of the time on average;
-//   k = 33 (the staged merges go by whole lists), fp32 H = 2564, five of 65 groups, 8 tokens 220, 98;
-//   matrix-core path: H = 5120, one token, 64 44, 25, 6 tokens, 32 97, 83.  Only where its blocks
-//   fill a good part of one round over the compute units it is ahead: 6 tokens, 48 66, 73; 9 tokens,
-//   64 67, 76; log-probabilities, H = 8192, 6 tokens, 64 101, 120.
-bool long_rows_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob) {
-    int um, lds;
-    if (tiles_fit(M, H, V, G, g, k, dt, &um, &lds) && (!logprob || G <= kWave)) {
-        const double blocks = expected_blocks(M, V, G, g);
-        return M < 4 || k > 10 || blocks <= (logprob ? 110 : 145) || blocks > kMaxWorkgroups + 6;
-    }
-    return G <= (!logprob ? 64 : M >= 7 ? 60 : 40) || G + 6 * M <= (logprob ? 80 : 135) + (k > 10 ? 8 * (k - 10) : 0);
-}
+// Rows beyond 8 KB: the single launch takes them unless there are more scores than the workgroups can share
+// (every one of them would then compute hundreds of groups' scores by itself).  us, the multi-kernel paths
+// against the single launch with the shared gate, over 260 random heads (8 to 128 groups, 1 to 14 tokens) that
+// the own gate had kept there: 1.45 times as fast on average, one of them 2 % slower; bf16 H = 7296, 117
+// groups, 6 tokens 76, 36; fp32 H = 3072, 109 groups, 5 tokens 56, 28; f16 H = 5120, 20 groups, 11 tokens
+// 65, 63; log-probabilities, f16 H = 6144, 128 groups, 8 tokens 74, 29; bf16 H = 5632, 83 groups, 9
+// tokens 131, 134.  With few groups and tokens the gate is not shared, and cheap: bf16 H = 4616, 128100
+// rows, one token, 100 groups 40, 30; 3 tokens, 80 groups 45, 41.
+bool long_rows_take_fused(int M, int G) { return M * G <= coral_ctrl::kGateScoreWords; }
 
 // Log-probability mode: whether the single-launch kernel runs a call.  (Beyond 32 tokens only where
 // the tile kernels cannot: 256-wide head, V = 900000, 36 tokens, 2 of 32 groups 180 us here, 707 us
@@ -376,7 +363,7 @@ bool long_rows_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype 
 bool logprob_takes_fused(int M, int H, int V, int G, int g, int k, int jp, coral_dtype dt) {
     int um, lds;
     return fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups) &&
-           (jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, true)) &&
+           (jp <= 8 || long_rows_take_fused(M, G)) &&
            (M <= kLogprobFusedMaxTokens || !tile_kernels_fit(M, H, V, G, g, k, dt, &um, &lds));
 }
 
@@ -587,7 +574,7 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
         return pl;
     }
     const bool fused_ok =
-        fused_rows_fit(jp) && (dense || jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, false)) &&
+        fused_rows_fit(jp) && (dense || jp <= 8 || long_rows_take_fused(M, G)) &&
         fused_lds_layout(M, dense ? 0 : G, dense ? 0 : g, k, jp, dense,
                          fused_gate_mode(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp, dt)).total <= kLdsLimit;
     const bool tiles_ok =
