@@ -132,7 +132,7 @@ int coral_lmhead_logprob_path(int M, int H, int V, int G, int g, int k, coral_dt
  * rows to the workgroups of the tile path, and hold the gate's scores where the
  * workgroups of the single launch share the gate.  A call that fails with CORAL_ERR_HIP may
  * leave them non-zero: prepare the workspace again before reusing it.
- *   workspace [device], 256-byte aligned, at least 256 bytes.
+ *   workspace [device], 256-byte aligned, of coral_lmhead_workspace_bytes.
  */
 coral_status coral_lmhead_workspace_init(void *workspace, size_t workspace_bytes,
                                          void *hip_stream);

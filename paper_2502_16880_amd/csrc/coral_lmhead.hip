@@ -870,12 +870,11 @@ extern "C" int coral_lmhead_logprob_path(int M, int H, int V, int G, int g, int 
 
 extern "C" coral_status coral_lmhead_workspace_init(void* workspace, size_t workspace_bytes,
                                                     void* hip_stream) {
-    // (a workspace that a call takes holds all control words)
-    coral_status st = check_workspace(workspace, workspace_bytes, kCountedCtrlBytes);
+    coral_status st = check_workspace(workspace, workspace_bytes, kCtrlBytes);
     if (st != CORAL_OK) return st;
-    const int words = (int)((workspace_bytes < kCtrlBytes ? workspace_bytes : kCtrlBytes) / 4);
-    hipLaunchKernelGGL(k_zero_words, dim3((words + 255) / 256), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
-                       static_cast<unsigned int*>(workspace), words);
+    hipLaunchKernelGGL(k_zero_words, dim3((kCtrlBytes / 4 + 255) / 256), dim3(256), 0,
+                       static_cast<hipStream_t>(hip_stream), static_cast<unsigned int*>(workspace),
+                       (int)(kCtrlBytes / 4));
     return launch_status();
 }
 
