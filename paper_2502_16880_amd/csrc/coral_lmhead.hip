@@ -347,15 +347,29 @@ double expected_blocks(int M, int V, int G, int g) {
     return expected_groups(M, G, g) * ((V / G + kTileRows - 1) / kTileRows);
 }
 
-// Rows beyond 8 KB: the single launch takes them unless there are more scores than the workgroups can share
-// (every one of them would then compute hundreds of groups' scores by itself).  us, the multi-kernel paths
-// against the single launch with the shared gate, over 260 random heads (8 to 128 groups, 1 to 14 tokens) that
-// the own gate had kept there: 1.45 times as fast on average, one of them 2 % slower; bf16 H = 7296, 117
-// groups, 6 tokens 76, 36; fp32 H = 3072, 109 groups, 5 tokens 56, 28; f16 H = 5120, 20 groups, 11 tokens
-// 65, 63; log-probabilities, f16 H = 6144, 128 groups, 8 tokens 74, 29; bf16 H = 5632, 83 groups, 9
-// tokens 131, 134.  With few groups and tokens the gate is not shared, and cheap: bf16 H = 4616, 128100
-// rows, one token, 100 groups 40, 30; 3 tokens, 80 groups 45, 41.
-bool long_rows_take_fused(int M, int G) { return M * G <= coral_ctrl::kGateScoreWords; }
+// Rows beyond 8 KB: the single launch takes them where the workgroups can share the gate's scores.  us, the
+// general path against it, over the heads off the matrix-core path among 380 random ones (8 to 1000 groups, 1 to
+// 14 tokens) that the own gate had kept there: 1.5 to 1.9 times as fast on average, none slower by more than 2 %;
+// bf16 H = 7296, 117 groups, 6 tokens 76, 36; fp32 H = 3072, 109 groups, 5 tokens 56, 28; log-probabilities, f16
+// H = 6144, 128 groups, 8 tokens 74, 29; bf16 H = 5632, 83 groups, 9 tokens 131, 134.
+// The lines from before that stay where
+//   - the matrix-core path is the other choice: taken while tokens are few or where its blocks do not fill a
+//     good part of one round over the compute units (H = 5120, 6 tokens, 32 groups 97, 83; with the shared gate
+//     the single launch would be ahead beyond them too, by 4 to 27 %: 7 tokens, 126 groups 79, 68);
+//   - the last of a row's segments is filled to less than a quarter, or there are more scores than words for
+//     them: few groups and tokens, or many candidates (the staged merges go by whole lists; own gate, H = 4616,
+//     128100 rows, one token, 128 groups 40, 30, 300 groups 38, 46; 6 tokens, 80 groups 72, 62, 300 groups
+//     46, 103; log-probabilities, 6 tokens, 64 groups 79, 80).  Both are pinned by the routes' tests.
+bool long_rows_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob) {
+    int um, lds;
+    if (tiles_fit(M, H, V, G, g, k, dt, &um, &lds) && (!logprob || G <= kWave)) {
+        const double blocks = expected_blocks(M, V, G, g);
+        return M < 4 || k > 10 || blocks <= (logprob ? 110 : 145) || blocks > kMaxWorkgroups + 6;
+    }
+    const int n_vec = H / (is_16bit(dt) ? 8 : 4), last = n_vec % kWave;
+    if (M * G <= coral_ctrl::kGateScoreWords && (last == 0 || last >= kWave / 4)) return true;
+    return G <= (!logprob ? 64 : M >= 7 ? 60 : 40) || G + 6 * M <= (logprob ? 80 : 135) + (k > 10 ? 8 * (k - 10) : 0);
+}
 
 // Log-probability mode: whether the single-launch kernel runs a call.  (Beyond 32 tokens only where
 // the tile kernels cannot: 256-wide head, V = 900000, 36 tokens, 2 of 32 groups 180 us here, 707 us
@@ -363,7 +377,7 @@ bool long_rows_take_fused(int M, int G) { return M * G <= coral_ctrl::kGateScore
 bool logprob_takes_fused(int M, int H, int V, int G, int g, int k, int jp, coral_dtype dt) {
     int um, lds;
     return fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups) &&
-           (jp <= 8 || long_rows_take_fused(M, G)) &&
+           (jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, true)) &&
            (M <= kLogprobFusedMaxTokens || !tile_kernels_fit(M, H, V, G, g, k, dt, &um, &lds));
 }
 
@@ -574,7 +588,7 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
         return pl;
     }
     const bool fused_ok =
-        fused_rows_fit(jp) && (dense || jp <= 8 || long_rows_take_fused(M, G)) &&
+        fused_rows_fit(jp) && (dense || jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, false)) &&
         fused_lds_layout(M, dense ? 0 : G, dense ? 0 : g, k, jp, dense,
                          fused_gate_mode(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp, dt)).total <= kLdsLimit;
     const bool tiles_ok =
