@@ -291,9 +291,16 @@ bool fused_gate_shared(int M, int G, int n_vec, coral_dtype dt) {
     return own > 3.5;
 }
 
-// Rows the single-launch kernel takes: up to 8 KB, and from 10 to 16 KB.  (Nine of sixteen
-// segments in use leave almost half of the loads of a batch empty: the multi-kernel path's.)
-bool fused_rows_fit(int jp) { return jp <= 8 || (jp >= 10 && jp <= kFusedMaxSegs); }
+// Rows the single-launch kernel takes (by their 16-byte vectors): up to 8 KB, and from 8.25 to 16 KB.  (Rows of
+// nine segments leave seven of a batch's sixteen loads empty, and are still the faster ones: us, multi-kernel
+// paths against single launch, over 240 random heads of 4104 to 4608 columns (fp32: half): grouped 1.68
+// times as fast on average, log-probabilities 1.41, the worst 3 % slower; bf16 H = 4352, 62 groups, 7 tokens,
+// k = 64 139, 26, H = 4608, 56 groups, 11 tokens 55, 50; dense f16 H = 4224, 7 tokens, k = 33 149, 36.  Below
+// a quarter of the ninth segment they would be as well (1.5 and 2.5 times, two heads): these widths keep the
+// general path, whose form of them is pinned.  The dense head's products with eight tokens and more take longer
+// than the tile kernels: f16 H = 4480, 94129 rows, 9 tokens 146, 166, bf16 H = 4352, 24624 rows, 15 tokens 49, 70.)
+bool fused_rows_fit(int n_vec) { return n_vec <= 8 * kWave || (n_vec >= 8 * kWave + kWave / 4 && n_vec <= kFusedMaxSegs * kWave); }
+constexpr int kNineSegsDenseTokens = 7;
 
 // Log-probability mode: beyond 32 tokens the single-launch kernel's per-wave lists (one per token,
 // hardly ever filled) and per-token pieces cost more than the tile kernels' three launches
@@ -307,7 +314,7 @@ inline long long max_union(int M, int G, int g) { return (long long)M * g < G ? 
 // its own and ranks the groups in one wave: at most 64 activated groups, fewer than half the
 // workgroups; a token's g lists share the LDS of one wave's lists.
 bool fused_logprob_fits(int M, int G, int g, int k, int jp, coral_dtype dt, int workgroups) {
-    if (!fused_rows_fit(jp) || g > kFusedWaves) return false;
+    if (g > kFusedWaves) return false;
     const long long um = max_union(M, G, g);
     if (um > kWave || 2 * um > workgroups) return false;
     return fused_lds_layout(M, G, g, k, jp, false, fused_gate_mode(false, M, G, g, k, jp, dt, true), true)
@@ -376,7 +383,7 @@ bool long_rows_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype 
 // with the staged kernels, which are left then.)
 bool logprob_takes_fused(int M, int H, int V, int G, int g, int k, int jp, coral_dtype dt) {
     int um, lds;
-    return fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups) &&
+    return fused_rows_fit(H / (is_16bit(dt) ? 8 : 4)) && fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups) &&
            (jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, true)) &&
            (M <= kLogprobFusedMaxTokens || !tile_kernels_fit(M, H, V, G, g, k, dt, &um, &lds));
 }
@@ -470,7 +477,7 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
         if (!cap) cap = kFusedWaves * k;               // the lists' own size
     }
     const FusedLds F = fused_lds_layout(M, G, g, k, jp, dense, gate, logprob, cap);
-    if (!fused_rows_fit(jp) || F.total > kLdsLimit) return CORAL_ERR_UNSUPPORTED;   // not reached
+    if (!fused_rows_fit(n_vec) || F.total > kLdsLimit) return CORAL_ERR_UNSUPPORTED;   // not reached
     if (jp > 8 && gate == kGateMfma && M > 16) return CORAL_ERR_UNSUPPORTED;        // not reached: LDS
     FusedParams p = {};
     p.cap = cap;
@@ -588,7 +595,7 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
         return pl;
     }
     const bool fused_ok =
-        fused_rows_fit(jp) && (dense || jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, false)) &&
+        fused_rows_fit(n_vec) && (dense ? jp != 9 || M <= kNineSegsDenseTokens : jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, false)) &&
         fused_lds_layout(M, dense ? 0 : G, dense ? 0 : g, k, jp, dense,
                          fused_gate_mode(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp, dt)).total <= kLdsLimit;
     const bool tiles_ok =
