@@ -571,6 +571,39 @@ bool general_tiles_faster(int M, int V, int n_vec, int k, coral_dtype dt) {
            4.0 + 0.9 * (7.7 + 0.42 * M + 98.0 * dots + 7.3 * rows + 0.041 * mb + 0.097 * k);
 }
 
+// The static scratch array (logit ranking only, no table of pieces).  Which shapes it takes is a
+// matter of sizes that callers rely on, and does not move with the kernels that run them: the
+// published and the staged lists must fit; or, for 16-bit heads of whole 512-column chunks whose rows
+// are beyond 8 KB or whose tokens and lists do not share the LDS of a workgroup with 24 KB for
+// merges, the tile path's arrays with 128-row blocks.
+size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
+    int um, lds;
+    bool tiles = tiles_fit(M, H, V, G, g, k, dt, &um, &lds);
+    const int jp = (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave;
+    if (tiles && jp <= 8) {
+        const FusedLds F = fused_lds_layout(M, G, g, k, jp, false, fused_gate_mode(false, M, G, g, k, jp, dt));
+        const int hidden = M * hidden_lds_stride(jp) * (int)sizeof(uint4), merges = 24 * 1024;
+        tiles = F.total - F.o_lists + (hidden > merges ? hidden : merges) > kLdsLimit;
+    }
+    return make_layout(M, V, G, g, k, Pieces{}, {tiles ? Tiles::kOwn : Tiles::kNone, false},
+                       tiles ? LayoutFor::kCounted : LayoutFor::kWorkspace).total - (kCtrlBytes - kCountedCtrlBytes);
+}
+
+// Grouped heads that fit the single launch, with many tokens: whether the tile kernels take less time.  16 bits,
+// from 37 tokens on (the single launch dots every row with each of its group's tokens on the vector units and
+// ranks every token's candidates in every workgroup).  Single launch against tiles over 450 random heads of 8 to
+// 152 K rows and 256 columns and more: from 37 tokens on 1.35 times as fast on average, 1.00 to 1.74 (us: bf16
+// H = 256, 48720 rows, 53 tokens 41, 28; H = 1024, 35310 rows, 37 tokens 38, 36); 33 to 36 tokens 1.18, but 0.87 to
+// 1.4 (H = 816, 146627 rows, 35 tokens 71, 82); 25 to 32 tokens 1.07, 0.85 to 1.40; up to 16 tokens 0.80; fp32
+// 0.87.  Not where the entry point without a workspace would have to go through the tokens in batches,
+// reading the weights again for each.
+bool grouped_tiles_faster(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
+    if (!is_16bit(dt) || V < 8192 || H < 256 || M < 37) return false;
+    const Tiles kind = H % (kChunkVecs * 8) == 0 ? Tiles::kOwn : Tiles::kGeneral;
+    return make_layout(M, V, G, g, k, Pieces{}, {kind, false}, LayoutFor::kTiles).total <= kStaticArrayBytes ||
+           static_counted_bytes(M, H, V, G, g, k, dt) > kStaticScratchBytes;
+}
+
 // The general path takes what the other two do not: fp32 rows beyond the single-launch kernel,
 // widths that are no multiple of 512, more than 64 groups with log-probabilities.  It runs the
 // tile kernels too, whose column tail is then guarded and whose fp32 form multiplies in full fp32
@@ -609,8 +642,9 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
                        !collect_cap(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp,
                                     fused_gate_mode(dense, M, G, g, k, jp, dt), dense ? V : (V + G - 1) / G,
                                     kMaxWorkgroups, &single);
-    const bool many = dense && fused_ok && V >= 8192 && M >= (is_16bit(dt) ? 16 : 24) && general_tiles_faster(M, V, n_vec, k, dt);
-    if (((dense && dense_prefers_tiles(M, V)) || lists) && tiles_ok)
+    const bool many = fused_ok && (dense ? V >= 8192 && M >= (is_16bit(dt) ? 16 : 24) && general_tiles_faster(M, V, n_vec, k, dt)
+                                         : grouped_tiles_faster(M, H, V, G, g, k, dt));
+    if (((dense ? dense_prefers_tiles(M, V) : many) || lists) && tiles_ok)
         pl.path = 2;
     else if ((lists || many) && tile_kernels_fit(M, H, V, dense ? 0 : G, dense ? 0 : g, k, dt, &pl.tile_umax, &pl.tile_lds))
         pl.path = 0;
@@ -900,24 +934,6 @@ extern "C" coral_status coral_lmhead_workspace_init(void* workspace, size_t work
 }
 
 namespace {
-
-// The static scratch array (logit ranking only, no table of pieces).  Which shapes it takes is a
-// matter of sizes that callers rely on, and does not move with the kernels that run them: the
-// published and the staged lists must fit; or, for 16-bit heads of whole 512-column chunks whose rows
-// are beyond 8 KB or whose tokens and lists do not share the LDS of a workgroup with 24 KB for
-// merges, the tile path's arrays with 128-row blocks.
-size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
-    int um, lds;
-    bool tiles = tiles_fit(M, H, V, G, g, k, dt, &um, &lds);
-    const int jp = (H / (is_16bit(dt) ? 8 : 4) + kWave - 1) / kWave;
-    if (tiles && jp <= 8) {
-        const FusedLds F = fused_lds_layout(M, G, g, k, jp, false, fused_gate_mode(false, M, G, g, k, jp, dt));
-        const int hidden = M * hidden_lds_stride(jp) * (int)sizeof(uint4), merges = 24 * 1024;
-        tiles = F.total - F.o_lists + (hidden > merges ? hidden : merges) > kLdsLimit;
-    }
-    return make_layout(M, V, G, g, k, Pieces{}, {tiles ? Tiles::kOwn : Tiles::kNone, false},
-                       tiles ? LayoutFor::kCounted : LayoutFor::kWorkspace).total - (kCtrlBytes - kCountedCtrlBytes);
-}
 
 // The tile kernels' arrays for M tokens in the static scratch.
 Layout static_tiles_layout(const PathPlan& plan, int M, int V, int G, int g, int k) {

@@ -475,3 +475,15 @@ def test_rows_of_nine_segments(coral, dtype, H):
         assert coral.coral_lmhead_path(False, M, H, cfg.V, cfg.G, 4, 9, code) == 1
         assert coral.coral_lmhead_path(True, M, H, cfg.V, 0, 0, 9, code) == 1 or M > 7
     check_all(coral, cfg, sizes, (1, 3, 7, 9))
+
+
+@pytest.mark.parametrize("dtype,H,M,path", [("bf16", 512, 37, 2), ("f16", 264, 64, 0), ("bf16", 1000, 38, 0), ("bf16", 512, 36, 1), ("f32", 512, 40, 1)])
+def test_grouped_heads_with_many_tokens(coral, dtype, H, M, path):
+    """Either side of the rule by tokens and storage type; whole and partly filled chunks."""
+    sizes = [300 + 37 * n for n in range(20)]
+    cfg = HeadConfig(f"many{H}", dtype, H, sum(sizes), 20, 3, (M,), 8, 980 + H + M, True)
+    code = {"f32": coral.CORAL_F32, "bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
+    assert coral.coral_lmhead_path(False, M, H, cfg.V, 20, 3, 8, code) == path
+    dh = DeviceHead(coral, ragged_head(cfg, sizes))
+    hidden = make_hidden(cfg, M, M)
+    check_grouped(dh, hidden, 3, 8, run_grouped(coral, dh, hidden, 3, 8))
