@@ -99,9 +99,9 @@ size_t coral_lmhead_workspace_bytes(int M, int H, int V, int G, int g, int k,
  * 0 = general path (one launch per stage: the tile path's kernels in a form for any storage
  * type and width, or staged kernels on the vector units where these do not fit or are
  * slower), 1 = single-launch path (gate, selection, row streaming and top-k of section 3.3 in
- * one persistent kernel: rows of up to 8 KB whose token batch fits on chip, or of 10 to 16 KB
- * with few groups and tokens; not 16 tokens and more dense, 32 grouped, whose candidates do
- * not fit beside them), 2 = matrix-core tile path (bf16 or fp16, H a multiple of 512, weights
+ * one persistent kernel: rows of up to 16 KB (but 8 to 8.25) whose token batch fits on chip;
+ * not 16 tokens and more dense, 32 grouped, whose candidates do not fit beside them, nor 37
+ * and more grouped in 16 bits), 2 = matrix-core tile path (bf16 or fp16, H a multiple of 512, weights
  * below 4 GiB: groups shared by many tokens, the appendix's tree-decoding case, when the
  * hidden vectors do not fit on chip; dense head with 8 or more tokens and at least 65536
  * rows),
@@ -114,7 +114,7 @@ int coral_lmhead_path(int dense, int M, int H, int V, int G, int g, int k, coral
 /*
  * The same for coral_lmhead_grouped_logprob (Eq. 8's output): 1 = single-launch kernel
  * (at most 64 activated groups, min(M*g, G) <= 64, g <= 16, and its LDS plan fits; beyond 32
- * tokens only where the tile kernels do not fit; rows of 10 to 16 KB as above),
+ * tokens only where the tile kernels do not fit; rows of up to 16 KB as above),
  * 2 = matrix-core tile path (where that path's conditions hold and G <= 64; more groups go to
  * the general path's form of the same kernels),
  * 0 = general path, -1 = sizes not supported.  Host-only.
