@@ -122,17 +122,19 @@ int coral_lmhead_path(int dense, int M, int H, int V, int G, int g, int k, coral
 int coral_lmhead_logprob_path(int M, int H, int V, int G, int g, int k, coral_dtype dt);
 
 /*
- * Prepares a freshly allocated workspace: zeroes its control words (a small kernel
+ * Prepares a freshly allocated workspace: its control words (512 bytes) and, as far as
+ * workspace_bytes goes, the 16 KB behind them that hold the gate's scores (a small kernel
  * on hip_stream, no memset node, so it may be captured in a HIP graph).  Required
  * once before the first coral_lmhead_grouped / coral_lmhead_dense call that uses the
- * workspace; every completed call leaves the control words ready for the next one.
+ * workspace; every completed call leaves the words ready for the next one.
  * The control words count the workgroups that have published their partial top-k
  * lists, so that the last one can merge them (the per-token top-k of the appendix's
- * "Tree decoding" paragraph) without a further launch, hand out blocks of weight
- * rows to the workgroups of the tile path, and hold the gate's scores where the
- * workgroups of the single launch share the gate.  A call that fails with CORAL_ERR_HIP may
- * leave them non-zero: prepare the workspace again before reusing it.
- *   workspace [device], 256-byte aligned, of coral_lmhead_workspace_bytes.
+ * "Tree decoding" paragraph) without a further launch, and hand out blocks of weight
+ * rows to the workgroups of the tile path.  The scores are where the workgroups of the
+ * single launch share the gate; where they were not prepared, the first such call has
+ * every workgroup compute the gate, and prepares them.  A call that fails with
+ * CORAL_ERR_HIP may leave the words in use: prepare the workspace again before reusing it.
+ *   workspace [device], 256-byte aligned, at least 512 bytes.
  */
 coral_status coral_lmhead_workspace_init(void *workspace, size_t workspace_bytes,
                                          void *hip_stream);

@@ -1,7 +1,7 @@
-// Map of the control words at the start of the workspace (32-bit words, all zero between
-// calls; coral_lmhead_workspace_init zeroes them once, every kernel that uses one leaves it
-// zero again).  Plain constants so that a host compiler can include this file too: a test
-// builds the table below and checks that no two entries overlap and all lie inside the
+// Map of the control words at the start of the workspace (32-bit words, all but kGatePolls and
+// kGateGaveUp zero between calls; coral_lmhead_workspace_init prepares them once, every kernel that
+// uses one leaves it as it was).  Plain constants so that a host compiler can include this file too:
+// a test builds the table below and checks that no two entries overlap and all lie inside the
 // control area.
 #pragma once
 
@@ -13,16 +13,23 @@ struct Entry {
     int n_words;
 };
 
-constexpr int kWords = 128 + 4096;          // size of the control area in words (16.5 KB)
+constexpr int kWords = 128;                 // size of the control area in words (512 bytes)
 constexpr int kFusedArrival = 0;            // single-launch path: workgroups that have published
 constexpr int kGateSelectArrival = 8;       // tile path: per token tile, k_gate_select workgroups that
 constexpr int kGateSelectArrivalWords = 4;  //   have stored their scores (at most 4 token tiles)
 constexpr int kTileQueue = 4;               // tile path: next block of k_tiles
 constexpr int kLpGroupArrival = 64;         // log-probability mode: one counter per activated
 constexpr int kLpGroupArrivalWords = 64;    //   group (at most 64 in the single-launch kernel)
-constexpr int kGateDone = 1;                // single-launch path, shared gate: workgroups that have read the
-constexpr int kGateScores = 128;            //   scores, and the scores' bit patterns (0: not there yet),
-constexpr int kGateScoreWords = 4096;       //   group by group
+constexpr int kGateDone = 1;                // single-launch path, shared gate: workgroups that have read the scores,
+constexpr int kGatePolls = 2;               //   how often a workgroup asks for them at most (0: nobody has
+                                            //   cleared the score words yet; the next such call does),
+constexpr int kGateGaveUp = 3;              //   and how many workgroups had to compute the gate alone so far
+
+// Behind the control area: the shared gate's scores, group by group (bit patterns; 0: not there yet, and
+// so between calls).
+constexpr int kGateScores = kWords;
+constexpr int kGateScoreWords = 4096;
+constexpr int kPreparedWords = kWords + kGateScoreWords;
 
 constexpr Entry kMap[] = {
     {"fused_arrival", kFusedArrival, 1},
@@ -30,7 +37,8 @@ constexpr Entry kMap[] = {
     {"tile_queue", kTileQueue, 1},
     {"logprob_group_arrival", kLpGroupArrival, kLpGroupArrivalWords},
     {"gate_done", kGateDone, 1},
-    {"gate_scores", kGateScores, kGateScoreWords},
+    {"gate_polls", kGatePolls, 1},
+    {"gate_gave_up", kGateGaveUp, 1},
 };
 constexpr int kMapEntries = sizeof(kMap) / sizeof(kMap[0]);
 

@@ -41,21 +41,30 @@
 // ends; in host code the name is only a handle for hipGetSymbolAddress, never an address.
 constexpr size_t kStaticScratchBytes = (size_t)CORAL_NOALLOC_SCRATCH_BYTES;
 // The array is larger than what calls are counted by (static_counted_bytes): the statistics of blocks
-// processed in halves, of which half of the workgroups have one at most, and the control words beyond the
-// 512 bytes that were counted when calls' sizes became what callers rely on.
+// processed in halves, of which half of the workgroups have one at most, and the gate's scores behind the
+// 512 bytes of control words.
 constexpr int kMaxWorkgroups = 256;    // upper bound of the persistent kernels' grids
 constexpr size_t upper_stat_bytes(int M) { return (size_t)(kMaxWorkgroups / 2) * M * sizeof(float2); }
 constexpr size_t kCtrlBytes = coral_ctrl::kWords * sizeof(unsigned int);   // control words at the start of the workspace
-constexpr size_t kCountedCtrlBytes = 512;
-static_assert(kCtrlBytes % 256 == 0, "");
-constexpr size_t kStaticArrayBytes = kStaticScratchBytes + upper_stat_bytes(kMaxM) + kCtrlBytes - kCountedCtrlBytes;
+constexpr size_t kGateScoreBytes = coral_ctrl::kGateScoreWords * sizeof(unsigned int);   // and the scores behind them
+static_assert(kCtrlBytes % 256 == 0 && kGateScoreBytes % 256 == 0, "");
+constexpr size_t kStaticArrayBytes = kStaticScratchBytes + upper_stat_bytes(kMaxM) + kGateScoreBytes;
 static __device__ __align__(256) unsigned char scratch[kStaticArrayBytes];
 
 namespace {
 
-__global__ void k_zero_words(unsigned int* p, int n) {
+// The first n words of a workspace: control words, and the gate's scores as far as n goes.  Only where
+// it holds all of these may the workgroups wait for each other's scores.
+__global__ void k_prepare_words(unsigned int* p, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
+    if (i < n) p[i] = i == coral_ctrl::kGatePolls && n >= coral_ctrl::kPreparedWords ? (unsigned)kGatePollsMax : 0u;
+}
+
+coral_status prepare_words(void* workspace, size_t bytes, hipStream_t stream) {
+    const size_t most = coral_ctrl::kPreparedWords * sizeof(unsigned int);
+    const int n = (int)((bytes < most ? bytes : most) / sizeof(unsigned int));
+    hipLaunchKernelGGL(k_prepare_words, dim3((n + 255) / 256), dim3(256), 0, stream, static_cast<unsigned int*>(workspace), n);
+    return hipGetLastError() == hipSuccess ? CORAL_OK : CORAL_ERR_HIP;
 }
 
 // ---------------------------------------------------------------- host side
@@ -106,7 +115,7 @@ Layout make_layout(int M, int V, int G, int g, int k, Pieces pieces, TileArrays 
         off = align_up(off + bytes, 256);
         return at;
     };
-    L.ctrl = take(kCtrlBytes);
+    L.ctrl = take(kCtrlBytes + kGateScoreBytes);
     const size_t single = what != LayoutFor::kTiles && what != LayoutFor::kCounted ? 1 : 0;
     const size_t logprob = what == LayoutFor::kWorkspace ? 1 : 0;
     const size_t staged = what == LayoutFor::kWorkspace ? 1 : 0;
@@ -586,7 +595,7 @@ size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtyp
         tiles = F.total - F.o_lists + (hidden > merges ? hidden : merges) > kLdsLimit;
     }
     return make_layout(M, V, G, g, k, Pieces{}, {tiles ? Tiles::kOwn : Tiles::kNone, false},
-                       tiles ? LayoutFor::kCounted : LayoutFor::kWorkspace).total - (kCtrlBytes - kCountedCtrlBytes);
+                       tiles ? LayoutFor::kCounted : LayoutFor::kWorkspace).total - kGateScoreBytes;
 }
 
 // Grouped heads that fit the single launch, with many tokens: whether the tile kernels take less time.  16 bits,
@@ -927,10 +936,7 @@ extern "C" coral_status coral_lmhead_workspace_init(void* workspace, size_t work
                                                     void* hip_stream) {
     coral_status st = check_workspace(workspace, workspace_bytes, kCtrlBytes);
     if (st != CORAL_OK) return st;
-    hipLaunchKernelGGL(k_zero_words, dim3((kCtrlBytes / 4 + 255) / 256), dim3(256), 0,
-                       static_cast<hipStream_t>(hip_stream), static_cast<unsigned int*>(workspace),
-                       (int)(kCtrlBytes / 4));
-    return launch_status();
+    return prepare_words(workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream));
 }
 
 namespace {
@@ -1026,12 +1032,10 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
     }
     if (plan.path < 0) return CORAL_ERR_UNSUPPORTED;       // before anything is enqueued
     if (static_workspace) {
-        // this device's copy of the array; its control words are cleared by a fill kernel on
+        // this device's copy of the array; its control words are prepared by a fill kernel on
         // the call's stream (the array keeps whatever the last call on this GPU left there)
         if ((st = static_scratch(&workspace)) != CORAL_OK) return st;
-        hipLaunchKernelGGL(k_zero_words, dim3((kCtrlBytes / 4 + 255) / 256), dim3(256), 0, stream,
-                           static_cast<unsigned int*>(workspace), (int)(kCtrlBytes / 4));
-        if ((st = launch_status()) != CORAL_OK) return st;
+        if ((st = prepare_words(workspace, kStaticArrayBytes, stream)) != CORAL_OK) return st;
     }
     char* ws = static_cast<char*>(workspace);
     if (plan.path == 1)

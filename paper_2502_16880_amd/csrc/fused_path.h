@@ -49,7 +49,8 @@ __host__ __device__ constexpr int log2_small(int n) { return n <= 1 ? 0 : 1 + lo
 constexpr int kLdsLimit = 160 * 1024;
 // Log-probability mode: a batch's cost in a workgroup's time is its load latency plus
 // the dot products of every token that selected its group; measured in units of one
-// token's dot products the latency is about this much.
+// token's dot products the latency is about this much.  (A cost for 16-bit rows beyond 4 KB that goes by
+// the load first was tried: over 1722 random heads 1.0005 times as fast on average, 0.93 to 1.06.)
 constexpr int kLpBaseCost = 10;
 // Batches of a workgroup where there are few: fewer workgroups then leave fewer lists to merge (three
 // groups of 101 rows, one token: 24.8 us with all 256, 22.0 with four batches each, 22.4 with 16; six
@@ -70,10 +71,13 @@ constexpr int kLpGroupCounters = coral_ctrl::kLpGroupArrival - coral_ctrl::kFuse
 // coral_lmhead.hip).  The LDS plan goes by the first two whichever runs.
 enum GateMode { kGateVector = 0, kGateMfma = 1, kGateShared = 2 };
 // Shared gate: its words behind FusedParams::counter, and how often a score is asked for (about 1 us each)
-// before the workgroup computes the gate itself.
+// before the workgroup computes the gate itself (the control word holds this number, or less: 0 where the
+// score words are not cleared).
 constexpr int kGateScoresAt = coral_ctrl::kGateScores - coral_ctrl::kFusedArrival;
 constexpr int kGateDoneAt = coral_ctrl::kGateDone - coral_ctrl::kFusedArrival;
-constexpr int kGatePolls = 48;
+constexpr int kGatePollsAt = coral_ctrl::kGatePolls - coral_ctrl::kFusedArrival;
+constexpr int kGateGaveUpAt = coral_ctrl::kGateGaveUp - coral_ctrl::kFusedArrival;
+constexpr int kGatePollsMax = 48;
 static_assert(coral_ctrl::kGateScoreWords <= kFusedBlock * 4, "a thread reads four scores");
 constexpr int kGateTileFloats = 256;          // a wave's partial 16 x 16 tile
 
@@ -99,7 +103,8 @@ struct FusedParams {
     int n_next;
     unsigned int* counter;      // arrival counter, zero between calls; the log-probability
                                 // mode also uses words kLpGroupCounters .. + 63, the shared gate
-                                // kGateDoneAt and kGateScoresAt .. + M G - 1, zero as well
+                                // kGateDoneAt and kGateScoresAt .. + M G - 1, zero as well, and
+                                // kGatePollsAt, kGateGaveUpAt (control_words.h)
     int32_t* topk_ids;          // [M, k]
     float* topk_logits;         // [M, k]
     int M, V, G, g, k;
@@ -473,8 +478,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             // load and stores scattered over the lines of all groups the hand-over took 4 us longer
             // than with these (256 workgroups ask for the same lines while the stores are on their way).
             // Bounded: the workgroups before this one may not be running yet where other kernels
-            // hold the compute units.  After kGatePolls requests the workgroup computes all scores itself,
-            // in the same loop, hence with the same bits.
+            // hold the compute units.  After as many requests as the control word says the workgroup computes
+            // all scores itself, in the same loop, hence with the same bits.
             uint4 ga[SEGS];
             auto load_gate_row = [&](int n) {
                 int left = p.n_vec - lane;
@@ -485,6 +490,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
                     if (j * kWave < left) ga[j] = p.gate_W[(size_t)n * p.n_vec + j * kWave + lane];
                 }
             };
+            const unsigned polls_r = __hip_atomic_load(p.counter + kGatePollsAt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             int first_n = blockIdx.x, step_n = gridDim.x;
             int pairs = (int)blockIdx.x < p.G ? ((p.G - 1 - (int)blockIdx.x) / (int)gridDim.x + 1) * M : 0;
             if (wave < pairs) load_gate_row(first_n + wave / M * step_n);
@@ -492,6 +498,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             small_commit();
             hidden_rest();
             __syncthreads();
+            const int polls = (int)min((unsigned)uni((int)polls_r), (unsigned)kGatePollsMax);
             unsigned* words = p.counter + kGateScoresAt;       // [G][M]
             const int n_words = M * p.G;
 #pragma unroll 1
@@ -519,9 +526,9 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
                     int ln = lane;
                     asm volatile("" : "+v"(ln));
                     const int e0 = (wave * kWave + ln) * 4;
-                    u32x4_t v;
+                    u32x4_t v = {0u, 0u, 0u, 0u};
                     bool all = false;
-                    for (int i = 0; i < kGatePolls; ++i) {
+                    for (int i = 0; i < polls; ++i) {
                         v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, e0 * (int)sizeof(unsigned), 0, 16 /* sc1: from memory */);
                         asm volatile("" ::: "memory");     // (the request is made again)
                         all = true;
@@ -534,11 +541,13 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
                         const int e = e0 + c, n = e / M;
-                        if (e < n_words) s_lds[(e - n * M) * p.G + n] = __uint_as_float(v[c]);
+                        if (all && e < n_words) s_lds[(e - n * M) * p.G + n] = __uint_as_float(v[c]);
                     }
                 }
                 __syncthreads();
                 if (!uni(flags[3])) break;                 // block-uniform
+                if (threadIdx.x == 0)
+                    __hip_atomic_fetch_add(p.counter + kGateGaveUpAt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 first_n = 0;
                 step_n = 1;
                 pairs = n_words;
@@ -931,7 +940,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     // Workgroups without a batch leave here; the last merge goes by the others' lists.
     const int P_act = LP ? uni(wgstart[uni(flags[0])]) : min((int)gridDim.x, (total_batches + (1 << deal) - 1) >> deal);
     // Shared gate: the workgroup has read the scores and its own are in memory; the last of all
-    // workgroups that gets here, those without a batch among them, leaves the words at zero for the next call.
+    // workgroups that gets here, those without a batch among them, leaves the words at zero for the next call
+    // (all that any call may use, where nobody has cleared them before).
     auto gate_through = [&]() {
         if (GATE != kGateShared || wave != 0) return;
         __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wave's stores are out
@@ -941,10 +951,14 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         if (uni(through) != (int)gridDim.x - 1) return;
         int ln = lane;
         asm volatile("" : "+v"(ln));                   // (see wave_merge_lists)
-        for (int e = ln; e < M * p.G; e += kWave)
+        const bool first = uni((int)__hip_atomic_load(p.counter + kGatePollsAt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0;
+        const int n_words = first ? coral_ctrl::kGateScoreWords : M * p.G;
+        for (int e = ln; e < n_words; e += kWave)
             __hip_atomic_store(p.counter + kGateScoresAt + e, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (lane == 0)
+        if (lane == 0) {
             __hip_atomic_store(p.counter + kGateDoneAt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (first) __hip_atomic_store(p.counter + kGatePollsAt, (unsigned)kGatePollsMax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     };
     if ((int)blockIdx.x >= P_act) {                    // block-uniform
         gate_through();

@@ -487,3 +487,53 @@ def test_grouped_heads_with_many_tokens(coral, dtype, H, M, path):
     dh = DeviceHead(coral, ragged_head(cfg, sizes))
     hidden = make_hidden(cfg, M, M)
     check_grouped(dh, hidden, 3, 8, run_grouped(coral, dh, hidden, 3, 8))
+
+
+# storage, H, groups, tokens: scores that are and are not a whole number of 16-byte words, more groups
+# than workgroups, more than a wave's 256 words
+GATE_ALONE = [("bf16", 8192, 40, 4), ("f16", 4096, 65, 5), ("bf16", 4096, 300, 13), ("f32", 1000, 64, 16), ("f16", 6664, 37, 3)]
+
+
+@pytest.mark.parametrize("dtype,H,G,M", GATE_ALONE)
+def test_shared_gate_where_workgroups_give_up(coral, dtype, H, G, M):
+    """A workspace of which only the 512 bytes of control words were prepared: every workgroup computes
+    the gate alone, with the bits of the shared one, and leaves the score words fit for sharing.  One
+    request for the scores: who finds them all goes on, who does not computes them."""
+    sizes = [9 + (7 * n) % 11 for n in range(G)]
+    V, g, k = sum(sizes), 3, 6
+    cfg = HeadConfig(f"alone{G}", dtype, H, V, G, g, (M,), k, 970 + G, True)
+    dh = DeviceHead(coral, ragged_head(cfg, sizes))
+    code = {"f32": coral.CORAL_F32, "bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
+    hidden = make_hidden(cfg, M, M)
+    d_hidden = coral.device_tensor(hidden, dtype)
+    routed = coral.device_tensor(make_hidden(cfg, M, M + 1), dtype)
+    ws = coral.alloc_workspace(M, H, V, G, g, k, code)
+    words = ws[:4 * (128 + 4096)].view(torch.int32)
+    polls, gave_up = 2, 3
+    workgroups = min(256, torch.cuda.get_device_properties(0).multi_processor_count)
+    print(f"case {cfg.name} {dtype} H={H} M={M}", flush=True)
+
+    def call(logprob, gate_hidden):
+        out = coral.coral_lmhead_grouped(d_hidden, dh.gate_W, dh.bias, dh.lm_W, dh.gi, g, k, workspace=ws, logprob=logprob,
+                                         gate_hidden=gate_hidden)
+        return [x.cpu().numpy() for x in out]
+
+    for logprob in (False, True):
+        for gate_hidden in (None, routed):
+            coral.coral_lmhead_workspace_init(ws)
+            most = int(words[polls])
+            shared = call(logprob, gate_hidden)
+            if gate_hidden is None:
+                (check_logprob if logprob else check_grouped)(dh, hidden, g, k, tuple(shared))
+            ws.fill_(0xAB)
+            coral.coral_lmhead_workspace_init(ws[:512])
+            assert int(words[polls]) == 0
+            alone = call(logprob, gate_hidden)
+            assert int(words[gave_up]) == workgroups and int(words[polls]) == most > 0
+            assert not words[128:].any() and int(words[0]) == 0 and int(words[1]) == 0
+            words[polls] = 1
+            some = call(logprob, gate_hidden)
+            words[polls] = most
+            for out in (alone, some, call(logprob, gate_hidden)):
+                assert all(np.array_equal(x, y) for x, y in zip(shared, out))
+            assert not words[128:].any() and int(words[0]) == 0 and int(words[1]) == 0
