@@ -21,9 +21,10 @@ constexpr int kTileQueue = 4;               // tile path: next block of k_tiles
 constexpr int kLpGroupArrival = 64;         // log-probability mode: one counter per activated
 constexpr int kLpGroupArrivalWords = 64;    //   group (at most 64 in the single-launch kernel)
 constexpr int kGateDone = 1;                // single-launch path, shared gate: workgroups that have read the scores,
-constexpr int kGatePolls = 2;               //   how often a workgroup asks for them at most (0: nobody has
-                                            //   cleared the score words yet; the next such call does),
-constexpr int kGateGaveUp = 3;              //   and how many workgroups had to compute the gate alone so far
+constexpr int kGateGaveUp = 2;              //   how many had to compute the gate alone so far,
+constexpr int kGatePolls = 32;              //   and how often a workgroup asks for the scores at most (0: nobody
+                                            //   has cleared the score words yet; the next such call does);
+                                            //   in a 128-byte line without counters, as it is read through the caches
 
 // Behind the control area: the shared gate's scores, group by group (bit patterns; 0: not there yet, and
 // so between calls).

@@ -71,13 +71,22 @@ constexpr int kLpGroupCounters = coral_ctrl::kLpGroupArrival - coral_ctrl::kFuse
 // coral_lmhead.hip).  The LDS plan goes by the first two whichever runs.
 enum GateMode { kGateVector = 0, kGateMfma = 1, kGateShared = 2 };
 // Shared gate: its words behind FusedParams::counter, and how often a score is asked for (about 1 us each)
-// before the workgroup computes the gate itself (the control word holds this number, or less: 0 where the
-// score words are not cleared).
+// before the workgroup stops waiting (the control word holds this number, or less: 0 where the score words
+// are not cleared).  Undisturbed, nobody gives up with 16 requests over eight heads, with 12 up to a sixth
+// do; other kernels in the way, the number hardly matters from 12 to 48.  What the waiting then costs, own
+// gate against shared, us a step: Llama3 shape, 8 tokens, beside large matrix products 247, 260, beside
+// the same step on another stream 201, 209, H = 8192, one token 199, 205 and 67.5, 74.9; with a large
+// gate it is ahead there too (120 groups, H = 8192, 8 tokens 212, 189 and 99, 39).
 constexpr int kGateScoresAt = coral_ctrl::kGateScores - coral_ctrl::kFusedArrival;
 constexpr int kGateDoneAt = coral_ctrl::kGateDone - coral_ctrl::kFusedArrival;
 constexpr int kGatePollsAt = coral_ctrl::kGatePolls - coral_ctrl::kFusedArrival;
 constexpr int kGateGaveUpAt = coral_ctrl::kGateGaveUp - coral_ctrl::kFusedArrival;
-constexpr int kGatePollsMax = 48;
+constexpr int kGatePollsMax = 24;
+// Groups left that a workgroup which gave up computes without publishing them or looking again: two rounds
+// of its waves, where 256 workgroups' stores to the same few lines take longer (fp32 Llama2, 16 groups, all
+// giving up: 45 us a step, 270 with them).  With many left it is the other way round (every workgroup alone
+// and a pair at a time: 120 groups, H = 8192, 8 tokens 150 us, 52; 1000 groups, 4 tokens 340, 74).
+constexpr int kGateAloneGroups = 2 * kFusedWaves;
 static_assert(coral_ctrl::kGateScoreWords <= kFusedBlock * 4, "a thread reads four scores");
 constexpr int kGateTileFloats = 256;          // a wave's partial 16 x 16 tile
 
@@ -478,8 +487,11 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             // load and stores scattered over the lines of all groups the hand-over took 4 us longer
             // than with these (256 workgroups ask for the same lines while the stores are on their way).
             // Bounded: the workgroups before this one may not be running yet where other kernels
-            // hold the compute units.  After as many requests as the control word says the workgroup computes
-            // all scores itself, in the same loop, hence with the same bits.
+            // hold the compute units.  After as many requests as the control word says, the workgroups that
+            // run compute what is still missing between them: a wave a group with all its tokens at a time,
+            // each workgroup's from another place on, published like a share, and what others have
+            // published read in between.  Any workgroup gets to the end of that by itself.  A score has the
+            // same bits wherever it is computed.
             uint4 ga[SEGS];
             auto load_gate_row = [&](int n) {
                 int left = p.n_vec - lane;
@@ -490,67 +502,105 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
                     if (j * kWave < left) ga[j] = p.gate_W[(size_t)n * p.n_vec + j * kWave + lane];
                 }
             };
-            const unsigned polls_r = __hip_atomic_load(p.counter + kGatePollsAt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int first_n = blockIdx.x, step_n = gridDim.x;
-            int pairs = (int)blockIdx.x < p.G ? ((p.G - 1 - (int)blockIdx.x) / (int)gridDim.x + 1) * M : 0;
+            auto score = [&](int n, int m) {
+                float s = 0.f;
+#pragma unroll
+                for (int j = 0; j < SEGS; ++j)
+                    if (j < p.jp) s = dot_vec<DT>(ga[j], hs[m * hs_stride + j * kWave + lane], s);
+                s = wave_sum(s) + bias_lds[n];
+                if (lane == 0) s_lds[m * p.G + n] = s == 0.f ? -0.f : s;
+            };
+            int polls_at = kGatePollsAt;
+            asm volatile("" : "+v"(polls_at));         // (a vector load: a scalar one holds up the gate rows' addresses)
+            const unsigned polls_r = p.counter[polls_at];
+            const int first_n = blockIdx.x, step_n = gridDim.x;
+            const int pairs = first_n < p.G ? ((p.G - 1 - first_n) / step_n + 1) * M : 0;
             if (wave < pairs) load_gate_row(first_n + wave / M * step_n);
+            const int n_words = M * p.G;
+            for (int e = threadIdx.x; e < n_words; e += kFusedBlock) s_lds[e] = 0.f;       // (+0: missing)
             hidden_commit(0);
             small_commit();
             hidden_rest();
             __syncthreads();
             const int polls = (int)min((unsigned)uni((int)polls_r), (unsigned)kGatePollsMax);
             unsigned* words = p.counter + kGateScoresAt;       // [G][M]
-            const int n_words = M * p.G;
-#pragma unroll 1
-            for (bool alone = false;; alone = true) {
-                for (int q = wave; q < pairs; q += kFusedWaves) {      // wave-uniform
+            auto publish = [&](int n, int m, float s) {
+                __hip_atomic_store(words + n * M + m, __float_as_uint(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            };
+            // this wave's words, asked for up to `times` times; whether all are there
+            auto read_scores = [&](int times) {
+                const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(words, 0, n_words * (int)sizeof(unsigned), 0x00027000);
+                int ln = lane;
+                asm volatile("" : "+v"(ln));
+                const int e0 = (wave * kWave + ln) * 4;
+                u32x4_t v = {0u, 0u, 0u, 0u};
+                bool all = false;
+                for (int i = 0; i < times; ++i) {
+                    v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, e0 * (int)sizeof(unsigned), 0, 16 /* sc1: from memory */);
+                    asm volatile("" ::: "memory");     // (the request is made again)
+                    all = true;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) all = all && (e0 + c >= n_words || v[c] != 0u);
+                    if (__ballot(!all) == 0ull) break;
+                    __builtin_amdgcn_s_sleep(2);
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int e = e0 + c, n = e / M;
+                    if (e < n_words && v[c] != 0u) s_lds[(e - n * M) * p.G + n] = __uint_as_float(v[c]);
+                }
+                return all;
+            };
+            const bool reads = polls > 0 && wave * 4 * kWave < n_words;        // wave-uniform
+            for (int q = wave; q < pairs; q += kFusedWaves) {  // wave-uniform
+                const int i = q / M, n = first_n + i * step_n;
+                if (q != wave) load_gate_row(n);
+                score(n, q - i * M);
+            }
+            __syncthreads();
+            if (wave == 0)                             // (one wave: gate_through waits for its stores)
+                for (int q = lane; q < pairs; q += kWave) {
                     const int i = q / M, m = q - i * M, n = first_n + i * step_n;
-                    if (alone || q != wave) load_gate_row(n);
-                    float s = 0.f;
-#pragma unroll
-                    for (int j = 0; j < SEGS; ++j)
-                        if (j < p.jp) s = dot_vec<DT>(ga[j], hs[m * hs_stride + j * kWave + lane], s);
-                    s = wave_sum(s) + bias_lds[n];
-                    if (lane == 0) s_lds[m * p.G + n] = s == 0.f ? -0.f : s;
+                    publish(n, m, s_lds[m * p.G + n]);
                 }
-                __syncthreads();
-                if (alone) break;
-                if (wave == 0)                             // (one wave: gate_through waits for its stores)
-                    for (int q = lane; q < pairs; q += kWave) {
-                        const int i = q / M, m = q - i * M, n = first_n + i * step_n;
-                        __hip_atomic_store(words + n * M + m, __float_as_uint(s_lds[m * p.G + n]), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                if (wave * 4 * kWave < n_words) {          // wave-uniform
-                    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(words, 0, n_words * (int)sizeof(unsigned), 0x00027000);
-                    int ln = lane;
-                    asm volatile("" : "+v"(ln));
-                    const int e0 = (wave * kWave + ln) * 4;
-                    u32x4_t v = {0u, 0u, 0u, 0u};
-                    bool all = false;
-                    for (int i = 0; i < polls; ++i) {
-                        v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, e0 * (int)sizeof(unsigned), 0, 16 /* sc1: from memory */);
-                        asm volatile("" ::: "memory");     // (the request is made again)
-                        all = true;
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) all = all && (e0 + c >= n_words || v[c] != 0u);
-                        if (__ballot(!all) == 0ull) break;
-                        __builtin_amdgcn_s_sleep(2);
-                    }
-                    if (!all) flags[3] = 1;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int e = e0 + c, n = e / M;
-                        if (all && e < n_words) s_lds[(e - n * M) * p.G + n] = __uint_as_float(v[c]);
-                    }
-                }
-                __syncthreads();
-                if (!uni(flags[3])) break;                 // block-uniform
+            if (polls == 0 || (reads && !read_scores(polls))) flags[3] = 1;
+            __syncthreads();
+            if (uni(flags[3])) {                       // block-uniform
                 if (threadIdx.x == 0)
                     __hip_atomic_fetch_add(p.counter + kGateGaveUpAt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                first_n = 0;
-                step_n = 1;
-                pairs = n_words;
+                auto missing = [&](int base) {         // of the 64 groups from base on
+                    const int n = base + lane;
+                    bool out = false;
+                    if (n < p.G)
+                        for (int m = 0; m < M; ++m) out = out || __float_as_uint(s_lds[m * p.G + n]) == 0u;
+                    return __ballot(out);
+                };
+                for (;;) {
+                    int total = 0;
+                    for (int base = 0; base < p.G; base += kWave) total += __popcll(missing(base));
+                    int rank = (int)(blockIdx.x * kFusedWaves + wave) % max(total, 1), mine = -1;
+                    if (wave < total)
+                        for (int base = 0; mine < 0; base += kWave) {
+                            const unsigned long long b = missing(base);
+                            const unsigned long long at = __ballot((b >> lane & 1ull) && __popcll(b & ((1ull << lane) - 1ull)) == rank);
+                            if (at) mine = base + __ffsll(at) - 1;
+                            rank -= __popcll(b);
+                        }
+                    __syncthreads();                   // (nobody writes a score before all have looked)
+                    if (total == 0) break;             // block-uniform
+                    const bool shares = polls > 0 && total > kGateAloneGroups;
+                    if (mine >= 0) {
+                        load_gate_row(mine);
+#pragma unroll 1
+                        for (int m = 0; m < M; ++m) score(mine, m);
+                        if (shares) {                  // (the wave's own LDS words: in order)
+                            if (lane < M) publish(mine, lane, s_lds[lane * p.G + mine]);
+                            __builtin_amdgcn_s_waitcnt(0x0F70);    // vmcnt(0), for gate_through
+                        }
+                    }
+                    if (shares && reads) read_scores(1);
+                    __syncthreads();
+                }
             }
         } else if (GATE == kGateMfma) {
             // ---- 2a. gate on the matrix cores: s[16 groups x 16 tokens] tiles, the H
