@@ -285,16 +285,19 @@ int fused_gate_mode(bool dense, int M, int G, int g, int k, int jp, coral_dtype 
 // every workgroup by itself longer than the hand-over, about 4 us.  Estimates in us of the former: on the
 // matrix cores by passes of 32 groups, on the vector units of 16 groups and two tokens, each with the bytes
 // of its rows.  Fitted to 2 x 343 heads (512 to 8192 columns, 8 to 120 groups, 1 to 32 tokens, bf16 and fp32,
-// 24000 rows): 1.08 times as fast on average (log-probabilities 1.05), hardly below the faster of the two
-// each time.  us, own gate against shared: bf16, 8 tokens, H = 8192, 8 groups 59, 55, 120 groups 74, 43;
-// H = 4096, 16 groups 27.8, 26.5, 64 groups 36, 28; H = 2048, 32 groups 22.0, 22.2; H = 512, 120 groups
-// 22.8, 20.6, 32 groups 16.4, 18.5; fp32, 16 tokens, H = 1024, 16 groups 33, 29, 4 tokens, H = 4096, 16
-// groups 30.4, 29.1, 64 groups 43, 30.  With few tokens the own gate starts early, and it matters whether
-// the gate's rows come from the caches: one token, 64 groups, H = 4096, 24000 rows 19.6, 20.0, 128256 rows
-// 28.9, 28.0; H = 8192, 32 groups 22.0, 22.5, 57.5, 56.4; H = 4096, 32 groups 16.8, 18.8, 34.7, 35.9.
+// 24000 rows): 1.08 times as fast on average (log-probabilities 1.05).  us, own gate against shared: bf16, 8
+// tokens, H = 8192, 8 groups 59, 55, 120 groups 74, 43; H = 4096, 16 groups 27.8, 26.5, 64 groups 36, 28; H =
+// 2048, 32 groups 22.0, 22.2; H = 512, 120 groups 22.8, 20.6, 32 groups 16.4, 18.5; fp32, 16 tokens, H = 1024,
+// 16 groups 33, 29, 4 tokens, H = 4096, 16 groups 30.4, 29.1, 64 groups 43, 30.
+// With up to three tokens the own gate starts early and goes by the bytes of the whole gate.  Over 1291 heads
+// (8192 rows and more, 8 to 256 groups) with those below kFewTokensKb the worst are 0.907 (one token), 0.927
+// (two) and 0.951 (three) times as fast as with the own gate, without them 0.963, 0.999 and 1.008; the heads
+// left out are 0.98, 1.00 and 1.03 on average (one token, H = 2776, 66 groups 16.7, 18.4; H = 8192, 32 groups 56.1, 54.5).
 bool fused_gate_shared(int M, int G, int n_vec, coral_dtype dt) {
+    constexpr double kFewTokensKb[3] = {480, 300, 200};
     if (M * G > coral_ctrl::kGateScoreWords) return false;
     const double kb = n_vec / 64.0;                        // of a gate row
+    if (M <= 3 && G * kb < kFewTokensKb[M - 1]) return false;
     const double own = is_16bit(dt) && M >= 4 ? (G + 31) / 32 * (0.4 + 0.68 * kb)
                                               : (G + 15) / 16 * 0.5 * (0.3 + 0.05 * M + (0.1 + 0.11 * M) * kb);
     return own > 3.5;

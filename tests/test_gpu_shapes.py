@@ -540,3 +540,28 @@ def test_shared_gate_where_workgroups_give_up(coral, dtype, H, G, M):
             for out in (alone, some, call(logprob, gate_hidden)):
                 assert all(np.array_equal(x, y) for x, y in zip(shared, out))
             assert not words[128:].any() and int(words[0]) == 0 and int(words[1]) == 0
+
+
+def gate_is_shared(coral, dtype, H, G, M, k=2, g=2):
+    """Whether the single launch shares the gate at these sizes: such a call is what marks the score words of
+    a workspace as cleared (control word 32) whose first 512 bytes only were prepared."""
+    code = {"f32": coral.CORAL_F32, "bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
+    sizes = [3] * G
+    assert coral.coral_lmhead_path(False, M, H, sum(sizes), G, g, k, code) == 1
+    dh = DeviceHead(coral, ragged_head(HeadConfig("which", dtype, H, sum(sizes), G, g, (M,), k, 5, True), sizes))
+    ws = coral.alloc_workspace(M, H, sum(sizes), G, g, k, code)
+    coral.coral_lmhead_workspace_init(ws[:512])
+    hidden = coral.device_tensor(make_hidden(dh.head.cfg, M, M), dtype)
+    coral.coral_lmhead_grouped(hidden, dh.gate_W, dh.bias, dh.lm_W, dh.gi, g, k, workspace=ws)
+    return int(ws[:512].view(torch.int32)[32]) != 0
+
+
+# either side of the bytes of a gate that up to three tokens share, and of the estimate that more go by
+WHICH_GATE = [("bf16", 2776, 66, 1, False), ("bf16", 8192, 30, 1, True), ("bf16", 8192, 29, 1, False), ("f16", 2048, 70, 2, False),
+              ("f16", 2048, 80, 2, True), ("bf16", 4096, 24, 3, False), ("bf16", 4096, 26, 3, True), ("f32", 2004, 52, 1, False),
+              ("f32", 2048, 64, 1, True), ("bf16", 2048, 32, 8, False), ("bf16", 4096, 32, 8, True), ("bf16", 8192, 900, 5, False)]
+
+
+@pytest.mark.parametrize("dtype,H,G,M,shared", WHICH_GATE)
+def test_which_gates_are_shared(coral, dtype, H, G, M, shared):
+    assert gate_is_shared(coral, dtype, H, G, M) == shared
