@@ -305,14 +305,16 @@ bool fused_gate_shared(int M, int G, int n_vec, coral_dtype dt) {
 
 // Rows the single-launch kernel takes (by their 16-byte vectors): up to 8 KB, and from 8.25 to 16 KB.  (Rows of
 // nine segments leave seven of a batch's sixteen loads empty, and are still the faster ones: us, multi-kernel
-// paths against single launch, over 240 random heads of 4104 to 4608 columns (fp32: half): grouped 1.68
-// times as fast on average, log-probabilities 1.41, the worst 3 % slower; bf16 H = 4352, 62 groups, 7 tokens,
-// k = 64 139, 26, H = 4608, 56 groups, 11 tokens 55, 50; dense f16 H = 4224, 7 tokens, k = 33 149, 36.  Below
-// a quarter of the ninth segment they would be as well (1.5 and 2.5 times, two heads): these widths keep the
-// general path, whose form of them is pinned.  The dense head's products with eight tokens and more take longer
-// than the tile kernels: f16 H = 4480, 94129 rows, 9 tokens 146, 166, bf16 H = 4352, 24624 rows, 15 tokens 49, 70.)
+// paths against single launch, over 972 random heads of 4224 to 4608 columns (fp32: half): grouped 1.8 times
+// as fast on average, the worst 1.03; log-probabilities up to eight tokens 1.53, the worst 1.006; bf16 H =
+// 4352, 62 groups, 7 tokens, k = 64 139, 26, H = 4608, 56 groups, 11 tokens 55, 50; dense f16 H = 4224, 7
+// tokens, k = 33 149, 36.  With more tokens a group's rows cost their products: log-probabilities from nine
+// tokens on 0.75 to 2.3 (bf16 H = 4328, 6 of 8 groups, 12 tokens 176, 234), the dense head from eight tokens on
+// f16 H = 4480, 94129 rows, 9 tokens 146, 166, bf16 H = 4352, 24624 rows, 15 tokens 49, 70.  Below a quarter of
+// the ninth segment two heads measured 1.5 and 2.5 times as fast on the single launch: not a loss, but these
+// widths are where the general path's form of long rows is pinned, and they stay there.)
 bool fused_rows_fit(int n_vec) { return n_vec <= 8 * kWave || (n_vec >= 8 * kWave + kWave / 4 && n_vec <= kFusedMaxSegs * kWave); }
-constexpr int kNineSegsDenseTokens = 7;
+constexpr int kNineSegsDenseTokens = 7, kNineSegsLogprobTokens = 8;
 
 // Log-probability mode: beyond 32 tokens the single-launch kernel's per-wave lists (one per token,
 // hardly ever filled) and per-token pieces cost more than the tile kernels' three launches
@@ -396,6 +398,7 @@ bool long_rows_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype 
 bool logprob_takes_fused(int M, int H, int V, int G, int g, int k, int jp, coral_dtype dt) {
     int um, lds;
     return fused_rows_fit(H / (is_16bit(dt) ? 8 : 4)) && fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups) &&
+           (jp != 9 || M <= kNineSegsLogprobTokens) &&
            (jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, true)) &&
            (M <= kLogprobFusedMaxTokens || !tile_kernels_fit(M, H, V, G, g, k, dt, &um, &lds));
 }

@@ -14,7 +14,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "coral_lmhead.h")
 
 OK, NULL, SHAPE, GROUP_INDEX, UNSUPPORTED, WORKSPACE, HIP = range(7)
-F32, BF16 = 0, 1
+F32, BF16, F16 = 0, 1, 2
 FAKE = 0x7000_0000_1000          # never dereferenced: every check below fails before a launch
 
 
@@ -379,3 +379,14 @@ def test_dense_heads_with_many_tokens_take_the_tile_kernels():
     assert path(True, 26, 944, 33_304, 0, 0, 10, F32) == 1 and path(True, 26, 944, 32_700, 0, 0, 10, F32) == 0
     # the plain form where a workgroup would keep sorted lists, and where the vocabulary is large
     assert path(True, 16, 4096, 60_000, 0, 0, 10, BF16) == 2 and path(True, 8, 1024, 65_536, 0, 0, 10, BF16) == 2
+
+
+@pytest.mark.parametrize("H,dt", [(4224, BF16), (4352, F16), (4608, BF16), (2112, F32), (2304, F32)])
+def test_route_of_rows_of_nine_segments(H, dt):
+    """Single launch: log-probabilities up to eight tokens, dense up to seven, grouped whatever the tokens (but
+    for whole 512-column chunks in 16 bits, where the matrix-core path takes some)."""
+    for M in (1, 7, 8, 9, 12):
+        if H != 4608:
+            assert coral.coral_lmhead_path(False, M, H, 91704, 8, 6, 8, dt) == 1
+        assert (coral.coral_lmhead_logprob_path(M, H, 91704, 8, 6, 8, dt) == 1) == (M <= 8)
+        assert (coral.coral_lmhead_path(True, M, H, 24624, 0, 0, 8, dt) == 1) == (M <= 7)

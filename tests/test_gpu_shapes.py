@@ -467,14 +467,15 @@ def test_shared_gate_with_scores_of_zero(coral):
 
 @pytest.mark.parametrize("dtype,H", [("bf16", 4224), ("f16", 4600), ("bf16", 4608), ("f32", 2112), ("f32", 2304)])
 def test_rows_of_nine_segments(coral, dtype, H):
-    """From a quarter of the ninth segment on, up to a whole one; the dense head up to seven tokens."""
+    """From a quarter of the ninth segment on, up to a whole one; the dense head up to seven tokens, log-probabilities up to eight."""
     sizes = [1, 2, 3, 15, 16, 17, 64, 130] + [40] * 25
     cfg = HeadConfig(f"nine{H}", dtype, H, sum(sizes), len(sizes), 4, (1,), 9, 950 + H, True)
     code = {"f32": coral.CORAL_F32, "bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
-    for M in (1, 3, 7, 9):
+    for M in (1, 3, 7, 8, 9):
         assert coral.coral_lmhead_path(False, M, H, cfg.V, cfg.G, 4, 9, code) == 1
-        assert coral.coral_lmhead_path(True, M, H, cfg.V, 0, 0, 9, code) == 1 or M > 7
-    check_all(coral, cfg, sizes, (1, 3, 7, 9))
+        assert (coral.coral_lmhead_path(True, M, H, cfg.V, 0, 0, 9, code) == 1) == (M <= 7)
+        assert (coral.coral_lmhead_logprob_path(M, H, cfg.V, cfg.G, 4, 9, code) == 1) == (M <= 8)
+    check_all(coral, cfg, sizes, (1, 3, 7, 8, 9))
 
 
 @pytest.mark.parametrize("dtype,H,M,path", [("bf16", 512, 37, 2), ("f16", 264, 64, 0), ("bf16", 1000, 38, 0), ("bf16", 512, 36, 1), ("f32", 512, 40, 1)])
