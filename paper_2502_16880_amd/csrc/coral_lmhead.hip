@@ -606,15 +606,27 @@ size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtyp
 
 // Grouped heads that fit the single launch, with many tokens: whether the tile kernels take less time.  16 bits,
 // from 37 tokens on (the single launch dots every row with each of its group's tokens on the vector units and
-// ranks every token's candidates in every workgroup).  Single launch against tiles over 450 random heads of 8 to
-// 152 K rows and 256 columns and more: from 37 tokens on 1.35 times as fast on average, 1.00 to 1.74 (us: bf16
-// H = 256, 48720 rows, 53 tokens 41, 28; H = 1024, 35310 rows, 37 tokens 38, 36); 33 to 36 tokens 1.18, but 0.87 to
-// 1.4 (H = 816, 146627 rows, 35 tokens 71, 82); 25 to 32 tokens 1.07, 0.85 to 1.40; up to 16 tokens 0.80; fp32
-// 0.87.  Not where the entry point without a workspace would have to go through the tokens in batches,
-// reading the weights again for each.
+// ranks every token's candidates in every workgroup).  Up to 49 tokens, and nine to a group, not where
+//   - one or two candidates are wanted (the single launch's ranking goes by k) and a row is more than one chunk,
+//     or part of one and the blocks more than one round over the compute units, or
+//   - the last chunk is partly filled (it costs as much as a whole one), there are about two rounds of chunks over
+//     the compute units or more, and two tokens or more to a group.
+// Single launch against tiles over 5500 random heads of 8 to 152 K rows, 8 to 1024 groups and 256 to 1096 columns:
+// 1.47 times as fast on average, the worst 0.97 (us: bf16 H = 256, 48720 rows, 53 tokens 41, 28); in the two
+// exceptions, 7 in a hundred heads, 1.19, but down to 0.86 (f16 H = 776, 38275 rows, 41 tokens, k = 1 35, 41; bf16 H = 488,
+// 125086 rows, 37 tokens 44, 50).  33 to 36 tokens 1.18, 0.87 to 1.4 (H = 816, 146627 rows, 35 tokens 71, 82); 25
+// to 32 tokens 1.07, 0.85 to 1.40; up to 16 tokens 0.80; fp32 0.87.  Not where the entry point without a workspace
+// would have to go through the tokens in batches, reading the weights again for each.
 bool grouped_tiles_faster(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
     if (!is_16bit(dt) || V < 8192 || H < 256 || M < 37) return false;
     const Tiles kind = H % (kChunkVecs * 8) == 0 ? Tiles::kOwn : Tiles::kGeneral;
+    const int chunk = kChunkVecs * 8, chunks = (H + chunk - 1) / chunk;
+    const double group_tokens = M * g / expected_groups(M, G, g);
+    if (M < 50 && group_tokens <= 9.0) {
+        const bool part = H % chunk != 0;
+        if (k <= 2 && (chunks > 1 || (part && V > kMaxWorkgroups * kTileRows))) return false;
+        if (part && group_tokens >= 1.8 && (long long)V * chunks > 62000) return false;
+    }
     return make_layout(M, V, G, g, k, Pieces{}, {kind, false}, LayoutFor::kTiles).total <= kStaticArrayBytes ||
            static_counted_bytes(M, H, V, G, g, k, dt) > kStaticScratchBytes;
 }

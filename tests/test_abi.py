@@ -381,6 +381,21 @@ def test_dense_heads_with_many_tokens_take_the_tile_kernels():
     assert path(True, 16, 4096, 60_000, 0, 0, 10, BF16) == 2 and path(True, 8, 1024, 65_536, 0, 0, 10, BF16) == 2
 
 
+# tokens, H, V, groups, g, k, storage: either side of where the tile kernels take 16-bit grouped heads with many
+# tokens; what stays on the single launch measured 0.86 to 0.95 of its speed there
+MANY_TOKENS = [((41, 776, 38275, 59, 3, 1, F16), 1), ((40, 520, 10371, 27, 1, 1, BF16), 1), ((40, 520, 10371, 27, 1, 4, BF16), 0),
+               ((40, 512, 11353, 18, 1, 1, BF16), 2), ((39, 472, 35451, 27, 2, 1, F16), 1), ((39, 472, 32768, 27, 2, 1, F16), 0),
+               ((38, 712, 32295, 29, 2, 2, F16), 1), ((38, 712, 32295, 29, 8, 2, F16), 0), ((37, 488, 125086, 13, 1, 10, BF16), 1),
+               ((37, 512, 125086, 13, 1, 10, BF16), 2), ((37, 488, 50000, 13, 1, 10, BF16), 0), ((38, 984, 33128, 33, 4, 10, BF16), 1),
+               ((38, 984, 31000, 33, 4, 10, BF16), 0), ((40, 488, 125086, 200, 1, 10, BF16), 0), ((40, 488, 125086, 8, 4, 10, BF16), 0),
+               ((50, 776, 38275, 59, 3, 1, F16), 0), ((49, 312, 142728, 24, 2, 8, F16), 1), ((50, 312, 142728, 24, 2, 8, F16), 0)]
+
+
+@pytest.mark.parametrize("sizes,path", MANY_TOKENS)
+def test_route_of_grouped_heads_with_many_tokens(sizes, path):
+    assert coral.coral_lmhead_path(False, *sizes) == path
+
+
 @pytest.mark.parametrize("H,dt", [(4224, BF16), (4352, F16), (4608, BF16), (2112, F32), (2304, F32)])
 def test_route_of_rows_of_nine_segments(H, dt):
     """Single launch: log-probabilities up to eight tokens, dense up to seven, grouped whatever the tokens (but
