@@ -47,11 +47,17 @@ __host__ __device__ constexpr int fused_rows(int segs) { return kFusedLoads / se
 inline int fused_segs(int jp) { return jp <= 2 ? 2 : jp <= 4 ? 4 : jp <= 8 ? 8 : 16; }
 __host__ __device__ constexpr int log2_small(int n) { return n <= 1 ? 0 : 1 + log2_small(n / 2); }
 constexpr int kLdsLimit = 160 * 1024;
-// Log-probability mode: a batch's cost in a workgroup's time is its load latency plus
-// the dot products of every token that selected its group; measured in units of one
-// token's dot products the latency is about this much.  (A cost for 16-bit rows beyond 4 KB that goes by
-// the load first was tried: over 1722 random heads 1.0005 times as fast on average, 0.93 to 1.06.)
-constexpr int kLpBaseCost = 10;
+// Log-probability mode: a batch's cost in a workgroup's time by the tokens that selected its group: its load,
+// and their dot products (10 + tokens).  16-bit rows beyond 4 KB, groups with two to three and a half tokens on
+// average: little more than the load while the tokens are few, more than that beyond four.  10 + tokens against
+// this over 1722 random heads: there 1.01 times as fast on average, 0.98 to 1.05 (us: bf16 H = 3584, 152064
+// rows, 16 tokens 164.6, 162.1); fewer tokens a group 0.998, 0.97 to 1.03; more 1.007, 0.93 to 1.06; shorter
+// rows and fp32 the same on average.
+template <int DT, int SEGS>
+__device__ __forceinline__ int lp_batch_cost(int tokens, int pairs, int groups) {
+    if (DT == kF32 || SEGS < 8 || pairs < 2 * groups || 2 * pairs > 7 * groups) return 10 + tokens;   // wave-uniform
+    return 2 * (20 + tokens) + (tokens > 4 ? 4 * (tokens - 4) : 0);
+}
 // Batches of a workgroup where there are few: fewer workgroups then leave fewer lists to merge (three
 // groups of 101 rows, one token: 24.8 us with all 256, 22.0 with four batches each, 22.4 with 16; six
 // tokens over 9500 rows 29.1, 29.0, 39.4; over small heads 4 % with 5 to 7 tokens, 1 % with 10 to 17).
@@ -796,7 +802,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         // Log-probability mode: every workgroup streams rows of one group only (it keeps one
         // list and one log-sum-exp state per token, Eq. 8 normalises per group), so the
         // workgroups are shared out among the count <= 64 activated groups in proportion to
-        // their cost, batches x (kLpBaseCost + tokens that selected the group): one each,
+        // their cost, batches x lp_batch_cost(tokens that selected the group): one each,
         // the rest by the groups' shares rounded down, what is then left one more each to the
         // groups with the highest cost per workgroup.  The numbers add up to n_share: gridDim.x, or
         // fewer where there are few batches (the workgroups behind leave before the stream: P_act).
@@ -807,7 +813,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
             // (batches scaled to 16 bits so that the products below stay in 31)
             const int shift = max(0, 16 - __clz(all_pairs));
             const unsigned cost =
-                lane < count ? (unsigned)(nb_u >> shift) * (unsigned)(kLpBaseCost + __popcll(umask[lane])) : 0u;
+                lane < count ? (unsigned)(nb_u >> shift) *
+                                   (unsigned)lp_batch_cost<DT, SEGS>(__popcll(umask[lane]), M * p.g, count) : 0u;
             const unsigned total = (unsigned)__builtin_amdgcn_readlane(wave_scan_inclusive((int)cost), 63);
             // (the reciprocal rounded down, so that the shares never add up to more than there are)
             const float scale = (float)(n_share - count) * __builtin_amdgcn_rcpf((float)(total ? total : 1u)) * (1.f - 0x1p-20f);
