@@ -273,9 +273,9 @@ bool allow_lds(const void* fn, int bytes) {
     return true;
 }
 
-// Gate of the single-launch path where every workgroup computes it, and what the LDS plan goes by: from four tokens on it goes through the matrix cores (16-bit
-// storage only; measured at the Llama3 shape: two tokens 52.1 against 50.8 us on the vector
-// units, three equal, four 81.0 against 81.5).
+// Gate of the single-launch path where every workgroup computes it, and what the LDS plan goes by:
+// from four tokens on it goes through the matrix cores (16-bit storage only; measured at the Llama3
+// shape: two tokens 52.1 against 50.8 us on the vector units, three equal, four 81.0 against 81.5).
 int fused_gate_mode(bool dense, int M, int G, int g, int k, int jp, coral_dtype dt, bool logprob = false) {
     (void)G; (void)g; (void)k; (void)jp; (void)logprob;
     return dense || !is_16bit(dt) || M <= 3 ? kGateVector : kGateMfma;
@@ -291,10 +291,10 @@ int fused_gate_mode(bool dense, int M, int G, int g, int k, int jp, coral_dtype 
 // 16 groups 33, 29, 4 tokens, H = 4096, 16 groups 30.4, 29.1, 64 groups 43, 30.
 // With up to three tokens the own gate starts early and goes by the bytes of the whole gate.  Over 1291 heads
 // (8192 rows and more, 8 to 256 groups) with those below kFewTokensKb the worst are 0.907 (one token), 0.927
-// (two) and 0.951 (three) times as fast as with the own gate, without them 0.963, 0.999 and 1.008; the heads
+// (two) and 0.951 (three) times as fast as with the own gate, without them 0.963, 0.976 and 1.008; the heads
 // left out are 0.98, 1.00 and 1.03 on average (one token, H = 2776, 66 groups 16.7, 18.4; H = 8192, 32 groups 56.1, 54.5).
 bool fused_gate_shared(int M, int G, int n_vec, coral_dtype dt) {
-    constexpr double kFewTokensKb[3] = {480, 300, 200};
+    constexpr double kFewTokensKb[3] = {500, 300, 200};
     if (M * G > coral_ctrl::kGateScoreWords) return false;
     const double kb = n_vec / 64.0;                        // of a gate row
     if (M <= 3 && G * kb < kFewTokensKb[M - 1]) return false;
@@ -533,7 +533,8 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
     const auto getter = CORAL_PICK_DT(dt, short_rows ? coral_fused_short_f32 : coral_fused_long_f32,
                                       short_rows ? coral_fused_short_bf16 : coral_fused_long_bf16,
                                       short_rows ? coral_fused_short_f16 : coral_fused_long_f16);
-    const void* fn = getter(dense, !dense && fused_gate_shared(M, G, n_vec, dt) ? (int)kGateShared : gate, routed, logprob, segs);
+    const bool shared = !dense && fused_gate_shared(M, G, n_vec, dt);
+    const void* fn = getter(dense, shared ? (int)kGateShared : gate, routed, logprob, segs);
     if (!allow_lds(fn, F.total)) return CORAL_ERR_HIP;
     void* args[] = {&p};
     return launch_timed(fn, dim3(P), dim3(kFusedBlock), F.total, stream, ev_before, ev_after, args);
@@ -619,7 +620,6 @@ size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtyp
 // would have to go through the tokens in batches, reading the weights again for each.
 bool grouped_tiles_faster(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
     if (!is_16bit(dt) || V < 8192 || H < 256 || M < 37) return false;
-    const Tiles kind = H % (kChunkVecs * 8) == 0 ? Tiles::kOwn : Tiles::kGeneral;
     const int chunk = kChunkVecs * 8, chunks = (H + chunk - 1) / chunk;
     const double group_tokens = M * g / expected_groups(M, G, g);
     if (M < 50 && group_tokens <= 9.0) {
@@ -627,6 +627,7 @@ bool grouped_tiles_faster(int M, int H, int V, int G, int g, int k, coral_dtype 
         if (k <= 2 && (chunks > 1 || (part && V > kMaxWorkgroups * kTileRows))) return false;
         if (part && group_tokens >= 1.8 && (long long)V * chunks > 62000) return false;
     }
+    const Tiles kind = H % (kChunkVecs * 8) == 0 ? Tiles::kOwn : Tiles::kGeneral;
     return make_layout(M, V, G, g, k, Pieces{}, {kind, false}, LayoutFor::kTiles).total <= kStaticArrayBytes ||
            static_counted_bytes(M, H, V, G, g, k, dt) > kStaticScratchBytes;
 }
@@ -655,7 +656,9 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
         return pl;
     }
     const bool fused_ok =
-        fused_rows_fit(n_vec) && (dense ? jp != 9 || M <= kNineSegsDenseTokens : jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, false)) &&
+        fused_rows_fit(n_vec) &&
+        (dense ? jp != 9 || M <= kNineSegsDenseTokens
+               : jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, false)) &&
         fused_lds_layout(M, dense ? 0 : G, dense ? 0 : g, k, jp, dense,
                          fused_gate_mode(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp, dt)).total <= kLdsLimit;
     const bool tiles_ok =

@@ -393,7 +393,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
     constexpr int ROWS = fused_rows(SEGS);
     extern __shared__ uint4 smem[];
     char* lds = reinterpret_cast<char*>(smem);
-    const FusedLds lay = fused_lds_layout(p.M, p.G, p.g, p.k, p.jp, DENSE, GATE != kGateShared ? GATE : DT == kF32 || p.M <= 3 ? kGateVector : kGateMfma, LP, p.cap);
+    const int lds_gate = GATE != kGateShared ? GATE : DT == kF32 || p.M <= 3 ? kGateVector : kGateMfma;
+    const FusedLds lay = fused_lds_layout(p.M, p.G, p.g, p.k, p.jp, DENSE, lds_gate, LP, p.cap);
     uint4* hs = reinterpret_cast<uint4*>(lds + lay.o_hidden);
     Cand* lists = reinterpret_cast<Cand*>(lds + lay.o_lists);
     float* s_lds = reinterpret_cast<float*>(lds + lay.o_s);

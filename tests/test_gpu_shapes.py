@@ -558,7 +558,7 @@ def gate_is_shared(coral, dtype, H, G, M, k=2, g=2):
 
 
 # either side of the bytes of a gate that up to three tokens share, and of the estimate that more go by
-WHICH_GATE = [("bf16", 2776, 66, 1, False), ("bf16", 8192, 30, 1, True), ("bf16", 8192, 29, 1, False), ("f16", 2048, 70, 2, False),
+WHICH_GATE = [("bf16", 2776, 66, 1, False), ("bf16", 8192, 32, 1, True), ("bf16", 8192, 31, 1, False), ("f16", 2048, 70, 2, False),
               ("f16", 2048, 80, 2, True), ("bf16", 4096, 24, 3, False), ("bf16", 4096, 26, 3, True), ("f32", 2004, 52, 1, False),
               ("f32", 2048, 64, 1, True), ("bf16", 2048, 32, 8, False), ("bf16", 4096, 32, 8, True), ("bf16", 8192, 900, 5, False)]
 
