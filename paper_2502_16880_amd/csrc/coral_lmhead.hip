@@ -304,17 +304,12 @@ bool fused_gate_shared(int M, int G, int n_vec, coral_dtype dt) {
 }
 
 // Rows the single-launch kernel takes (by their 16-byte vectors): up to 8 KB, and from 8.25 to 16 KB.  (Rows of
-// nine segments leave seven of a batch's sixteen loads empty, and are still the faster ones: us, multi-kernel
-// paths against single launch, over 972 random heads of 4224 to 4608 columns (fp32: half): grouped 1.8 times
-// as fast on average, the worst 1.03; log-probabilities up to eight tokens 1.53, the worst 1.006; bf16 H =
-// 4352, 62 groups, 7 tokens, k = 64 139, 26, H = 4608, 56 groups, 11 tokens 55, 50; dense f16 H = 4224, 7
-// tokens, k = 33 149, 36.  With more tokens a group's rows cost their products: log-probabilities from nine
-// tokens on 0.75 to 2.3 (bf16 H = 4328, 6 of 8 groups, 12 tokens 176, 234), the dense head from eight tokens on
-// f16 H = 4480, 94129 rows, 9 tokens 146, 166, bf16 H = 4352, 24624 rows, 15 tokens 49, 70.  Below a quarter of
-// the ninth segment two heads measured 1.5 and 2.5 times as fast on the single launch: not a loss, but these
+// nine segments leave seven of a batch's sixteen loads empty: nine_segs_take_fused.  Below a quarter of the
+// ninth segment two heads measured 1.5 and 2.5 times as fast on the single launch: not a loss, but these
 // widths are where the general path's form of long rows is pinned, and they stay there.)
-bool fused_rows_fit(int n_vec) { return n_vec <= 8 * kWave || (n_vec >= 8 * kWave + kWave / 4 && n_vec <= kFusedMaxSegs * kWave); }
-constexpr int kNineSegsDenseTokens = 7, kNineSegsLogprobTokens = 8;
+bool fused_rows_fit(int n_vec) {
+    return n_vec <= 8 * kWave || (n_vec >= 8 * kWave + kWave / 4 && n_vec <= kFusedMaxSegs * kWave);
+}
 
 // Log-probability mode: beyond 32 tokens the single-launch kernel's per-wave lists (one per token,
 // hardly ever filled) and per-token pieces cost more than the tile kernels' three launches
@@ -368,11 +363,45 @@ double expected_blocks(int M, int V, int G, int g) {
     return expected_groups(M, G, g) * ((V / G + kTileRows - 1) / kTileRows);
 }
 
+// Rows of nine segments (4224 to 4608 columns, fp32 half of that): whether the single launch takes them.  us,
+// multi-kernel paths against single launch, over 6100 random heads (8 to 4000 groups, 1 to 17 tokens, any k) that
+// had all taken it:
+//   - grouped: 1.9 times as fast off the matrix-core path, 1.2 times beside it, while a group has few tokens.
+//     With many, a row's products on the vector units take longer than its load: k <= 16, beside the matrix-core
+//     path from six tokens a group on 0.84 on average (f16 H = 4608, 106958 rows, 5 of 8 groups, 14 tokens 175,
+//     261); off it, where the other path's blocks fill rounds over the compute units, 16 bits from 7.5 on 0.97, 0.57
+//     to 1.2 (H = 4224, 16 of 26 groups, 14 tokens 150, 225), fp32 from 8.5 on 0.98, 0.68 to 1.3 (H = 2144, 25 of 27
+//     groups, 15 tokens 138, 202).  Where they fill half of a round, or little of the second, the single launch
+//     stays ahead (1.2 and 1.25, but two of 84 heads 0.80 and 0.95).  Beyond k = 16 (the other paths' merges go by
+//     whole lists) it is up to ten tokens a group, 1.05 and more on average, above 0.98;
+//   - more scores than the workgroups can share, where the other choice is the matrix-core path: every workgroup
+//     computed them all, 54 heads 0.13 to 0.57 (bf16 H = 4608, 1021 groups, 6 tokens 40, 294);
+//   - log-probabilities: up to eight tokens 1.6 times as fast off the matrix-core path (from six tokens a group on,
+//     k <= 16, 0.88), 1.17 beside it (from 3.5 tokens a group on 0.92 to 1.26, with k > 40 from 1.6 on 0.75 to 1.2);
+//     with more tokens 0.75 to 2.3 (bf16 H = 4328, 6 of 8 groups, 12 tokens 176, 234);
+//   - dense: f16 H = 4224, 7 tokens, k = 33 149, 36, but from eight tokens on f16 H = 4480, 94129 rows, 9 tokens 146,
+//     166, bf16 H = 4352, 24624 rows, 15 tokens 49, 70.
+constexpr int kNineSegsDenseTokens = 7, kNineSegsLogprobTokens = 8;
+bool nine_segs_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob) {
+    int um, lds;
+    const bool tiles = tiles_fit(M, H, V, G, g, k, dt, &um, &lds) && (!logprob || G <= kWave);
+    const double group_tokens = M * g / expected_groups(M, G, g);
+    if (logprob) {
+        if (M > kNineSegsLogprobTokens) return false;
+        return group_tokens <= (tiles ? (k <= 40 ? 3.5 : 1.6) : k <= 16 ? 6.0 : 8.0);
+    }
+    if (tiles && M * G > coral_ctrl::kGateScoreWords) return false;
+    if (group_tokens <= (k > 16 ? 10.0 : tiles ? 6.0 : is_16bit(dt) ? 7.5 : 8.5)) return true;
+    const double rounds = expected_blocks(M, V, G, g) / kMaxWorkgroups;
+    return !tiles && (rounds <= 0.75 || (rounds > 1.0 && rounds <= 1.5));
+}
+
 // Rows beyond 8 KB: the single launch takes them where the workgroups can share the gate's scores.  us, the
 // general path against it, over the heads off the matrix-core path among 380 random ones (8 to 1000 groups, 1 to
 // 14 tokens) that the own gate had kept there: 1.5 to 1.9 times as fast on average, none slower by more than 2 %;
 // bf16 H = 7296, 117 groups, 6 tokens 76, 36; fp32 H = 3072, 109 groups, 5 tokens 56, 28; log-probabilities, f16
-// H = 6144, 128 groups, 8 tokens 74, 29; bf16 H = 5632, 83 groups, 9 tokens 131, 134.
+// H = 6144, 128 groups, 8 tokens 74, 29; bf16 H = 5632, 83 groups, 9 tokens 131, 134.  Not where a group has
+// more than ten tokens (fp32 H = 2816, 109 of 126 groups, 12 tokens 246, 278).
 // The lines from before that stay where
 //   - the matrix-core path is the other choice: taken while tokens are few or where its blocks do not fill a
 //     good part of one round over the compute units (H = 5120, 6 tokens, 32 groups 97, 83; with the shared gate
@@ -383,12 +412,15 @@ double expected_blocks(int M, int V, int G, int g) {
 //     46, 103; log-probabilities, 6 tokens, 64 groups 79, 80).  Both are pinned by the routes' tests.
 bool long_rows_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob) {
     int um, lds;
+    const int n_vec = H / (is_16bit(dt) ? 8 : 4), last = n_vec % kWave;
+    if (n_vec <= 9 * kWave && !nine_segs_take_fused(M, H, V, G, g, k, dt, logprob)) return false;
     if (tiles_fit(M, H, V, G, g, k, dt, &um, &lds) && (!logprob || G <= kWave)) {
         const double blocks = expected_blocks(M, V, G, g);
         return M < 4 || k > 10 || blocks <= (logprob ? 110 : 145) || blocks > kMaxWorkgroups + 6;
     }
-    const int n_vec = H / (is_16bit(dt) ? 8 : 4), last = n_vec % kWave;
-    if (M * G <= coral_ctrl::kGateScoreWords && (last == 0 || last >= kWave / 4)) return true;
+    if (M * G <= coral_ctrl::kGateScoreWords && (last == 0 || last >= kWave / 4) &&
+        (n_vec <= 9 * kWave || M * g <= 10 * expected_groups(M, G, g)))
+        return true;
     return G <= (!logprob ? 64 : M >= 7 ? 60 : 40) || G + 6 * M <= (logprob ? 80 : 135) + (k > 10 ? 8 * (k - 10) : 0);
 }
 
@@ -398,7 +430,6 @@ bool long_rows_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype 
 bool logprob_takes_fused(int M, int H, int V, int G, int g, int k, int jp, coral_dtype dt) {
     int um, lds;
     return fused_rows_fit(H / (is_16bit(dt) ? 8 : 4)) && fused_logprob_fits(M, G, g, k, jp, dt, kMaxWorkgroups) &&
-           (jp != 9 || M <= kNineSegsLogprobTokens) &&
            (jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, true)) &&
            (M <= kLogprobFusedMaxTokens || !tile_kernels_fit(M, H, V, G, g, k, dt, &um, &lds));
 }

@@ -398,10 +398,32 @@ def test_route_of_grouped_heads_with_many_tokens(sizes, path):
 
 @pytest.mark.parametrize("H,dt", [(4224, BF16), (4352, F16), (4608, BF16), (2112, F32), (2304, F32)])
 def test_route_of_rows_of_nine_segments(H, dt):
-    """Single launch: log-probabilities up to eight tokens, dense up to seven, grouped whatever the tokens (but
-    for whole 512-column chunks in 16 bits, where the matrix-core path takes some)."""
-    for M in (1, 7, 8, 9, 12):
-        if H != 4608:
-            assert coral.coral_lmhead_path(False, M, H, 91704, 8, 6, 8, dt) == 1
-        assert (coral.coral_lmhead_logprob_path(M, H, 91704, 8, 6, 8, dt) == 1) == (M <= 8)
+    """Single launch: dense up to seven tokens; log-probabilities up to eight, and with few tokens a group (6 of 8
+    groups: 0.75 of them); grouped by tokens a group.  Whole 512-column chunks in 16 bits: where the matrix-core
+    path is the other choice, fewer tokens a group, and no more scores than words for them."""
+    chunks = H == 4608
+    for M in (1, 4, 7, 8, 9, 11, 12):
+        tokens = M * 6 / (8 * (1 - 0.25 ** M))
+        path = coral.coral_lmhead_path(False, M, H, 91704, 8, 6, 8, dt)
+        assert (path == 1) == (tokens <= (6.0 if chunks else 8.5 if dt == F32 else 7.5))
+        assert path in (1, 2 if chunks else 0)
+        assert coral.coral_lmhead_path(False, M, H, 91704, 8, 6, 17, dt) == 1
+        lp = coral.coral_lmhead_logprob_path(M, H, 91704, 8, 6, 8, dt)
+        assert (lp == 1) == (M <= 8 and tokens <= (3.5 if chunks else 6.0))
         assert (coral.coral_lmhead_path(True, M, H, 24624, 0, 0, 8, dt) == 1) == (M <= 7)
+    assert coral.coral_lmhead_path(False, 14, H, 56000, 8, 7, 64, dt) != 1
+    # many tokens a group, blocks of half a round over the compute units, of most of one, of little more and two
+    for V, fused in ((16000, True), (30000, False), (40000, True), (60000, False)):
+        assert (coral.coral_lmhead_path(False, 14, H, V, 8, 7, 8, dt) == 1) == (fused and not chunks)
+    # 4096 scores and more than that
+    assert coral.coral_lmhead_path(False, 4, H, 80000, 1024, 3, 17, dt) == 1
+    assert coral.coral_lmhead_path(False, 4, H, 80000, 1025, 3, 17, dt) != 1
+    # log-probabilities, many candidates beside the matrix-core path: 3 of 24 groups, 13 of 24 groups
+    assert coral.coral_lmhead_logprob_path(3, H, 10896, 24, 3, 64, dt) == 1
+    assert (coral.coral_lmhead_logprob_path(3, H, 10896, 24, 13, 64, dt) == 1) == (not chunks)
+
+
+def test_route_of_longer_rows_by_tokens_a_group():
+    """More groups than the own gate was taken for: up to ten tokens a group."""
+    assert coral.coral_lmhead_path(False, 12, 2816, 111132, 126, 100, 1, F32) == 1
+    assert coral.coral_lmhead_path(False, 12, 2816, 111132, 126, 109, 1, F32) == 0
