@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 from coral_inputs import Head, HeadConfig, make_hidden, to_storage  # noqa: E402
-from test_gpu_parity import (DeviceHead, check_dense, check_grouped, check_logprob, coral, run_dense,  # noqa: E402,F401
+from oracle import compare  # noqa: E402
+from test_gpu_parity import (TIGHT_LOGIT_ERR, TIGHT_LOGP_ERR, DeviceHead, check_dense, check_grouped, check_logprob, coral, run_dense,  # noqa: E402,F401
                              run_grouped, run_logprob)
 
 
@@ -566,3 +567,38 @@ WHICH_GATE = [("bf16", 2776, 66, 1, False), ("bf16", 8192, 32, 1, True), ("bf16"
 @pytest.mark.parametrize("dtype,H,G,M,shared", WHICH_GATE)
 def test_which_gates_are_shared(coral, dtype, H, G, M, shared):
     assert gate_is_shared(coral, dtype, H, G, M) == shared
+
+
+# storage, H, groups, tokens, route with log-probabilities where every workgroup computes the gate on the matrix cores for itself: gates too
+# small to be shared, and more scores than there are words for (rows of one, two and four passes of loads)
+OWN_GATE = [("bf16", 2048, 32, 4, 1), ("f16", 2048, 32, 8, 1), ("bf16", 2048, 32, 16, 1), ("f16", 520, 64, 33, 0),
+            ("bf16", 512, 1024, 5, 1), ("bf16", 4096, 300, 14, 1), ("f16", 3080, 830, 5, 1), ("bf16", 8192, 900, 5, 0)]
+
+
+@pytest.mark.parametrize("dtype,H,G,M,logprob_path", OWN_GATE)
+def test_own_gate_on_the_matrix_cores(coral, dtype, H, G, M, logprob_path):
+    """Plain and routed, both output modes; that the gate was not shared is read from the workspace."""
+    sizes = [20 + (7 * n) % 11 for n in range(G)]
+    V, g, k = sum(sizes), 3, 6
+    cfg = HeadConfig(f"own{G}", dtype, H, V, G, g, (M,), k, 990 + G + M, True)
+    dh = DeviceHead(coral, ragged_head(cfg, sizes))
+    h = dh.head
+    code = {"bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
+    assert coral.coral_lmhead_path(False, M, H, V, G, g, k, code) == 1
+    assert coral.coral_lmhead_logprob_path(M, H, V, G, g, k, code) == logprob_path
+    hidden, gate_hidden = make_hidden(cfg, M, M), make_hidden(cfg, M, M + 1)
+    d_hidden, d_gate_hidden = coral.device_tensor(hidden, dtype), coral.device_tensor(gate_hidden, dtype)
+    ws = coral.alloc_workspace(M, H, V, G, g, k, code)
+    ws.fill_(0xAB)
+    coral.coral_lmhead_workspace_init(ws[:512])
+    for logprob in (False, True):
+        for seen, d_seen in ((hidden, None), (gate_hidden, d_gate_hidden)):
+            print(f"case {cfg.name} {dtype} H={H} M={M} logprob={logprob} routed={d_seen is not None}", flush=True)
+            out = coral.coral_lmhead_grouped(d_hidden, dh.gate_W, dh.bias, dh.lm_W, dh.gi, g, k, workspace=ws, logprob=logprob,
+                                             gate_hidden=d_seen)
+            out = [x.cpu().numpy() for x in out]
+            check = compare.check_grouped_logprob if logprob else compare.check_grouped
+            rep = check(hidden, h.gate_W, h.gate_bias, h.lm_W, h.group_offsets, h.group_rows, g, k, dtype, *out,
+                        gate_hidden=None if d_seen is None else seen)
+            assert rep.max_abs_err <= (TIGHT_LOGP_ERR if logprob else TIGHT_LOGIT_ERR)[dtype]
+            assert int(ws[:512].view(torch.int32)[32]) == 0        # no call that shares the gate
