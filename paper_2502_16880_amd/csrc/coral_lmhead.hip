@@ -566,6 +566,7 @@ coral_status launch_fused(bool dense, const void* hidden, const void* gate_hidde
                                       short_rows ? coral_fused_short_f16 : coral_fused_long_f16);
     const bool shared = !dense && fused_gate_shared(M, G, n_vec, dt);
     const void* fn = getter(dense, shared ? (int)kGateShared : gate, routed, logprob, segs);
+    if (!fn) return CORAL_ERR_UNSUPPORTED;             // not reached
     if (!allow_lds(fn, F.total)) return CORAL_ERR_HIP;
     void* args[] = {&p};
     return launch_timed(fn, dim3(P), dim3(kFusedBlock), F.total, stream, ev_before, ev_after, args);

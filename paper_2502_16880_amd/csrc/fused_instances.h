@@ -14,9 +14,14 @@ const void* fused_instance(bool dense, int gate, bool routed, bool logprob) {
         return logprob ? (routed ? CORAL_FUSED(false, kGateShared, true, true) : CORAL_FUSED(false, kGateShared, false, true))
                        : (routed ? CORAL_FUSED(false, kGateShared, true, false) : CORAL_FUSED(false, kGateShared, false, false));
     if constexpr (DT != kF32) {
-        if (gate == kGateMfma)
-            return logprob ? (routed ? CORAL_FUSED(false, kGateMfma, true, true) : CORAL_FUSED(false, kGateMfma, false, true))
-                           : (routed ? CORAL_FUSED(false, kGateMfma, true, false) : CORAL_FUSED(false, kGateMfma, false, false));
+        if (gate == kGateMfma && !logprob)
+            return routed ? CORAL_FUSED(false, kGateMfma, true, false) : CORAL_FUSED(false, kGateMfma, false, false);
+        if constexpr (SEGS <= 8) {     // (rows beyond 8 KB with log-probabilities: always shared, or another path)
+            if (gate == kGateMfma)
+                return routed ? CORAL_FUSED(false, kGateMfma, true, true) : CORAL_FUSED(false, kGateMfma, false, true);
+        } else {
+            if (gate == kGateMfma) return nullptr;
+        }
     }
     return logprob ? (routed ? CORAL_FUSED(false, kGateVector, true, true) : CORAL_FUSED(false, kGateVector, false, true))
                    : (routed ? CORAL_FUSED(false, kGateVector, true, false) : CORAL_FUSED(false, kGateVector, false, false));

@@ -427,3 +427,13 @@ def test_route_of_longer_rows_by_tokens_a_group():
     """More groups than the own gate was taken for: up to ten tokens a group."""
     assert coral.coral_lmhead_path(False, 12, 2816, 111132, 126, 100, 1, F32) == 1
     assert coral.coral_lmhead_path(False, 12, 2816, 111132, 126, 109, 1, F32) == 0
+
+
+@pytest.mark.parametrize("H", [4224, 4608, 4616, 4736, 5120, 8192])
+def test_no_own_gate_with_log_probabilities_beyond_8_kb(H):
+    """16 bits, four tokens and more, more scores than can be shared: the single launch has no form for it."""
+    for M in (4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 16, 32, 64):
+        for G in sorted({4096 // M + 1, 4096 // M + 9, 256, 400, 512, 513, 1024}):
+            for k in (1, 10, 33, 50, 64):
+                for g in {1, 3, max(1, 64 // M)}:
+                    assert M * G <= 4096 or coral.coral_lmhead_logprob_path(M, H, 150000, G, g, k, BF16) != 1
