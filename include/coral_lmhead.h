@@ -99,9 +99,11 @@ size_t coral_lmhead_workspace_bytes(int M, int H, int V, int G, int g, int k,
  * 0 = general path (one launch per stage: the tile path's kernels in a form for any storage
  * type and width, or staged kernels on the vector units where these do not fit or are
  * slower), 1 = single-launch path (gate, selection, row streaming and top-k of section 3.3 in
- * one persistent kernel: rows of up to 16 KB (but 8 to 8.25) whose token batch fits on chip;
- * not 16 tokens and more dense, 32 grouped, whose candidates do not fit beside them, nor 37
- * and more grouped in 16 bits), 2 = matrix-core tile path (bf16 or fp16, H a multiple of 512, weights
+ * one persistent kernel, where the token batch fits on chip: rows of up to 8 KB; of rows of
+ * 8.25 to 16 KB those whose groups, tokens and k make it the faster one (dense: rows of up to
+ * 9 KB with at most 7 tokens, longer ones as the tokens fit); not 16 tokens and more dense, 32
+ * grouped, whose candidates do not fit beside them, nor most 16-bit grouped heads of 37 tokens
+ * and more), 2 = matrix-core tile path (bf16 or fp16, H a multiple of 512, weights
  * below 4 GiB: groups shared by many tokens, the appendix's tree-decoding case, when the
  * hidden vectors do not fit on chip; dense head with 8 or more tokens and at least 65536
  * rows),
@@ -114,7 +116,8 @@ int coral_lmhead_path(int dense, int M, int H, int V, int G, int g, int k, coral
 /*
  * The same for coral_lmhead_grouped_logprob (Eq. 8's output): 1 = single-launch kernel
  * (at most 64 activated groups, min(M*g, G) <= 64, g <= 16, and its LDS plan fits; beyond 32
- * tokens only where the tile kernels do not fit; rows of up to 16 KB as above),
+ * tokens only where the tile kernels do not fit; rows of 8.25 to 16 KB as above, of up to
+ * 9 KB with at most 8 tokens),
  * 2 = matrix-core tile path (where that path's conditions hold and G <= 64; more groups go to
  * the general path's form of the same kernels),
  * 0 = general path, -1 = sizes not supported.  Host-only.
@@ -183,7 +186,7 @@ coral_status coral_lmhead_grouped(const void *hidden, const void *gate_W,
  * allocation.  Same operation, arguments, results (bit for bit) and errors as
  * coral_lmhead_grouped, with no workspace argument: the kernels' scratch (published partial
  * lists, arrival counters, the staged path's hand-over arrays) lives in a static device array
- * of CORAL_NOALLOC_SCRATCH_BYTES and 64 KB inside the library, one copy per GPU, held until the
+ * of CORAL_NOALLOC_SCRATCH_BYTES and 80 KB inside the library, one copy per GPU, held until the
  * process ends.  The call allocates and frees nothing.
  *   - Shapes whose published and staged lists (16-bit shapes with whole 512-column chunks that
  *     are beyond the single-launch path, or have rows beyond 8 KB: the tile path's logits

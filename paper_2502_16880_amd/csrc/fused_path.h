@@ -589,7 +589,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
                     if (wave < total)
                         for (int base = 0; mine < 0; base += kWave) {
                             const unsigned long long b = missing(base);
-                            const unsigned long long at = __ballot((b >> lane & 1ull) && __popcll(b & ((1ull << lane) - 1ull)) == rank);
+                            const unsigned long long before = b & ((1ull << lane) - 1ull);
+                            const unsigned long long at = __ballot((b >> lane & 1ull) && __popcll(before) == rank);
                             if (at) mine = base + __ffsll(at) - 1;
                             rank -= __popcll(b);
                         }
@@ -1009,13 +1010,16 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused(FusedParams p) {
         if (uni(through) != (int)gridDim.x - 1) return;
         int ln = lane;
         asm volatile("" : "+v"(ln));                   // (see wave_merge_lists)
-        const bool first = uni((int)__hip_atomic_load(p.counter + kGatePollsAt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0;
+        const bool first =
+            uni((int)__hip_atomic_load(p.counter + kGatePollsAt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0;
         const int n_words = first ? coral_ctrl::kGateScoreWords : M * p.G;
         for (int e = ln; e < n_words; e += kWave)
             __hip_atomic_store(p.counter + kGateScoresAt + e, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (lane == 0) {
             __hip_atomic_store(p.counter + kGateDoneAt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (first) __hip_atomic_store(p.counter + kGatePollsAt, (unsigned)kGatePollsMax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (first)
+                __hip_atomic_store(p.counter + kGatePollsAt, (unsigned)kGatePollsMax, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
         }
     };
     if ((int)blockIdx.x >= P_act) {                    // block-uniform

@@ -468,7 +468,8 @@ def test_shared_gate_with_scores_of_zero(coral):
 
 @pytest.mark.parametrize("dtype,H", [("bf16", 4224), ("f16", 4600), ("bf16", 4608), ("f32", 2112), ("f32", 2304)])
 def test_rows_of_nine_segments(coral, dtype, H):
-    """From a quarter of the ninth segment on, up to a whole one; the dense head up to seven tokens, log-probabilities up to eight."""
+    """From a quarter of the ninth segment on, up to a whole one; the dense head up to seven tokens,
+    log-probabilities up to eight."""
     sizes = [1, 2, 3, 15, 16, 17, 64, 130] + [40] * 25
     cfg = HeadConfig(f"nine{H}", dtype, H, sum(sizes), len(sizes), 4, (1,), 9, 950 + H, True)
     code = {"f32": coral.CORAL_F32, "bf16": coral.CORAL_BF16, "f16": coral.CORAL_F16}[dtype]
