@@ -364,7 +364,7 @@ double expected_blocks(int M, int V, int G, int g) {
 }
 
 // Rows of nine segments (4224 to 4608 columns, fp32 half of that): whether the single launch takes them.  us,
-// multi-kernel paths against single launch, over 6100 random heads (8 to 4000 groups, 1 to 17 tokens, any k) that
+// multi-kernel paths against single launch, over 8000 random heads (8 to 4000 groups, 1 to 17 tokens, any k) that
 // had all taken it:
 //   - grouped: 1.9 times as fast off the matrix-core path, 1.2 times beside it, while a group has few tokens.
 //     With many, a row's products on the vector units take longer than its load: k <= 16, beside the matrix-core
@@ -372,15 +372,17 @@ double expected_blocks(int M, int V, int G, int g) {
 //     261); off it, where the other path's blocks fill rounds over the compute units, 16 bits from 7.5 on 0.97, 0.57
 //     to 1.2 (H = 4224, 16 of 26 groups, 14 tokens 150, 225), fp32 from 8.5 on 0.98, 0.68 to 1.3 (H = 2144, 25 of 27
 //     groups, 15 tokens 138, 202).  Where they fill half of a round, or little of the second, the single launch
-//     stays ahead (1.2 and 1.25, but two of 84 heads 0.80 and 0.95).  Beyond k = 16 (the other paths' merges go by
+//     stays ahead (1.2 and 1.25, but six of 130 heads 0.80 to 0.97).  Beyond k = 16 (the other paths' merges go by
 //     whole lists) it is up to ten tokens a group, 1.05 and more on average, above 0.98;
 //   - more scores than the workgroups can share, where the other choice is the matrix-core path: every workgroup
 //     computed them all, 54 heads 0.13 to 0.57 (bf16 H = 4608, 1021 groups, 6 tokens 40, 294);
-//   - log-probabilities: up to eight tokens 1.6 times as fast off the matrix-core path (from six tokens a group on,
-//     k <= 16, 0.88), 1.17 beside it (from 3.5 tokens a group on 0.92 to 1.26, with k > 40 from 1.6 on 0.75 to 1.2);
-//     with more tokens 0.75 to 2.3 (bf16 H = 4328, 6 of 8 groups, 12 tokens 176, 234);
-//   - dense: f16 H = 4224, 7 tokens, k = 33 149, 36, but from eight tokens on f16 H = 4480, 94129 rows, 9 tokens 146,
-//     166, bf16 H = 4352, 24624 rows, 15 tokens 49, 70.
+//   - log-probabilities: up to eight tokens 1.6 times as fast off the matrix-core path (16 bits, k <= 16, from six
+//     tokens a group on and several rounds of blocks 0.88 to 1.1), 1.17 beside it, but from 3.5 tokens a group on
+//     0.92 to 1.26, and where a token's groups have more than 520 candidates between them 0.75 to 1.05 (bf16, 10 of
+//     47 groups, 3 tokens, k = 64 51, 64; up to 520 1.05 and more); with more tokens 0.75 to 2.3 (bf16 H = 4328, 6 of 8 groups, 12 tokens 176, 234);
+//   - dense: up to seven tokens 2.9 times as fast off the matrix-core path, 1.3 beside it, but there seven tokens
+//     0.92 to 0.99 from 22000 rows on (f16 H = 4608, 83005 rows 133, 144; 9057 rows 1.35); more tokens f16 H = 4480,
+//     94129 rows, 9 tokens 146, 166, bf16 H = 4352, 24624 rows, 15 tokens 49, 70.
 constexpr int kNineSegsDenseTokens = 7, kNineSegsLogprobTokens = 8;
 bool nine_segs_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype dt, bool logprob) {
     int um, lds;
@@ -388,12 +390,18 @@ bool nine_segs_take_fused(int M, int H, int V, int G, int g, int k, coral_dtype 
     const double group_tokens = M * g / expected_groups(M, G, g);
     if (logprob) {
         if (M > kNineSegsLogprobTokens) return false;
-        return group_tokens <= (tiles ? (k <= 40 ? 3.5 : 1.6) : k <= 16 ? 6.0 : 8.0);
+        if (tiles) return group_tokens <= 3.5 && g * k <= 520;
+        return group_tokens <= 6.0 || k > 16 || !is_16bit(dt) || expected_blocks(M, V, G, g) <= kMaxWorkgroups;
     }
     if (tiles && M * G > coral_ctrl::kGateScoreWords) return false;
     if (group_tokens <= (k > 16 ? 10.0 : tiles ? 6.0 : is_16bit(dt) ? 7.5 : 8.5)) return true;
     const double rounds = expected_blocks(M, V, G, g) / kMaxWorkgroups;
     return !tiles && (rounds <= 0.75 || (rounds > 1.0 && rounds <= 1.5));
+}
+bool nine_segs_take_fused_dense(int M, int H, int V, int k, coral_dtype dt) {
+    int um, lds;
+    if (M != kNineSegsDenseTokens) return M < kNineSegsDenseTokens;
+    return V < 16384 || !tiles_fit(M, H, V, 0, 0, k, dt, &um, &lds);
 }
 
 // Rows beyond 8 KB: the single launch takes them where the workgroups can share the gate's scores.  us, the
@@ -689,7 +697,7 @@ PathPlan plan_path_kind(bool dense, int M, int H, int V, int G, int g, int k, co
     }
     const bool fused_ok =
         fused_rows_fit(n_vec) &&
-        (dense ? jp != 9 || M <= kNineSegsDenseTokens
+        (dense ? jp != 9 || nine_segs_take_fused_dense(M, H, V, k, dt)
                : jp <= 8 || long_rows_take_fused(M, H, V, G, g, k, dt, false)) &&
         fused_lds_layout(M, dense ? 0 : G, dense ? 0 : g, k, jp, dense,
                          fused_gate_mode(dense, M, dense ? 0 : G, dense ? 0 : g, k, jp, dt)).total <= kLdsLimit;

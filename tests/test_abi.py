@@ -409,8 +409,10 @@ def test_route_of_rows_of_nine_segments(H, dt):
         assert path in (1, 2 if chunks else 0)
         assert coral.coral_lmhead_path(False, M, H, 91704, 8, 6, 17, dt) == 1
         lp = coral.coral_lmhead_logprob_path(M, H, 91704, 8, 6, 8, dt)
-        assert (lp == 1) == (M <= 8 and tokens <= (3.5 if chunks else 6.0))
-        assert (coral.coral_lmhead_path(True, M, H, 24624, 0, 0, 8, dt) == 1) == (M <= 7)
+        assert (lp == 1) == (M <= 8 and tokens <= (3.5 if chunks else 8.0 if dt == F32 else 6.0))
+        assert (coral.coral_lmhead_path(True, M, H, 24624, 0, 0, 8, dt) == 1) == (M <= (6 if chunks else 7))
+        assert (coral.coral_lmhead_path(True, M, H, 16383, 0, 0, 8, dt) == 1) == (M <= 7)
+        assert chunks or (coral.coral_lmhead_logprob_path(M, H, 16000, 8, 6, 8, dt) == 1) == (M <= 8)
     assert coral.coral_lmhead_path(False, 14, H, 56000, 8, 7, 64, dt) != 1
     # many tokens a group, blocks of half a round over the compute units, of most of one, of little more and two
     for V, fused in ((16000, True), (30000, False), (40000, True), (60000, False)):
@@ -418,9 +420,10 @@ def test_route_of_rows_of_nine_segments(H, dt):
     # 4096 scores and more than that
     assert coral.coral_lmhead_path(False, 4, H, 80000, 1024, 3, 17, dt) == 1
     assert coral.coral_lmhead_path(False, 4, H, 80000, 1025, 3, 17, dt) != 1
-    # log-probabilities, many candidates beside the matrix-core path: 3 of 24 groups, 13 of 24 groups
-    assert coral.coral_lmhead_logprob_path(3, H, 10896, 24, 3, 64, dt) == 1
-    assert (coral.coral_lmhead_logprob_path(3, H, 10896, 24, 13, 64, dt) == 1) == (not chunks)
+    # log-probabilities, many candidates beside the matrix-core path: 8 of 24 groups, 9 of 24 groups, one token
+    for M in (1, 3):
+        assert coral.coral_lmhead_logprob_path(M, H, 10896, 24, 8, 64, dt) == 1
+        assert (coral.coral_lmhead_logprob_path(M, H, 10896, 24, 9, 64, dt) == 1) == (not chunks)
 
 
 def test_route_of_longer_rows_by_tokens_a_group():
