@@ -653,10 +653,11 @@ size_t static_counted_bytes(int M, int H, int V, int G, int g, int k, coral_dtyp
 //   - the last chunk is partly filled (it costs as much as a whole one), there are about two rounds of chunks over
 //     the compute units or more, and two tokens or more to a group.
 // Single launch against tiles over 5500 random heads of 8 to 152 K rows, 8 to 1024 groups and 256 to 1096 columns:
-// 1.47 times as fast on average, the worst 0.97 (us: bf16 H = 256, 48720 rows, 53 tokens 41, 28); in the two
-// exceptions, 7 in a hundred heads, 1.19, but down to 0.86 (f16 H = 776, 38275 rows, 41 tokens, k = 1 35, 41; bf16 H = 488,
-// 125086 rows, 37 tokens 44, 50).  33 to 36 tokens 1.18, 0.87 to 1.4 (H = 816, 146627 rows, 35 tokens 71, 82); 25
-// to 32 tokens 1.07, 0.85 to 1.40; up to 16 tokens 0.80; fp32 0.87.  Not where the entry point without a workspace
+// 1.47 times as fast on average, the worst 0.97, over 1000 more the worst 0.93 (us: bf16 H = 256, 48720 rows, 53
+// tokens 41, 28; H = 512, 150991 rows, one of 28 groups, 37 tokens 40, 43); in the two exceptions, 7 in a hundred
+// heads, 1.19, but down to 0.86 (f16 H = 776, 38275 rows, 41 tokens, k = 1 35, 41; bf16 H = 488, 125086 rows, 37
+// tokens 44, 50).  33 to 36 tokens 1.18, 0.87 to 1.4 (H = 816, 146627 rows, 35 tokens 71, 82); 25 to 32 tokens
+// 1.07, 0.85 to 1.40; up to 16 tokens 0.80; fp32 0.87.  Not where the entry point without a workspace
 // would have to go through the tokens in batches, reading the weights again for each.
 bool grouped_tiles_faster(int M, int H, int V, int G, int g, int k, coral_dtype dt) {
     if (!is_16bit(dt) || V < 8192 || H < 256 || M < 37) return false;
@@ -1094,9 +1095,11 @@ coral_status grouped_impl(const void* hidden, const void* gate_hidden, const voi
     if (plan.path < 0) return CORAL_ERR_UNSUPPORTED;       // before anything is enqueued
     if (static_workspace) {
         // this device's copy of the array; its control words are prepared by a fill kernel on
-        // the call's stream (the array keeps whatever the last call on this GPU left there)
+        // the call's stream (the array keeps whatever the last call on this GPU left there); the
+        // scores' words only where they are used (small heads 0.1 us)
         if ((st = static_scratch(&workspace)) != CORAL_OK) return st;
-        if ((st = prepare_words(workspace, kStaticArrayBytes, stream)) != CORAL_OK) return st;
+        const bool shared = plan.path == 1 && fused_gate_shared(M, G, H / (is_16bit(dt) ? 8 : 4), dt);
+        if ((st = prepare_words(workspace, shared ? kStaticArrayBytes : kCtrlBytes, stream)) != CORAL_OK) return st;
     }
     char* ws = static_cast<char*>(workspace);
     if (plan.path == 1)

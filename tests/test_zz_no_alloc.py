@@ -83,6 +83,17 @@ def test_noalloc_at_full_size_then_a_smaller_vocabulary(coral):
         assert torch.equal(a, b)
 
 
+def test_noalloc_with_own_and_shared_gate_in_turn(coral):
+    """The scores' words are prepared only by calls that use them, whatever lay there before."""
+    tree, llama = CONFIGS["wide_tree"].scaled(V=64 * 126), CONFIGS["llama3_8b"].scaled(V=32 * 203)
+    heads = {c.name: upload(coral, make_head(c)) for c in (tree, llama)}
+    for call, (cfg, M) in enumerate(((tree, 64), (llama, 8), (llama, 1), (llama, 16), (tree, 40), (llama, 2), (llama, 5))):
+        print(f"case {cfg.name} M={M}", flush=True)
+        want, got = both(coral, cfg, heads[cfg.name], M, cfg.g, cfg.k, batch=call)
+        for a, b in zip(want, got):
+            assert torch.equal(a, b)
+
+
 def test_noalloc_refuses_shapes_beyond_its_scratch(coral):
     """64 tokens x 16 candidates at the full vocabulary need 37 MB: refused before any launch
     (the weights here are a small dummy; the size check sees the declared shape only)."""
